@@ -527,12 +527,9 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
         ctx->timing.decide_launches++;
     }
     HIP_TRY(ctx, hipEventRecord(ctx->ev[1], st));
-    if (proposal == TKDV_PROP_MIXTURE) {
-        for (int ki = 0; ki < kNumK; ++ki)
-            if (v.plist_n[ki]) HIP_TRY(ctx, launch_fixup_mix(8 << ki, a, ctx->n_cu, st));
-    } else {
-        HIP_TRY(ctx, launch_fixup(a, ctx->n_cu, st));
-    }
+    auto fixup = proposal == TKDV_PROP_MIXTURE ? launch_fixup_mix : launch_fixup;
+    for (int ki = 0; ki < kNumK; ++ki)
+        if (v.plist_n[ki]) HIP_TRY(ctx, fixup(8 << ki, a, ctx->n_cu, st));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[2], st));
     if (stats) {
         HIP_TRY(ctx, launch_segments(a, v.total_segs, w.seg_cnt, w.seg_base, w.results, ctx->n_cu, st));
@@ -966,7 +963,8 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
                                                d_plist + call.plist_off[ki], call.plist_n[ki], ctx->n_cu,
                                                pool_words, sst, nullptr));
         }
-        HIP_TRY(ctx, launch_fixup(a, ctx->n_cu, sst));
+        for (int ki = 0; ki < kNumK; ++ki)
+            if (call.plist_n[ki]) HIP_TRY(ctx, launch_fixup(8 << ki, a, ctx->n_cu, sst));
         HIP_TRY(ctx, launch_segments(a, max_segs, seg_cnt, seg_base, res, ctx->n_cu, sst));
         for (int ki = 0; ki < kNumK; ++ki) {
             if (call.plist_n[ki] == 0) continue;

@@ -108,7 +108,6 @@ struct DevCounters {
     unsigned long long accepted;      // decisions that were definite accepts
     unsigned long long violations;    // proposals with log a > 0
     unsigned long long deferred;      // proposals sent to the FP64 re-decision
-    unsigned long long fix_accepted;  // of those, accepted
     unsigned long long last_index;    // accepted-count mode: index of the target-th sample
     unsigned int max_log_a_key;       // order-preserving encoding of the largest log a
     unsigned int pad;

@@ -18,7 +18,8 @@ hipError_t launch_decide_variant(int K, int prec, int prop, int variant, const K
                                  int n_plist, int n_cu, unsigned long long tiles, hipStream_t st, int *grid_out);
 int decide_variant_block(int K, int variant);
 int decide_variant_max_blocks_per_cu(int K, int prec, int variant);
-hipError_t launch_fixup(const KernelArgs &a, int n_cu, hipStream_t st);
+// FP64 re-decision of the listed proposals of the points with this K
+hipError_t launch_fixup(int K, const KernelArgs &a, int n_cu, hipStream_t st);
 hipError_t launch_fixup_mix(int K, const KernelArgs &a, int n_cu, hipStream_t st);
 hipError_t launch_segments(const KernelArgs &a, unsigned long long total_segs, unsigned long long *seg_cnt,
                            unsigned long long *seg_base, PointResult *res, int n_cu, hipStream_t st);
