@@ -658,11 +658,12 @@ void fill_stats(tkdv_stats &s, const DevPoint &P, const PointResult &r, const De
         s.n_proposed = r.n_processed;
     s.n_accepted = r.n_samples;
     s.n_written = r.n_written;
-    s.n_fp64_fixups = c.deferred;
-    s.n_M_violations = c.violations;
+    const CounterShard ct = shard_totals(c);
+    s.n_fp64_fixups = ct.deferred;
+    s.n_M_violations = ct.violations;
     s.n_exceed_2sigma = r.n_exceed;
     s.n_grid_values = r.n_samples * (uint64_t)N;
-    s.max_log_a = c.max_log_a_key ? (double)key_to_float(c.max_log_a_key) : -INFINITY;
+    s.max_log_a = ct.max_log_a_key ? (double)key_to_float(ct.max_log_a_key) : -INFINITY;
     s.S1 = r.S1;
     s.S2 = r.S2;
     s.S3 = r.S3;
@@ -723,6 +724,10 @@ tkdv_status prepare(tkdv_ctx *ctx, Call &call, int n_points, const tkdv_point *p
         d.n = ncov;
         d.n_tiles = (ncov + kTile - 1) / kTile;
         d.target = mode == TKDV_COUNT_ACCEPTED ? n[p] : ~0ull;
+        d.static_tiles = static_share(d.n_tiles, mode == TKDV_COUNT_ACCEPTED
+                                                     ? std::max(kAlwaysTiles / (uint64_t)n_points, n[p] / kTile)
+                                                     : d.n_tiles,
+                                      n_points);
         d.bm_off = bm;
         d.seg_off = segs;
         d.n_segs = (d.n_tiles + kSegWords - 1) / kSegWords;
@@ -856,6 +861,7 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
         d.n_tiles = (d.n + kTile - 1) / kTile;
         d.n_segs = (d.n_tiles + kSegWords - 1) / kSegWords;
         d.target = targets[p];
+        d.static_tiles = static_share(d.n_tiles, targets[p] / kTile, np);
         d.bm_off = first_words;
         d.out_off = out_offset ? out_offset[p] : 0;
         d.capacity = capacity ? capacity[p] : 0;
@@ -1196,6 +1202,8 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
         d.n = covered;
         d.n_tiles = n_tiles;
         d.target = mode == TKDV_COUNT_ACCEPTED ? n : ~0ull;
+        d.static_tiles =
+            static_share(n_tiles, mode == TKDV_COUNT_ACCEPTED ? std::max(kAlwaysTiles, n / kTile) : n_tiles, 1);
         d.bm_off = 0;
         d.seg_off = 0;
         d.n_segs = n_segs;

@@ -552,6 +552,225 @@ __device__ __forceinline__ unsigned long long pack_defer(int p, uint64_t i)
     return ((unsigned long long)p << 40) | (unsigned long long)i;
 }
 
+// ---------------------------------------------------------------------------
+// Work queues of the decision kernels
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ unsigned long long load_relaxed(const unsigned long long *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Lane 0's value, as a wave-uniform (scalar) value.  The claim loops branch
+// on it: a per-lane copy would make their exits divergent for the compiler,
+// which may then split a loop so that lanes wait on a lane that has left it.
+__device__ __forceinline__ unsigned long long bcast_lane0(unsigned long long v)
+{
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// Per-wave counter update: every lane issues the atomic (lane 0 adds its
+// wave-uniform value, the others 0), see claim_tiles.
+__device__ __forceinline__ void add_lane0(unsigned long long *ctr, unsigned long long v, int lane)
+{
+    if (bcast_lane0(v) != 0ull) atomicAdd(ctr, lane == 0 ? v : 0ull);
+}
+
+// Tiles of the point's range that are decided: the static ones and the claims.
+__device__ __forceinline__ unsigned long long tiles_taken(const DevPoint &P, unsigned long long next_tile)
+{
+    const unsigned long long t = P.static_tiles + next_tile;
+    return t < P.n_tiles ? t : P.n_tiles;
+}
+
+// A wave's even share [b, e) of point P's static tiles, W waves in all; the
+// remainders of successive points fall to different waves.
+__device__ __forceinline__ void static_range(const DevPoint &P, int p, unsigned gwave, unsigned W,
+                                             unsigned long long &b, unsigned long long &e)
+{
+    const unsigned w = (gwave + 977u * (unsigned)p) % W;
+    // wave-uniform; the quotient comes from the vector unit, so say so
+    const unsigned q = __builtin_amdgcn_readfirstlane((unsigned)P.static_tiles / W);  // at most kMaxStatic
+    const unsigned r = (unsigned)P.static_tiles - q * W;
+    b = bcast_lane0((unsigned long long)(q * w + (w < r ? w : r)));
+    e = b + q + (w < r ? 1 : 0);
+}
+
+// Claims [b, e) from the tiles after the static ones; false when none is left
+// or, in accepted-count mode, the target is met by the definite accepts of
+// finished work (the target-th sample is then among the tiles taken so far).
+// The length is guided by what is left: share = (points)/(2 waves) of the
+// point's remaining tiles, so that the last claims are short, and at least
+// kMinClaim; in accepted-count mode what is left is estimated from the
+// acceptance of the finished tiles, no claim is longer than that asks for, and
+// once the tiles taken should do (by four standard deviations) only every
+// 32nd wave, the keepers, goes on until the target is met.  (Claims of a fixed
+// 64 tiles by every wave gave a near-linear point of a million samples eight
+// times the proposals it needed: K = 16, 1.0 ms of decisions, now 0.18 ms.)
+// Every lane issues the atomic (lane 0 adds, the others add 0) and lane 0's
+// old value is taken, so no lane-divergent region sits next to the loop
+// back-edge (the compiler may otherwise thread lanes 1-63 past lane 0's region
+// to the broadcast and split the wave).
+template <int K>
+__device__ __forceinline__ bool claim_tiles(const DevPoint &P, DevCounters *C, int lane, float share, bool keeper,
+                                            unsigned long long &b, unsigned long long &e)
+{
+    // the shortest claim: a queue hands out about 5e7 claims a second
+    constexpr int kMinClaim = K == 128 ? 4 : (K == 64 ? 8 : 16);
+    if (P.static_tiles >= P.n_tiles) return false;
+    const unsigned long long next = P.static_tiles + bcast_lane0(load_relaxed(&C->next_tile));
+    if (next >= P.n_tiles) return false;
+    float rem = (float)(P.n_tiles - next);
+    if (P.target != ~0ull) {
+        // lane l reads shard l mod kShards
+        const CounterShard *sh = &C->shard[lane & (kShards - 1)];
+        unsigned long long va = load_relaxed(&sh->accepted), vf = load_relaxed(&sh->finished);
+#pragma unroll
+        for (int o = kShards / 2; o > 0; o >>= 1) {
+            va += __shfl_xor(va, o, 64);
+            vf += __shfl_xor(vf, o, 64);
+        }
+        const unsigned long long acc = bcast_lane0(va);
+        if (acc >= P.target) return false;
+        // tiles wanted beyond those taken, by the acceptance of the finished ones
+        const float nx = (float)next, fin = (float)bcast_lane0(vf), ac = (float)acc;
+        float est = 4.0f * nx + 256.0f;
+        if (acc != 0ull) {
+            const float all = (float)P.target * (fin / ac);
+            est = fmaxf(all - nx, 0.0f);
+            const bool enough = all * (1.0f + 4.0f * __builtin_amdgcn_rsqf(ac)) <= nx && acc >= 64ull;
+            if (__builtin_amdgcn_readfirstlane(enough && !keeper)) return false;
+        }
+        rem = fminf(rem, 2.0f * est);
+    }
+    const int want = (int)fminf(rem * share, (float)kClaimTiles);
+    const int len = __builtin_amdgcn_readfirstlane(want < kMinClaim ? kMinClaim : want & ~1);
+    b = P.static_tiles +
+        bcast_lane0(atomicAdd(&C->next_tile, lane == 0 ? (unsigned long long)len : 0ull));
+    e = b + len < P.n_tiles ? b + len : P.n_tiles;
+    return b < P.n_tiles;
+}
+
+// The claim's proposals for the FP64 pass, one list reservation per claim: lane
+// c holds the bits of tile c (first proposal i0 + 32 c).
+__device__ __forceinline__ void push_deferred(const KernelArgs &a, DevCounters *C, int p, uint64_t i0, uint32_t bits,
+                                              int lane)
+{
+    if (__ballot(bits != 0u) == 0ull) return;
+    const int cnt = __popc(bits);
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+    }
+    const unsigned long long total = (unsigned)__builtin_amdgcn_readlane(incl, 63);
+    const unsigned long long slot = bcast_lane0(atomicAdd(a.defer_count, lane == 0 ? total : 0ull));
+    atomicAdd(&C->shard[blockIdx.x % kShards].deferred, lane == 0 ? total : 0ull);
+    unsigned long long pos = slot + (unsigned)(incl - cnt);
+    while (bits) {
+        const int b = __ffs(bits) - 1;
+        bits &= bits - 1;
+        if (pos < a.defer_cap) a.defer_list[pos] = pack_defer(p, i0 + 32u * lane + b);
+        ++pos;
+    }
+}
+
+// What a wave has seen of a point since it last reported: violations of the
+// bound and the largest log a.  Reported when the wave leaves the point.
+struct PointTally {
+    unsigned int n_viol = 0;
+    float max_la = -INFINITY;
+    __device__ __forceinline__ void report(DevCounters *C, int lane)
+    {
+        CounterShard &S = C->shard[blockIdx.x % kShards];
+        if (__ballot(n_viol != 0u) != 0ull) {
+            unsigned int v = n_viol;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            add_lane0(&S.violations, v, lane);
+        }
+        float m = max_la;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        if (__builtin_amdgcn_readfirstlane(__float_as_uint(m)) == __float_as_uint(-INFINITY)) return;  // no work
+        const unsigned int key = __builtin_amdgcn_readfirstlane(float_key(m));
+        const unsigned int have = __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(&S.max_log_a_key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (key > have) atomicMax(&S.max_log_a_key, lane == 0 ? key : 0u);
+        n_viol = 0;
+        max_la = -INFINITY;
+    }
+};
+
+// Accepted-count mode: the finished tiles and their definite accepts (lane c:
+// the word of tile c).
+__device__ __forceinline__ void count_accepted(const DevPoint &P, DevCounters *C, uint32_t word, int len, int lane)
+{
+    if (P.target == ~0ull) return;  // proposal-count mode: the segments count
+    unsigned int v = __popc(word);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    CounterShard &S = C->shard[blockIdx.x % kShards];
+    add_lane0(&S.accepted, v, lane);
+    add_lane0(&S.finished, (unsigned long long)len, lane);
+}
+
+// The waves that stay with point p until its target is met (claim_tiles).
+__device__ __forceinline__ bool keeper_wave(int p, unsigned gwave, unsigned W)
+{
+    return W < 64u || ((gwave + (unsigned)p) & 31u) == 0u;
+}
+
+// The work of one wave over the points of a launch: its even share of every
+// point, then claims from the points' queues until all are empty.  next()
+// gives at most kClaimTiles tiles [base, base + len) of point p.
+template <int K>
+struct WaveWork {
+    unsigned long long cur = 0, end = 0;  // tiles in hand
+    int cursor, todo, misses = 0, p = -1; // todo: points whose share has not been taken
+    __device__ __forceinline__ WaveWork(unsigned gwave, int n_plist) : cursor((int)(gwave % (unsigned)n_plist)), todo(n_plist) {}
+    __device__ __forceinline__ bool next(const KernelArgs &a, const int *plist, int n_plist, unsigned gwave, unsigned W,
+                                         float share, int lane, PointTally &tally, unsigned long long &base, int &len)
+    {
+        // every quantity of this loop is wave-uniform; said for the compiler,
+        // which otherwise keeps the point's constants per lane
+        while (bcast_lane0(cur) >= bcast_lane0(end)) {
+            misses = __builtin_amdgcn_readfirstlane(misses);
+            todo = __builtin_amdgcn_readfirstlane(todo);
+            cursor = __builtin_amdgcn_readfirstlane(cursor);
+            p = __builtin_amdgcn_readfirstlane(p);
+            if (misses >= n_plist) {
+                if (p >= 0) tally.report(a.cnt + p, lane);
+                return false;
+            }
+            const int q = __builtin_amdgcn_readfirstlane(plist[cursor]);
+            if (q != p) {
+                if (p >= 0) tally.report(a.cnt + p, lane);
+                p = q;
+            }
+            const DevPoint &P = a.pts[q];
+            if (todo > 0) {
+                static_range(P, q, gwave, W, cur, end);
+                --todo;
+                cursor = (cursor + 1 == n_plist) ? 0 : cursor + 1;
+            } else if (claim_tiles<K>(P, a.cnt + q, lane, share, keeper_wave(q, gwave, W), cur, end)) {
+                misses = 0;
+            } else {
+                cur = end = 0;
+                cursor = (cursor + 1 == n_plist) ? 0 : cursor + 1;
+                ++misses;
+            }
+        }
+        base = bcast_lane0(cur);
+        const unsigned long long left = bcast_lane0(end) - base;
+        len = (int)(left < (unsigned long long)kClaimTiles ? left : (unsigned long long)kClaimTiles);
+        cur = base + len;
+        return true;
+    }
+};
+
 // log f = -beta'/(E0 K^2) (H2 - c H3) in FP64 at a point x of the sphere with
 // t = sum k^2 s_k: H2 = E0 t by Parseval and H3 by the double sum over the
 // triads k + (n - k) = n (Sec. IV.A).

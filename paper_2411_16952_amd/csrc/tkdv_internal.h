@@ -22,8 +22,30 @@ constexpr int decide_block(int K) { return K == 128 ? 768 : kBlock; }
 // lane; four waves spill inside the tile loop).
 constexpr int kHalfPeriod64Block = 768;
 constexpr int kSynthBlock = 512;   // threads per workgroup of the standalone synthesis kernel
-constexpr int kClaimTiles = 64;    // tiles claimed per work-queue claim (2048 proposals);
+constexpr int kClaimTiles = 64;    // most tiles of a work-queue claim (2048 proposals);
                                    // lane c keeps the accept word of tile c
+// Accepted-count sampling of one point or a batch decides at least this many
+// tiles (2^21 proposals, divided among the points), target met or not.
+constexpr uint64_t kAlwaysTiles = 1ull << 16;
+// Tiles of a point's range of n tiles that are dealt out evenly to the waves
+// instead of claimed (one of n_points points in the call).  The claims of one
+// queue serialise on its counter, about 20 ns each: guided claims down to two
+// tiles took 0.64 ms for a million proposals at K = 8, claims of a fixed 64 tiles
+// 0.22 ms with 489 waves busy, even shares 0.15 ms (decisions 90 -> 30 us); and
+// 2e7 proposals at K = 16 with FP32 products 0.94 ms claimed, 0.82 ms dealt out.
+// But the waves of a SIMD advance at different speeds (the oldest first), so
+// that a long even share leaves the youngest alone at its end: a billion
+// proposals at K = 32 took 50.2 ms claimed, 52.3 ms with half and 56.6 ms with
+// 7/8 of them dealt out.  So ranges up to 2^20 tiles per call are dealt out
+// and larger ones claimed.  at_least: tiles wanted in any case (accepted-count
+// mode, where the rest of the range may not be needed).
+constexpr uint64_t kMaxStatic = 1ull << 20;
+constexpr uint64_t static_share(uint64_t n, uint64_t at_least, int n_points)
+{
+    const uint64_t cap = kMaxStatic / (uint64_t)n_points;
+    if (at_least >= n) return n <= cap ? n : 0;
+    return at_least < cap ? at_least : cap;
+}
 constexpr int kSegWords = 2048;    // bitmap words per statistics segment (65536 proposals)
 constexpr int kNBins = TKDV_NBINS;
 constexpr int kMixBlock = 1024;    // threads per workgroup of the mixture sampling kernel
@@ -55,6 +77,7 @@ struct alignas(16) DevPoint {
     uint64_t n;              // proposals to cover (upper bound in accepted-count mode)
     uint64_t n_tiles;        // ceil(n / 32)
     uint64_t target;         // accepted-sample target (UINT64_MAX in proposal-count mode)
+    uint64_t static_tiles;   // the first tiles, dealt out evenly to the waves (static_share)
     uint64_t bm_off;         // first bitmap word of this point
     uint64_t seg_off;        // first statistics segment of this point
     uint64_t n_segs;         // statistics segments of this point
@@ -102,16 +125,41 @@ constexpr int mix_point_bytes()
     return 2 * mix_ytab_bf16_bytes<K>() + mix_ytab_f32_bytes<K>() + mix_rv_bytes<K>();
 }
 
-// Device-side counters per point (zeroed before every launch sequence).
-struct DevCounters {
-    unsigned long long next_tile;     // work-queue head (tiles)
-    unsigned long long accepted;      // decisions that were definite accepts
+// Device-side counters per point (zeroed before every launch sequence).  Updates
+// of one line by all waves serialise (10 to 20 ns each on a memory that eight
+// dies share), and in small calls all waves report at once; so what waves report
+// is spread over kShards lines, workgroup b using line b mod kShards (the
+// decisions of 2e6 proposals at K = 16 where nearly all are accepted: 0.31 ms
+// with one line, 0.18 ms with eight).
+constexpr int kShards = 8;
+struct alignas(128) CounterShard {
+    unsigned long long accepted;      // accepted-count mode: definite accepts of the finished tiles
+    unsigned long long finished;      // accepted-count mode: finished tiles
     unsigned long long violations;    // proposals with log a > 0
     unsigned long long deferred;      // proposals sent to the FP64 re-decision
-    unsigned long long last_index;    // accepted-count mode: index of the target-th sample
     unsigned int max_log_a_key;       // order-preserving encoding of the largest log a
     unsigned int pad;
 };
+struct alignas(128) DevCounters {
+    unsigned long long next_tile;     // work-queue head (tiles claimed after the static ones)
+    unsigned long long pad0[15];      // a line of its own: every claim goes through it
+    unsigned long long last_index;    // accepted-count mode: index of the target-th sample
+    unsigned long long pad1[15];
+    CounterShard shard[kShards];
+};
+// the sums over the shards
+constexpr CounterShard shard_totals(const DevCounters &c)
+{
+    CounterShard t = c.shard[0];
+    for (int s = 1; s < kShards; ++s) {
+        t.accepted += c.shard[s].accepted;
+        t.finished += c.shard[s].finished;
+        t.violations += c.shard[s].violations;
+        t.deferred += c.shard[s].deferred;
+        t.max_log_a_key = c.shard[s].max_log_a_key > t.max_log_a_key ? c.shard[s].max_log_a_key : t.max_log_a_key;
+    }
+    return t;
+}
 
 // Per-segment partial statistics (FP64 sums in a fixed order).
 struct SegStats {

@@ -34,51 +34,11 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
-__device__ __forceinline__ float wave_max_f32(float v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 __device__ __forceinline__ double wave_sum_f64(double v)
 {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
-}
-
-__device__ __forceinline__ unsigned long long load_relaxed(const unsigned long long *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Lane 0's value, as a wave-uniform (scalar) value.  The claim loops branch
-// on it: a per-lane copy would make their exits divergent for the compiler,
-// which may then split a loop so that lanes wait on a lane that has left it.
-__device__ __forceinline__ unsigned long long bcast_lane0(unsigned long long v)
-{
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return ((unsigned long long)hi << 32) | lo;
-}
-
-// Claim kClaimTiles tiles of point C's queue for this wave: every lane issues
-// the atomic (lane 0 adds, the others add 0) and lane 0's old value is taken,
-// so no lane-divergent region sits next to the loop back-edge (the compiler
-// may otherwise thread lanes 1-63 past lane 0's region to the broadcast and
-// split the wave).  ~0 when the point's accepted-sample target is met.
-__device__ __forceinline__ unsigned long long claim_tiles(const DevPoint &P, DevCounters *C, int lane)
-{
-    const bool open = P.target == ~0ull || bcast_lane0(load_relaxed(&C->accepted)) < P.target;
-    const unsigned long long old =
-        atomicAdd(&C->next_tile, (open && lane == 0) ? (unsigned long long)kClaimTiles : 0ull);
-    return open ? bcast_lane0(old) : ~0ull;
-}
-
-// Per-wave counter update with the same structure: lane 0's (wave-uniform) value.
-__device__ __forceinline__ void add_lane0(unsigned long long *ctr, unsigned long long v, int lane)
-{
-    if (bcast_lane0(v) != 0ull) atomicAdd(ctr, lane == 0 ? v : 0ull);
 }
 
 static_assert(kClaimTiles == kWave, "one accept word per lane per claim");
@@ -111,6 +71,7 @@ template <int K, int PREC, int PROP, int B = decide_block(K), int G = 1>
 __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, int n_plist)
 {
     static_assert(K < 16 || (K / 16) % G == 0, "G must divide the tile pairs");
+    if (a.d_total_segs && *a.d_total_segs == 0ull) return;  // a sweep window without unfinished points
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int tab = decide_tab_bytes<K, PREC>();
     if constexpr (!decide_half_period<K>()) {
@@ -128,27 +89,24 @@ __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, in
     const char *lds_hi = lds;
     const char *lds_lo = lds + tab;
     const int lane = threadIdx.x & 63, half = lane >> 5, pl = lane & 31;
-    const int gwave = blockIdx.x * (B / kWave) + (threadIdx.x >> 6);
-    int cursor = gwave % n_plist;
-    int misses = 0;
-    while (misses < n_plist) {
-        const int p = __builtin_amdgcn_readfirstlane(plist[cursor]);
+    const unsigned gwave = __builtin_amdgcn_readfirstlane(blockIdx.x * (B / kWave) + (threadIdx.x >> 6));
+    const unsigned W = gridDim.x * (B / kWave);
+    const float share = (float)n_plist / (2.0f * (float)W);
+    PointTally tally;
+    WaveWork<K> work(gwave, n_plist);
+    unsigned long long base;
+    int len;
+    while (work.next(a, plist, n_plist, gwave, W, share, lane, tally, base, len)) {
+        const int p = __builtin_amdgcn_readfirstlane(work.p);
         const DevPoint &P = a.pts[p];
         DevCounters *C = a.cnt + p;
-        const unsigned long long base = claim_tiles(P, C, lane);
-        if (base >= P.n_tiles) {
-            cursor = (cursor + 1 == n_plist) ? 0 : cursor + 1;
-            ++misses;
-            continue;
-        }
-        misses = 0;
-        unsigned long long n_acc = 0, n_def = 0;
-        unsigned int n_viol = 0;
-        float max_la = -INFINITY;
-        uint32_t my_word = 0u;  // accept bits of tile `lane` of this claim
-        for (int c = 0; c < kClaimTiles; ++c) {
+        // accept bits and FP64 bits of tile `lane` of this claim
+        uint32_t my_word = 0u, my_def = 0u;
+        for (int c = 0; c < len; ++c) {
+            // the point's constants stay in memory from tile to tile: hoisted out
+            // of this loop they would take K registers a lane
+            asm volatile("" ::: "memory");
             const unsigned long long tile = base + c;
-            if (tile >= P.n_tiles) break;
             const unsigned long long local = tile * kTile + pl;
             const bool valid = local < P.n;
             const uint64_t i = P.i0 + local;
@@ -180,11 +138,13 @@ __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, in
             const unsigned long long bacc = __ballot(accept);
             const unsigned long long bdef = __ballot(defer);
             if (lane == c) my_word = (uint32_t)bacc;
-            n_acc += __popcll(bacc);
+            if (bdef) {
+                if (lane == c) my_def = (uint32_t)bdef;
+            }
             if (mine) {
                 // window proposals are counted by their FP64 value (k_fixup)
-                n_viol += (la > 0.0f && !defer) ? 1u : 0u;
-                max_la = fmaxf(max_la, la);
+                tally.n_viol += (la > 0.0f && !defer) ? 1u : 0u;
+                tally.max_la = fmaxf(tally.max_la, la);
                 if (a.dbg_t) {
                     a.dbg_t[local] = t;
                     a.dbg_s3[local] = s3;
@@ -192,25 +152,11 @@ __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, in
                     a.dbg_log_u[local] = log_u_word(w_acc);
                 }
             }
-            if (bdef) {
-                const unsigned long long nd = __popcll(bdef);
-                const unsigned long long slot = bcast_lane0(atomicAdd(a.defer_count, lane == 0 ? nd : 0ull));
-                if (defer) {
-                    const unsigned long long pos = slot + __popcll(bdef & ((1ull << lane) - 1ull));
-                    if (pos < a.defer_cap) a.defer_list[pos] = pack_defer(p, i);
-                }
-                n_def += nd;
-            }
         }
         // one coalesced store of the claim's accept words
-        if (base + lane < P.n_tiles) a.bitmap[P.bm_off + base + lane] = my_word;
-        const unsigned long long viol = wave_sum_u64(n_viol);
-        max_la = wave_max_f32(max_la);
-        add_lane0(&C->accepted, n_acc, lane);
-        add_lane0(&C->violations, viol, lane);
-        add_lane0(&C->deferred, n_def, lane);
-        if (__builtin_amdgcn_readfirstlane(__float_as_uint(max_la)) != __float_as_uint(-INFINITY))
-            atomicMax(&C->max_log_a_key, lane == 0 ? float_key(max_la) : 0u);
+        if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
+        push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
+        count_accepted(P, C, my_word, len, lane);
     }
 }
 
@@ -272,6 +218,10 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
     const float *rv = reinterpret_cast<const float *>(lds + phi_bytes + ytab_bytes);
     const int lane = threadIdx.x & 63, half = lane >> 5, pl = lane & 31;
     const float Kf = (float)K;
+    // the workgroups come to the points in turn: all waves share each queue
+    const unsigned W = gridDim.x * (kMixBlock / kWave);
+    const unsigned gwave = __builtin_amdgcn_readfirstlane(blockIdx.x * (kMixBlock / kWave) + (threadIdx.x >> 6));
+    const float share = 1.0f / (2.0f * (float)W);
     for (int q = 0; q < n_plist; ++q) {
         const int p = __builtin_amdgcn_readfirstlane(plist[(blockIdx.x + q) % n_plist]);
         const DevPoint &P = a.pts[p];
@@ -296,16 +246,17 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
             for (int v = threadIdx.x; v < rv_bytes / 16; v += kMixBlock) drv[v] = srv[v];
         }
         __syncthreads();
-        while (true) {
-            const unsigned long long base = claim_tiles(P, C, lane);
-            if (base >= P.n_tiles) break;  // scalar branch
-            unsigned long long n_acc = 0, n_def = 0;
-            unsigned int n_viol = 0;
-            float max_la = -INFINITY;
-            uint32_t my_word = 0u;
-            for (int c = 0; c < kClaimTiles; ++c) {
+        PointTally tally;
+        unsigned long long cur, end;
+        static_range(P, p, gwave, W, cur, end);
+        while (cur < end || claim_tiles<K>(P, C, lane, share, keeper_wave(p, gwave, W), cur, end)) {  // scalar branches
+            const unsigned long long base = bcast_lane0(cur), left = bcast_lane0(end) - base;
+            const int len = (int)(left < (unsigned long long)kClaimTiles ? left : (unsigned long long)kClaimTiles);
+            cur = base + len;
+            uint32_t my_word = 0u, my_def = 0u;
+            for (int c = 0; c < len; ++c) {
+                asm volatile("" ::: "memory");  // as in k_decide: no hoisting of the constants
                 const unsigned long long tile = base + c;
-                if (tile >= P.n_tiles) break;
                 const unsigned long long local = tile * kTile + pl;
                 const bool valid = local < P.n;
                 const uint64_t i = P.i0 + local;
@@ -357,10 +308,12 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
                 const unsigned long long bacc = __ballot(accept);
                 const unsigned long long bdef = __ballot(defer);
                 if (lane == c) my_word = (uint32_t)bacc;
-                n_acc += __popcll(bacc);
+                if (bdef) {
+                    if (lane == c) my_def = (uint32_t)bdef;
+                }
                 if (mine) {
-                    n_viol += (la > 0.0f && !defer) ? 1u : 0u;  // window proposals: k_fixup_mix
-                    max_la = fmaxf(max_la, la);
+                    tally.n_viol += (la > 0.0f && !defer) ? 1u : 0u;  // window proposals: k_fixup_mix
+                    tally.max_la = fmaxf(tally.max_la, la);
                     if (a.dbg_t) {
                         a.dbg_t[local] = t;
                         a.dbg_s3[local] = s3;
@@ -368,26 +321,12 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
                         a.dbg_log_u[local] = log_u_word(w_acc);
                     }
                 }
-                if (bdef) {
-                    const unsigned long long nd = __popcll(bdef);
-                    const unsigned long long slot =
-                        bcast_lane0(atomicAdd(a.defer_count, lane == 0 ? nd : 0ull));
-                    if (defer) {
-                        const unsigned long long pos = slot + __popcll(bdef & ((1ull << lane) - 1ull));
-                        if (pos < a.defer_cap) a.defer_list[pos] = pack_defer(p, i);
-                    }
-                    n_def += nd;
-                }
             }
-            if (base + lane < P.n_tiles) a.bitmap[P.bm_off + base + lane] = my_word;
-            const unsigned long long viol = wave_sum_u64(n_viol);
-            max_la = wave_max_f32(max_la);
-            add_lane0(&C->accepted, n_acc, lane);
-            add_lane0(&C->violations, viol, lane);
-            add_lane0(&C->deferred, n_def, lane);
-            if (__builtin_amdgcn_readfirstlane(__float_as_uint(max_la)) != __float_as_uint(-INFINITY))
-                atomicMax(&C->max_log_a_key, lane == 0 ? float_key(max_la) : 0u);
+            if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
+            push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
+            count_accepted(P, C, my_word, len, lane);
         }
+        tally.report(C, lane);
     }
 }
 
@@ -495,8 +434,8 @@ __global__ void __launch_bounds__(kBlock) k_fixup(KernelArgs a)
                 atomicOr(&a.bitmap[P.bm_off + local / 32], 1u << (local % 32));
             }
             if (la > 0.0) {  // f/(M g) > 1 (eq. M_sup broken): counted here for window proposals
-                atomicAdd(&a.cnt[p].violations, 1ull);
-                atomicMax(&a.cnt[p].max_log_a_key, float_key((float)la));
+                atomicAdd(&a.cnt[p].shard[0].violations, 1ull);
+                atomicMax(&a.cnt[p].shard[0].max_log_a_key, float_key((float)la));
             }
         }
         // the next proposals overwrite this wave's copies of x^
@@ -672,8 +611,8 @@ __global__ void __launch_bounds__(kBlock) k_fixup_mix(KernelArgs a)
             if (__builtin_amdgcn_readlane((int)viol, 32 * hh) != 0) {
                 const int pp = __builtin_amdgcn_readlane(p, 32 * hh);
                 const unsigned int key = __builtin_amdgcn_readlane(float_key((float)log_a), 32 * hh);
-                atomicAdd(&a.cnt[pp].violations, lane == 0 ? 1ull : 0ull);
-                atomicMax(&a.cnt[pp].max_log_a_key, lane == 0 ? key : 0u);
+                atomicAdd(&a.cnt[pp].shard[0].violations, lane == 0 ? 1ull : 0ull);
+                atomicMax(&a.cnt[pp].shard[0].max_log_a_key, lane == 0 ? key : 0u);
             }
         }
         // the next proposals overwrite this wave's copies of x^
@@ -695,12 +634,6 @@ __device__ __forceinline__ int point_of_segment(const DevPoint *pts, int n_point
     return lo;
 }
 
-__device__ __forceinline__ unsigned long long processed_words(const DevPoint &P, const DevCounters &C)
-{
-    const unsigned long long nt = C.next_tile;
-    return nt < P.n_tiles ? nt : P.n_tiles;
-}
-
 __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a, unsigned long long total_segs,
                                                       unsigned long long *seg_cnt)
 {
@@ -709,7 +642,7 @@ __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a, unsigned lon
     for (unsigned long long gs = blockIdx.x; gs < total_segs; gs += gridDim.x) {
         const int p = point_of_segment(a.pts, a.n_points, gs);
         const DevPoint &P = a.pts[p];
-        const unsigned long long nw = processed_words(P, a.cnt[p]);
+        const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
         const unsigned long long w0 = (gs - P.seg_off) * kSegWords;
         unsigned long long c = 0;
         for (int k = threadIdx.x; k < kSegWords; k += kBlock) {
@@ -753,8 +686,8 @@ __global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a, const unsigned 
         }
         if (threadIdx.x == 0) {
             res[p].n_accepted = run;
-            res[p].n_processed = processed_words(P, a.cnt[p]) * kTile < P.n
-                                     ? processed_words(P, a.cnt[p]) * kTile
+            res[p].n_processed = tiles_taken(P, a.cnt[p].next_tile) * kTile < P.n
+                                     ? tiles_taken(P, a.cnt[p].next_tile) * kTile
                                      : P.n;
         }
         __syncthreads();
@@ -813,7 +746,7 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, const int 
         const unsigned long long limit = P.target;  // ranks >= target are not part of the result
         if (!mine_k || seg_cnt[gs] == 0 || seg_base[gs] >= limit) continue;  // block-uniform
         for (int b = threadIdx.x; b < kNBins; b += kBlock) hist[b] = 0u;
-        const unsigned long long nw = processed_words(P, a.cnt[p]);
+        const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
         const unsigned long long seg_w0 = (gs - P.seg_off) * kSegWords;
         const unsigned long long w_first = seg_w0 + (unsigned long long)wv * kWaveWords;
         // this wave's accepted count -> rank base
@@ -1126,9 +1059,10 @@ __global__ void __launch_bounds__(1024) k_window_advance(DevPoint *pts, const De
         for (int b = 0; b < kNBins; ++b) S.total.hist[b] += r.hist[b];
         S.accepted += r.n_samples;
         S.written += r.n_written;
-        S.n_fixups += c.deferred;
-        S.n_violations += c.violations;
-        if (c.max_log_a_key > S.max_log_a_key) S.max_log_a_key = c.max_log_a_key;
+        const CounterShard ct = shard_totals(c);
+        S.n_fixups += ct.deferred;
+        S.n_violations += ct.violations;
+        if (ct.max_log_a_key > S.max_log_a_key) S.max_log_a_key = ct.max_log_a_key;
         if (S.accepted >= S.target) {
             S.n_proposed = c.last_index - S.i_start + 1;
             S.done = 1;
@@ -1170,6 +1104,7 @@ __global__ void __launch_bounds__(1024) k_window_advance(DevPoint *pts, const De
         if (S.done) {
             P.n = 0;
             P.n_tiles = 0;
+            P.static_tiles = 0;
             P.n_segs = 0;
             continue;
         }
@@ -1187,6 +1122,13 @@ __global__ void __launch_bounds__(1024) k_window_advance(DevPoint *pts, const De
         P.n_tiles = (P.n + kTile - 1) / kTile;
         P.n_segs = (P.n_tiles + kSegWords - 1) / kSegWords;
         P.target = S.target - S.accepted;
+        // dealt out evenly: three quarters of what the measured acceptance asks for
+        const double used = (double)(P.i0 - S.i_start);
+        P.static_tiles = static_share(
+            P.n_tiles,
+            S.accepted > 0 ? (unsigned long long)(0.75 / kTile * (double)P.target * used / (double)S.accepted)
+                           : P.n_tiles / 4,
+            n_points);
         P.capacity = S.capacity > S.written ? S.capacity - S.written : 0;
         P.out_off = S.out_off + S.written;
         bm += P.n_tiles;
@@ -1234,8 +1176,8 @@ static hipError_t launch_decide_t(const KernelArgs &a, const int *plist, int n_p
     if (e != hipSuccess) return e;
     if (a.blocks_per_cu > 0 && a.blocks_per_cu < per_cu) per_cu = a.blocks_per_cu;
     if (per_cu < 1) per_cu = 1;
-    unsigned long long want = (total_tiles + (unsigned long long)(B / kWave) * kClaimTiles - 1) /
-                              ((unsigned long long)(B / kWave) * kClaimTiles);
+    // at least two tiles per wave (the shortest claim)
+    unsigned long long want = (total_tiles + 2ull * (B / kWave) - 1) / (2ull * (B / kWave));
     unsigned long long grid = (unsigned long long)per_cu * n_cu;
     if (want < grid) grid = want;
     if (grid < 1) grid = 1;
@@ -1406,8 +1348,7 @@ static hipError_t launch_decide_mix_t(const KernelArgs &a, const int *plist, int
     if (e != hipSuccess) return e;
     if (a.blocks_per_cu > 0 && a.blocks_per_cu < per_cu) per_cu = a.blocks_per_cu;
     if (per_cu < 1) per_cu = 1;
-    unsigned long long want = (total_tiles + (unsigned long long)(kMixBlock / kWave) * kClaimTiles - 1) /
-                              ((unsigned long long)(kMixBlock / kWave) * kClaimTiles);
+    unsigned long long want = (total_tiles + 2ull * (kMixBlock / kWave) - 1) / (2ull * (kMixBlock / kWave));
     unsigned long long grid = (unsigned long long)per_cu * n_cu;
     if (want < grid) grid = want;
     if (grid < 1) grid = 1;

@@ -12,25 +12,8 @@ namespace tkdv {
 
 namespace {
 
-// Work-queue claim as in the other decision kernels: every lane issues the
-// atomic (lane 0 adds), lane 0's old value broadcast; ~0 when the target is met.
-__device__ __forceinline__ unsigned long long claim128(const DevPoint &P, DevCounters *C, int lane)
-{
-    const bool open =
-        P.target == ~0ull ||
-        bcast0(__hip_atomic_load(&C->accepted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < P.target;
-    const unsigned long long old =
-        atomicAdd(&C->next_tile, (open && lane == 0) ? (unsigned long long)kClaimTiles : 0ull);
-    return open ? bcast0(old) : ~0ull;
-}
-__device__ __forceinline__ void add0(unsigned long long *ctr, unsigned long long v, int lane)
-{
-    if (bcast0(v) != 0ull) atomicAdd(ctr, lane == 0 ? v : 0ull);
-}
-
-
 // ---------------------------------------------------------------------------
-// k_decide128: persistent; claims of 64 accept words (2048 proposals, 128
+// k_decide128: persistent; claims of up to 64 accept words (2048 proposals, 128
 // tiles of 16) from per-point queues, as the other decision kernels.
 // ---------------------------------------------------------------------------
 // DBG: the verification entry's instantiation (per-proposal outputs written,
@@ -43,6 +26,7 @@ __device__ __forceinline__ void add0(unsigned long long *ctr, unsigned long long
 template <int K, int PREC, int PROP, bool DBG, int BL = decide_block(K)>
 __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist, int n_plist)
 {
+    if (a.d_total_segs && *a.d_total_segs == 0ull) return;  // a sweep window without unfinished points
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int B = BL, CPL = K / 4;
     {
@@ -58,27 +42,22 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
     const char *lds_hi = lds;
     const char *lds_lo = lds + (PREC == PREC_FP32 ? 0 : Quarter<K>::BF16_BYTES);
     const int lane = threadIdx.x & 63, g = lane >> 4, pl = lane & 15;
-    const int gwave = blockIdx.x * (B / kWave) + (threadIdx.x >> 6);
-    int cursor = gwave % n_plist;
-    int misses = 0;
-    while (misses < n_plist) {
-        const int p = __builtin_amdgcn_readfirstlane(plist[cursor]);
+    const unsigned gwave = __builtin_amdgcn_readfirstlane(blockIdx.x * (B / kWave) + (threadIdx.x >> 6));
+    const unsigned W = gridDim.x * (B / kWave);
+    const float share = (float)n_plist / (2.0f * (float)W);
+    PointTally tally;
+    WaveWork<K> work(gwave, n_plist);
+    unsigned long long base;
+    int len;
+    while (work.next(a, plist, n_plist, gwave, W, share, lane, tally, base, len)) {
+        const int p = __builtin_amdgcn_readfirstlane(work.p);
         const DevPoint &P = a.pts[p];
         DevCounters *C = a.cnt + p;
-        const unsigned long long base = claim128(P, C, lane);
-        if (base >= P.n_tiles) {
-            cursor = (cursor + 1 == n_plist) ? 0 : cursor + 1;
-            ++misses;
-            continue;
-        }
-        misses = 0;
-        unsigned long long n_acc = 0, n_def = 0;
-        unsigned int n_viol = 0;
-        float max_la = -INFINITY;
-        uint32_t my_word = 0u;  // accept bits of word `lane` of this claim
-        for (int c2 = 0; c2 < 2 * kClaimTiles; ++c2) {
+        // accept bits and FP64 bits of word `lane` of this claim
+        uint32_t my_word = 0u, my_def = 0u;
+        for (int c2 = 0; c2 < 2 * len; ++c2) {
+            asm volatile("" ::: "memory");  // as in k_decide: no hoisting of the constants
             const unsigned long long word = base + (c2 >> 1);
-            if (word >= P.n_tiles) break;
             const unsigned long long local = word * kTile + (c2 & 1) * kTile16 + pl;
             const bool valid = local < P.n;
             const uint64_t i = P.i0 + local;
@@ -140,10 +119,12 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
             const unsigned long long bacc = __ballot(accept);
             const unsigned long long bdef = __ballot(defer);
             if (lane == (c2 >> 1)) my_word |= (uint32_t)(bacc & 0xffffull) << (16 * (c2 & 1));
-            n_acc += __popcll(bacc);
+            if (bdef) {
+                if (lane == (c2 >> 1)) my_def |= (uint32_t)(bdef & 0xffffull) << (16 * (c2 & 1));
+            }
             if (mine) {
-                n_viol += (la > 0.0f && !defer) ? 1u : 0u;  // window proposals: k_fixup
-                max_la = fmaxf(max_la, la);
+                tally.n_viol += (la > 0.0f && !defer) ? 1u : 0u;  // window proposals: k_fixup
+                tally.max_la = fmaxf(tally.max_la, la);
                 if (DBG && a.dbg_t) {
                     a.dbg_t[local] = t;
                     a.dbg_s3[local] = s3;
@@ -151,24 +132,10 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
                     a.dbg_log_u[local] = log_u_word(w_acc);
                 }
             }
-            if (bdef) {
-                const unsigned long long nd = __popcll(bdef);
-                const unsigned long long slot = bcast0(atomicAdd(a.defer_count, lane == 0 ? nd : 0ull));
-                if (defer) {
-                    const unsigned long long pos = slot + __popcll(bdef & ((1ull << lane) - 1ull));
-                    if (pos < a.defer_cap) a.defer_list[pos] = pack_defer(p, i);
-                }
-                n_def += nd;
-            }
         }
-        if (base + lane < P.n_tiles) a.bitmap[P.bm_off + base + lane] = my_word;
-        const unsigned long long viol = wave_sum_u64_128(n_viol);
-        max_la = wave_max_128(max_la);
-        add0(&C->accepted, n_acc, lane);
-        add0(&C->violations, viol, lane);
-        add0(&C->deferred, n_def, lane);
-        if (__builtin_amdgcn_readfirstlane(__float_as_uint(max_la)) != __float_as_uint(-INFINITY))
-            atomicMax(&C->max_log_a_key, lane == 0 ? float_key(max_la) : 0u);
+        if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
+        push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
+        count_accepted(P, C, my_word, len, lane);
     }
 }
 
@@ -234,8 +201,7 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
         const unsigned long long limit = P.target;  // ranks >= target are not part of the result
         if (P.K != K || P.proposal != PROP || seg_cnt[gs] == 0 || seg_base[gs] >= limit) continue;  // uniform
         for (int b = threadIdx.x; b < kNBins; b += B) hist[b] = 0u;
-        const unsigned long long nt = a.cnt[p].next_tile;
-        const unsigned long long nw = nt < P.n_tiles ? nt : P.n_tiles;
+        const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
         const unsigned long long w_first = (gs - P.seg_off) * kSegWords + (unsigned long long)wv * WW;
         unsigned long long cw = 0;
         for (int k = lane; k < WW; k += kWave) {
@@ -565,7 +531,7 @@ hipError_t launch_decide128_t(const KernelArgs &a, const int *plist, int n_plist
     if (e != hipSuccess) return e;
     if (a.blocks_per_cu > 0 && a.blocks_per_cu < per_cu) per_cu = a.blocks_per_cu;
     if (per_cu < 1) per_cu = 1;
-    const unsigned long long per_block = (unsigned long long)(B / kWave) * kClaimTiles;
+    const unsigned long long per_block = 2ull * (B / kWave);  // at least two accept words per wave
     unsigned long long want = (total_tiles + per_block - 1) / per_block;
     unsigned long long grid = (unsigned long long)per_cu * n_cu;
     if (want < grid) grid = want;
