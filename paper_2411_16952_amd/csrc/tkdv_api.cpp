@@ -62,7 +62,7 @@ struct tkdv_ctx {
     int device = 0;
     int n_cu = 0;
     std::string last_error;
-    DevBuf bitmap, defer_list, defer_count, counters, points, seg_cnt, seg_base, seg_stats, results, plist;
+    DevBuf bitmap, defer_list, defer_count, counters, points, seg, seg_cnt, seg_base, seg_stats, hist, results, plist;
     DevBuf mix, mix_tab;  // learned-proposal constants and tables of the current call
     // K = 128 (index 4): the quarter-period tables of k_decide128 (BF16 hi, lo, FP32)
     DevBuf phi_hi[kNumK], phi_lo[kNumK], phi_f32[kNumK];
@@ -424,7 +424,7 @@ struct Call {
     std::vector<DevPoint> pts;
     std::vector<int> plist_off, plist_n;  // per K index
     std::vector<int> plist;               // concatenated point lists
-    unsigned long long total_tiles = 0, total_segs = 0, bitmap_words = 0;
+    unsigned long long total_tiles = 0, max_segs = 0, bitmap_words = 0;
 };
 
 // Device buffers of one launch sequence (from the context's growable buffers,
@@ -434,7 +434,9 @@ struct Workspace {
     unsigned long long *defer_list, *defer_count, defer_cap;
     DevCounters *counters;
     DevPoint *points;
-    unsigned long long *seg_cnt, *seg_base;
+    SegPlan *seg;
+    unsigned int *seg_cnt;
+    unsigned long long *seg_base, *hist;
     SegStats *seg_stats;
     PointResult *results;
     int *plist;
@@ -448,7 +450,7 @@ struct CallView {
     const int *plist;
     int plist_len;
     int plist_off[kNumK], plist_n[kNumK];
-    unsigned long long total_segs;
+    unsigned long long max_segs;
 };
 
 CallView view_of(const Call &call)
@@ -462,7 +464,7 @@ CallView view_of(const Call &call)
         v.plist_off[ki] = call.plist_off[ki];
         v.plist_n[ki] = call.plist_n[ki];
     }
-    v.total_segs = call.total_segs;
+    v.max_segs = call.max_segs;
     return v;
 }
 
@@ -488,9 +490,16 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
     HIP_TRY(ctx, launch_fill_u32(w.counters, sizeof(DevCounters) * np / 4, 0u, st));
     HIP_TRY(ctx, launch_fill_u32(w.results, sizeof(PointResult) * np / 4, 0u, st));
     HIP_TRY(ctx, launch_fill_u32(w.defer_count, 2, 0u, st));
+    HIP_TRY(ctx, launch_fill_u32(w.hist, (unsigned long long)np * kShards * kNBins * 2, 0u, st));
 
     KernelArgs a;
     std::memset(&a, 0, sizeof(a));
+    a.seg = w.seg;
+    a.seg_cnt = w.seg_cnt;
+    a.seg_base = w.seg_base;
+    a.seg_stats = w.seg_stats;
+    a.hist = w.hist;
+    a.res = w.results;
     a.pts = w.points;
     a.n_points = np;
     a.cnt = w.counters;
@@ -528,21 +537,23 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
     }
     HIP_TRY(ctx, hipEventRecord(ctx->ev[1], st));
     auto fixup = proposal == TKDV_PROP_MIXTURE ? launch_fixup_mix : launch_fixup;
-    for (int ki = 0; ki < kNumK; ++ki)
-        if (v.plist_n[ki]) HIP_TRY(ctx, fixup(8 << ki, a, ctx->n_cu, st));
+    bool plan = stats;  // the first launch lays out the segments
+    for (int ki = 0; ki < kNumK; ++ki) {
+        if (v.plist_n[ki] == 0) continue;
+        HIP_TRY(ctx, fixup(8 << ki, a, plan, ctx->n_cu, st));
+        plan = false;
+    }
     HIP_TRY(ctx, hipEventRecord(ctx->ev[2], st));
     if (stats) {
-        HIP_TRY(ctx, launch_segments(a, v.total_segs, w.seg_cnt, w.seg_base, w.results, ctx->n_cu, st));
+        HIP_TRY(ctx, launch_segments(a, v.max_segs, ctx->n_cu, st));
         HIP_TRY(ctx, hipEventRecord(ctx->ev[3], st));
         for (int ki = 0; ki < kNumK; ++ki) {
             if (v.plist_n[ki] == 0) continue;
             a.phi_hi = ki >= 3 ? ctx->qstat[ki - 3].p : ctx->phi_f32[ki].p;
-            HIP_TRY(ctx, launch_materialize(8 << ki, proposal, a, d_plist + v.plist_off[ki], v.plist_n[ki],
-                                            v.total_segs, w.seg_cnt, w.seg_base, w.seg_stats, w.results, d_xhat,
-                                            d_index, ctx->n_cu, st));
+            HIP_TRY(ctx, launch_materialize(8 << ki, proposal, a, v.max_segs, d_xhat, d_index, ctx->n_cu, st));
         }
         HIP_TRY(ctx, hipEventRecord(ctx->ev[4], st));
-        HIP_TRY(ctx, launch_finalize(a, w.seg_cnt, w.seg_base, w.seg_stats, w.results, st));
+        HIP_TRY(ctx, launch_finalize(a, st));
         HIP_TRY(ctx, hipEventRecord(ctx->ev[5], st));
         HIP_TRY(ctx, hipMemcpyAsync(ctx->h_results, w.results, sizeof(PointResult) * np, hipMemcpyDeviceToHost, st));
     }
@@ -578,6 +589,17 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
     return TKDV_OK;
 }
 
+// The ordered output's buffers for at most max_segs segments and np points.
+hipError_t ensure_segments(tkdv_ctx *ctx, unsigned long long max_segs, int np)
+{
+    hipError_t e = ensure(ctx->seg, seg_plan_bytes(np));
+    if (e == hipSuccess) e = ensure(ctx->seg_cnt, sizeof(unsigned int) * max_segs);
+    if (e == hipSuccess) e = ensure(ctx->seg_base, sizeof(unsigned long long) * max_segs);
+    if (e == hipSuccess) e = ensure(ctx->seg_stats, sizeof(SegStats) * max_segs);
+    if (e == hipSuccess) e = ensure(ctx->hist, sizeof(unsigned long long) * kShards * kNBins * (size_t)np);
+    return e;
+}
+
 // One sampling call with the context's buffers, grown as the call needs.
 tkdv_status run(tkdv_ctx *ctx, Call &call, int precision, int proposal, float *d_xhat,
                 unsigned long long *d_index, hipStream_t st, std::vector<PointResult> *res_out,
@@ -593,9 +615,7 @@ tkdv_status run(tkdv_ctx *ctx, Call &call, int precision, int proposal, float *d
     HIP_TRY(ctx, ensure(ctx->defer_count, 16));
     HIP_TRY(ctx, ensure(ctx->counters, sizeof(DevCounters) * np));
     HIP_TRY(ctx, ensure(ctx->points, sizeof(DevPoint) * np));
-    HIP_TRY(ctx, ensure(ctx->seg_cnt, 8 * std::max<unsigned long long>(call.total_segs, 1)));
-    HIP_TRY(ctx, ensure(ctx->seg_base, 8 * std::max<unsigned long long>(call.total_segs, 1)));
-    HIP_TRY(ctx, ensure(ctx->seg_stats, sizeof(SegStats) * std::max<unsigned long long>(call.total_segs, 1)));
+    HIP_TRY(ctx, ensure_segments(ctx, call.max_segs, np));
     HIP_TRY(ctx, ensure(ctx->results, sizeof(PointResult) * np));
     HIP_TRY(ctx, ensure(ctx->plist, sizeof(int) * call.plist.size()));
     HIP_TRY(ctx, ensure_host(ctx->h_points, ctx->h_points_bytes, sizeof(DevPoint) * np));
@@ -614,8 +634,10 @@ tkdv_status run(tkdv_ctx *ctx, Call &call, int precision, int proposal, float *d
     w.defer_cap = defer_cap;
     w.counters = reinterpret_cast<DevCounters *>(ctx->counters.p);
     w.points = reinterpret_cast<DevPoint *>(ctx->points.p);
-    w.seg_cnt = reinterpret_cast<unsigned long long *>(ctx->seg_cnt.p);
+    w.seg = reinterpret_cast<SegPlan *>(ctx->seg.p);
+    w.seg_cnt = reinterpret_cast<unsigned int *>(ctx->seg_cnt.p);
     w.seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
+    w.hist = reinterpret_cast<unsigned long long *>(ctx->hist.p);
     w.seg_stats = reinterpret_cast<SegStats *>(ctx->seg_stats.p);
     w.results = reinterpret_cast<PointResult *>(ctx->results.p);
     w.plist = reinterpret_cast<int *>(ctx->plist.p);
@@ -701,7 +723,7 @@ tkdv_status prepare(tkdv_ctx *ctx, Call &call, int n_points, const tkdv_point *p
     call.plist_n.assign(kNumK, 0);
     call.plist_off.assign(kNumK, 0);
     std::vector<std::vector<int>> by_k(kNumK);
-    unsigned long long bm = 0, segs = 0, tiles = 0;
+    unsigned long long bm = 0, tiles = 0;
     for (int p = 0; p < n_points; ++p) {
         tkdv_status s = check_point(ctx, pts[p]);
         if (s != TKDV_OK) return s;
@@ -729,13 +751,10 @@ tkdv_status prepare(tkdv_ctx *ctx, Call &call, int n_points, const tkdv_point *p
                                                      : d.n_tiles,
                                       n_points);
         d.bm_off = bm;
-        d.seg_off = segs;
-        d.n_segs = (d.n_tiles + kSegWords - 1) / kSegWords;
         d.out_off = out_offset ? out_offset[p] : 0;
         d.capacity = capacity ? capacity[p] : 0;
         d.row_stride = row_stride;
         bm += d.n_tiles;
-        segs += d.n_segs;
         tiles += d.n_tiles;
         by_k[kindex(pts[p].K)].push_back(p);
     }
@@ -746,7 +765,7 @@ tkdv_status prepare(tkdv_ctx *ctx, Call &call, int n_points, const tkdv_point *p
         call.plist.insert(call.plist.end(), by_k[ki].begin(), by_k[ki].end());
     }
     call.bitmap_words = bm;
-    call.total_segs = segs;
+    call.max_segs = max_segments(bm, n_points);
     call.total_tiles = tiles;
     return TKDV_OK;
 }
@@ -859,7 +878,6 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
         d.i0 = 0;
         d.n = std::min<uint64_t>(W, maxp[p]);
         d.n_tiles = (d.n + kTile - 1) / kTile;
-        d.n_segs = (d.n_tiles + kSegWords - 1) / kSegWords;
         d.target = targets[p];
         d.static_tiles = static_share(d.n_tiles, targets[p] / kTile, np);
         d.bm_off = first_words;
@@ -883,16 +901,8 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     unsigned long long pool_words = first_words;
     if (adaptive) pool_words = std::max<unsigned long long>(first_words, std::min<unsigned long long>(
                                                                               (1ull << 33) / kTile, sum_maxp / kTile));
-    const unsigned long long bm_words = pool_words + (unsigned long long)np * kSegWords;
-    const unsigned long long max_segs = bm_words / kSegWords + np;
-    {
-        unsigned long long segs = 0;
-        for (int p = 0; p < np; ++p) {
-            call.pts[p].seg_off = segs;
-            segs += call.pts[p].n_segs;
-        }
-        call.total_segs = segs;
-    }
+    const unsigned long long bm_words = pool_words + (unsigned long long)np * 2048;
+    const unsigned long long max_segs = max_segments(bm_words, np);
     call.plist.clear();
     for (int ki = 0; ki < kNumK; ++ki) {
         call.plist_off[ki] = (int)call.plist.size();
@@ -906,9 +916,7 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     HIP_TRY(ctx, ensure(ctx->defer_count, 16));
     HIP_TRY(ctx, ensure(ctx->counters, sizeof(DevCounters) * np));
     HIP_TRY(ctx, ensure(ctx->points, sizeof(DevPoint) * np));
-    HIP_TRY(ctx, ensure(ctx->seg_cnt, 8 * max_segs));
-    HIP_TRY(ctx, ensure(ctx->seg_base, 8 * max_segs));
-    HIP_TRY(ctx, ensure(ctx->seg_stats, sizeof(SegStats) * max_segs));
+    HIP_TRY(ctx, ensure_segments(ctx, max_segs, np));
     HIP_TRY(ctx, ensure(ctx->results, sizeof(PointResult) * np));
     HIP_TRY(ctx, ensure(ctx->plist, sizeof(int) * call.plist.size()));
     HIP_TRY(ctx, ensure(ctx->sweep, sizeof(SweepState) * np));
@@ -921,7 +929,6 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     SweepGlobal g0;
     std::memset(&g0, 0, sizeof(g0));
     g0.pool_tiles = pool_words;
-    g0.total_segs = call.total_segs;
     g0.active = (unsigned long long)np;
     g0.defer_cap = defer_cap;
     g0.adaptive = adaptive ? 1 : 0;
@@ -946,18 +953,21 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     a.defer_list = reinterpret_cast<unsigned long long *>(ctx->defer_list.p);
     a.defer_count = reinterpret_cast<unsigned long long *>(ctx->defer_count.p);
     a.defer_cap = defer_cap;
-    a.d_total_segs = &dG->total_segs;
+    a.d_active = &dG->active;
+    a.seg = reinterpret_cast<SegPlan *>(ctx->seg.p);
+    a.seg_cnt = reinterpret_cast<unsigned int *>(ctx->seg_cnt.p);
+    a.seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
+    a.seg_stats = reinterpret_cast<SegStats *>(ctx->seg_stats.p);
+    a.hist = reinterpret_cast<unsigned long long *>(ctx->hist.p);
+    a.res = reinterpret_cast<PointResult *>(ctx->results.p);
     const int *d_plist = reinterpret_cast<const int *>(ctx->plist.p);
-    unsigned long long *seg_cnt = reinterpret_cast<unsigned long long *>(ctx->seg_cnt.p);
-    unsigned long long *seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
-    SegStats *seg_stats = reinterpret_cast<SegStats *>(ctx->seg_stats.p);
-    PointResult *res = reinterpret_cast<PointResult *>(ctx->results.p);
     // one window: every launch is sized for the largest window (persistent
     // kernels), the device holds the current window's extent
     auto window = [&]() -> tkdv_status {
         HIP_TRY(ctx, launch_fill_u32(ctx->counters.p, sizeof(DevCounters) * np / 4, 0u, sst));
         HIP_TRY(ctx, launch_fill_u32(ctx->results.p, sizeof(PointResult) * np / 4, 0u, sst));
         HIP_TRY(ctx, launch_fill_u32(ctx->defer_count.p, 2, 0u, sst));
+        HIP_TRY(ctx, launch_fill_u32(ctx->hist.p, (unsigned long long)np * kShards * kNBins * 2, 0u, sst));
         for (int ki = 0; ki < kNumK; ++ki) {
             if (call.plist_n[ki] == 0) continue;
             const int K = 8 << ki;
@@ -969,18 +979,21 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
                                                d_plist + call.plist_off[ki], call.plist_n[ki], ctx->n_cu,
                                                pool_words, sst, nullptr));
         }
-        for (int ki = 0; ki < kNumK; ++ki)
-            if (call.plist_n[ki]) HIP_TRY(ctx, launch_fixup(8 << ki, a, ctx->n_cu, sst));
-        HIP_TRY(ctx, launch_segments(a, max_segs, seg_cnt, seg_base, res, ctx->n_cu, sst));
+        bool plan = true;  // the first launch lays out the segments
+        for (int ki = 0; ki < kNumK; ++ki) {
+            if (call.plist_n[ki] == 0) continue;
+            HIP_TRY(ctx, launch_fixup(8 << ki, a, plan, ctx->n_cu, sst));
+            plan = false;
+        }
+        HIP_TRY(ctx, launch_segments(a, max_segs, ctx->n_cu, sst));
         for (int ki = 0; ki < kNumK; ++ki) {
             if (call.plist_n[ki] == 0) continue;
             a.phi_hi = ki >= 3 ? ctx->qstat[ki - 3].p : ctx->phi_f32[ki].p;
-            HIP_TRY(ctx, launch_materialize(8 << ki, TKDV_PROP_SIGMA, a, d_plist + call.plist_off[ki],
-                                            call.plist_n[ki], max_segs, seg_cnt, seg_base, seg_stats, res, d_xhat,
+            HIP_TRY(ctx, launch_materialize(8 << ki, TKDV_PROP_SIGMA, a, max_segs, d_xhat,
                                             reinterpret_cast<unsigned long long *>(d_index), ctx->n_cu, sst));
         }
-        HIP_TRY(ctx, launch_finalize(a, seg_cnt, seg_base, seg_stats, res, sst));
-        HIP_TRY(ctx, launch_window_advance(reinterpret_cast<DevPoint *>(ctx->points.p), a.cnt, res,
+        HIP_TRY(ctx, launch_finalize(a, sst));
+        HIP_TRY(ctx, launch_window_advance(reinterpret_cast<DevPoint *>(ctx->points.p), a.cnt, a.res,
                                            reinterpret_cast<SweepState *>(ctx->sweep.p), np, dG,
                                            reinterpret_cast<const unsigned long long *>(ctx->defer_count.p), sst));
         return TKDV_OK;
@@ -1172,7 +1185,7 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
     }
     // the scratch: accept bitmap, FP64 re-decision list, then the small
     // records, each 256-byte aligned
-    const uint64_t n_tiles = (covered + kTile - 1) / kTile, n_segs = (n_tiles + kSegWords - 1) / kSegWords;
+    const uint64_t n_tiles = (covered + kTile - 1) / kTile;
     auto carve = [&](size_t &off, size_t bytes) {
         char *p = base + off;
         off += (bytes + 255) & ~(size_t)255;
@@ -1188,10 +1201,12 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
     w.points = reinterpret_cast<DevPoint *>(carve(off, sizeof(DevPoint)));
     w.results = reinterpret_cast<PointResult *>(carve(off, sizeof(PointResult)));
     w.plist = reinterpret_cast<int *>(carve(off, sizeof(int)));
-    const size_t max_segs = (kScratchMaxProposals / 32 + kSegWords - 1) / kSegWords;
-    w.seg_cnt = reinterpret_cast<unsigned long long *>(carve(off, max_segs * 8));
+    const size_t max_segs = max_segments(kScratchMaxProposals / 32, 1);
+    w.seg = reinterpret_cast<SegPlan *>(carve(off, seg_plan_bytes(1)));
+    w.seg_cnt = reinterpret_cast<unsigned int *>(carve(off, max_segs * sizeof(unsigned int)));
     w.seg_base = reinterpret_cast<unsigned long long *>(carve(off, max_segs * 8));
     w.seg_stats = reinterpret_cast<SegStats *>(carve(off, max_segs * sizeof(SegStats)));
+    w.hist = reinterpret_cast<unsigned long long *>(carve(off, sizeof(unsigned long long) * kShards * kNBins));
     if (off > kScratchBytes) return set_err(ctx, TKDV_E_CAPACITY, "fixed scratch layout exceeds its size");
     tkdv_plan pl = *plan;
     const int plist0 = 0;
@@ -1205,8 +1220,6 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
         d.static_tiles =
             static_share(n_tiles, mode == TKDV_COUNT_ACCEPTED ? std::max(kAlwaysTiles, n / kTile) : n_tiles, 1);
         d.bm_off = 0;
-        d.seg_off = 0;
-        d.n_segs = n_segs;
         d.out_off = 0;
         d.capacity = capacity;
         d.row_stride = 2 * (uint64_t)pt->K;
@@ -1217,7 +1230,7 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
         v.plist_len = 1;
         for (int q = 0; q < kNumK; ++q) v.plist_off[q] = v.plist_n[q] = 0;
         v.plist_n[ki] = 1;
-        v.total_segs = n_segs;
+        v.max_segs = max_segments(n_tiles, 1);
         PointResult res;
         DevCounters cnt;
         s = launch_sequence(ctx, v, w, precision, proposal, d_xhat, reinterpret_cast<unsigned long long *>(d_index),
@@ -1237,7 +1250,7 @@ tkdv_status tkdv_destroy(tkdv_ctx *ctx)
     if (!ctx) return TKDV_OK;
     (void)hipSetDevice(ctx->device);
     DevBuf *bufs[] = {&ctx->bitmap, &ctx->defer_list, &ctx->defer_count, &ctx->counters, &ctx->points,
-                      &ctx->seg_cnt, &ctx->seg_base, &ctx->seg_stats, &ctx->results, &ctx->plist,
+                      &ctx->seg, &ctx->seg_cnt, &ctx->seg_base, &ctx->seg_stats, &ctx->hist, &ctx->results, &ctx->plist,
                       &ctx->mix, &ctx->mix_tab, &ctx->sweep, &ctx->active, &ctx->plan_pts, &ctx->plan_val,
                       &ctx->plan_x, &ctx->plan_ev, &ctx->plan_mix, &ctx->plan_user, &ctx->ext_keys, &ctx->ext_jmax, &ctx->ext_misc,
                       &ctx->ext_list, &ctx->sir_pt, &ctx->sir_w, &ctx->sir_tile, &ctx->sir_chunk, &ctx->sir_part};

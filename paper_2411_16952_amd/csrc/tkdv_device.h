@@ -771,6 +771,97 @@ struct WaveWork {
     }
 };
 
+// The segments of a call from the tiles decided (one workgroup of B threads):
+// their size and each point's first one.
+template <int B>
+__device__ void plan_segments(const KernelArgs &a)
+{
+    __shared__ unsigned long long buf[B];
+    __shared__ unsigned long long words_s;
+    const int tid = threadIdx.x;
+    unsigned long long sum = 0;
+    for (int p = tid; p < a.n_points; p += B) sum += tiles_taken(a.pts[p], a.cnt[p].next_tile);
+    buf[tid] = sum;
+    __syncthreads();
+    for (int o = B / 2; o > 0; o >>= 1) {
+        if (tid < o) buf[tid] += buf[tid + o];
+        __syncthreads();
+    }
+    if (tid == 0) {
+        words_s = seg_words_for(buf[0]);
+        a.seg->words = words_s;
+    }
+    __syncthreads();
+    const unsigned long long w = words_s;
+    const int sh = __ffsll((long long)w) - 1;
+    unsigned long long run = 0;
+    for (int p0 = 0; p0 < a.n_points; p0 += B) {
+        const int p = p0 + tid;
+        const unsigned long long v = p < a.n_points ? (tiles_taken(a.pts[p], a.cnt[p].next_tile) + w - 1) >> sh : 0ull;
+        __syncthreads();
+        buf[tid] = v;
+        __syncthreads();
+        for (int o = 1; o < B; o <<= 1) {  // inclusive scan
+            const unsigned long long add = tid >= o ? buf[tid - o] : 0ull;
+            __syncthreads();
+            buf[tid] += add;
+            __syncthreads();
+        }
+        if (p < a.n_points) a.seg->off[p] = run + buf[tid] - v;
+        run += buf[B - 1];
+    }
+    if (tid == 0) a.seg->off[a.n_points] = run;
+}
+
+// The point of segment gs: the last one whose first segment is at or before it.
+__device__ __forceinline__ int point_of_segment(const KernelArgs &a, unsigned long long gs)
+{
+    int lo = 0, hi = a.n_points - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (a.seg->off[mid] <= gs) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Per-wave u(0) histogram in LDS, kept while the wave stays with one point and
+// added to the point's global one (a shard per workgroup) when it leaves.
+struct WaveHist {
+    unsigned int *bins;  // this wave's kNBins counters
+    int p = -1;
+    __device__ __forceinline__ void enter(const KernelArgs &a, int q, int lane)
+    {
+        if (q == p) return;
+        flush(a, lane);
+        bins[lane] = 0u;
+        p = q;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    __device__ __forceinline__ void flush(const KernelArgs &a, int lane)
+    {
+        if (p < 0) return;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const unsigned int c = bins[lane];
+        if (c) atomicAdd(&a.hist[((size_t)p * kShards + blockIdx.x % kShards) * kNBins + lane], (unsigned long long)c);
+    }
+};
+static_assert(kNBins == kWave, "one bin per lane");
+
+__device__ __forceinline__ unsigned int wave_sum_u32(unsigned int v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
 // log f = -beta'/(E0 K^2) (H2 - c H3) in FP64 at a point x of the sphere with
 // t = sum k^2 s_k: H2 = E0 t by Parseval and H3 by the double sum over the
 // triads k + (n - k) = n (Sec. IV.A).

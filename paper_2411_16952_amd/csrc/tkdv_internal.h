@@ -46,7 +46,25 @@ constexpr uint64_t static_share(uint64_t n, uint64_t at_least, int n_points)
     if (at_least >= n) return n <= cap ? n : 0;
     return at_least < cap ? at_least : cap;
 }
-constexpr int kSegWords = 2048;    // bitmap words per statistics segment (65536 proposals)
+// The accept words of a call are cut into segments of 8 to 2048 words (a power
+// of two), one wave each in the ordered output: about kSegments of them, so that
+// small calls fill the chip too.  Fixed segments of 2048 words, a workgroup each,
+// left a million near-linear samples at K = 16 to 16 workgroups (1.6 ms of
+// ordered output, now 0.12 ms).
+constexpr int kSegWordsMin = 8, kSegWordsMax = 2048;
+constexpr int kSegments = 8192;
+constexpr unsigned long long seg_words_for(unsigned long long words)
+{
+    unsigned long long s = kSegWordsMin;
+    while (s < (unsigned long long)kSegWordsMax && words > s * kSegments) s *= 2;
+    return s;
+}
+// most segments of a call of n_points points with `words` accept words
+constexpr unsigned long long max_segments(unsigned long long words, int n_points)
+{
+    const unsigned long long by_size = words / kSegWordsMax;
+    return (by_size > (unsigned long long)kSegments ? by_size : (unsigned long long)kSegments) + (unsigned long long)n_points;
+}
 constexpr int kNBins = TKDV_NBINS;
 constexpr int kMixBlock = 1024;    // threads per workgroup of the mixture sampling kernel
 constexpr int kMixS = TKDV_MIX_S;  // xi-shifts of the learned mixture
@@ -79,8 +97,6 @@ struct alignas(16) DevPoint {
     uint64_t target;         // accepted-sample target (UINT64_MAX in proposal-count mode)
     uint64_t static_tiles;   // the first tiles, dealt out evenly to the waves (static_share)
     uint64_t bm_off;         // first bitmap word of this point
-    uint64_t seg_off;        // first statistics segment of this point
-    uint64_t n_segs;         // statistics segments of this point
     uint64_t out_off;        // first output row of this point
     uint64_t capacity;       // output rows available to this point
     uint64_t row_stride;     // floats between consecutive output rows
@@ -201,10 +217,17 @@ struct SweepState {
     PointResult total;            // statistics of the accepted samples so far
 };
 
+// The segments of the tiles decided so far (plan_segments): their size, and
+// per point the first one (off[n_points]: their number).
+struct SegPlan {
+    unsigned long long words;
+    unsigned long long off[1];
+};
+constexpr size_t seg_plan_bytes(int n_points) { return sizeof(SegPlan) + sizeof(unsigned long long) * (size_t)n_points; }
+
 // Shared state of a sweep on the device.
 struct SweepGlobal {
     unsigned long long pool_tiles;   // accept-bitmap words available to one window
-    unsigned long long total_segs;   // statistics segments of the current window
     unsigned long long active;       // points not done
     unsigned long long windows;      // windows run with at least one point active
     unsigned long long overflow;     // a window's FP64 re-decision list overflowed
@@ -228,9 +251,16 @@ struct KernelArgs {
     const char *mix_tab;   // mixture tables (learned proposal only)
     // optional per-proposal outputs of the evaluation entry point (point 0 only)
     float *dbg_xhat, *dbg_t, *dbg_s3, *dbg_log_a, *dbg_log_u;
-    // sweeps: the current window's segment count on the device (the windows
-    // change size there); NULL elsewhere (the launch's own count is used)
-    const unsigned long long *d_total_segs;
+    // sweeps: the number of unfinished points (NULL elsewhere)
+    const unsigned long long *d_active;
+    // ordered output: the segments, their accept counts and exclusive prefix,
+    // their statistics, and the u(0) histograms [point][kShards][kNBins]
+    SegPlan *seg;
+    unsigned int *seg_cnt;
+    unsigned long long *seg_base;
+    SegStats *seg_stats;
+    unsigned long long *hist;
+    PointResult *res;
 };
 
 }  // namespace tkdv

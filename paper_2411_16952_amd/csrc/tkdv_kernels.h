@@ -18,18 +18,15 @@ hipError_t launch_decide_variant(int K, int prec, int prop, int variant, const K
                                  int n_plist, int n_cu, unsigned long long tiles, hipStream_t st, int *grid_out);
 int decide_variant_block(int K, int variant);
 int decide_variant_max_blocks_per_cu(int K, int prec, int variant);
-// FP64 re-decision of the listed proposals of the points with this K
-hipError_t launch_fixup(int K, const KernelArgs &a, int n_cu, hipStream_t st);
-hipError_t launch_fixup_mix(int K, const KernelArgs &a, int n_cu, hipStream_t st);
-hipError_t launch_segments(const KernelArgs &a, unsigned long long total_segs, unsigned long long *seg_cnt,
-                           unsigned long long *seg_base, PointResult *res, int n_cu, hipStream_t st);
-hipError_t launch_materialize(int K, int prop, const KernelArgs &a, const int *plist, int n_plist,
-                              unsigned long long total_segs, const unsigned long long *seg_cnt,
-                              const unsigned long long *seg_base, SegStats *seg_stats, PointResult *res,
-                              float *out_xhat, unsigned long long *out_index, int n_cu, hipStream_t st);
-hipError_t launch_finalize(const KernelArgs &a, const unsigned long long *seg_cnt,
-                           const unsigned long long *seg_base, const SegStats *seg_stats, PointResult *res,
-                           hipStream_t st);
+// FP64 re-decision of the listed proposals of the points with this K; with plan
+// the launch also lays out the segments of the ordered output
+hipError_t launch_fixup(int K, const KernelArgs &a, bool plan, int n_cu, hipStream_t st);
+hipError_t launch_fixup_mix(int K, const KernelArgs &a, bool plan, int n_cu, hipStream_t st);
+// accept counts of the segments and their prefix, n_segs_max segments at most
+hipError_t launch_segments(const KernelArgs &a, unsigned long long n_segs_max, int n_cu, hipStream_t st);
+hipError_t launch_materialize(int K, int prop, const KernelArgs &a, unsigned long long n_segs_max, float *out_xhat,
+                              unsigned long long *out_index, int n_cu, hipStream_t st);
+hipError_t launch_finalize(const KernelArgs &a, hipStream_t st);
 // the standalone synthesis (tkdv_synth.hip); ev_start (optional) is recorded
 // on st immediately before the kernel launch
 hipError_t launch_synth(int K, int prec, const float *xhat, unsigned long long n, float *s3, const void *phi_hi,
@@ -60,10 +57,8 @@ int decide_n_variants(int K, int prec);
 size_t quarter_table_bytes(int K, int prec);
 // The ordered output and statistics at K = 64 and 128 (quarter-period form on
 // the statistics grid; a.phi_hi: the table of upload_quarter_stats).
-hipError_t launch_materialize_quarter(int K, int prop, const KernelArgs &a, unsigned long long total_segs,
-                                     const unsigned long long *seg_cnt, const unsigned long long *seg_base,
-                                     SegStats *seg_stats, PointResult *res, float *out_xhat,
-                                     unsigned long long *out_index, int n_cu, hipStream_t st);
+hipError_t launch_materialize_quarter(int K, int prop, const KernelArgs &a, unsigned long long n_segs_max,
+                                      float *out_xhat, unsigned long long *out_index, int n_cu, hipStream_t st);
 hipError_t launch_window_advance(DevPoint *pts, const DevCounters *cnt, const PointResult *res, SweepState *sw,
                                  int n_points, SweepGlobal *G, const unsigned long long *defer_count, hipStream_t st);
 hipError_t launch_fill_u32(void *p, unsigned long long n_words, uint32_t v, hipStream_t st);

@@ -25,22 +25,6 @@
 
 namespace tkdv {
 
-// ---------------------------------------------------------------------------
-// Wave reductions (fixed butterfly order: deterministic)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ double wave_sum_f64(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 static_assert(kClaimTiles == kWave, "one accept word per lane per claim");
 
 // k_decide's synthesis form: the half-period form (half the matrix work and
@@ -71,7 +55,7 @@ template <int K, int PREC, int PROP, int B = decide_block(K), int G = 1>
 __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, int n_plist)
 {
     static_assert(K < 16 || (K / 16) % G == 0, "G must divide the tile pairs");
-    if (a.d_total_segs && *a.d_total_segs == 0ull) return;  // a sweep window without unfinished points
+    if (a.d_active && *a.d_active == 0ull) return;  // a sweep window without unfinished points
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int tab = decide_tab_bytes<K, PREC>();
     if constexpr (!decide_half_period<K>()) {
@@ -345,8 +329,10 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
 // K = 128; split over lanes 0.03 ms and 0.02 ms.
 // ---------------------------------------------------------------------------
 template <int K>
-__global__ void __launch_bounds__(kBlock) k_fixup(KernelArgs a)
+__global__ void __launch_bounds__(kBlock) k_fixup(KernelArgs a, int plan)
 {
+    // the last workgroup lays out the segments (they depend on the decided range only)
+    if (plan && blockIdx.x == gridDim.x - 1) plan_segments<kBlock>(a);
     constexpr int LP = K / 2, PER = kWave / LP;  // lanes per proposal, proposals per wave
     static_assert(LP * PER == kWave, "K/2 lanes per proposal");
     __shared__ double xs[kBlock / kWave][PER * 2 * K];
@@ -475,8 +461,10 @@ __device__ __forceinline__ unsigned long long read_lane_u64(unsigned long long v
 }
 
 template <int K>
-__global__ void __launch_bounds__(kBlock) k_fixup_mix(KernelArgs a)
+__global__ void __launch_bounds__(kBlock) k_fixup_mix(KernelArgs a, int plan)
 {
+    // the last workgroup lays out the segments (they depend on the decided range only)
+    if (plan && blockIdx.x == gridDim.x - 1) plan_segments<kBlock>(a);
     static_assert(K <= 32 && kMixS == 32, "one lane per Box-Muller pair, triad mode and shift");
     __shared__ double xs[kBlock / kWave][2][2 * K];
     const int lane = threadIdx.x & 63, h = lane >> 5, l = lane & 31;
@@ -622,82 +610,66 @@ __global__ void __launch_bounds__(kBlock) k_fixup_mix(KernelArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Segments
+// Segments: accept counts (a wave per segment) and their prefix per point.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int point_of_segment(const DevPoint *pts, int n_points, unsigned long long gs)
+__global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a)
 {
-    int lo = 0, hi = n_points - 1;
-    while (lo < hi) {  // last p with seg_off <= gs
-        const int mid = (lo + hi + 1) >> 1;
-        if (pts[mid].seg_off <= gs) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-__global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a, unsigned long long total_segs,
-                                                      unsigned long long *seg_cnt)
-{
-    __shared__ unsigned long long red[kBlock / kWave];
-    if (a.d_total_segs) total_segs = *a.d_total_segs;
-    for (unsigned long long gs = blockIdx.x; gs < total_segs; gs += gridDim.x) {
-        const int p = point_of_segment(a.pts, a.n_points, gs);
+    const int lane = threadIdx.x & 63;
+    const unsigned long long total = a.seg->off[a.n_points], S = a.seg->words;
+    const unsigned long long waves = (unsigned long long)gridDim.x * (kBlock / kWave);
+    for (unsigned long long gs = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6));
+         gs < total; gs += waves) {
+        const int p = point_of_segment(a, gs);
         const DevPoint &P = a.pts[p];
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long w0 = (gs - P.seg_off) * kSegWords;
-        unsigned long long c = 0;
-        for (int k = threadIdx.x; k < kSegWords; k += kBlock) {
-            const unsigned long long w = w0 + k;
-            if (w < nw) c += __popc(a.bitmap[P.bm_off + w]);
-        }
-        c = wave_sum_u64(c);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = c;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long s = 0;
-            for (int w = 0; w < kBlock / kWave; ++w) s += red[w];
-            seg_cnt[gs] = s;
-        }
-        __syncthreads();
+        const unsigned long long w0 = (gs - a.seg->off[p]) * S, w1 = w0 + S < nw ? w0 + S : nw;
+        unsigned int c = 0;
+        for (unsigned long long w = w0 + lane; w < w1; w += kWave) c += __popc(a.bitmap[P.bm_off + w]);
+        c = wave_sum_u32(c);
+        if (lane == 0) a.seg_cnt[gs] = c;
     }
 }
 
-// One block: per point, exclusive scan of its segment counts.
-__global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a, const unsigned long long *seg_cnt,
-                                                   unsigned long long *seg_base, PointResult *res)
+// One workgroup per point: exclusive prefix of its segments' counts (each
+// thread a contiguous run of them), and the point's totals.
+__global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a)
 {
-    __shared__ unsigned long long buf[1024];
-    for (int p = 0; p < a.n_points; ++p) {
+    __shared__ unsigned long long wsum[16];
+    const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const unsigned long long s0 = a.seg->off[p], n = a.seg->off[p + 1] - s0;
+    const unsigned long long per = (n + 1023) / 1024, b = per * tid < n ? per * tid : n, e = b + per < n ? b + per : n;
+    unsigned long long own = 0;
+    for (unsigned long long s = b; s < e; ++s) own += a.seg_cnt[s0 + s];
+    unsigned long long incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+    }
+    if (lane == 63) wsum[tid >> 6] = incl;
+    __syncthreads();
+    unsigned long long before = 0, all = 0;
+    for (int w = 0; w < 16; ++w) {
+        if (w < (tid >> 6)) before += wsum[w];
+        all += wsum[w];
+    }
+    unsigned long long run = before + incl - own;
+    for (unsigned long long s = b; s < e; ++s) {
+        a.seg_base[s0 + s] = run;
+        run += a.seg_cnt[s0 + s];
+    }
+    if (tid == 0) {
         const DevPoint &P = a.pts[p];
-        unsigned long long run = 0;
-        for (unsigned long long s0 = 0; s0 < P.n_segs; s0 += 1024) {
-            const unsigned long long s = s0 + threadIdx.x;
-            const unsigned long long v = s < P.n_segs ? seg_cnt[P.seg_off + s] : 0ull;
-            buf[threadIdx.x] = v;
-            __syncthreads();
-            for (int o = 1; o < 1024; o <<= 1) {  // Hillis-Steele inclusive scan
-                const unsigned long long add = threadIdx.x >= (unsigned)o ? buf[threadIdx.x - o] : 0ull;
-                __syncthreads();
-                buf[threadIdx.x] += add;
-                __syncthreads();
-            }
-            if (s < P.n_segs) seg_base[P.seg_off + s] = run + buf[threadIdx.x] - v;
-            run += buf[1023];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            res[p].n_accepted = run;
-            res[p].n_processed = tiles_taken(P, a.cnt[p].next_tile) * kTile < P.n
-                                     ? tiles_taken(P, a.cnt[p].next_tile) * kTile
-                                     : P.n;
-        }
-        __syncthreads();
+        const unsigned long long done = tiles_taken(P, a.cnt[p].next_tile) * kTile;
+        a.res[p].n_accepted = all;
+        a.res[p].n_processed = done < P.n ? done : P.n;
     }
 }
 
 // ---------------------------------------------------------------------------
-// k_materialize: one block per segment, one wave per quarter segment.
+// k_materialize: one wave per segment; no work past the accepted-sample target
+// (dense segments beyond it cost a map of 500 samples per cell 26 ms of 37).
 // ---------------------------------------------------------------------------
-constexpr int kWaveWords = kSegWords / (kBlock / kWave);  // 512 words per wave
 constexpr int kGroupWords = kWave;                         // one word per lane per group
 constexpr int kQueue = kGroupWords * 32 + kTile;           // one group's offsets + a partial chunk
 
@@ -710,65 +682,51 @@ __host__ __device__ constexpr int materialize_tab_bytes()
 template <int K>
 __host__ __device__ constexpr int materialize_lds_bytes()
 {
-    return materialize_tab_bytes<K>() + (kBlock / kWave) * kQueue * 2 + 1024;
+    return materialize_tab_bytes<K>() + (kBlock / kWave) * (kQueue * 2 + kNBins * 4);
 }
 
 template <int K, int PROP>
-__global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, const int *plist, int n_plist,
-                                                        unsigned long long total_segs,
-                                                        const unsigned long long *seg_cnt,
-                                                        const unsigned long long *seg_base,
-                                                        SegStats *seg_stats, PointResult *res,
-                                                        float *out_xhat, unsigned long long *out_index)
+__global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out_xhat, unsigned long long *out_index)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int tab = materialize_tab_bytes<K>();
-    uint16_t *lists = reinterpret_cast<uint16_t *>(lds + tab);
-    unsigned int *hist = reinterpret_cast<unsigned int *>(lds + tab + (kBlock / kWave) * kQueue * 2);
-    __shared__ unsigned long long wave_cnt[kBlock / kWave];
-    __shared__ double wave_S[kBlock / kWave][4];
-    __shared__ unsigned long long wave_ex[kBlock / kWave][3];
-    __shared__ unsigned long long wave_peak_idx[kBlock / kWave];
-    __shared__ unsigned int wave_peak_key[kBlock / kWave];
+    const unsigned long long total = a.seg->off[a.n_points], S = a.seg->words;
+    if ((unsigned long long)blockIdx.x * (kBlock / kWave) >= total) return;
     {
         const uint4 *s0 = reinterpret_cast<const uint4 *>(a.phi_hi);
         uint4 *d = reinterpret_cast<uint4 *>(lds);
         for (int v = threadIdx.x; v < tab / 16; v += kBlock) d[v] = s0[v];
     }
-    const int lane = threadIdx.x & 63, half = lane >> 5, pl = lane & 31, wv = threadIdx.x >> 6;
-    uint16_t *mylist = lists + wv * kQueue;
-    if (a.d_total_segs) total_segs = *a.d_total_segs;
+    const int lane = threadIdx.x & 63, half = lane >> 5, pl = lane & 31;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint16_t *mylist = reinterpret_cast<uint16_t *>(lds + tab) + wv * kQueue;
+    WaveHist hist;
+    hist.bins = reinterpret_cast<unsigned int *>(lds + tab + (kBlock / kWave) * kQueue * 2) + wv * kNBins;
     __syncthreads();
-    for (unsigned long long gs = blockIdx.x; gs < total_segs; gs += gridDim.x) {
-        const int p = point_of_segment(a.pts, a.n_points, gs);
+    const unsigned long long waves = (unsigned long long)gridDim.x * (kBlock / kWave);
+    for (unsigned long long gs = (unsigned long long)blockIdx.x * (kBlock / kWave) + wv; gs < total; gs += waves) {
+        const int p = __builtin_amdgcn_readfirstlane(point_of_segment(a, gs));
         const DevPoint &P = a.pts[p];
-        bool mine_k = P.K == K && P.proposal == PROP;
         const unsigned long long limit = P.target;  // ranks >= target are not part of the result
-        if (!mine_k || seg_cnt[gs] == 0 || seg_base[gs] >= limit) continue;  // block-uniform
-        for (int b = threadIdx.x; b < kNBins; b += kBlock) hist[b] = 0u;
+        const unsigned long long first = bcast_lane0(a.seg_base[gs]);
+        const unsigned int in_seg = __builtin_amdgcn_readfirstlane(a.seg_cnt[gs]);
+        if (P.K != K || P.proposal != PROP || in_seg == 0u || first >= limit) continue;
+        hist.enter(a, p, lane);
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long seg_w0 = (gs - P.seg_off) * kSegWords;
-        const unsigned long long w_first = seg_w0 + (unsigned long long)wv * kWaveWords;
-        // this wave's accepted count -> rank base
-        unsigned long long c = 0;
-        for (int k = lane; k < kWaveWords; k += kWave) {
-            const unsigned long long w = w_first + k;
-            if (w < nw) c += __popc(a.bitmap[P.bm_off + w]);
-        }
-        c = wave_sum_u64(c);
-        if (lane == 0) wave_cnt[wv] = c;
-        __syncthreads();
-        unsigned long long rank = seg_base[gs];
-        for (int w = 0; w < wv; ++w) rank += wave_cnt[w];
+        const unsigned long long w_first = (gs - a.seg->off[p]) * S;
+        unsigned long long rank = first;
         double S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
-        unsigned long long n_ex = 0, n_ex4 = 0, n_max4 = 0, peak_idx = ~0ull;
+        unsigned int n_ex = 0, n_ex4 = 0, n_max4 = 0;
+        unsigned long long peak_idx = ~0ull;
         unsigned int peak_key = 0u;
-        // accepted offsets (proposals from the wave's first word) queue up in
+        // accepted offsets (proposals from the segment's first word) queue up in
         // index order; full chunks are regenerated, the last group flushes
         int queued = 0;
-        for (int g = 0; g < kWaveWords / kGroupWords; ++g) {
-            const unsigned long long w = w_first + (unsigned long long)g * kGroupWords + lane;
-            const uint32_t word = w < nw ? a.bitmap[P.bm_off + w] : 0u;
+        const int groups = (int)((S + kGroupWords - 1) / kGroupWords);
+        for (int g = 0; g < groups && rank < limit; ++g) {
+            const unsigned wi = (unsigned)(g * kGroupWords + lane);
+            const unsigned long long w = w_first + wi;
+            const uint32_t word = wi < S && w < nw ? a.bitmap[P.bm_off + w] : 0u;
             const int cntw = __popc(word);
             // inclusive prefix over lanes
             int incl = cntw;
@@ -777,21 +735,21 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, const int 
                 const int up = __shfl_up(incl, o, 64);
                 if (lane >= o) incl += up;
             }
-            const int total = __shfl(incl, 63, 64);
+            const int total_g = __builtin_amdgcn_readlane(incl, 63);
             int pos = queued + incl - cntw;
             uint32_t m = word;
             while (m) {
                 const int bit = __ffs(m) - 1;
                 m &= m - 1;
-                mylist[pos++] = (uint16_t)((g * kGroupWords + lane) * 32 + bit);
+                mylist[pos++] = (uint16_t)(wi * 32 + bit);
             }
-            queued += total;
-            const int upto = g + 1 == kWaveWords / kGroupWords ? queued : queued & ~(kTile - 1);
+            queued += total_g;
+            const int upto = g + 1 == groups ? queued : queued & ~(kTile - 1);
             if (upto == 0) continue;
             // the list is written and read by lanes of this wave only
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            for (int c0 = 0; c0 < upto; c0 += kTile) {
+            for (int c0 = 0; c0 < upto && rank + c0 < limit; c0 += kTile) {
                 const bool in_chunk = c0 + pl < upto;
                 const int off = in_chunk ? (int)mylist[c0 + pl] : 0;
                 const unsigned long long local = w_first * kTile + (unsigned long long)off;
@@ -830,8 +788,8 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, const int 
                     S2 += u2;
                     S3 += u2 * u;
                     S4 += u2 * u2;
-                    n_ex += uf > kTwoSigmaT ? 1ull : 0ull;    // u > 2 sqrt(E0/pi)
-                    n_ex4 += uf > kFourSigmaT ? 1ull : 0ull;  // u > 4 sqrt(E0/pi)
+                    n_ex += uf > kTwoSigmaT ? 1u : 0u;    // u > 2 sqrt(E0/pi)
+                    n_ex4 += uf > kFourSigmaT ? 1u : 0u;  // u > 4 sqrt(E0/pi)
                     umax = fmaxf(umax, uf);
                 };
                 if constexpr (K >= 16) {
@@ -876,7 +834,7 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, const int 
                 // the proposal's grid values are split over lanes l and l + 32
                 umax = fmaxf(umax, __shfl_xor(umax, 32, 64));
                 if (valid && half == 0) {
-                    n_max4 += umax > kFourSigmaT ? 1ull : 0ull;
+                    n_max4 += umax > kFourSigmaT ? 1u : 0u;
                     peak_merge(peak_key, peak_idx, float_key(umax), i);
                 }
                 if (valid && half == 0) {
@@ -887,7 +845,7 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, const int 
                     double posb = (s0 / sqrt((double)K) + 1.0) * (0.5 * kNBins);
                     int bin = (int)floor(posb);
                     bin = bin < 0 ? 0 : (bin > kNBins - 1 ? kNBins - 1 : bin);
-                    atomicAdd(&hist[bin], 1u);
+                    atomicAdd(&hist.bins[bin], 1u);
                 }
             }
             rank += upto;
@@ -905,113 +863,92 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, const int 
         S2 = wave_sum_f64(S2);
         S3 = wave_sum_f64(S3);
         S4 = wave_sum_f64(S4);
-        n_ex = wave_sum_u64(n_ex);
-        n_ex4 = wave_sum_u64(n_ex4);
-        n_max4 = wave_sum_u64(n_max4);
+        n_ex = wave_sum_u32(n_ex);
+        n_ex4 = wave_sum_u32(n_ex4);
+        n_max4 = wave_sum_u32(n_max4);
         wave_peak(peak_key, peak_idx);
         if (lane == 0) {
-            wave_S[wv][0] = S1;
-            wave_S[wv][1] = S2;
-            wave_S[wv][2] = S3;
-            wave_S[wv][3] = S4;
-            wave_ex[wv][0] = n_ex;
-            wave_ex[wv][1] = n_ex4;
-            wave_ex[wv][2] = n_max4;
-            wave_peak_key[wv] = peak_key;
-            wave_peak_idx[wv] = peak_idx;
+            const unsigned long long left = limit - first;
+            const unsigned long long ns = in_seg < left ? in_seg : left;
+            a.seg_stats[gs] = SegStats{S1, S2, S3, S4, n_ex, ns, n_ex4, n_max4, peak_idx, peak_key, 0u};
         }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            SegStats st = {0.0, 0.0, 0.0, 0.0, 0ull, 0ull, 0ull, 0ull, ~0ull, 0u, 0u};
-            for (int w = 0; w < kBlock / kWave; ++w) {
-                st.S1 += wave_S[w][0];
-                st.S2 += wave_S[w][1];
-                st.S3 += wave_S[w][2];
-                st.S4 += wave_S[w][3];
-                st.n_exceed += wave_ex[w][0];
-                st.n_exceed4 += wave_ex[w][1];
-                st.n_max4 += wave_ex[w][2];
-                peak_merge(st.peak_key, st.peak_index, wave_peak_key[w], wave_peak_idx[w]);
-            }
-            const unsigned long long sb = seg_base[gs];
-            const unsigned long long se = sb + seg_cnt[gs];
-            st.n_samples = (se < limit ? se : limit) - sb;
-            seg_stats[gs] = st;
-        }
-        for (int b = threadIdx.x; b < kNBins; b += kBlock)
-            if (hist[b]) atomicAdd(&res[p].hist[b], (unsigned long long)hist[b]);
-        __syncthreads();
     }
+    hist.flush(a, lane);
 }
 
 // Per point (one workgroup): segment partials summed in a fixed order --
-// each thread takes a contiguous run of segments in order, then a fixed
-// pairwise tree over the threads -- so the result does not depend on
-// scheduling.
-__global__ void __launch_bounds__(kBlock) k_finalize(KernelArgs a, const unsigned long long *seg_cnt,
-                                                     const unsigned long long *seg_base,
-                                                     const SegStats *seg_stats, PointResult *res)
+// each thread takes every 1024th segment in order, then a fixed pairwise tree
+// over the threads -- so the result does not depend on scheduling.
+constexpr int kFinBlock = 1024;
+__global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
 {
-    __shared__ double sS[4][kBlock];
-    __shared__ unsigned long long sE[3][kBlock], sN[kBlock], sPI[kBlock];
-    __shared__ unsigned int sPK[kBlock];
-    const int p = blockIdx.x, tid = threadIdx.x;
+    __shared__ double sS[4][kFinBlock / kWave];
+    __shared__ unsigned long long sE[4][kFinBlock / kWave], sPI[kFinBlock / kWave];
+    __shared__ unsigned int sPK[kFinBlock / kWave];
+    if (a.d_active && *a.d_active == 0ull) return;
+    const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const DevPoint &P = a.pts[p];
-    const unsigned long long per = (P.n_segs + kBlock - 1) / kBlock;
-    const unsigned long long s0 = per * tid, s1 = s0 + per < P.n_segs ? s0 + per : P.n_segs;
-    double S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
-    unsigned long long ex = 0, ex4 = 0, mx4 = 0, ns = 0, pi = ~0ull;
+    const unsigned long long s0 = a.seg->off[p], s1 = a.seg->off[p + 1];
+    double S[4] = {0.0, 0.0, 0.0, 0.0};
+    unsigned long long E[4] = {0, 0, 0, 0}, pi = ~0ull;  // above 2 sigma, 4 sigma, samples above 4 sigma, samples
     unsigned int pk = 0u;
-    for (unsigned long long s = s0; s < s1; ++s) {
-        const unsigned long long gs = P.seg_off + s;
-        if (seg_cnt[gs] == 0 || seg_base[gs] >= P.target) continue;
-        const SegStats &st = seg_stats[gs];
-        S1 += st.S1;
-        S2 += st.S2;
-        S3 += st.S3;
-        S4 += st.S4;
-        ex += st.n_exceed;
-        ex4 += st.n_exceed4;
-        mx4 += st.n_max4;
-        ns += st.n_samples;
+    // the next record's loads are issued beside this one's sums
+#pragma unroll 4
+    for (unsigned long long gs = s0 + tid; gs < s1; gs += kFinBlock) {
+        const bool in = a.seg_cnt[gs] != 0u && a.seg_base[gs] < P.target;
+        SegStats st = a.seg_stats[gs];  // not written where !in
+        if (!in) st = SegStats{0.0, 0.0, 0.0, 0.0, 0ull, 0ull, 0ull, 0ull, ~0ull, 0u, 0u};
+        S[0] += st.S1;
+        S[1] += st.S2;
+        S[2] += st.S3;
+        S[3] += st.S4;
+        E[0] += st.n_exceed;
+        E[1] += st.n_exceed4;
+        E[2] += st.n_max4;
+        E[3] += st.n_samples;
         peak_merge(pk, pi, st.peak_key, st.peak_index);
     }
-    sS[0][tid] = S1;
-    sS[1][tid] = S2;
-    sS[2][tid] = S3;
-    sS[3][tid] = S4;
-    sE[0][tid] = ex;
-    sE[1][tid] = ex4;
-    sE[2][tid] = mx4;
-    sN[tid] = ns;
-    sPK[tid] = pk;
-    sPI[tid] = pi;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if (tid < w) {
-            for (int q = 0; q < 4; ++q) sS[q][tid] += sS[q][tid + w];
-            for (int q = 0; q < 3; ++q) sE[q][tid] += sE[q][tid + w];
-            sN[tid] += sN[tid + w];
-            unsigned int k0 = sPK[tid];
-            unsigned long long i0 = sPI[tid];
-            peak_merge(k0, i0, sPK[tid + w], sPI[tid + w]);
-            sPK[tid] = k0;
-            sPI[tid] = i0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        S[q] = wave_sum_f64(S[q]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) E[q] += __shfl_xor(E[q], o, 64);
+    }
+    wave_peak(pk, pi);
+    if (lane == 0) {
+        for (int q = 0; q < 4; ++q) {
+            sS[q][wv] = S[q];
+            sE[q][wv] = E[q];
         }
-        __syncthreads();
+        sPK[wv] = pk;
+        sPI[wv] = pi;
+    }
+    __syncthreads();
+    PointResult &R = a.res[p];
+    if (tid < kNBins) {
+        unsigned long long h = 0;
+        for (int s = 0; s < kShards; ++s) h += a.hist[((size_t)p * kShards + s) * kNBins + tid];
+        R.hist[tid] = h;
     }
     if (tid == 0) {
-        res[p].S1 = sS[0][0];
-        res[p].S2 = sS[1][0];
-        res[p].S3 = sS[2][0];
-        res[p].S4 = sS[3][0];
-        res[p].n_exceed = sE[0][0];
-        res[p].n_exceed4 = sE[1][0];
-        res[p].n_max4 = sE[2][0];
-        res[p].peak_key = sPK[0];
-        res[p].peak_index = sPI[0];
-        res[p].n_samples = sN[0];
-        res[p].n_written = sN[0] < P.capacity ? sN[0] : P.capacity;
+        for (int w = 1; w < kFinBlock / kWave; ++w) {
+            for (int q = 0; q < 4; ++q) {
+                S[q] += sS[q][w];
+                E[q] += sE[q][w];
+            }
+            peak_merge(pk, pi, sPK[w], sPI[w]);
+        }
+        R.S1 = S[0];
+        R.S2 = S[1];
+        R.S3 = S[2];
+        R.S4 = S[3];
+        R.n_exceed = E[0];
+        R.n_exceed4 = E[1];
+        R.n_max4 = E[2];
+        R.peak_key = pk;
+        R.peak_index = pi;
+        R.n_samples = E[3];
+        R.n_written = E[3] < P.capacity ? E[3] : P.capacity;
     }
 }
 
@@ -1095,32 +1032,29 @@ __global__ void __launch_bounds__(1024) k_window_advance(DevPoint *pts, const De
     }
     const double pool = (double)G->pool_tiles * kTile;
     const double scale = sum_need > pool ? pool / sum_need : 1.0;
-    unsigned long long bm = 0, segs = 0, active = 0;
+    unsigned long long bm = 0, active = 0;
     for (int p = 0; p < n_points; ++p) {
         SweepState &S = sw[p];
         DevPoint &P = pts[p];
         P.bm_off = bm;
-        P.seg_off = segs;
         if (S.done) {
             P.n = 0;
             P.n_tiles = 0;
             P.static_tiles = 0;
-            P.n_segs = 0;
             continue;
         }
         P.i0 += P.n;
         const unsigned long long left = S.i_end - P.i0;
         unsigned long long w = S.window;
         if (G->adaptive && p < 1024) {
-            // whole segments (65536 proposals), at least one, within the pool share
+            // whole blocks of 65536 proposals, at least one, within the pool share
             const double share = need[p] * scale;
-            const unsigned long long seg = (unsigned long long)kSegWords * kTile;
+            const unsigned long long seg = 65536;
             w = (unsigned long long)(share / (double)seg) * seg;
             w = w < seg ? seg : w;
         }
         P.n = left < w ? left : w;
         P.n_tiles = (P.n + kTile - 1) / kTile;
-        P.n_segs = (P.n_tiles + kSegWords - 1) / kSegWords;
         P.target = S.target - S.accepted;
         // dealt out evenly: three quarters of what the measured acceptance asks for
         const double used = (double)(P.i0 - S.i_start);
@@ -1132,10 +1066,8 @@ __global__ void __launch_bounds__(1024) k_window_advance(DevPoint *pts, const De
         P.capacity = S.capacity > S.written ? S.capacity - S.written : 0;
         P.out_off = S.out_off + S.written;
         bm += P.n_tiles;
-        segs += P.n_segs;
         ++active;
     }
-    G->total_segs = segs;
     G->active = active;
 }
 
@@ -1369,74 +1301,63 @@ hipError_t launch_decide_mix(int K, int prec, const KernelArgs &a, const int *pl
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_fixup_mix(int K, const KernelArgs &a, int n_cu, hipStream_t st)
+hipError_t launch_fixup_mix(int K, const KernelArgs &a, bool plan, int n_cu, hipStream_t st)
 {
     const dim3 g(8 * n_cu), b(kBlock);
     switch (K) {
-    case 8: hipLaunchKernelGGL(k_fixup_mix<8>, g, b, 0, st, a); break;
-    case 16: hipLaunchKernelGGL(k_fixup_mix<16>, g, b, 0, st, a); break;
-    case 32: hipLaunchKernelGGL(k_fixup_mix<32>, g, b, 0, st, a); break;
+    case 8: hipLaunchKernelGGL(k_fixup_mix<8>, g, b, 0, st, a, plan ? 1 : 0); break;
+    case 16: hipLaunchKernelGGL(k_fixup_mix<16>, g, b, 0, st, a, plan ? 1 : 0); break;
+    case 32: hipLaunchKernelGGL(k_fixup_mix<32>, g, b, 0, st, a, plan ? 1 : 0); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_fixup(int K, const KernelArgs &a, int n_cu, hipStream_t st)
+hipError_t launch_fixup(int K, const KernelArgs &a, bool plan, int n_cu, hipStream_t st)
 {
     const dim3 g(4 * n_cu), b(kBlock);
     switch (K) {
-    case 8: hipLaunchKernelGGL(k_fixup<8>, g, b, 0, st, a); break;
-    case 16: hipLaunchKernelGGL(k_fixup<16>, g, b, 0, st, a); break;
-    case 32: hipLaunchKernelGGL(k_fixup<32>, g, b, 0, st, a); break;
-    case 64: hipLaunchKernelGGL(k_fixup<64>, g, b, 0, st, a); break;
-    case 128: hipLaunchKernelGGL(k_fixup<128>, g, b, 0, st, a); break;
+    case 8: hipLaunchKernelGGL(k_fixup<8>, g, b, 0, st, a, plan ? 1 : 0); break;
+    case 16: hipLaunchKernelGGL(k_fixup<16>, g, b, 0, st, a, plan ? 1 : 0); break;
+    case 32: hipLaunchKernelGGL(k_fixup<32>, g, b, 0, st, a, plan ? 1 : 0); break;
+    case 64: hipLaunchKernelGGL(k_fixup<64>, g, b, 0, st, a, plan ? 1 : 0); break;
+    case 128: hipLaunchKernelGGL(k_fixup<128>, g, b, 0, st, a, plan ? 1 : 0); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_segments(const KernelArgs &a, unsigned long long total_segs, unsigned long long *seg_cnt,
-                           unsigned long long *seg_base, PointResult *res, int n_cu, hipStream_t st)
+hipError_t launch_segments(const KernelArgs &a, unsigned long long n_segs_max, int n_cu, hipStream_t st)
 {
-    unsigned long long g = total_segs < (unsigned long long)(32 * n_cu) ? total_segs : 32ull * n_cu;
-    if (g < 1) g = 1;
-    hipLaunchKernelGGL(k_seg_count, dim3((unsigned)g), dim3(kBlock), 0, st, a, total_segs, seg_cnt);
+    unsigned long long g = (n_segs_max + kBlock / kWave - 1) / (kBlock / kWave);
+    if (g > 8ull * n_cu) g = 8ull * n_cu;
+    hipLaunchKernelGGL(k_seg_count, dim3((unsigned)g), dim3(kBlock), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, st, a, seg_cnt, seg_base, res);
+    hipLaunchKernelGGL(k_seg_scan, dim3(a.n_points), dim3(1024), 0, st, a);
     return hipGetLastError();
 }
 
 template <int K, int PROP>
-static hipError_t launch_materialize_t(const KernelArgs &a, const int *plist, int n_plist,
-                                       unsigned long long total_segs, const unsigned long long *seg_cnt,
-                                       const unsigned long long *seg_base, SegStats *seg_stats,
-                                       PointResult *res, float *out_xhat, unsigned long long *out_index,
-                                       int n_cu, hipStream_t st)
+static hipError_t launch_materialize_t(const KernelArgs &a, unsigned long long n_segs_max, float *out_xhat,
+                                       unsigned long long *out_index, int n_cu, hipStream_t st)
 {
     constexpr int lds = materialize_lds_bytes<K>();
     auto kern = k_materialize<K, PROP>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    unsigned long long g = total_segs < (unsigned long long)(8 * n_cu) ? total_segs : 8ull * n_cu;
-    if (g < 1) g = 1;
-    hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(kBlock), lds, st, a, plist, n_plist, total_segs,
-                       seg_cnt, seg_base, seg_stats, res, out_xhat, out_index);
+    unsigned long long g = (n_segs_max + kBlock / kWave - 1) / (kBlock / kWave);
+    if (g > 8ull * n_cu) g = 8ull * n_cu;
+    hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(kBlock), lds, st, a, out_xhat, out_index);
     return hipGetLastError();
 }
 
-hipError_t launch_materialize(int K, int prop, const KernelArgs &a, const int *plist, int n_plist,
-                              unsigned long long total_segs, const unsigned long long *seg_cnt,
-                              const unsigned long long *seg_base, SegStats *seg_stats, PointResult *res,
-                              float *out_xhat, unsigned long long *out_index, int n_cu, hipStream_t st)
+hipError_t launch_materialize(int K, int prop, const KernelArgs &a, unsigned long long n_segs_max, float *out_xhat,
+                              unsigned long long *out_index, int n_cu, hipStream_t st)
 {
-    if (K == 64 || K == 128)
-        return launch_materialize_quarter(K, prop, a, total_segs, seg_cnt, seg_base, seg_stats, res, out_xhat,
-                                          out_index, n_cu, st);
-#define TKDV_DISPATCH_M(KK, PP)                                                                          \
-    if (K == KK && prop == PP)                                                                           \
-        return launch_materialize_t<KK, PP>(a, plist, n_plist, total_segs, seg_cnt, seg_base, seg_stats, \
-                                            res, out_xhat, out_index, n_cu, st);
+    if (K == 64 || K == 128) return launch_materialize_quarter(K, prop, a, n_segs_max, out_xhat, out_index, n_cu, st);
+#define TKDV_DISPATCH_M(KK, PP) \
+    if (K == KK && prop == PP) return launch_materialize_t<KK, PP>(a, n_segs_max, out_xhat, out_index, n_cu, st);
     TKDV_DISPATCH_M(8, PROP_UNIFORM)
     TKDV_DISPATCH_M(8, PROP_SIGMA)
     TKDV_DISPATCH_M(16, PROP_UNIFORM)
@@ -1450,11 +1371,9 @@ hipError_t launch_materialize(int K, int prop, const KernelArgs &a, const int *p
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_finalize(const KernelArgs &a, const unsigned long long *seg_cnt,
-                           const unsigned long long *seg_base, const SegStats *seg_stats, PointResult *res,
-                           hipStream_t st)
+hipError_t launch_finalize(const KernelArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_finalize, dim3(a.n_points), dim3(kBlock), 0, st, a, seg_cnt, seg_base, seg_stats, res);
+    hipLaunchKernelGGL(k_finalize, dim3(a.n_points), dim3(kFinBlock), 0, st, a);
     return hipGetLastError();
 }
 

@@ -58,18 +58,6 @@ struct Quarter {
     static constexpr int lds(int prec) { return prec == PREC_FP32 ? F32_BYTES : 2 * BF16_BYTES; }
 };
 
-__device__ __forceinline__ unsigned long long wave_sum_u64_128(unsigned long long v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ double wave_sum_f64_128(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 // sum over the four lanes of a proposal (l, l^16, l^32, l^48); every lane
 // gets the same two operands in the last addition, hence the same bits
 __device__ __forceinline__ float sum4(float v)

@@ -26,7 +26,7 @@ namespace {
 template <int K, int PREC, int PROP, bool DBG, int BL = decide_block(K)>
 __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist, int n_plist)
 {
-    if (a.d_total_segs && *a.d_total_segs == 0ull) return;  // a sweep window without unfinished points
+    if (a.d_active && *a.d_active == 0ull) return;  // a sweep window without unfinished points
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int B = BL, CPL = K / 4;
     {
@@ -141,10 +141,10 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
 
 // ---------------------------------------------------------------------------
 // k_materialize_q: the ordered output and the statistics at K = 64 and 128.
-// One workgroup per 65536-proposal segment, its W waves taking equal runs of
-// its accept words in groups of 32; accepted proposals in chunks of 16 (the
-// decision kernel's layout), regenerated with the decision kernel's
-// arithmetic and written at their rank.  The grid values come from the
+// A wave takes one segment at a time, its accept words in groups of 32;
+// accepted proposals in chunks of 16 (the decision kernel's layout),
+// regenerated with the decision kernel's arithmetic and written at their
+// rank, up to the accepted-sample target.  The grid values come from the
 // quarter-period form on the statistics grid xi_j = -pi + 2 pi j/N itself:
 // representatives xi_rho = 2 pi rho/N, rho < K (FP32 16x16x4 products, table
 // in LDS, entries unscaled), each giving u at xi, -xi, pi - xi and xi - pi
@@ -157,7 +157,6 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
 template <int K>
 struct MatQ {
     static constexpr int W = K == 128 ? 8 : 4;       // waves per workgroup
-    static constexpr int WAVE_WORDS = kSegWords / W; // accept words per wave
     static constexpr int GROUP = 32;                 // words per group (lanes 0..31)
     static constexpr int QUEUE = GROUP * 32 + 16;    // one group's offsets + a partial chunk
     static constexpr int LIST_BYTES = W * QUEUE * 2;
@@ -165,61 +164,49 @@ struct MatQ {
 };
 
 template <int K, int PROP>
-__global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs a, unsigned long long total_segs,
-                                                                      const unsigned long long *seg_cnt,
-                                                                      const unsigned long long *seg_base,
-                                                                      SegStats *seg_stats, PointResult *res,
-                                                                      float *out_xhat, unsigned long long *out_index)
+__global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs a, float *out_xhat,
+                                                                      unsigned long long *out_index)
 {
     constexpr int W = MatQ<K>::W, B = W * kWave, CPL = K / 4, QG = Quarter<K>::QG;
-    constexpr int WW = MatQ<K>::WAVE_WORDS, GW = MatQ<K>::GROUP;
+    constexpr int GW = MatQ<K>::GROUP;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    __shared__ unsigned int hist[kNBins];
-    __shared__ unsigned long long wave_cnt[W];
-    __shared__ double wave_S[W][4];
-    __shared__ unsigned long long wave_ex[W][3];
-    __shared__ unsigned long long wave_peak_idx[W];
-    __shared__ unsigned int wave_peak_key[W];
+    __shared__ unsigned int wave_hist[W][kNBins];
+    const unsigned long long total = a.seg->off[a.n_points], S = a.seg->words;
+    if ((unsigned long long)blockIdx.x * W >= total) return;
     {
         const uint4 *s0 = reinterpret_cast<const uint4 *>(a.phi_hi);
         uint4 *d = reinterpret_cast<uint4 *>(lds);
         for (int v = threadIdx.x; v < Quarter<K>::F32_BYTES / 16; v += B) d[v] = s0[v];
     }
     const float4 *tab = reinterpret_cast<const float4 *>(lds);
-    const int lane = threadIdx.x & 63, g = lane >> 4, pl = lane & 15, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, g = lane >> 4, pl = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint16_t *mylist = reinterpret_cast<uint16_t *>(lds + Quarter<K>::F32_BYTES) + wv * MatQ<K>::QUEUE;
-    if (a.d_total_segs) total_segs = *a.d_total_segs;
+    WaveHist hist;
+    hist.bins = wave_hist[wv];
     __syncthreads();
-    for (unsigned long long gs = blockIdx.x; gs < total_segs; gs += gridDim.x) {
-        int lo = 0, hi = a.n_points - 1;
-        while (lo < hi) {  // last point whose first segment is <= gs
-            const int mid = (lo + hi + 1) >> 1;
-            if (a.pts[mid].seg_off <= gs) lo = mid; else hi = mid - 1;
-        }
-        const int p = lo;
+    const unsigned long long waves = (unsigned long long)gridDim.x * W;
+    for (unsigned long long gs = (unsigned long long)blockIdx.x * W + wv; gs < total; gs += waves) {
+        const int p = __builtin_amdgcn_readfirstlane(point_of_segment(a, gs));
         const DevPoint &P = a.pts[p];
         const unsigned long long limit = P.target;  // ranks >= target are not part of the result
-        if (P.K != K || P.proposal != PROP || seg_cnt[gs] == 0 || seg_base[gs] >= limit) continue;  // uniform
-        for (int b = threadIdx.x; b < kNBins; b += B) hist[b] = 0u;
+        const unsigned long long first = bcast_lane0(a.seg_base[gs]);
+        const unsigned int in_seg = __builtin_amdgcn_readfirstlane(a.seg_cnt[gs]);
+        if (P.K != K || P.proposal != PROP || in_seg == 0u || first >= limit) continue;
+        hist.enter(a, p, lane);
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long w_first = (gs - P.seg_off) * kSegWords + (unsigned long long)wv * WW;
-        unsigned long long cw = 0;
-        for (int k = lane; k < WW; k += kWave) {
-            const unsigned long long w = w_first + k;
-            if (w < nw) cw += __popc(a.bitmap[P.bm_off + w]);
-        }
-        cw = wave_sum_u64_128(cw);
-        if (lane == 0) wave_cnt[wv] = cw;
-        __syncthreads();
-        unsigned long long rank = seg_base[gs];
-        for (int w = 0; w < wv; ++w) rank += wave_cnt[w];
+        const unsigned long long w_first = (gs - a.seg->off[p]) * S;
+        unsigned long long rank = first;
         double S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
-        unsigned long long n_ex = 0, n_ex4 = 0, n_max4 = 0, peak_idx = ~0ull;
+        unsigned int n_ex = 0, n_ex4 = 0, n_max4 = 0;
+        unsigned long long peak_idx = ~0ull;
         unsigned int peak_key = 0u;
-        int queued = 0;  // offsets (proposals from the wave's first word) waiting in mylist
-        for (int grp = 0; grp < WW / GW; ++grp) {
-            const unsigned long long w = w_first + (unsigned long long)grp * GW + lane;
-            const uint32_t word = (lane < GW && w < nw) ? a.bitmap[P.bm_off + w] : 0u;
+        int queued = 0;  // offsets (proposals from the segment's first word) waiting in mylist
+        const int groups = (int)((S + GW - 1) / GW);
+        for (int grp = 0; grp < groups && rank < limit; ++grp) {
+            const unsigned wi = (unsigned)(grp * GW + lane);
+            const unsigned long long w = w_first + wi;
+            const uint32_t word = (lane < GW && wi < S && w < nw) ? a.bitmap[P.bm_off + w] : 0u;
             const int cntw = __popc(word);
             int incl = cntw;
 #pragma unroll
@@ -227,21 +214,21 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                 const int up = __shfl_up(incl, o, 64);
                 if (lane >= o) incl += up;
             }
-            const int total = __shfl(incl, 63, 64);
+            const int total_g = __builtin_amdgcn_readlane(incl, 63);
             int pos = queued + incl - cntw;
             uint32_t m = word;
             while (m) {
                 const int bit = __ffs(m) - 1;
                 m &= m - 1;
-                mylist[pos++] = (uint16_t)((grp * GW + lane) * 32 + bit);
+                mylist[pos++] = (uint16_t)(wi * 32 + bit);
             }
-            queued += total;
-            const int upto = grp + 1 == WW / GW ? queued : queued & ~(kTile16 - 1);
+            queued += total_g;
+            const int upto = grp + 1 == groups ? queued : queued & ~(kTile16 - 1);
             if (upto == 0) continue;
             // the list is written and read by lanes of this wave only
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            for (int c0 = 0; c0 < upto; c0 += kTile16) {
+            for (int c0 = 0; c0 < upto && rank + c0 < limit; c0 += kTile16) {
                 const bool in_chunk = c0 + pl < upto;
                 const int off = in_chunk ? (int)mylist[c0 + pl] : 0;
                 const unsigned long long local = w_first * kTile + (unsigned long long)off;
@@ -271,8 +258,8 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                     S2 += u2;
                     S3 += u2 * u;
                     S4 += u2 * u2;
-                    n_ex += uf > kTwoSigmaT ? 1ull : 0ull;    // u > 2 sqrt(E0/pi)
-                    n_ex4 += uf > kFourSigmaT ? 1ull : 0ull;  // u > 4 sqrt(E0/pi)
+                    n_ex += uf > kTwoSigmaT ? 1u : 0u;    // u > 2 sqrt(E0/pi)
+                    n_ex4 += uf > kFourSigmaT ? 1u : 0u;  // u > 4 sqrt(E0/pi)
                     umax = fmaxf(umax, uf);
                 };
 #pragma unroll 1
@@ -329,12 +316,12 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                 s0 += __shfl_xor(s0, 16, 64);
                 s0 += __shfl_xor(s0, 32, 64);
                 if (valid && g == 0) {
-                    n_max4 += umax > kFourSigmaT ? 1ull : 0ull;
+                    n_max4 += umax > kFourSigmaT ? 1u : 0u;
                     peak_merge(peak_key, peak_idx, float_key(umax), i);
                     double posb = (s0 / sqrt((double)K) + 1.0) * (0.5 * kNBins);
                     int bin = (int)floor(posb);
                     bin = bin < 0 ? 0 : (bin > kNBins - 1 ? kNBins - 1 : bin);
-                    atomicAdd(&hist[bin], 1u);
+                    atomicAdd(&hist.bins[bin], 1u);
                 }
             }
             rank += upto;
@@ -348,47 +335,21 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
-        S1 = wave_sum_f64_128(S1);
-        S2 = wave_sum_f64_128(S2);
-        S3 = wave_sum_f64_128(S3);
-        S4 = wave_sum_f64_128(S4);
-        n_ex = wave_sum_u64_128(n_ex);
-        n_ex4 = wave_sum_u64_128(n_ex4);
-        n_max4 = wave_sum_u64_128(n_max4);
+        S1 = wave_sum_f64(S1);
+        S2 = wave_sum_f64(S2);
+        S3 = wave_sum_f64(S3);
+        S4 = wave_sum_f64(S4);
+        n_ex = wave_sum_u32(n_ex);
+        n_ex4 = wave_sum_u32(n_ex4);
+        n_max4 = wave_sum_u32(n_max4);
         wave_peak(peak_key, peak_idx);
         if (lane == 0) {
-            wave_S[wv][0] = S1;
-            wave_S[wv][1] = S2;
-            wave_S[wv][2] = S3;
-            wave_S[wv][3] = S4;
-            wave_ex[wv][0] = n_ex;
-            wave_ex[wv][1] = n_ex4;
-            wave_ex[wv][2] = n_max4;
-            wave_peak_key[wv] = peak_key;
-            wave_peak_idx[wv] = peak_idx;
+            const unsigned long long left = limit - first;
+            const unsigned long long ns = in_seg < left ? in_seg : left;
+            a.seg_stats[gs] = SegStats{S1, S2, S3, S4, n_ex, ns, n_ex4, n_max4, peak_idx, peak_key, 0u};
         }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            SegStats st = {0.0, 0.0, 0.0, 0.0, 0ull, 0ull, 0ull, 0ull, ~0ull, 0u, 0u};
-            for (int w = 0; w < W; ++w) {
-                st.S1 += wave_S[w][0];
-                st.S2 += wave_S[w][1];
-                st.S3 += wave_S[w][2];
-                st.S4 += wave_S[w][3];
-                st.n_exceed += wave_ex[w][0];
-                st.n_exceed4 += wave_ex[w][1];
-                st.n_max4 += wave_ex[w][2];
-                peak_merge(st.peak_key, st.peak_index, wave_peak_key[w], wave_peak_idx[w]);
-            }
-            const unsigned long long sb = seg_base[gs];
-            const unsigned long long se = sb + seg_cnt[gs];
-            st.n_samples = (se < limit ? se : limit) - sb;
-            seg_stats[gs] = st;
-        }
-        for (int b = threadIdx.x; b < kNBins; b += B)
-            if (hist[b]) atomicAdd(&res[p].hist[b], (unsigned long long)hist[b]);
-        __syncthreads();
     }
+    hist.flush(a, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -495,9 +456,7 @@ hipError_t launch_synth_q_t(const float *xhat, unsigned long long n, float *s3, 
 }
 
 template <int K, int PROP>
-hipError_t launch_materialize_q_t(const KernelArgs &a, unsigned long long total_segs,
-                                  const unsigned long long *seg_cnt, const unsigned long long *seg_base,
-                                  SegStats *seg_stats, PointResult *res, float *out_xhat,
+hipError_t launch_materialize_q_t(const KernelArgs &a, unsigned long long n_segs_max, float *out_xhat,
                                   unsigned long long *out_index, int n_cu, hipStream_t st)
 {
     constexpr int lds = MatQ<K>::LDS, B = MatQ<K>::W * kWave;
@@ -509,10 +468,10 @@ hipError_t launch_materialize_q_t(const KernelArgs &a, unsigned long long total_
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
     unsigned long long g = (unsigned long long)per_cu * n_cu;
-    if (total_segs < g) g = total_segs;
+    const unsigned long long want = (n_segs_max + MatQ<K>::W - 1) / MatQ<K>::W;
+    if (want < g) g = want;
     if (g < 1) g = 1;
-    hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(B), lds, st, a, total_segs, seg_cnt, seg_base, seg_stats, res,
-                       out_xhat, out_index);
+    hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(B), lds, st, a, out_xhat, out_index);
     return hipGetLastError();
 }
 
@@ -633,15 +592,11 @@ int decide_quarter64_max_blocks_per_cu(int prec)
                              : blocks_per_cu128_t<64, PREC_BF16X3, PROP_SIGMA>();
 }
 
-hipError_t launch_materialize_quarter(int K, int prop, const KernelArgs &a, unsigned long long total_segs,
-                                     const unsigned long long *seg_cnt, const unsigned long long *seg_base,
-                                     SegStats *seg_stats, PointResult *res, float *out_xhat,
-                                     unsigned long long *out_index, int n_cu, hipStream_t st)
+hipError_t launch_materialize_quarter(int K, int prop, const KernelArgs &a, unsigned long long n_segs_max,
+                                      float *out_xhat, unsigned long long *out_index, int n_cu, hipStream_t st)
 {
-#define TKDV_DISPATCH_MQ(KK, PP)                                                                            \
-    if (K == KK && prop == PP)                                                                             \
-        return launch_materialize_q_t<KK, PP>(a, total_segs, seg_cnt, seg_base, seg_stats, res, out_xhat, \
-                                              out_index, n_cu, st);
+#define TKDV_DISPATCH_MQ(KK, PP) \
+    if (K == KK && prop == PP) return launch_materialize_q_t<KK, PP>(a, n_segs_max, out_xhat, out_index, n_cu, st);
     TKDV_DISPATCH_MQ(64, PROP_SIGMA)
     TKDV_DISPATCH_MQ(64, PROP_UNIFORM)
     TKDV_DISPATCH_MQ(128, PROP_SIGMA)
