@@ -76,50 +76,107 @@ __device__ __forceinline__ float neg2_log_u_word(uint32_t w)
 // which is U below 1/2 and -(1 - U) above, both exact while |s| < 2^24, so one
 // conversion yields d = |qs| without the integer fold; fract(qs) is the log's
 // argument (U, or 1 - d rounded) without a subtraction and a selection; and
-// the factor 2 ln 2 is left out.  Series below d = 2^-12, i.e. for words
-// w >= 2^32 - 2^20 (one integer comparison):
-// -log2(1 - d) = d (1 + d/2)/ln 2, truncation below d^2/3 relative.
-__device__ __forceinline__ float neg_log2_u_word_signed(uint32_t w)
+// the factor 2 ln 2 is left out.  For words from kSeriesWord = 2^32 - 2^20 on
+// (d < 2^-12) the series -log2(1 - d) = d (1 + d/2)/ln 2, truncation below d^2/3
+// relative, takes the log's place (draw_fast applies it).
+constexpr uint32_t kSeriesWord = 0xFFF00000u;
+__device__ __forceinline__ float signed_uniform(uint32_t w)
 {
-    const float two_m32 = 2.3283064365386963e-10f;
-    const float qs = __builtin_fmaf((float)(int32_t)w, two_m32, 0.5f * two_m32);
+    return __builtin_fmaf((float)(int32_t)w, 2.3283064365386963e-10f, 0.5f * 2.3283064365386963e-10f);
+}
+__device__ __forceinline__ float neg_log2_u_signed(float qs) { return -log2_hw(__builtin_amdgcn_fractf(qs)); }
+__device__ __forceinline__ float neg_log2_u_series(float qs)
+{
     const float d = __builtin_fabsf(qs);
-    const float ser = d * __builtin_fmaf(d, 0.72134752044448170f, 1.4426950408889634f);  // 1/(2 ln 2), 1/ln 2
-    const float lg = -log2_hw(__builtin_amdgcn_fractf(qs));
-    return w >= 0xFFF00000u ? ser : lg;
+    return d * __builtin_fmaf(d, 0.72134752044448170f, 1.4426950408889634f);  // 1/(2 ln 2), 1/ln 2
 }
 
 // ln U of a word (the same arithmetic, scaled by -1/2).
 __device__ __forceinline__ float log_u_word(uint32_t w) { return -0.5f * neg2_log_u_word(w); }
 
-// One Box-Muller pair: r = sqrt(-2 ln U1), (r cos 2 pi U2, r sin 2 pi U2).
-// FAST, for the decision and weight kernels, whose FP32 values only steer the
-// exact FP64 decision: r from the signed-word -log2 U1, i.e. every coordinate
-// scaled by 1/sqrt(2 ln 2), a common factor that the projection onto the
-// sphere removes (x^, t, S3 |x|^-3 and the mixture's ratios are invariant),
-// and the angle from the signed word without the shift by half a turn.  The
-// kernels that write rows for the caller keep the folded-word form and the
-// unit scale, so that the rows' bits (and what is fitted to them, such as the
-// learned proposal's networks) do not move with that choice.
-template <bool FAST = false>
+// One Box-Muller pair: r = sqrt(-2 ln U1), (r cos 2 pi U2, r sin 2 pi U2), for
+// the kernels that write rows: the folded-word form and the unit scale, so
+// that the rows' bits (and what is fitted to them, such as the learned
+// proposal's networks) do not move with the decision path's choices (draw_fast).
 __device__ __forceinline__ void box_muller_f32(uint32_t w1, uint32_t w2, float &z0, float &z1)
 {
-    const float r = __builtin_amdgcn_sqrtf(FAST ? neg_log2_u_word_signed(w1)
-                                                : neg2_log_u_word(w1));  // argument below 45
+    const float r = __builtin_amdgcn_sqrtf(neg2_log_u_word(w1));  // argument below 45
+    // U2 - 1/2 = (w2 - 2^31 + 1/2) 2^-32 in revolutions, centred on zero for
+    // the hardware sin/cos; the signed integer w2 - 2^31 is formed exactly.
+    const float rev = __builtin_fmaf((float)(int32_t)(w2 ^ 0x80000000u), 2.3283064365386963e-10f,
+                                     1.1641532182693481e-10f);
+    // sin/cos(2 pi (U2 - 1/2)) = -sin/-cos(2 pi U2)
+    z0 = -r * __builtin_amdgcn_cosf(rev);
+    z1 = -r * __builtin_amdgcn_sinf(rev);
+}
+
+// The same draw for the decision and weight kernels, whose FP32 values only
+// steer the exact FP64 decision: r from the signed-word -log2 U1, i.e. every
+// coordinate scaled by 1/sqrt(2 ln 2), a common factor that the projection onto
+// the sphere removes (x^, t, S3 |x|^-3 and the mixture's ratios are invariant),
+// and the angle from the signed word U2 or U2 - 1 (the same angle in
+// revolutions).  Pairs (w1[q], w2[q]) -> x[2q], x[2q + 1], P pairs together: the
+// series near U1 = 1 takes four instructions a pair when selected each time,
+// though one pair in 4096 needs it; here the wave looks once at the largest
+// word and applies it only when some lane has one (one group of eight pairs in
+// eight).  Every value is the one a selection per pair gives.  Decisions of 1e9
+// proposals at K = 32: 48.5 -> 46.5 ms, of the mixture 74.1 -> 72.1 ms.
+template <int P>
+__device__ __forceinline__ void draw_fast(const uint32_t (&w1)[P], const uint32_t (&w2)[P], float *x)
+{
+    float l[P];
+    uint32_t m = w1[0];
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        l[q] = neg_log2_u_signed(signed_uniform(w1[q]));
+        m = w1[q] > m ? w1[q] : m;
+    }
+    if (__builtin_expect(__ballot(m >= kSeriesWord) != 0ull, 0)) {
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const float ser = neg_log2_u_series(signed_uniform(w1[q]));
+            l[q] = w1[q] >= kSeriesWord ? ser : l[q];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        const float r = __builtin_amdgcn_sqrtf(l[q]);
+        const float rev = signed_uniform(w2[q]);
+        x[2 * q] = r * __builtin_amdgcn_cosf(rev);
+        x[2 * q + 1] = r * __builtin_amdgcn_sinf(rev);
+    }
+}
+
+// Coordinates 4 b .. 4 b + 3 from Philox block blk0 + b, b < NB (FAST: draw_fast
+// in groups of kDrawBlocks blocks).
+constexpr int kDrawBlocks = 4;
+template <int NB, bool FAST>
+__device__ __forceinline__ void draw_blocks(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t blk0, uint32_t k0,
+                                            uint32_t k1, float *x)
+{
     if constexpr (FAST) {
-        // w2 read as a signed integer: (s2 + 1/2) 2^-32 is U2 or U2 - 1, the same
-        // angle in revolutions, in [-1/2, 1/2) as below
-        const float rev = __builtin_fmaf((float)(int32_t)w2, 2.3283064365386963e-10f, 1.1641532182693481e-10f);
-        z0 = r * __builtin_amdgcn_cosf(rev);
-        z1 = r * __builtin_amdgcn_sinf(rev);
+        constexpr int G = NB < kDrawBlocks ? NB : kDrawBlocks;
+        static_assert(NB % G == 0, "whole groups");
+#pragma unroll
+        for (int g = 0; g < NB; g += G) {
+            uint32_t w1[2 * G], w2[2 * G];
+#pragma unroll
+            for (int b = 0; b < G; ++b) {
+                const uint4 w = philox4x32_10(c0, c1, c2, blk0 + (uint32_t)(g + b), k0, k1);
+                w1[2 * b] = w.x;
+                w2[2 * b] = w.y;
+                w1[2 * b + 1] = w.z;
+                w2[2 * b + 1] = w.w;
+            }
+            draw_fast<2 * G>(w1, w2, x + 4 * g);
+        }
     } else {
-        // U2 - 1/2 = (w2 - 2^31 + 1/2) 2^-32 in revolutions, centred on zero for
-        // the hardware sin/cos; the signed integer w2 - 2^31 is formed exactly.
-        const float rev = __builtin_fmaf((float)(int32_t)(w2 ^ 0x80000000u), 2.3283064365386963e-10f,
-                                         1.1641532182693481e-10f);
-        // sin/cos(2 pi (U2 - 1/2)) = -sin/-cos(2 pi U2)
-        z0 = -r * __builtin_amdgcn_cosf(rev);
-        z1 = -r * __builtin_amdgcn_sinf(rev);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const uint4 w = philox4x32_10(c0, c1, c2, blk0 + (uint32_t)b, k0, k1);
+            box_muller_f32(w.x, w.y, x[4 * b + 0], x[4 * b + 1]);
+            box_muller_f32(w.z, w.w, x[4 * b + 2], x[4 * b + 3]);
+        }
     }
 }
 
@@ -141,21 +198,16 @@ __device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, 64); 
 // point, and the acceptance word.  With NORMALIZE the coordinates are
 // projected onto the sphere (x^ = x |x|^-1); otherwise the caller scales
 // whatever it derives from x.  Both lanes of a proposal compute bitwise
-// identical |x|^2 and t.  FAST selects the Box-Muller form (box_muller_f32):
-// by default the signed-word form where the draw only feeds a decision or a
-// weight, the folded-word form where rows are written.
+// identical |x|^2 and t.  FAST selects the Box-Muller form: by default
+// the signed-word form (draw_fast) where the draw only feeds a decision or a
+// weight, the folded-word form (box_muller_f32) where rows are written.
 // ---------------------------------------------------------------------------
 template <int K, int PROP, bool NORMALIZE, bool FAST = !NORMALIZE>
 __device__ __forceinline__ float gen_xhat(const DevPoint &P, uint64_t i, int half, float (&x)[K],
                                           float &t, uint32_t &w_acc)
 {
     const uint32_t c0 = (uint32_t)i, c1 = (uint32_t)(i >> 32), c2 = P.point_id;
-#pragma unroll
-    for (int b = 0; b < K / 4; ++b) {
-        uint4 w = philox4x32_10(c0, c1, c2, (uint32_t)(half * (K / 4) + b), P.key0, P.key1);
-        box_muller_f32<FAST>(w.x, w.y, x[4 * b + 0], x[4 * b + 1]);
-        box_muller_f32<FAST>(w.z, w.w, x[4 * b + 2], x[4 * b + 3]);
-    }
+    draw_blocks<K / 4, FAST>(c0, c1, c2, (uint32_t)(half * (K / 4)), P.key0, P.key1, x);
     w_acc = philox4x32_10(c0, c1, c2, (uint32_t)(K / 2), P.key0, P.key1).x;
     if (PROP == PROP_SIGMA) {
 #pragma unroll
@@ -913,20 +965,19 @@ __device__ __forceinline__ float gen_x_mix(const DevPoint &P, const DevMix &M, c
                                            int half, float (&x)[K], float &t, float &Qa, uint32_t &w_acc)
 {
     const uint32_t c0 = (uint32_t)i, c1 = (uint32_t)(i >> 32), c2 = P.point_id;
-#pragma unroll
-    for (int b = 0; b < K / 4; ++b) {
-        uint4 w = philox4x32_10(c0, c1, c2, (uint32_t)(half * (K / 4) + b), P.key0, P.key1);
-        box_muller_f32<FAST>(w.x, w.y, x[4 * b + 0], x[4 * b + 1]);
-        box_muller_f32<FAST>(w.z, w.w, x[4 * b + 2], x[4 * b + 3]);
-    }
+    draw_blocks<K / 4, FAST>(c0, c1, c2, (uint32_t)(half * (K / 4)), P.key0, P.key1, x);
     const uint4 wl = philox4x32_10(c0, c1, c2, (uint32_t)(K / 2), P.key0, P.key1);
     w_acc = wl.x;
     const int comp = mix_component(M, wl.y);
     const bool def = comp < 0;
-    float e0, e1;
-    box_muller_f32<FAST>(wl.z, wl.w, e0, e1);
-    e0 = def ? 0.0f : e0;
-    e1 = def ? 0.0f : e1;
+    float eta[2];
+    if constexpr (FAST) {
+        const uint32_t w1[1] = {wl.z}, w2[1] = {wl.w};
+        draw_fast<1>(w1, w2, eta);
+    } else {
+        box_muller_f32(wl.z, wl.w, eta[0], eta[1]);
+    }
+    const float e0 = def ? 0.0f : eta[0], e1 = def ? 0.0f : eta[1];
     const float2 *row = reinterpret_cast<const float2 *>(rv + (2 * (def ? 0 : comp) + half) * (2 * K + 2));
 #pragma unroll
     for (int j = 0; j < K; ++j) {

@@ -72,18 +72,13 @@ __device__ __forceinline__ float sum4(float v)
 // word pairs; X = Sigma^{1/2} z for the paper's proposal), and their
 // contributions to |X|^2, sum (j+1) X^2 and sum (j+1)^2 X^2 (t = sum k^2 X_k^2
 // over both blocks, k = K g/4 + j + 1).  FAST: the Box-Muller form of the
-// decision and weight kernels (box_muller_f32).
+// decision and weight kernels (draw_fast).
 template <int K, int PROP, bool FAST = true>
 __device__ __forceinline__ void gen_block128(const DevPoint &P, uint32_t c0, uint32_t c1, int g, int b,
                                              float (&v)[K / 4], float &r2, float &a1, float &a2)
 {
     constexpr int NB = Quarter<K>::NB;
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-        const uint4 w = philox4x32_10(c0, c1, P.point_id, (uint32_t)(b * (K / 4) + NB * g + q), P.key0, P.key1);
-        box_muller_f32<FAST>(w.x, w.y, v[4 * q + 0], v[4 * q + 1]);
-        box_muller_f32<FAST>(w.z, w.w, v[4 * q + 2], v[4 * q + 3]);
-    }
+    draw_blocks<NB, FAST>(c0, c1, P.point_id, (uint32_t)(b * (K / 4) + NB * g), P.key0, P.key1, v);
     if (PROP == PROP_SIGMA) {
         const float4 *sg = reinterpret_cast<const float4 *>(P.sig + (K / 4) * g);
 #pragma unroll
