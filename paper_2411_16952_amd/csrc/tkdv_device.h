@@ -190,45 +190,110 @@ __device__ __forceinline__ float log1p_f32(float y)
     return den == 0.0f ? y : lg * (y * __builtin_amdgcn_rcpf(den));
 }
 
-__device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, 64); }
+// Half-wave exchange: lanes 32-63 of a and lanes 0-31 of b change places.
+__device__ __forceinline__ void swap32(float &a, float &b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+// The odd rows (of 16 lanes) of a and the even rows of b change places.
+__device__ __forceinline__ void swap16(float &a, float &b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+// v of lane l + 32 (mod 64)
+__device__ __forceinline__ float xor32(float v)
+{
+    float lo = v, hi = v;
+    swap32(lo, hi);  // lo: lanes 0-31 twice, hi: lanes 32-63 twice
+    return (threadIdx.x & 32) ? lo : hi;
+}
+// Lane l and l + 32 both get v(l mod 32) + v(l mod 32 + 32).
+__device__ __forceinline__ float sum32(float v)
+{
+    float lo = v, hi = v;
+    swap32(lo, hi);
+    return lo + hi;
+}
+// One wave's LDS copies of N values of the two tiles of a pair, N x 2 x 64 floats.
+// In registers they would be live through the second tile's draw and products,
+// where the decision kernels have none left.
+template <int N>
+struct PairCarry {
+    float *buf;
+    __device__ __forceinline__ void put(int n, int tile, int lane, float v) const { buf[(n * 2 + tile) * 64 + lane] = v; }
+    // proposal (tile, pl): the sum over its two lanes, or its first lane's value
+    __device__ __forceinline__ float sum(int n, int tile, int pl) const
+    {
+        const float *b = buf + (n * 2 + tile) * 64 + pl;
+        return b[0] + b[32];
+    }
+    __device__ __forceinline__ float first(int n, int tile, int pl) const { return buf[(n * 2 + tile) * 64 + pl]; }
+    static constexpr int BYTES = N * 2 * 64 * 4;
+};
+// LDS written by a wave's lanes, read by others of the same wave.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 // ---------------------------------------------------------------------------
 // Proposal generation: the K coordinates x of this lane's block (scaled by the
-// proposal's standard deviations), |x|^-1, t = sum_k k^2 s_k of the projected
-// point, and the acceptance word.  With NORMALIZE the coordinates are
-// projected onto the sphere (x^ = x |x|^-1); otherwise the caller scales
-// whatever it derives from x.  Both lanes of a proposal compute bitwise
-// identical |x|^2 and t.  FAST selects the Box-Muller form: by default
-// the signed-word form (draw_fast) where the draw only feeds a decision or a
-// weight, the folded-word form (box_muller_f32) where rows are written.
+// proposal's standard deviations, not projected) and the lane's parts of
+// |x|^2 and sum_k k^2 x_k^2; the caller sums them over the proposal's two
+// lanes and scales what it derives from x by |x|^-1.  FAST selects the
+// Box-Muller form: the signed-word form (draw_fast) where the draw only feeds
+// a decision or a weight, the folded-word form (box_muller_f32) where rows are
+// written.
 // ---------------------------------------------------------------------------
-template <int K, int PROP, bool NORMALIZE, bool FAST = !NORMALIZE>
-__device__ __forceinline__ float gen_xhat(const DevPoint &P, uint64_t i, int half, float (&x)[K],
-                                          float &t, uint32_t &w_acc)
+// Floats that no kernel writes while it reads them, for scalar loads: as
+// ordinary memory, written to by the kernel's atomics as far as the compiler
+// knows, they came through vector loads into K registers a lane (1e9 proposals
+// at K = 32: 45.7 -> 45.3 ms).
+typedef const __attribute__((address_space(4))) float *ConstFloats;
+__device__ __forceinline__ ConstFloats const_floats(const float *p) { return (ConstFloats)(uint64_t)p; }
+
+template <int K, int PROP, bool FAST>
+__device__ __forceinline__ void gen_x_part(const DevPoint &P, uint64_t i, int half, float (&x)[K], float &r2, float &tk)
 {
-    const uint32_t c0 = (uint32_t)i, c1 = (uint32_t)(i >> 32), c2 = P.point_id;
-    draw_blocks<K / 4, FAST>(c0, c1, c2, (uint32_t)(half * (K / 4)), P.key0, P.key1, x);
-    w_acc = philox4x32_10(c0, c1, c2, (uint32_t)(K / 2), P.key0, P.key1).x;
+    draw_blocks<K / 4, FAST>((uint32_t)i, (uint32_t)(i >> 32), P.point_id, (uint32_t)(half * (K / 4)), P.key0, P.key1, x);
     if (PROP == PROP_SIGMA) {
+        const ConstFloats sg = const_floats(P.sig);
 #pragma unroll
-        for (int j = 0; j < K; ++j) x[j] *= P.sig[j];
+        for (int j = 0; j < K; ++j) x[j] *= sg[j];
     }
-    float r2 = 0.0f, tk = 0.0f;
+    r2 = 0.0f;
+    tk = 0.0f;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         const float sq = x[j] * x[j];
         r2 += sq;
         tk = __builtin_fmaf((float)((j + 1) * (j + 1)), sq, tk);
     }
-    r2 = r2 + xor32(r2);
-    tk = tk + xor32(tk);
-    const float inv = __builtin_amdgcn_rsqf(r2);
-    t = tk * (inv * inv);
-    if (NORMALIZE) {
+}
+
+// The acceptance word of proposal i (word 2K).
+template <int K>
+__device__ __forceinline__ uint32_t acceptance_word(const DevPoint &P, uint64_t i)
+{
+    return philox4x32_10((uint32_t)i, (uint32_t)(i >> 32), P.point_id, (uint32_t)(K / 2), P.key0, P.key1).x;
+}
+
+// The projected point of proposal i (rows for the caller): x^ = x |x|^-1 and t;
+// the bits do not depend on the decision path's choices (box_muller_f32).
+template <int K, int PROP>
+__device__ __forceinline__ void gen_xhat(const DevPoint &P, uint64_t i, int half, float (&x)[K], float &t)
+{
+    float r2, tk;
+    gen_x_part<K, PROP, false>(P, i, half, x, r2, tk);
+    const float inv = __builtin_amdgcn_rsqf(sum32(r2));
+    t = sum32(tk) * (inv * inv);
 #pragma unroll
-        for (int j = 0; j < K; ++j) x[j] *= inv;
-    }
-    return inv;
+    for (int j = 0; j < K; ++j) x[j] *= inv;
 }
 
 // ---------------------------------------------------------------------------
@@ -566,6 +631,21 @@ __device__ __forceinline__ float log_a_f32(const DevPoint &P, float t, float s3)
     return lf - P.log_M;
 }
 
+// The fast path's verdict on a proposal from log a and its acceptance word:
+// ln U < ln a - tau <=> U < a e^-tau (accept); within the window: FP64.
+// U = (w + 1/2) 2^-32; a = 2^(la log2 e) underflows to 0 only where U > a e^tau.
+// Above the bound by no more than the fast path's error (0 < log a <= tau) the
+// decision and the check of eq. (M_sup) are left to the FP64 pass.
+__device__ __forceinline__ void verdict(const DevPoint &P, float la, uint32_t w_acc, bool valid, bool &accept, bool &defer)
+{
+    const float U = __builtin_fmaf((float)w_acc, 2.3283064365386963e-10f, 1.1641532182693481e-10f);
+    const float alin = __builtin_amdgcn_exp2f(la * 1.4426950408889634f);
+    const float lo_edge = alin * P.e_lo, hi_edge = alin * P.e_hi;
+    const bool near_bound = la > 0.0f && la <= P.tau;
+    defer = valid && ((U >= lo_edge && U < hi_edge) || near_bound);
+    accept = valid && U < lo_edge && !near_bound;
+}
+
 // Order-preserving map float -> uint32 for atomicMax.
 __device__ __forceinline__ unsigned int float_key(float f)
 {
@@ -636,17 +716,19 @@ __device__ __forceinline__ unsigned long long tiles_taken(const DevPoint &P, uns
     return t < P.n_tiles ? t : P.n_tiles;
 }
 
-// A wave's even share [b, e) of point P's static tiles, W waves in all; the
-// remainders of successive points fall to different waves.
+// A wave's even share [b, e) of point P's static tiles, W waves in all, in
+// pairs of tiles (which the decision kernels settle together); the remainders
+// of successive points fall to different waves.
 __device__ __forceinline__ void static_range(const DevPoint &P, int p, unsigned gwave, unsigned W,
                                              unsigned long long &b, unsigned long long &e)
 {
     const unsigned w = (gwave + 977u * (unsigned)p) % W;
+    const unsigned n = (unsigned)P.static_tiles, n2 = (n + 1) / 2;  // at most kMaxStatic
     // wave-uniform; the quotient comes from the vector unit, so say so
-    const unsigned q = __builtin_amdgcn_readfirstlane((unsigned)P.static_tiles / W);  // at most kMaxStatic
-    const unsigned r = (unsigned)P.static_tiles - q * W;
-    b = bcast_lane0((unsigned long long)(q * w + (w < r ? w : r)));
-    e = b + q + (w < r ? 1 : 0);
+    const unsigned q = __builtin_amdgcn_readfirstlane(n2 / W), r = n2 - q * W;
+    const unsigned b0 = 2u * (q * w + (w < r ? w : r)), e0 = b0 + 2u * (q + (w < r ? 1u : 0u));
+    b = bcast_lane0((unsigned long long)(b0 < n ? b0 : n));
+    e = e0 < n ? e0 : n;
 }
 
 // Claims [b, e) from the tiles after the static ones; false when none is left
@@ -823,6 +905,15 @@ struct WaveWork {
     }
 };
 
+// One past the last proposal of a claim of len tiles from base.  The decision
+// kernels settle tiles in groups; a claim that is no multiple of the group draws
+// the tiles after it and drops them.
+__device__ __forceinline__ unsigned long long claim_stop(const DevPoint &P, unsigned long long base, int len)
+{
+    const unsigned long long e = (base + len) * kTile;
+    return e < P.n ? e : P.n;
+}
+
 // The segments of a call from the tiles decided (one workgroup of B threads):
 // their size and each point's first one.
 template <int B>
@@ -955,19 +1046,17 @@ __device__ __forceinline__ int mix_component(const DevMix &M, uint32_t w)
 }
 
 // Draw of proposal i from q_mix: this lane's K coordinates of X (words
-// 0..2K-1 as for the paper's proposal, word 2K the acceptance word, 2K+1 the
-// component word, 2K+2 and 2K+3 the pair eta), |X|^-1, t of the projected
-// point and Qa = sum over this proposal of a_c X_c^2 (unprojected).  rv
-// points to the RV table of the point (LDS or global memory).  FAST as for
-// gen_xhat.
-template <int K, bool NORMALIZE, bool FAST = !NORMALIZE>
-__device__ __forceinline__ float gen_x_mix(const DevPoint &P, const DevMix &M, const float *rv, uint64_t i,
-                                           int half, float (&x)[K], float &t, float &Qa, uint32_t &w_acc)
+// 0..2K-1 as for the paper's proposal, 2K+1 the component word, 2K+2 and 2K+3
+// the pair eta; wl is the last Philox block) and its parts of |X|^2, of
+// sum_k k^2 X_k^2 and of Qa = sum a_c X_c^2.  rv points to the RV table of the
+// point (LDS or global memory).  FAST as for gen_x_part.
+template <int K, bool FAST>
+__device__ __forceinline__ void gen_x_mix_part(const DevPoint &P, const DevMix &M, const float *rv, uint64_t i, int half,
+                                               float (&x)[K], float &r2, float &tk, float &qa)
 {
     const uint32_t c0 = (uint32_t)i, c1 = (uint32_t)(i >> 32), c2 = P.point_id;
     draw_blocks<K / 4, FAST>(c0, c1, c2, (uint32_t)(half * (K / 4)), P.key0, P.key1, x);
     const uint4 wl = philox4x32_10(c0, c1, c2, (uint32_t)(K / 2), P.key0, P.key1);
-    w_acc = wl.x;
     const int comp = mix_component(M, wl.y);
     const bool def = comp < 0;
     float eta[2];
@@ -984,25 +1073,30 @@ __device__ __forceinline__ float gen_x_mix(const DevPoint &P, const DevMix &M, c
         const float sc = def ? P.sig[j] : M.sqd[j];
         const float2 v = row[j];
         x[j] = __builtin_fmaf(v.x, e0, __builtin_fmaf(v.y, e1, sc * x[j]));
+        if (j % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // the loads of eight coordinates at a time
     }
-    float r2 = 0.0f, tk = 0.0f, qa = 0.0f;
+    r2 = tk = qa = 0.0f;
+    const ConstFloats am = const_floats(M.a);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
         const float sq = x[j] * x[j];
         r2 += sq;
         tk = __builtin_fmaf((float)((j + 1) * (j + 1)), sq, tk);
-        qa = __builtin_fmaf(M.a[j], sq, qa);
+        qa = __builtin_fmaf(am[j], sq, qa);
     }
-    r2 = r2 + xor32(r2);
-    tk = tk + xor32(tk);
-    Qa = qa + xor32(qa);
-    const float inv = __builtin_amdgcn_rsqf(r2);
-    t = tk * (inv * inv);
-    if (NORMALIZE) {
+}
+
+// The projected point of proposal i of the mixture sampler (rows for the caller).
+template <int K>
+__device__ __forceinline__ void gen_xhat_mix(const DevPoint &P, const DevMix &M, const float *rv, uint64_t i, int half,
+                                             float (&x)[K], float &t)
+{
+    float r2, tk, qa;
+    gen_x_mix_part<K, false>(P, M, rv, i, half, x, r2, tk, qa);
+    const float inv = __builtin_amdgcn_rsqf(sum32(r2));
+    t = sum32(tk) * (inv * inv);
 #pragma unroll
-        for (int j = 0; j < K; ++j) x[j] *= inv;
-    }
-    return inv;
+    for (int j = 0; j < K; ++j) x[j] *= inv;
 }
 
 // z = (R_j A V C^T)^T X for the S shifts on the matrix cores (C^T C = G^-1, so
@@ -1093,13 +1187,14 @@ __device__ __forceinline__ void mix_y_eo(const float (&x)[K], const bf16x8 (&eh)
 //   ln q_net + ln(1 - eps) = c_net - K ln(Qa |X|^-2) + ln sum_j r_j^-K,
 //   ln(eps g_Sigma) = c_g - K ln(1 + alpha beta' t/K^3).
 // The sum is taken relative to the smallest r_j of the proposal (all terms
-// <= 1, the largest exactly 1).  Both lanes of a proposal return the same.
-__device__ __forceinline__ float mix_log_q_f32(const DevPoint &P, const DevMix &M, const f32x16 &y0,
-                                               const f32x16 &y1, float Qa, float inv2, float t, float Kf)
+// <= 1, the largest exactly 1).  mix_shift_sum: this lane's 16 terms, and
+// log2 of the smallest ratio over both lanes; mix_log_q_f32: the rest, from the
+// sum over both lanes.
+__device__ __forceinline__ float mix_shift_sum(const f32x16 &y0, const f32x16 &y1, float Qa, float Kf, float &lmin)
 {
     const float invQ = __builtin_amdgcn_rcpf(Qa);
     float l[16];
-    float lmin = INFINITY;
+    lmin = INFINITY;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const float a0 = y0[v], a1 = y1[v];
@@ -1108,14 +1203,20 @@ __device__ __forceinline__ float mix_log_q_f32(const DevPoint &P, const DevMix &
         l[v] = log2_hw(r);
         lmin = fminf(lmin, l[v]);
     }
-    lmin = fminf(lmin, xor32(lmin));
+    float lo = lmin, hi = lmin;
+    swap32(lo, hi);
+    lmin = fminf(lo, hi);
     // K (lmin - l) as one FMA: K is a power of two (8, 16, 32), so K lmin is
     // exact and the FMA rounds the same exact value as the difference scaled
     const float klmin = Kf * lmin;
     float sum = __builtin_amdgcn_exp2f(__builtin_fmaf(-Kf, l[0], klmin));
 #pragma unroll
     for (int v = 1; v < 16; ++v) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(-Kf, l[v], klmin));
-    sum = sum + xor32(sum);
+    return sum;
+}
+__device__ __forceinline__ float mix_log_q_f32(const DevPoint &P, const DevMix &M, float sum, float lmin, float Qa,
+                                               float inv2, float t, float Kf)
+{
     const float ln2 = 0.69314718055994531f;
     const float LN = M.c_net + ln2 * (log2_hw(sum) - Kf * (lmin + log2_hw(Qa * inv2)));
     const float LG = M.c_g - Kf * log1p_f32(P.g_coef * t);

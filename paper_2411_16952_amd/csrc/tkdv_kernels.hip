@@ -77,6 +77,8 @@ __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, in
     const unsigned W = gridDim.x * (B / kWave);
     const float share = (float)n_plist / (2.0f * (float)W);
     PointTally tally;
+    const PairCarry<3> carry{reinterpret_cast<float *>(lds + decide_lds_bytes<K, PREC>()) +
+                             (threadIdx.x >> 6) * (PairCarry<3>::BYTES / 4)};
     WaveWork<K> work(gwave, n_plist);
     unsigned long long base;
     int len;
@@ -86,46 +88,54 @@ __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, in
         DevCounters *C = a.cnt + p;
         // accept bits and FP64 bits of tile `lane` of this claim
         uint32_t my_word = 0u, my_def = 0u;
-        for (int c = 0; c < len; ++c) {
+        const int len2 = (len + 1) & ~1;
+        const unsigned long long stop = claim_stop(P, base, len);
+#pragma unroll 1
+        for (int c = 0; c < len2; ++c) {
             // the point's constants stay in memory from tile to tile: hoisted out
             // of this loop they would take K registers a lane
             asm volatile("" ::: "memory");
             const unsigned long long tile = base + c;
-            const unsigned long long local = tile * kTile + pl;
-            const bool valid = local < P.n;
-            const uint64_t i = P.i0 + local;
-            float x[K];
-            float t;
-            uint32_t w_acc;
+            float x[K], r2, tk;
             // x is not projected: the cube sum of u~' = Phi^T x is scaled by |x|^-3
-            const float inv = gen_xhat<K, PROP, false>(P, i, half, x, t, w_acc);
-            if (a.dbg_xhat && valid) {
+            gen_x_part<K, PROP, true>(P, P.i0 + tile * kTile + pl, half, x, r2, tk);
+            if (a.dbg_xhat) {
+                const float inv = __builtin_amdgcn_rsqf(sum32(r2));
+                const unsigned long long local = tile * kTile + pl;
+                if (local < stop) {
 #pragma unroll
-                for (int j = 0; j < K; ++j) a.dbg_xhat[local * (2 * K) + half * K + j] = x[j] * inv;
+                    for (int j = 0; j < K; ++j) a.dbg_xhat[local * (2 * K) + half * K + j] = x[j] * inv;
+                }
             }
             float s3l;
             if constexpr (decide_half_period<K>()) s3l = eo_cube_sum<K, PREC, G>(x, lds_hi, lds_lo, lane);
             else s3l = synth_cube_sum<K, PREC>(x, lds_hi, lds_lo, lane);
-            const float s3 = (s3l + xor32(s3l)) * (inv * inv * inv);
+            carry.put(0, c & 1, lane, r2);
+            carry.put(1, c & 1, lane, tk);
+            carry.put(2, c & 1, lane, s3l);
+            if ((c & 1) == 0) continue;
+            // settle both tiles at once, a proposal per lane: lane l takes proposal
+            // 32 (c - 1) + l of the claim (one acceptance word, log a and verdict for
+            // each proposal instead of two).  1e9 proposals at K = 32: 46.8 -> 45.2 ms; 2e7 at
+            // K = 16 in FP32: 800 -> 752 us
+            wave_lds_sync();
+            const float inv = __builtin_amdgcn_rsqf(carry.sum(0, half, pl));
+            const float t = carry.sum(1, half, pl) * (inv * inv);
+            const float s3 = carry.sum(2, half, pl) * (inv * inv * inv);
+            wave_lds_sync();
+            const unsigned long long local = (tile - 1) * kTile + lane;
+            const bool valid = local < stop;
+            const uint32_t w_acc = acceptance_word<K>(P, P.i0 + local);
             const float la = log_a_f32<PROP>(P, t, s3);
-            // ln U < ln a - tau  <=>  U < a e^-tau (accept); within the window: FP64.
-            // U = (w + 1/2) 2^-32; a = 2^(la log2 e) underflows to 0 only where U > a e^tau.
-            const float U = __builtin_fmaf((float)w_acc, 2.3283064365386963e-10f, 1.1641532182693481e-10f);
-            const float alin = __builtin_amdgcn_exp2f(la * 1.4426950408889634f);
-            const float lo_edge = alin * P.e_lo, hi_edge = alin * P.e_hi;
-            const bool mine = valid && half == 0;
-            // above the bound by no more than the fast path's error (0 < log a <= tau):
-            // the decision and the check of eq. (M_sup) are left to the FP64 pass
-            const bool near_bound = la > 0.0f && la <= P.tau;
-            const bool defer = mine && ((U >= lo_edge && U < hi_edge) || near_bound);
-            const bool accept = mine && U < lo_edge && !near_bound;
+            bool accept, defer;
+            verdict(P, la, w_acc, valid, accept, defer);
             const unsigned long long bacc = __ballot(accept);
             const unsigned long long bdef = __ballot(defer);
-            if (lane == c) my_word = (uint32_t)bacc;
+            if ((lane | 1) == c) my_word = (uint32_t)((lane & 1) ? bacc >> 32 : bacc);
             if (bdef) {
-                if (lane == c) my_def = (uint32_t)bdef;
+                if ((lane | 1) == c) my_def = (uint32_t)((lane & 1) ? bdef >> 32 : bdef);
             }
-            if (mine) {
+            if (valid) {
                 // window proposals are counted by their FP64 value (k_fixup)
                 tally.n_viol += (la > 0.0f && !defer) ? 1u : 0u;
                 tally.max_la = fmaxf(tally.max_la, la);
@@ -200,6 +210,8 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
     const char *y_hi = lds + phi_bytes;
     const char *y_lo = lds + phi_bytes + yb;
     const float *rv = reinterpret_cast<const float *>(lds + phi_bytes + ytab_bytes);
+    const PairCarry<6> carry{reinterpret_cast<float *>(lds + phi_bytes + ytab_bytes + rv_bytes) +
+                             (threadIdx.x >> 6) * (PairCarry<6>::BYTES / 4)};
     const int lane = threadIdx.x & 63, half = lane >> 5, pl = lane & 31;
     const float Kf = (float)K;
     // the workgroups come to the points in turn: all waves share each queue
@@ -238,20 +250,26 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
             const int len = (int)(left < (unsigned long long)kClaimTiles ? left : (unsigned long long)kClaimTiles);
             cur = base + len;
             uint32_t my_word = 0u, my_def = 0u;
-            for (int c = 0; c < len; ++c) {
+            const int len2 = (len + 1) & ~1;
+        const unsigned long long stop = claim_stop(P, base, len);
+#pragma unroll 1
+            for (int c = 0; c < len2; ++c) {
                 asm volatile("" ::: "memory");  // as in k_decide: no hoisting of the constants
                 const unsigned long long tile = base + c;
-                const unsigned long long local = tile * kTile + pl;
-                const bool valid = local < P.n;
-                const uint64_t i = P.i0 + local;
-                float x[K];
-                float t, Qa;
-                uint32_t w_acc;
-                const float inv = gen_x_mix<K, false>(P, M, rv, i, half, x, t, Qa, w_acc);
-                if (a.dbg_xhat && valid) {
+                float x[K], r2, tk, qa;
+                gen_x_mix_part<K, true>(P, M, rv, P.i0 + tile * kTile + pl, half, x, r2, tk, qa);
+                carry.put(0, c & 1, lane, r2);
+                carry.put(1, c & 1, lane, tk);
+                qa = sum32(qa);
+                if (a.dbg_xhat) {
+                    const float inv = __builtin_amdgcn_rsqf(sum32(r2));
+                    const unsigned long long local = tile * kTile + pl;
+                    if (local < stop) {
 #pragma unroll
-                    for (int j = 0; j < K; ++j) a.dbg_xhat[local * (2 * K) + half * K + j] = x[j] * inv;
+                        for (int j = 0; j < K; ++j) a.dbg_xhat[local * (2 * K) + half * K + j] = x[j] * inv;
+                    }
                 }
+                float sum = 0.0f, lmin = 0.0f;
                 float s3l;
                 f32x16 y0, y1;
                 if constexpr (EO && PREC == PREC_FP32) {
@@ -262,8 +280,14 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
                     constexpr int S = eo_steps<K>();
                     bf16x8 eh[S], el[S], oh[S], ol[S];
                     split_eo<K, PREC>(x, eh, el, oh, ol);
-                    s3l = cube_sum_eo_bf16<K, PREC, 1>(eh, el, oh, ol, lds_hi, lds_lo, lane);
+                    // the shifts first: their sum is settled before the cube sum's accumulators
                     mix_y_eo<K, PREC>(x, eh, el, oh, ol, y_hi, y_lo, lane, y0, y1);
+                    sum = mix_shift_sum(y0, y1, qa, Kf, lmin);
+                    carry.put(3, c & 1, lane, sum);
+                    carry.put(4, c & 1, lane, qa);
+                    carry.put(5, c & 1, lane, lmin);
+                    __builtin_amdgcn_sched_barrier(0);
+                    s3l = cube_sum_eo_bf16<K, PREC, 1>(eh, el, oh, ol, lds_hi, lds_lo, lane);
                 } else if constexpr (EO) {  // BF16: hi operands only
                     constexpr int S = eo_steps<K>();
                     bf16x8 eh[S], oh[S];
@@ -276,26 +300,37 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
                     s3l = cube_sum_ops<K, PREC>(x, bh, bl, lds_hi, lds_lo, lane);
                     mix_y<K, PREC>(x, bh, bl, y_hi, y_lo, lane, y0, y1);
                 }
-                const float s3 = (s3l + xor32(s3l)) * (inv * inv * inv);
-                const float lq = mix_log_q_f32(P, M, y0, y1, Qa, inv * inv, t, Kf);
+                if constexpr (!(EO && PREC == PREC_BF16X3)) sum = mix_shift_sum(y0, y1, qa, Kf, lmin);
+                carry.put(2, c & 1, lane, s3l);
+                if constexpr (!(EO && PREC == PREC_BF16X3)) {
+                    carry.put(3, c & 1, lane, sum);
+                    carry.put(4, c & 1, lane, qa);
+                    carry.put(5, c & 1, lane, lmin);
+                }
+                if ((c & 1) == 0) continue;
+                // settle both tiles at once, a proposal per lane (k_decide)
+                wave_lds_sync();
+                asm volatile("" ::: "memory");
+                const float inv = __builtin_amdgcn_rsqf(carry.sum(0, half, pl));
+                const float t = carry.sum(1, half, pl) * (inv * inv);
+                const float s3 = carry.sum(2, half, pl) * (inv * inv * inv);
+                const float lq = mix_log_q_f32(P, M, carry.sum(3, half, pl), carry.first(5, half, pl),
+                                               carry.first(4, half, pl), inv * inv, t, Kf);
+                wave_lds_sync();
                 const float lf = __builtin_fmaf(P.neg_bp_K2, t, P.c3coef * s3);
                 const float la = (lf - lq) - P.log_M;
-                const float U = __builtin_fmaf((float)w_acc, 2.3283064365386963e-10f, 1.1641532182693481e-10f);
-                const float alin = __builtin_amdgcn_exp2f(la * 1.4426950408889634f);
-                const float lo_edge = alin * P.e_lo, hi_edge = alin * P.e_hi;
-                const bool mine = valid && half == 0;
-                // above the bound by no more than the fast path's error (0 < log a <= tau):
-                // the decision and the check of eq. (M_sup) are left to the FP64 pass
-                const bool near_bound = la > 0.0f && la <= P.tau;
-                const bool defer = mine && ((U >= lo_edge && U < hi_edge) || near_bound);
-                const bool accept = mine && U < lo_edge && !near_bound;
+                const unsigned long long local = (tile - 1) * kTile + lane;
+                const bool valid = local < stop;
+                const uint32_t w_acc = acceptance_word<K>(P, P.i0 + local);
+                bool accept, defer;
+                verdict(P, la, w_acc, valid, accept, defer);
                 const unsigned long long bacc = __ballot(accept);
                 const unsigned long long bdef = __ballot(defer);
-                if (lane == c) my_word = (uint32_t)bacc;
+                if ((lane | 1) == c) my_word = (uint32_t)((lane & 1) ? bacc >> 32 : bacc);
                 if (bdef) {
-                    if (lane == c) my_def = (uint32_t)bdef;
+                    if ((lane | 1) == c) my_def = (uint32_t)((lane & 1) ? bdef >> 32 : bdef);
                 }
-                if (mine) {
+                if (valid) {
                     tally.n_viol += (la > 0.0f && !defer) ? 1u : 0u;  // window proposals: k_fixup_mix
                     tally.max_la = fmaxf(tally.max_la, la);
                     if (a.dbg_t) {
@@ -758,15 +793,13 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
                 const bool valid = in_chunk && r < limit;
                 float x[K];
                 float t;
-                uint32_t w_acc;
                 if constexpr (PROP == PROP_MIXTURE) {
                     const DevMix &M = a.mix[p];
                     const float *rvg = reinterpret_cast<const float *>(
                         a.mix_tab + M.tab_off + 2 * mix_ytab_bf16_bytes<K>() + mix_ytab_f32_bytes<K>());
-                    float Qa;
-                    gen_x_mix<K, true>(P, M, rvg, i, half, x, t, Qa, w_acc);
+                    gen_xhat_mix<K>(P, M, rvg, i, half, x, t);
                 } else {
-                    gen_xhat<K, PROP, true>(P, i, half, x, t, w_acc);
+                    gen_xhat<K, PROP>(P, i, half, x, t);
                 }
                 if (valid && r < P.capacity) {
                     if (out_xhat) {
@@ -1099,7 +1132,7 @@ template <int K, int PREC, int PROP, int B = decide_block(K), int G = 1>
 static hipError_t launch_decide_t(const KernelArgs &a, const int *plist, int n_plist, int n_cu,
                                   unsigned long long total_tiles, hipStream_t st, int *grid_out)
 {
-    constexpr int lds = decide_lds_bytes<K, PREC>();
+    constexpr int lds = decide_lds_bytes<K, PREC>() + (B / kWave) * PairCarry<3>::BYTES;
     auto kern = k_decide<K, PREC, PROP, B, G>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
@@ -1135,7 +1168,7 @@ static hipError_t launch_decide_k(int prec, int prop, const KernelArgs &a, const
 template <int K, int PREC, int PROP, int B = decide_block(K), int G = 1>
 static int decide_blocks_per_cu_t()
 {
-    constexpr int lds = decide_lds_bytes<K, PREC>();
+    constexpr int lds = decide_lds_bytes<K, PREC>() + (B / kWave) * PairCarry<3>::BYTES;
     auto kern = k_decide<K, PREC, PROP, B, G>;
     if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return 1;
@@ -1271,7 +1304,7 @@ template <int K, int PREC>
 static hipError_t launch_decide_mix_t(const KernelArgs &a, const int *plist, int n_plist, int n_cu,
                                       unsigned long long total_tiles, hipStream_t st, int *grid_out)
 {
-    constexpr int lds = decide_mix_lds_bytes<K, PREC>();
+    constexpr int lds = decide_mix_lds_bytes<K, PREC>() + (kMixBlock / kWave) * PairCarry<6>::BYTES;
     auto kern = k_decide_mix<K, PREC>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;

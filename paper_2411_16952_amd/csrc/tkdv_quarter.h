@@ -62,8 +62,11 @@ struct Quarter {
 // gets the same two operands in the last addition, hence the same bits
 __device__ __forceinline__ float sum4(float v)
 {
-    v = v + __shfl_xor(v, 16, 64);
-    return v + __shfl_xor(v, 32, 64);
+    float lo = v, hi = v;
+    swap16(lo, hi);
+    lo = hi = lo + hi;
+    swap32(lo, hi);
+    return lo + hi;
 }
 
 
@@ -102,12 +105,16 @@ __device__ __forceinline__ void gen_block128(const DevPoint &P, uint32_t c0, uin
 // |X|^-1 and t of the projected point from the lane's partial sums (the four
 // lanes of a proposal end with bitwise identical values).
 template <int K>
-__device__ __forceinline__ float finish_norm128(int g, float r2, float a1, float a2, float &t)
+__device__ __forceinline__ float weighted_part128(int g, float r2, float a1, float a2)  // this lane's sum k^2 X_k^2
 {
     const float b = (float)((K / 4) * g);
-    float tk = __builtin_fmaf(b * b, r2, __builtin_fmaf(2.0f * b, a1, a2));
+    return __builtin_fmaf(b * b, r2, __builtin_fmaf(2.0f * b, a1, a2));
+}
+template <int K>
+__device__ __forceinline__ float finish_norm128(int g, float r2, float a1, float a2, float &t)
+{
+    const float tk = sum4(weighted_part128<K>(g, r2, a1, a2));
     r2 = sum4(r2);
-    tk = sum4(tk);
     const float inv = __builtin_amdgcn_rsqf(r2);
     t = tk * (inv * inv);
     return inv;
@@ -115,20 +122,19 @@ __device__ __forceinline__ float finish_norm128(int g, float r2, float a1, float
 
 // Proposal i of the point: this lane's K/4 cos and K/4 sin coordinates of X
 // (words 0..2K-1 as in every sampler: coordinate m from word m, Box-Muller on
-// word pairs; X = Sigma^{1/2} z for the paper's proposal), |X|^-1, t of the
-// projected point and the acceptance word (word 2K).  With NORMALIZE the
+// word pairs; X = Sigma^{1/2} z for the paper's proposal), |X|^-1 and t of the
+// projected point.  With NORMALIZE the
 // coordinates are projected onto the sphere (rows for the caller, drawn with
 // the folded-word Box-Muller form unless FAST).  The four lanes of a proposal
 // hold bitwise identical |X|^2 and t.
 template <int K, int PROP, bool NORMALIZE, bool FAST = !NORMALIZE>
 __device__ __forceinline__ float gen_x128(const DevPoint &P, uint64_t i, int g, float (&c)[K / 4],
-                                          float (&s)[K / 4], float &t, uint32_t &w_acc)
+                                          float (&s)[K / 4], float &t)
 {
     const uint32_t c0 = (uint32_t)i, c1 = (uint32_t)(i >> 32);
     float r2 = 0.0f, a1 = 0.0f, a2 = 0.0f;
     gen_block128<K, PROP, FAST>(P, c0, c1, g, 0, c, r2, a1, a2);
     gen_block128<K, PROP, FAST>(P, c0, c1, g, 1, s, r2, a1, a2);
-    w_acc = philox4x32_10(c0, c1, P.point_id, (uint32_t)(K / 2), P.key0, P.key1).x;
     const float inv = finish_norm128<K>(g, r2, a1, a2, t);
     if (NORMALIZE) {
 #pragma unroll

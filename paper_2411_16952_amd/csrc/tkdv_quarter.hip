@@ -12,6 +12,9 @@ namespace tkdv {
 
 namespace {
 
+// Bytes of LDS a wave of k_decide128 carries from tile to tile: three values of 64 proposals.
+constexpr int kCarry128 = 3 * kWave * 4;
+
 // ---------------------------------------------------------------------------
 // k_decide128: persistent; claims of up to 64 accept words (2048 proposals, 128
 // tiles of 16) from per-point queues, as the other decision kernels.
@@ -46,6 +49,7 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
     const unsigned W = gridDim.x * (B / kWave);
     const float share = (float)n_plist / (2.0f * (float)W);
     PointTally tally;
+    float *carry = reinterpret_cast<float *>(lds + Quarter<K>::lds(PREC)) + (threadIdx.x >> 6) * (kCarry128 / 4);
     WaveWork<K> work(gwave, n_plist);
     unsigned long long base;
     int len;
@@ -55,18 +59,18 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
         DevCounters *C = a.cnt + p;
         // accept bits and FP64 bits of word `lane` of this claim
         uint32_t my_word = 0u, my_def = 0u;
-        for (int c2 = 0; c2 < 2 * len; ++c2) {
+        const int tiles = (2 * len + 3) & ~3;  // groups of four tiles: two accept words
+        const unsigned long long stop = claim_stop(P, base, len);
+#pragma unroll 1
+        for (int c2 = 0; c2 < tiles; ++c2) {
             asm volatile("" ::: "memory");  // as in k_decide: no hoisting of the constants
-            const unsigned long long word = base + (c2 >> 1);
-            const unsigned long long local = word * kTile + (c2 & 1) * kTile16 + pl;
-            const bool valid = local < P.n;
-            const uint64_t i = P.i0 + local;
+            const unsigned long long first = (base + (c2 >> 1)) * kTile + (c2 & 1) * kTile16;  // the tile's first proposal
+            const uint64_t i = P.i0 + first + pl;
             if (DBG && a.dbg_xhat) {  // verification: the projected point, generated once more
                 float c[CPL], s[CPL], tt;
-                uint32_t ww;
-                gen_x128<K, PROP, true, true>(P, i, g, c, s, tt, ww);  // the decision's draw
-                if (valid) {
-                    float *row = a.dbg_xhat + local * (2 * K);
+                gen_x128<K, PROP, true, true>(P, i, g, c, s, tt);  // the decision's draw
+                if (first + pl < stop) {
+                    float *row = a.dbg_xhat + (first + pl) * (2 * K);
 #pragma unroll
                     for (int j = 0; j < CPL; ++j) {
                         row[CPL * g + j] = c[j];
@@ -75,13 +79,22 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
                 }
             }
             const uint32_t c0 = (uint32_t)i, c1 = (uint32_t)(i >> 32);
-            float r2 = 0.0f, a1 = 0.0f, a2 = 0.0f, s3l, t, inv;
+            float r2 = 0.0f, a1 = 0.0f, a2 = 0.0f, s3l;
+            float *mine = carry + (c2 & 3) * kTile16 + pl;  // this tile's |X|^2, sum k^2 X_k^2 and S3
+            auto norms = [&]() {
+                const float tk = weighted_part128<K>(g, r2, a1, a2);
+                const float r2s = sum4(r2), tks = sum4(tk);
+                if (g == 0) {
+                    mine[0] = r2s;
+                    mine[kWave] = tks;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
             if constexpr (PREC == PREC_FP32) {
                 float c[CPL], s[CPL];
                 gen_block128<K, PROP>(P, c0, c1, g, 0, c, r2, a1, a2);
                 gen_block128<K, PROP>(P, c0, c1, g, 1, s, r2, a1, a2);
-                inv = finish_norm128<K>(g, r2, a1, a2, t);
-                __builtin_amdgcn_sched_barrier(0);
+                norms();
                 s3l = cube_sum_q128_f32<K>(c, s, lds_hi, lane);
             } else {
                 // one block at a time: its coordinates die once split into operands
@@ -100,29 +113,34 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
                     // keep the next block's generation after this split (register pressure)
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                inv = finish_norm128<K>(g, r2, a1, a2, t);
-                __builtin_amdgcn_sched_barrier(0);
+                norms();
                 s3l = cube_sum_q128_bf16<K, PREC, K == 128 ? 2 : 1>(bh, bl, lds_hi, lds_lo, lane);
             }
-            const uint32_t w_acc = philox4x32_10(c0, c1, P.point_id, (uint32_t)(K / 2), P.key0, P.key1).x;
-            const float s3 = sum4(s3l) * (inv * inv * inv);
+            s3l = sum4(s3l);
+            if (g == 0) mine[2 * kWave] = s3l;
+            if ((c2 & 3) != 3) continue;
+            // settle four tiles at once, a proposal per lane: lane l takes proposal
+            // 16 (c2 - 3) + l of the claim (one acceptance word, log a and verdict for
+            // each proposal instead of four).  Four points of 6e7 at K = 64 and 128: 42.4 -> 41.4 ms
+            wave_lds_sync();
+            const float inv = __builtin_amdgcn_rsqf(carry[lane]);
+            const float t = carry[kWave + lane] * (inv * inv);
+            const float s3 = carry[2 * kWave + lane] * (inv * inv * inv);
+            wave_lds_sync();
+            const unsigned long long local = first - 3 * kTile16 + lane;
+            const bool valid = local < stop;
+            const uint32_t w_acc = acceptance_word<K>(P, P.i0 + local);
             const float la = log_a_f32<PROP>(P, t, s3);
-            const float U = __builtin_fmaf((float)w_acc, 2.3283064365386963e-10f, 1.1641532182693481e-10f);
-            const float alin = __builtin_amdgcn_exp2f(la * 1.4426950408889634f);
-            const float lo_edge = alin * P.e_lo, hi_edge = alin * P.e_hi;
-            const bool mine = valid && g == 0;
-            // above the bound by no more than the fast path's error (0 < log a <= tau):
-            // the decision and the check of eq. (M_sup) are left to the FP64 pass
-            const bool near_bound = la > 0.0f && la <= P.tau;
-            const bool defer = mine && ((U >= lo_edge && U < hi_edge) || near_bound);
-            const bool accept = mine && U < lo_edge && !near_bound;
+            bool accept, defer;
+            verdict(P, la, w_acc, valid, accept, defer);
             const unsigned long long bacc = __ballot(accept);
             const unsigned long long bdef = __ballot(defer);
-            if (lane == (c2 >> 1)) my_word |= (uint32_t)(bacc & 0xffffull) << (16 * (c2 & 1));
+            const bool word = (lane & ~1) == ((c2 >> 1) & ~1);  // lanes of the group's two accept words
+            if (word) my_word = (uint32_t)((lane & 1) ? bacc >> 32 : bacc);
             if (bdef) {
-                if (lane == (c2 >> 1)) my_def |= (uint32_t)(bdef & 0xffffull) << (16 * (c2 & 1));
+                if (word) my_def = (uint32_t)((lane & 1) ? bdef >> 32 : bdef);
             }
-            if (mine) {
+            if (valid) {
                 tally.n_viol += (la > 0.0f && !defer) ? 1u : 0u;  // window proposals: k_fixup
                 tally.max_la = fmaxf(tally.max_la, la);
                 if (DBG && a.dbg_t) {
@@ -236,8 +254,7 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                 const unsigned long long r = rank + c0 + pl;
                 const bool valid = in_chunk && r < limit;
                 float c[CPL], s[CPL], t;
-                uint32_t w_acc;
-                gen_x128<K, PROP, true>(P, i, g, c, s, t, w_acc);
+                gen_x128<K, PROP, true>(P, i, g, c, s, t);
                 if (valid && r < P.capacity) {
                     if (out_xhat) {
                         float *row = out_xhat + (P.out_off + r) * P.row_stride;
@@ -479,9 +496,9 @@ template <int K, int PREC, int PROP, int BL = decide_block(K)>
 hipError_t launch_decide128_t(const KernelArgs &a, const int *plist, int n_plist, int n_cu,
                               unsigned long long total_tiles, hipStream_t st, int *grid_out)
 {
-    constexpr int lds = Quarter<K>::lds(PREC), BD = Quarter<K>::BLOCK;
+    constexpr int BD = Quarter<K>::BLOCK;
     const bool dbg = a.dbg_xhat != nullptr || a.dbg_t != nullptr;
-    const int B = dbg ? BD : BL;
+    const int B = dbg ? BD : BL, lds = Quarter<K>::lds(PREC) + B / kWave * kCarry128;
     auto kern = dbg ? k_decide128<K, PREC, PROP, true, BD> : k_decide128<K, PREC, PROP, false, BL>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
@@ -503,7 +520,7 @@ hipError_t launch_decide128_t(const KernelArgs &a, const int *plist, int n_plist
 template <int K, int PREC, int PROP, int BL = decide_block(K)>
 int blocks_per_cu128_t()
 {
-    constexpr int lds = Quarter<K>::lds(PREC);
+    constexpr int lds = Quarter<K>::lds(PREC) + BL / kWave * kCarry128;
     auto kern = k_decide128<K, PREC, PROP, false, BL>;
     if (hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
         return 1;

@@ -204,10 +204,9 @@ __global__ void __launch_bounds__(kBlock) k_sir_weights(SirArgs a)
         const unsigned long long local = tile * kTile + pl;
         const bool valid = local < a.n;
         const uint64_t i = P.i0 + local;
-        float x[K];
-        float t;
-        uint32_t w_acc;
-        const float inv = gen_xhat<K, PROP, false>(P, i, half, x, t, w_acc);
+        float x[K], r2, tk;
+        gen_x_part<K, PROP, true>(P, i, half, x, r2, tk);
+        const float inv = __builtin_amdgcn_rsqf(sum32(r2)), t = sum32(tk) * (inv * inv);
         float s1, s2, s3, s4;
         grid_power_sums<K, PREC>(x, lds, lds + tab, lane, s1, s2, s3, s4);
         const float i2 = inv * inv;
@@ -489,8 +488,7 @@ __global__ void __launch_bounds__(kBlock) k_sir_resample(SirArgs a)
                     const unsigned long long d0 = __shfl(r0, pp, 64), d1 = __shfl(r1, pp, 64);
                     if (__ballot(d1 > d0) == 0ull) continue;
                     float c[CPL], s[CPL], t;
-                    uint32_t w_acc;
-                    gen_x128<K, PROP, true>(P, P.i0 + tile * kTile + pp, g, c, s, t, w_acc);
+                    gen_x128<K, PROP, true>(P, P.i0 + tile * kTile + pp, g, c, s, t);
                     for (unsigned long long r = d0; r < d1; ++r) {
                         float *dst = a.xhat + r * (2 * K) + CPL * g;
 #pragma unroll
@@ -503,8 +501,7 @@ __global__ void __launch_bounds__(kBlock) k_sir_resample(SirArgs a)
             } else {
                 float x[K];
                 float t;
-                uint32_t w_acc;
-                gen_xhat<K, PROP, true>(P, i, half, x, t, w_acc);
+                gen_xhat<K, PROP>(P, i, half, x, t);
                 for (unsigned long long r = q0; r < q1; ++r) {
                     float *dst = a.xhat + r * (2 * K) + half * K;
 #pragma unroll
