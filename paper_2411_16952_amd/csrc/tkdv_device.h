@@ -811,14 +811,25 @@ __device__ __forceinline__ void push_deferred(const KernelArgs &a, DevCounters *
     }
 }
 
+__device__ __forceinline__ unsigned int wave_sum_u32(unsigned int v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
 // What a wave has seen of a point since it last reported: violations of the
-// bound and the largest log a.  Reported when the wave leaves the point.
+// bound, the largest log a and, in long ranges, the accepted proposals.
+// Reported when the wave leaves the point.
 struct PointTally {
     unsigned int n_viol = 0;
+    unsigned int n_acc = 0;  // accepted, in proposal-count mode (wave-uniform)
     float max_la = -INFINITY;
     __device__ __forceinline__ void report(DevCounters *C, int lane)
     {
         CounterShard &S = C->shard[blockIdx.x % kShards];
+        if (n_acc) add_lane0(&S.accepted, n_acc, lane);
+        n_acc = 0;
         if (__ballot(n_viol != 0u) != 0ull) {
             unsigned int v = n_viol;
 #pragma unroll
@@ -838,14 +849,21 @@ struct PointTally {
     }
 };
 
-// Accepted-count mode: the finished tiles and their definite accepts (lane c:
-// the word of tile c).
-__device__ __forceinline__ void count_accepted(const DevPoint &P, DevCounters *C, uint32_t word, int len, int lane)
+// The finished tiles and their definite accepts (lane c: the word of tile c):
+// at once in accepted-count mode, where claims depend on them; otherwise with
+// the wave's other tallies, for the size of the segments (kTallyTiles).
+constexpr unsigned long long kTallyTiles = 1ull << 16;
+__device__ __forceinline__ void count_accepted(const DevPoint &P, DevCounters *C, PointTally &tally, uint32_t word,
+                                               int len, int lane)
 {
-    if (P.target == ~0ull) return;  // proposal-count mode: the segments count
-    unsigned int v = __popc(word);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    // a small range has the same segments whatever it accepted, and an atomic
+    // of every wave would show in its time
+    if (P.target == ~0ull && P.n_tiles < kTallyTiles) return;
+    const unsigned int v = __builtin_amdgcn_readfirstlane(wave_sum_u32(__popc(word)));
+    if (P.target == ~0ull) {
+        tally.n_acc += v;
+        return;
+    }
     CounterShard &S = C->shard[blockIdx.x % kShards];
     add_lane0(&S.accepted, v, lane);
     add_lane0(&S.finished, (unsigned long long)len, lane);
@@ -914,24 +932,73 @@ __device__ __forceinline__ unsigned long long claim_stop(const DevPoint &P, unsi
     return e < P.n ? e : P.n;
 }
 
+// A lane's share of the statistics of the grid values u = amp u~ of accepted
+// samples, from the FP32 values of u~: power sums of u~ in FP64 (scaled by powers
+// of amp at the end) and the values above 2 and 4 sigma, counted once per wave.
+// Six FP64 operations a value; with the scaling and two counters a lane it took
+// twelve instructions where nine do.
+struct GridSums {
+    double S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
+    unsigned int n_ex = 0, n_ex4 = 0;  // wave-uniform
+    float umax = -INFINITY;            // the largest value of this lane's proposal so far
+
+    __device__ __forceinline__ void add(float uf)
+    {
+        const double u = (double)uf, u2 = u * u;
+        S1 += u;
+        S2 += u2;
+        S3 = __builtin_fma(u2, u, S3);
+        S4 = __builtin_fma(u2, u2, S4);
+        n_ex += (unsigned)__popcll(__ballot(uf > kTwoSigmaT));  // u > 2 sqrt(E0/pi)
+    }
+    template <int N>
+    __device__ __forceinline__ void add(const float (&uf)[N])
+    {
+        float top = uf[0];
+#pragma unroll
+        for (int v = 1; v < N; ++v) top = fmaxf(top, uf[v]);
+        umax = fmaxf(umax, top);
+        if (__any(top > kFourSigmaT)) {  // u > 4 sqrt(E0/pi): rare
+#pragma unroll
+            for (int v = 0; v < N; ++v) n_ex4 += (unsigned)__popcll(__ballot(uf[v] > kFourSigmaT));
+        }
+#pragma unroll
+        for (int v = 0; v < N; ++v) {
+            add(uf[v]);
+            // four values at a time: else the masks of all N wait in SGPRs
+            if (v % 4 == 3) {
+                n_ex = __builtin_amdgcn_readfirstlane(n_ex);
+                asm volatile("" : "+s"(n_ex), "+v"(S1), "+v"(S2), "+v"(S3), "+v"(S4));
+            }
+        }
+    }
+};
+
 // The segments of a call from the tiles decided (one workgroup of B threads):
 // their size and each point's first one.
 template <int B>
 __device__ void plan_segments(const KernelArgs &a)
 {
-    __shared__ unsigned long long buf[B];
+    __shared__ unsigned long long buf[B], acc[B];
     __shared__ unsigned long long words_s;
     const int tid = threadIdx.x;
-    unsigned long long sum = 0;
-    for (int p = tid; p < a.n_points; p += B) sum += tiles_taken(a.pts[p], a.cnt[p].next_tile);
+    unsigned long long sum = 0, accepted = 0;
+    for (int p = tid; p < a.n_points; p += B) {
+        sum += tiles_taken(a.pts[p], a.cnt[p].next_tile);
+        for (int s = 0; s < kShards; ++s) accepted += load_relaxed(&a.cnt[p].shard[s].accepted);
+    }
     buf[tid] = sum;
+    acc[tid] = accepted;
     __syncthreads();
     for (int o = B / 2; o > 0; o >>= 1) {
-        if (tid < o) buf[tid] += buf[tid + o];
+        if (tid < o) {
+            buf[tid] += buf[tid + o];
+            acc[tid] += acc[tid + o];
+        }
         __syncthreads();
     }
     if (tid == 0) {
-        words_s = seg_words_for(buf[0]);
+        words_s = seg_words_for(buf[0], acc[0]);
         a.seg->words = words_s;
     }
     __syncthreads();
@@ -992,12 +1059,6 @@ struct WaveHist {
 };
 static_assert(kNBins == kWave, "one bin per lane");
 
-__device__ __forceinline__ unsigned int wave_sum_u32(unsigned int v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 __device__ __forceinline__ double wave_sum_f64(double v)
 {
 #pragma unroll

@@ -48,22 +48,31 @@ constexpr uint64_t static_share(uint64_t n, uint64_t at_least, int n_points)
 }
 // The accept words of a call are cut into segments of 8 to 2048 words (a power
 // of two), one wave each in the ordered output: about kSegments of them, so that
-// small calls fill the chip too.  Fixed segments of 2048 words, a workgroup each,
-// left a million near-linear samples at K = 16 to 16 workgroups (1.6 ms of
-// ordered output, now 0.12 ms).
-constexpr int kSegWordsMin = 8, kSegWordsMax = 2048;
-constexpr int kSegments = 8192;
-constexpr unsigned long long seg_words_for(unsigned long long words)
+// small calls fill the chip too; more, of no fewer than kSegWordsMid words, where
+// each still has kSegAccepts accepted proposals, so that waves of points of unlike
+// acceptance end together.  Fixed segments of 2048 words, a workgroup each, left a
+// million near-linear samples at K = 16 to 16 workgroups (1.6 ms of ordered
+// output, now 0.1 ms); 6.5e7 accepted of four points at K = 64 and 128 took
+// 28.7 ms in 7300 segments and take 25.0 in 58600, while 1e9 proposals with 5e5
+// accepted would pay 0.25 ms for as many.
+constexpr int kSegWordsMin = 8, kSegWordsMid = 128, kSegWordsMax = 2048;
+constexpr int kSegments = 8192, kSegmentsMax = 65536, kSegAccepts = 1024;
+constexpr unsigned long long seg_words_for(unsigned long long words, unsigned long long accepted)
 {
+    unsigned long long most = accepted / kSegAccepts;
+    if (most < (unsigned long long)kSegments) most = kSegments;
+    if (most > (unsigned long long)kSegmentsMax) most = kSegmentsMax;
     unsigned long long s = kSegWordsMin;
-    while (s < (unsigned long long)kSegWordsMax && words > s * kSegments) s *= 2;
+    while (s < (unsigned long long)kSegWordsMax && words > s * (s < (unsigned long long)kSegWordsMid ? kSegments : most)) s *= 2;
     return s;
 }
-// most segments of a call of n_points points with `words` accept words
+// most segments of a call of n_points points with at most `words` accept words
 constexpr unsigned long long max_segments(unsigned long long words, int n_points)
 {
-    const unsigned long long by_size = words / kSegWordsMax;
-    return (by_size > (unsigned long long)kSegments ? by_size : (unsigned long long)kSegments) + (unsigned long long)n_points;
+    const unsigned long long mid = words / kSegWordsMid, by_size = words / kSegWordsMax;
+    unsigned long long n = mid < (unsigned long long)kSegmentsMax ? mid : (unsigned long long)kSegmentsMax;
+    if (n < (unsigned long long)kSegments) n = kSegments;
+    return (by_size > n ? by_size : n) + (unsigned long long)n_points;
 }
 constexpr int kNBins = TKDV_NBINS;
 constexpr int kMixBlock = 1024;    // threads per workgroup of the mixture sampling kernel

@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, in
         // one coalesced store of the claim's accept words
         if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
         push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
-        count_accepted(P, C, my_word, len, lane);
+        count_accepted(P, C, tally, my_word, len, lane);
     }
 }
 
@@ -343,7 +343,7 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
             }
             if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
             push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
-            count_accepted(P, C, my_word, len, lane);
+            count_accepted(P, C, tally, my_word, len, lane);
         }
         tally.report(C, lane);
     }
@@ -659,6 +659,7 @@ __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a)
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
         const unsigned long long w0 = (gs - a.seg->off[p]) * S, w1 = w0 + S < nw ? w0 + S : nw;
         unsigned int c = 0;
+#pragma unroll 4
         for (unsigned long long w = w0 + lane; w < w1; w += kWave) c += __popc(a.bitmap[P.bm_off + w]);
         c = wave_sum_u32(c);
         if (lane == 0) a.seg_cnt[gs] = c;
@@ -674,6 +675,7 @@ __global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a)
     const unsigned long long s0 = a.seg->off[p], n = a.seg->off[p + 1] - s0;
     const unsigned long long per = (n + 1023) / 1024, b = per * tid < n ? per * tid : n, e = b + per < n ? b + per : n;
     unsigned long long own = 0;
+#pragma unroll 8
     for (unsigned long long s = b; s < e; ++s) own += a.seg_cnt[s0 + s];
     unsigned long long incl = own;
 #pragma unroll
@@ -689,6 +691,7 @@ __global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a)
         all += wsum[w];
     }
     unsigned long long run = before + incl - own;
+#pragma unroll 8
     for (unsigned long long s = b; s < e; ++s) {
         a.seg_base[s0 + s] = run;
         run += a.seg_cnt[s0 + s];
@@ -750,8 +753,8 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
         const unsigned long long w_first = (gs - a.seg->off[p]) * S;
         unsigned long long rank = first;
-        double S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
-        unsigned int n_ex = 0, n_ex4 = 0, n_max4 = 0;
+        GridSums sums;
+        unsigned int n_max4 = 0;
         unsigned long long peak_idx = ~0ull;
         unsigned int peak_key = 0u;
         // accepted offsets (proposals from the segment's first word) queue up in
@@ -813,18 +816,11 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
                 // statistics on the grid: u = sqrt(2 E0/pi) u~, u~ from FP32 products
                 // (K >= 16: the half-period form, u~ = E + O and E - O on the two halves)
                 const float4 *ftab = reinterpret_cast<const float4 *>(lds);
-                float umax = -INFINITY;  // the largest of this lane's grid values of the proposal
-                auto fold = [&](float uf) {
-                    const double u = P.amp * (double)uf;
-                    const double u2 = u * u;
-                    S1 += u;
-                    S2 += u2;
-                    S3 += u2 * u;
-                    S4 += u2 * u2;
-                    n_ex += uf > kTwoSigmaT ? 1u : 0u;    // u > 2 sqrt(E0/pi)
-                    n_ex4 += uf > kFourSigmaT ? 1u : 0u;  // u > 4 sqrt(E0/pi)
-                    umax = fmaxf(umax, uf);
-                };
+                if (__any(!valid)) {  // no sample, no contribution: u~ = 0
+#pragma unroll
+                    for (int j = 0; j < K; ++j) x[j] = valid ? x[j] : 0.0f;
+                }
+                sums.umax = -INFINITY;
                 if constexpr (K >= 16) {
 #pragma unroll
                     for (int tp = 0; tp < K / 16; ++tp) {
@@ -838,13 +834,13 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
                             co = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, x[4 * q + 2], co, 0, 0, 0);
                             ce = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, x[4 * q + 3], ce, 0, 0, 0);
                         }
-                        if (valid) {
+                        float u[32];
 #pragma unroll
-                            for (int v = 0; v < 16; ++v) {
-                                fold(ce[v] + co[v]);
-                                fold(ce[v] - co[v]);
-                            }
+                        for (int v = 0; v < 16; ++v) {
+                            u[2 * v] = ce[v] + co[v];
+                            u[2 * v + 1] = ce[v] - co[v];
                         }
+                        sums.add(u);
                     }
                 } else {
 #pragma unroll
@@ -858,14 +854,14 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
                             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, x[4 * q + 2], acc, 0, 0, 0);
                             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, x[4 * q + 3], acc, 0, 0, 0);
                         }
-                        if (valid) {
+                        float u[16];
 #pragma unroll
-                            for (int v = 0; v < 16; ++v) fold(acc[v]);
-                        }
+                        for (int v = 0; v < 16; ++v) u[v] = acc[v];
+                        sums.add(u);
                     }
                 }
                 // the proposal's grid values are split over lanes l and l + 32
-                umax = fmaxf(umax, __shfl_xor(umax, 32, 64));
+                const float umax = fmaxf(sums.umax, __shfl_xor(sums.umax, 32, 64));
                 if (valid && half == 0) {
                     n_max4 += umax > kFourSigmaT ? 1u : 0u;
                     peak_merge(peak_key, peak_idx, float_key(umax), i);
@@ -892,18 +888,15 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
-        S1 = wave_sum_f64(S1);
-        S2 = wave_sum_f64(S2);
-        S3 = wave_sum_f64(S3);
-        S4 = wave_sum_f64(S4);
-        n_ex = wave_sum_u32(n_ex);
-        n_ex4 = wave_sum_u32(n_ex4);
+        const double amp2 = P.amp * P.amp;
+        const double S1 = P.amp * wave_sum_f64(sums.S1), S2 = amp2 * wave_sum_f64(sums.S2);
+        const double S3 = amp2 * P.amp * wave_sum_f64(sums.S3), S4 = amp2 * amp2 * wave_sum_f64(sums.S4);
         n_max4 = wave_sum_u32(n_max4);
         wave_peak(peak_key, peak_idx);
         if (lane == 0) {
             const unsigned long long left = limit - first;
             const unsigned long long ns = in_seg < left ? in_seg : left;
-            a.seg_stats[gs] = SegStats{S1, S2, S3, S4, n_ex, ns, n_ex4, n_max4, peak_idx, peak_key, 0u};
+            a.seg_stats[gs] = SegStats{S1, S2, S3, S4, sums.n_ex, ns, sums.n_ex4, n_max4, peak_idx, peak_key, 0u};
         }
     }
     hist.flush(a, lane);
@@ -926,7 +919,7 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
     unsigned long long E[4] = {0, 0, 0, 0}, pi = ~0ull;  // above 2 sigma, 4 sigma, samples above 4 sigma, samples
     unsigned int pk = 0u;
     // the next record's loads are issued beside this one's sums
-#pragma unroll 4
+#pragma unroll 2
     for (unsigned long long gs = s0 + tid; gs < s1; gs += kFinBlock) {
         const bool in = a.seg_cnt[gs] != 0u && a.seg_base[gs] < P.target;
         SegStats st = a.seg_stats[gs];  // not written where !in
@@ -963,14 +956,21 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
         for (int s = 0; s < kShards; ++s) h += a.hist[((size_t)p * kShards + s) * kNBins + tid];
         R.hist[tid] = h;
     }
-    if (tid == 0) {
-        for (int w = 1; w < kFinBlock / kWave; ++w) {
-            for (int q = 0; q < 4; ++q) {
-                S[q] += sS[q][w];
-                E[q] += sE[q][w];
-            }
-            peak_merge(pk, pi, sPK[w], sPI[w]);
-        }
+    if (wv != 0) return;
+    // the waves' sums, a wave's by a lane (a loop of one thread over them was
+    // unrolled into 138 spilled registers)
+    const bool mine = lane < kFinBlock / kWave;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        S[q] = wave_sum_f64(mine ? sS[q][lane] : 0.0);
+        E[q] = mine ? sE[q][lane] : 0ull;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) E[q] += __shfl_xor(E[q], o, 64);
+    }
+    pk = mine ? sPK[lane] : 0u;
+    pi = mine ? sPI[lane] : ~0ull;
+    wave_peak(pk, pi);
+    if (lane == 0) {
         R.S1 = S[0];
         R.S2 = S[1];
         R.S3 = S[2];

@@ -153,7 +153,7 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
         }
         if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
         push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
-        count_accepted(P, C, my_word, len, lane);
+        count_accepted(P, C, tally, my_word, len, lane);
     }
 }
 
@@ -171,10 +171,14 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
 // are 0 or +-1.  Each wave queues its accepted offsets in LDS, in index order,
 // and regenerates full chunks only (the last group flushes the rest): at an
 // acceptance of 1e-3 a group of 32 words holds one accepted proposal.
+// Bound by the draw (VALU) and the FP32 products (matrix cores), which waves of
+// a SIMD overlap: four points of 6e7 proposals at K = 64 and 128, 6.5e7
+// accepted, 31.6 ms with ten FP64 operations and two counters a grid value,
+// three waves per SIMD at K = 64 and long segments; now 25.0.
 // ---------------------------------------------------------------------------
 template <int K>
 struct MatQ {
-    static constexpr int W = K == 128 ? 8 : 4;       // waves per workgroup
+    static constexpr int W = 8;                      // waves per workgroup
     static constexpr int GROUP = 32;                 // words per group (lanes 0..31)
     static constexpr int QUEUE = GROUP * 32 + 16;    // one group's offsets + a partial chunk
     static constexpr int LIST_BYTES = W * QUEUE * 2;
@@ -215,8 +219,8 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
         const unsigned long long w_first = (gs - a.seg->off[p]) * S;
         unsigned long long rank = first;
-        double S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0;
-        unsigned int n_ex = 0, n_ex4 = 0, n_max4 = 0;
+        GridSums sums;
+        unsigned int n_max4 = 0;
         unsigned long long peak_idx = ~0ull;
         unsigned int peak_key = 0u;
         int queued = 0;  // offsets (proposals from the segment's first word) waiting in mylist
@@ -267,18 +271,14 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                     if (out_index && g == 0) out_index[P.out_off + r] = i;
                 }
                 if (valid && g == 0 && r + 1 == limit) a.cnt[p].last_index = i;
-                float umax = -INFINITY;  // the largest of this lane's grid values of the proposal
-                auto fold = [&](float uf) {
-                    const double u = P.amp * (double)uf;
-                    const double u2 = u * u;
-                    S1 += u;
-                    S2 += u2;
-                    S3 += u2 * u;
-                    S4 += u2 * u2;
-                    n_ex += uf > kTwoSigmaT ? 1u : 0u;    // u > 2 sqrt(E0/pi)
-                    n_ex4 += uf > kFourSigmaT ? 1u : 0u;  // u > 4 sqrt(E0/pi)
-                    umax = fmaxf(umax, uf);
-                };
+                if (__any(!valid)) {  // no sample, no contribution: u~ = 0
+#pragma unroll
+                    for (int j = 0; j < CPL; ++j) {
+                        c[j] = valid ? c[j] : 0.0f;
+                        s[j] = valid ? s[j] : 0.0f;
+                    }
+                }
+                sums.umax = -INFINITY;
 #pragma unroll 1
                 for (int tau = 0; tau < Quarter<K>::TILES; ++tau) {
                     f32x4 acc[4] = {f32x4{}, f32x4{}, f32x4{}, f32x4{}};
@@ -295,19 +295,21 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                             acc[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, v[2 * (4 * q4 + 2) + par], acc[o], 0, 0, 0);
                             acc[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, v[2 * (4 * q4 + 3) + par], acc[o], 0, 0, 0);
                         }
-                    if (valid) {
+                    float u[16];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {  // representative rho = 16 tau + 4 g + v
-                            const float pe = acc[0][v] + acc[1][v], me = acc[0][v] - acc[1][v];
-                            const float ps = acc[2][v] + acc[3][v], ms = acc[2][v] - acc[3][v];
-                            fold(pe + ps);  // xi
-                            fold(me + ms);  // xi - pi
-                            if (tau != 0 || v != 0 || g != 0) {  // rho = 0: xi = 0 and pi only
-                                fold(pe - ps);  // -xi
-                                fold(me - ms);  // pi - xi
-                            }
-                        }
+                    for (int v = 0; v < 4; ++v) {  // representative rho = 16 tau + 4 g + v
+                        const float pe = acc[0][v] + acc[1][v], me = acc[0][v] - acc[1][v];
+                        const float ps = acc[2][v] + acc[3][v], ms = acc[2][v] - acc[3][v];
+                        u[4 * v] = pe + ps;      // xi
+                        u[4 * v + 1] = me + ms;  // xi - pi
+                        u[4 * v + 2] = pe - ps;  // -xi
+                        u[4 * v + 3] = me - ms;  // pi - xi
                     }
+                    // rho = 0: xi = 0 and pi only (u has mean 0, so its largest value is not below the 0)
+                    const bool twice = tau == 0 && g == 0;
+                    u[2] = twice ? 0.0f : u[2];
+                    u[3] = twice ? 0.0f : u[3];
+                    sums.add(u);
                 }
                 // xi = +-pi/2: A = sum_k a_k cos(k pi/2), B = sum_k b_k sin(k pi/2); mode
                 // K g/4 + j + 1 is j + 1 modulo 4
@@ -319,12 +321,12 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                 }
                 Av = sum4(Av);
                 Bv = sum4(Bv);
-                if (valid && g == 0) {
-                    fold(Av + Bv);
-                    fold(Av - Bv);
+                {
+                    const float u[2] = {g == 0 ? Av + Bv : 0.0f, g == 0 ? Av - Bv : 0.0f};
+                    sums.add(u);
                 }
                 // the proposal's grid values are split over lanes l, l ^ 16, l ^ 32, l ^ 48
-                umax = fmaxf(umax, __shfl_xor(umax, 16, 64));
+                float umax = fmaxf(sums.umax, __shfl_xor(sums.umax, 16, 64));
                 umax = fmaxf(umax, __shfl_xor(umax, 32, 64));
                 // u(0) = sqrt(2 E0/pi) sum_k x^_k; bin of u(0)/u_max = sum_k x^_k / sqrt(K)
                 double s0 = 0.0;
@@ -352,18 +354,15 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
-        S1 = wave_sum_f64(S1);
-        S2 = wave_sum_f64(S2);
-        S3 = wave_sum_f64(S3);
-        S4 = wave_sum_f64(S4);
-        n_ex = wave_sum_u32(n_ex);
-        n_ex4 = wave_sum_u32(n_ex4);
+        const double amp2 = P.amp * P.amp;
+        const double S1 = P.amp * wave_sum_f64(sums.S1), S2 = amp2 * wave_sum_f64(sums.S2);
+        const double S3 = amp2 * P.amp * wave_sum_f64(sums.S3), S4 = amp2 * amp2 * wave_sum_f64(sums.S4);
         n_max4 = wave_sum_u32(n_max4);
         wave_peak(peak_key, peak_idx);
         if (lane == 0) {
             const unsigned long long left = limit - first;
             const unsigned long long ns = in_seg < left ? in_seg : left;
-            a.seg_stats[gs] = SegStats{S1, S2, S3, S4, n_ex, ns, n_ex4, n_max4, peak_idx, peak_key, 0u};
+            a.seg_stats[gs] = SegStats{S1, S2, S3, S4, sums.n_ex, ns, sums.n_ex4, n_max4, peak_idx, peak_key, 0u};
         }
     }
     hist.flush(a, lane);
@@ -484,7 +483,10 @@ hipError_t launch_materialize_q_t(const KernelArgs &a, unsigned long long n_segs
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, B, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
-    unsigned long long g = (unsigned long long)per_cu * n_cu;
+    // several rounds of workgroups, so that they even out among the CUs: with one
+    // round a wave's segments of a dense and of a sparse point add up or not by
+    // chance (26.0 ms; 25.0 in four or eight)
+    unsigned long long g = 8ull * per_cu * n_cu;
     const unsigned long long want = (n_segs_max + MatQ<K>::W - 1) / MatQ<K>::W;
     if (want < g) g = want;
     if (g < 1) g = 1;
