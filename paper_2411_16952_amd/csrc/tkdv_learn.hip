@@ -2,23 +2,22 @@
 // of a point, and its training on the GPU (FP64 throughout).
 //
 // One training step (all on one stream):
-//   k_mlp_fwd       per point: z -> h1 -> h2 -> o (tanh layers)
-//   k_mix_prep      per point: o -> log d, V; A = D^-1, G^-1, log|L0| and
-//                   the gradient of log|L0|
+//   k_mlp_fwd       per point: z -> h1 -> h2 -> o (tanh layers); o -> log d, V;
+//                   A = D^-1, G^-1, log|L0| and the gradient of log|L0|
 //   k_mix_fwd_mm    per chunk of rows: the y products of all S shifts on the
-//                   FP64 matrix cores, log q_net and log q_mix
-//   k_loss_max      per point maximum of r_s = log f - log q_mix
-//   k_loss_chunk    per chunk of a point's rows: sum of exp(r_s/T - max), NLL
-//   k_loss_final    per point: chunk partials in order -> soft maximum, loss
+//                   FP64 matrix cores, log q_net and log q_mix; the chunk's
+//                   largest r_s/T (r_s = log f - log q_mix), its sum of
+//                   exp(r_s/T - max) and its NLL
+//   k_loss_final    per point: chunk partials -> soft maximum, loss
 //   k_mix_bwd_mm    per chunk: dL/d(log d, V) of the point from a second
 //                   product X^T C and per-mode rotations
-//   k_param_grad    per point: chunk partials in order, the log|L0| term,
-//                   dL/do
-//   k_mlp_bwd_*     back through the layers; dL/dweights summed over points
-//   k_adam          the update
-// Rows are grouped by point (an index order) and cut into chunks of at most
-// kChunk rows of one point; every sum runs in a fixed order, so a step is
-// deterministic.
+//   k_param_grad    per point: chunk partials, the log|L0| term, dL/do; back
+//                   through the hidden layers
+//   k_weights       dL/dweights summed over points, and Adam's update
+// Rows are grouped by point (an index order) and cut into chunks of whole tiles
+// of 16 rows of one point, a wave each, as many as the waves that the chip holds
+// at two per SIMD (one chunk a tile if there are fewer tiles); every sum runs in
+// a fixed order, so a step is deterministic.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,7 +37,8 @@ namespace tkdv {
 
 constexpr int kLKMax = 32;        // largest K of the learned proposal
 constexpr int kMaxHidden = 256;
-constexpr int kChunk = 32;        // rows per chunk of the reductions
+constexpr int kTileRows = 16;     // rows of a matrix tile
+constexpr int kStepWaves = 2;     // waves per SIMD of the row kernels
 
 struct LearnPoint {
     double z[3];
@@ -65,13 +65,14 @@ struct LearnParam {
 __constant__ double c_cs[kMixS], c_sn[kMixS];
 
 struct LearnStats {
-    unsigned long long maxkey;  // order-preserving key of max_s r_s/T
+    double max;                 // max_s r_s/T
     double sum;                 // sum_s exp(r_s/T - max)
     double nll;                 // sum over accepted rows of -log q_net
     double loss;
 };
 
-// Partials of one chunk: [sum, nll, csum, gd (K), gv (2K x 2)], csum = sum of
+// Partials of one chunk: [sum, nll, csum, gd (K), gv (2K x 2)], where csum holds
+// the chunk's largest r_s/T until the backward; csum = sum of
 // c_s = dL/d log q_net(x_s), gd/gv = sum of c_s d log q_net/d(log d, V)
 // without the log|L0| term.
 constexpr int chunk_part_len(int K) { return 3 + 5 * K; }
@@ -95,16 +96,6 @@ struct LearnArgs {
     double T, lambda, log_eps, log_1m_eps;
 };
 
-__device__ __forceinline__ unsigned long long dkey(double d)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(d);
-    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-}
-__device__ __forceinline__ double dkey_inv(unsigned long long k)
-{
-    const unsigned long long b = (k >> 63) ? (k & 0x7FFFFFFFFFFFFFFFull) : ~k;
-    return __longlong_as_double((long long)b);
-}
 __device__ __forceinline__ double wsum(double v)
 {
 #pragma unroll
@@ -112,9 +103,48 @@ __device__ __forceinline__ double wsum(double v)
     return v;
 }
 
+__device__ __forceinline__ double wmax(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    return v;
+}
+// A lane exchange within 16 lanes by DPP: xor 1, or rotation by N.
+constexpr int kXor1 = 0xB1, kRor = 0x120;
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xF, 0xF, true);
+    const unsigned hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// Sum or maximum over 16 lanes (over the 8 of one parity: FROM = 2), the same in each.
+template <int FROM = 1>
+__device__ __forceinline__ double sum16(double v)
+{
+    v += dpp<kRor + 8>(v);
+    v += dpp<kRor + 4>(v);
+    v += dpp<kRor + 2>(v);
+    if constexpr (FROM == 1) v += dpp<kXor1>(v);
+    return v;
+}
+__device__ __forceinline__ double max16(double v)
+{
+    v = fmax(v, dpp<kRor + 8>(v));
+    v = fmax(v, dpp<kRor + 4>(v));
+    v = fmax(v, dpp<kRor + 2>(v));
+    return fmax(v, dpp<kXor1>(v));
+}
+
 // ---------------------------------------------------------------------------
-// Network
+// Network: a workgroup of 16 waves per point, bound by the latency of reading
+// 0.8 MB of weights.  Each column's sum is split over four threads, each row's
+// over 16 lanes.  Sixteen points, 256 hidden units: forward with the mixture's
+// parameters 49 us as two kernels with a thread per unit, now 20; backward
+// with the chunk sums 109 us (rows of W read a thread each), now 23.
 // ---------------------------------------------------------------------------
+constexpr int kMlpBlock = 1024, kMlpParts = kMlpBlock / kMaxHidden;
 struct MlpView {
     const double *W1, *b1, *W2, *b2, *W3, *b3;
     __host__ __device__ MlpView(const double *W, int H, int n_out)
@@ -123,61 +153,138 @@ struct MlpView {
 };
 inline int64_t mlp_n_weights(int H, int n_out) { return 5ll * H + (int64_t)H * H + (int64_t)H * n_out + n_out; }
 
-__global__ void __launch_bounds__(kMaxHidden) k_mlp_fwd(const double *W, int H, int n_out, const double *z,
-                                                        double *h1, double *h2, double *out)
+// Mixture parameters of a point from the network output o (LDS), by every wave of
+// the workgroup: wave 0 writes them, the shifts' products B are divided up.
+template <int K>
+__device__ void mix_prep(const double *o, const LearnPoint &L, LearnParam &Q, double v_amp, double v_scale)
 {
-    __shared__ double s1[kMaxHidden], s2[kMaxHidden];
-    const int p = blockIdx.x, i = threadIdx.x;
+    const int m = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const bool first = wv == 0;
+    const bool act = m < 2 * K;
+    const int k = m % K;
+    const double logd = act ? L.logs2[k] + o[k] : 0.0;
+    const double a = act ? exp(-logd) : 0.0;
+    const double v00 = v_amp / sqrt((double)K);
+    double V0 = 0.0, V1 = 0.0;
+    if (act) {
+        V0 = (m < K ? v00 : 0.0) + v_scale * o[K + 2 * m];
+        V1 = (m >= K ? v00 : 0.0) + v_scale * o[K + 2 * m + 1];
+    }
+    if (act && first) {
+        Q.V[m][0] = V0;
+        Q.V[m][1] = V1;
+    }
+    if (m < K && first) {
+        Q.logd[m] = logd;
+        Q.a[m] = a;
+    }
+    const int src = act ? (m < K ? m + K : m - K) : m;
+    const double P0 = __shfl(V0, src, 64), P1 = __shfl(V1, src, 64);
+    // the y-product matrix: coordinate n of x enters w = R_j^T x at n (cos c) and at
+    // its partner n +- K (sin s): B[n][2j + q] = a (c V_nq +- s V_{n -+ K, q})
+    if (act) {
+        const double sg = m < K ? 1.0 : -1.0;
+        for (int j = wv; j < kMixS; j += kMlpBlock / kWave) {
+            const int mi = ((k + 1) * j) & (kMixS - 1);
+            const double c = c_cs[mi], sn = sg * c_sn[mi];
+            Q.B[m][2 * j] = a * (c * V0 + sn * P0);
+            Q.B[m][2 * j + 1] = a * (c * V1 + sn * P1);
+        }
+    }
+    if (!first) return;
+    const double G00 = 1.0 + wsum(a * V0 * V0), G01 = wsum(a * V0 * V1), G11 = 1.0 + wsum(a * V1 * V1);
+    const double det = G00 * G11 - G01 * G01;
+    const double i00 = G11 / det, i01 = -G01 / det, i11 = G00 / det;
+    const double ldD = wsum(m < K ? 2.0 * logd : 0.0);
+    // V_m G^-1
+    const double u0 = V0 * i00 + V1 * i01, u1 = V0 * i01 + V1 * i11;
+    if (act) {
+        Q.dld_V[m][0] = 2.0 * a * u0;
+        Q.dld_V[m][1] = 2.0 * a * u1;
+    }
+    // d log|L0| / d log d_k = sum over the mode's two coordinates of 1 - a_m V_m G^-1 V_m^T
+    const double own = act ? 1.0 - a * (u0 * V0 + u1 * V1) : 0.0;
+    const double partner = __shfl(own, (m + K) & 63, 64);
+    if (m < K) Q.dld_logd[m] = own + partner;
+    if (m == 0) {
+        Q.gi[0][0] = i00;
+        Q.gi[0][1] = i01;
+        Q.gi[1][0] = i01;
+        Q.gi[1][1] = i11;
+        Q.logdet = ldD + log(det);
+    }
+}
+
+template <int K>
+__global__ void __launch_bounds__(kMlpBlock) k_mlp_fwd(const double *W, int H, const double *z, const LearnPoint *pts,
+                                                       double *h1, double *h2, LearnParam *par, double v_amp,
+                                                       double v_scale)
+{
+    constexpr int n_out = 5 * K;
+    static_assert(n_out <= kMaxHidden, "a thread per output and part");
+    __shared__ double s1[kMaxHidden], s2[kMaxHidden], red[kMlpParts][kMaxHidden];
+    const int p = blockIdx.x, i = threadIdx.x % kMaxHidden, part = threadIdx.x / kMaxHidden;
     const MlpView w(W, H, n_out);
     const double *zp = z + 3 * p;
-    if (i < H) {
+    if (part == 0 && i < H) {
         const double a = w.b1[i] + w.W1[i] * zp[0] + w.W1[H + i] * zp[1] + w.W1[2 * H + i] * zp[2];
         s1[i] = tanh(a);
         h1[(size_t)p * H + i] = s1[i];
     }
     __syncthreads();
+    const int j0 = part * H / kMlpParts, j1 = (part + 1) * H / kMlpParts;
     if (i < H) {
+        double a = 0.0;
+#pragma unroll 16
+        for (int j = j0; j < j1; ++j) a += w.W2[(size_t)j * H + i] * s1[j];
+        red[part][i] = a;
+    }
+    __syncthreads();
+    if (part == 0 && i < H) {
         double a = w.b2[i];
-        for (int j = 0; j < H; ++j) a += w.W2[(size_t)j * H + i] * s1[j];
+        for (int q = 0; q < kMlpParts; ++q) a += red[q][i];
         s2[i] = tanh(a);
         h2[(size_t)p * H + i] = s2[i];
     }
     __syncthreads();
-    for (int o = i; o < n_out; o += blockDim.x) {
-        double a = w.b3[o];
-        for (int j = 0; j < H; ++j) a += w.W3[(size_t)j * n_out + o] * s2[j];
-        out[(size_t)p * n_out + o] = a;
-    }
-}
-
-// dh2 = (W3 dout) * (1 - h2^2), dh1 = (W2 dh2) * (1 - h1^2), per point.
-__global__ void __launch_bounds__(kMaxHidden) k_mlp_bwd_hidden(const double *W, int H, int n_out,
-                                                               const double *h1, const double *h2,
-                                                               const double *dout, double *dh1, double *dh2)
-{
-    __shared__ double s2[kMaxHidden];
-    const int p = blockIdx.x, j = threadIdx.x;
-    const MlpView w(W, H, n_out);
-    if (j < H) {
+    if (i < n_out) {
         double a = 0.0;
-        for (int o = 0; o < n_out; ++o) a += w.W3[(size_t)j * n_out + o] * dout[(size_t)p * n_out + o];
-        const double h = h2[(size_t)p * H + j];
-        s2[j] = a * (1.0 - h * h);
-        dh2[(size_t)p * H + j] = s2[j];
+#pragma unroll 16
+        for (int j = j0; j < j1; ++j) a += w.W3[(size_t)j * n_out + i] * s2[j];
+        red[part][i] = a;
     }
     __syncthreads();
-    if (j < H) {
+    if (part == 0 && i < n_out) {
+        double a = w.b3[i];
+        for (int q = 0; q < kMlpParts; ++q) a += red[q][i];
+        s1[i] = a;
+    }
+    __syncthreads();
+    mix_prep<K>(s1, pts[p], par[p], v_amp, v_scale);
+}
+
+// y_j (1 - h_j^2) for the rows j of M (row length n, y = M v): 16 lanes a row.
+__device__ __forceinline__ void mlp_rows_back(const double *M, int rows, int n, const double *v, const double *h,
+                                              double *y)
+{
+    const int l = threadIdx.x & 15;
+    for (int j = threadIdx.x >> 4; j < rows; j += kMlpBlock / 16) {
         double a = 0.0;
-        for (int k = 0; k < H; ++k) a += w.W2[(size_t)j * H + k] * s2[k];
-        const double h = h1[(size_t)p * H + j];
-        dh1[(size_t)p * H + j] = a * (1.0 - h * h);
+#pragma unroll 8
+        for (int k = l; k < n; k += 16) a += M[(size_t)j * n + k] * v[k];
+        a = sum16(a);
+        if (l == 0) y[j] = a * (1.0 - h[j] * h[j]);
     }
 }
 
-// dL/dweights = sum over points of the outer products (one thread per weight).
-__global__ void k_mlp_bwd_weights(int H, int n_out, int n_points, const double *z, const double *h1,
-                                  const double *h2, const double *dh1, const double *dh2, const double *dout,
-                                  double *gW)
+// dL/dweights = sum over points of the outer products (one thread per weight),
+// and Adam's update of the weight where a step is taken.
+struct Adam {
+    double *W, *m1, *m2;  // W NULL: the gradient alone
+    double lr, b1, b2, eps, c1, c2;
+};
+__global__ void k_weights(int H, int n_out, int n_points, const double *z, const double *h1, const double *h2,
+                          const double *dh1, const double *dh2, const double *dout, double *gW, Adam ad)
 {
     const long long nW = 5ll * H + (long long)H * H + (long long)H * n_out + n_out;
     for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < nW;
@@ -202,82 +309,13 @@ __global__ void k_mlp_bwd_weights(int H, int n_out, int n_points, const double *
             for (int p = 0; p < n_points; ++p) g += dout[(size_t)p * n_out + r];
         }
         gW[idx] = g;
-    }
-}
-
-__global__ void k_adam(double *W, const double *gW, double *m1, double *m2, long long n, double lr, double b1,
-                       double b2, double eps, double c1, double c2)
-{
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-        const double g = gW[i];
-        const double a = b1 * m1[i] + (1.0 - b1) * g;
-        const double b = b2 * m2[i] + (1.0 - b2) * g * g;
-        m1[i] = a;
-        m2[i] = b;
-        W[i] -= lr * (a / c1) / (sqrt(b / c2) + eps);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Mixture parameters of each point from the network output (one wave per point)
-// ---------------------------------------------------------------------------
-template <int K>
-__global__ void __launch_bounds__(64) k_mix_prep(const double *out, int n_out, const LearnPoint *pts,
-                                                 LearnParam *par, double v_amp, double v_scale)
-{
-    const int p = blockIdx.x, m = threadIdx.x;
-    const LearnPoint &L = pts[p];
-    LearnParam &Q = par[p];
-    const double *o = out + (size_t)p * n_out;
-    const bool act = m < 2 * K;
-    const int k = m % K;
-    const double logd = act ? L.logs2[k] + o[k] : 0.0;
-    const double a = act ? exp(-logd) : 0.0;
-    const double v00 = v_amp / sqrt((double)K);
-    double V0 = 0.0, V1 = 0.0;
-    if (act) {
-        V0 = (m < K ? v00 : 0.0) + v_scale * o[K + 2 * m];
-        V1 = (m >= K ? v00 : 0.0) + v_scale * o[K + 2 * m + 1];
-        Q.V[m][0] = V0;
-        Q.V[m][1] = V1;
-    }
-    if (m < K) {
-        Q.logd[m] = logd;
-        Q.a[m] = a;
-    }
-    const double G00 = 1.0 + wsum(a * V0 * V0), G01 = wsum(a * V0 * V1), G11 = 1.0 + wsum(a * V1 * V1);
-    const double det = G00 * G11 - G01 * G01;
-    const double i00 = G11 / det, i01 = -G01 / det, i11 = G00 / det;
-    const double ldD = wsum(m < K ? 2.0 * logd : 0.0);
-    // V_m G^-1
-    const double u0 = V0 * i00 + V1 * i01, u1 = V0 * i01 + V1 * i11;
-    if (act) {
-        Q.dld_V[m][0] = 2.0 * a * u0;
-        Q.dld_V[m][1] = 2.0 * a * u1;
-    }
-    // d log|L0| / d log d_k = sum over the mode's two coordinates of 1 - a_m V_m G^-1 V_m^T
-    const double own = act ? 1.0 - a * (u0 * V0 + u1 * V1) : 0.0;
-    const double partner = __shfl(own, (m + K) & 63, 64);
-    if (m < K) Q.dld_logd[m] = own + partner;
-    // the y-product matrix: coordinate n of x enters w = R_j^T x at n (cos c) and at
-    // its partner n +- K (sin s): B[n][2j + q] = a (c V_nq +- s V_{n -+ K, q})
-    const int src = act ? (m < K ? m + K : m - K) : m;
-    const double P0 = __shfl(V0, src, 64), P1 = __shfl(V1, src, 64);
-    if (act) {
-        const double sg = m < K ? 1.0 : -1.0;
-        for (int j = 0; j < kMixS; ++j) {
-            const int mi = ((k + 1) * j) & (kMixS - 1);
-            const double c = c_cs[mi], sn = sg * c_sn[mi];
-            Q.B[m][2 * j] = a * (c * V0 + sn * P0);
-            Q.B[m][2 * j + 1] = a * (c * V1 + sn * P1);
+        if (ad.W) {
+            const double a = ad.b1 * ad.m1[idx] + (1.0 - ad.b1) * g;
+            const double b = ad.b2 * ad.m2[idx] + (1.0 - ad.b2) * g * g;
+            ad.m1[idx] = a;
+            ad.m2[idx] = b;
+            ad.W[idx] -= ad.lr * (a / ad.c1) / (sqrt(b / ad.c2) + ad.eps);
         }
-    }
-    if (m == 0) {
-        Q.gi[0][0] = i00;
-        Q.gi[0][1] = i01;
-        Q.gi[1][0] = i01;
-        Q.gi[1][1] = i11;
-        Q.logdet = ldD + log(det);
     }
 }
 
@@ -316,60 +354,47 @@ __global__ void k_rows_append(const float *src, unsigned long long stride, unsig
     }
 }
 
-__global__ void k_loss_max(LearnArgs A)
+// Per point (one workgroup): chunk partials -> soft maximum and loss.  Each
+// thread takes every 256th chunk in order, then a fixed tree.
+__global__ void __launch_bounds__(256) k_loss_final(LearnArgs A)
 {
-    for (unsigned long long r = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; r < A.n;
-         r += (unsigned long long)gridDim.x * blockDim.x)
-        if (A.kind[r] != 2)  // kind 2: likelihood term only
-            atomicMax(&A.st[A.row_point[r]].maxkey, dkey((A.lf[r] - A.lmix[r]) / A.T));
-}
-
-// Sum of exp(r_s/T - max) and of -log q_net over the accepted rows, per chunk
-// (one wave; lane-strided then a fixed butterfly).
-__global__ void __launch_bounds__(256) k_loss_chunk(LearnArgs A)
-{
-    const int m = threadIdx.x & 63;
-    const unsigned c = __builtin_amdgcn_readfirstlane((blockIdx.x * 256 + threadIdx.x) >> 6);
-    if (c >= A.n_chunks) return;
-    const int p = A.chunk_point[c];
-    const double mx = dkey_inv(A.st[p].maxkey);
+    __shared__ double sv[3][256 / kWave];
+    const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    LearnStats &S = A.st[p];
+    const LearnPoint &L = A.pts[p];
+    double mx = -INFINITY;
+    for (unsigned c = L.chunk0 + tid; c < L.chunk1; c += 256) mx = fmax(mx, A.part[(size_t)c * A.pt_len + 2]);
+    mx = wmax(mx);
+    if (lane == 0) sv[2][wv] = mx;
+    __syncthreads();
+    for (int w = 0; w < 256 / kWave; ++w) mx = fmax(mx, sv[2][w]);
     double se = 0.0, nll = 0.0;
-    for (unsigned q = A.chunk_start[c] + m; q < A.chunk_start[c + 1]; q += 64) {
-        const unsigned r = A.order[q];
-        const uint8_t kd = A.kind[r];
-        se += kd != 2 ? exp((A.lf[r] - A.lmix[r]) / A.T - mx) : 0.0;
-        nll += kd != 1 ? -A.lnet[r] : 0.0;
+    for (unsigned c = L.chunk0 + tid; c < L.chunk1; c += 256) {
+        const double *o = A.part + (size_t)c * A.pt_len;
+        if (o[0] > 0.0) se += o[0] * exp(o[2] - mx);
+        nll += o[1];
     }
     se = wsum(se);
     nll = wsum(nll);
-    if (m == 0) {
-        A.part[(size_t)c * A.pt_len + 0] = se;
-        A.part[(size_t)c * A.pt_len + 1] = nll;
+    if (lane == 0) {
+        sv[0][wv] = se;
+        sv[1][wv] = nll;
     }
-}
-
-// Per point: chunk partials in chunk order -> soft maximum and loss.
-__global__ void k_loss_final(LearnArgs A, int n_points)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n_points) return;
-    LearnStats &S = A.st[p];
-    const LearnPoint &L = A.pts[p];
-    double se = 0.0, nll = 0.0;
-    for (unsigned c = L.chunk0; c < L.chunk1; ++c) {
-        se += A.part[(size_t)c * A.pt_len + 0];
-        nll += A.part[(size_t)c * A.pt_len + 1];
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < 256 / kWave; ++w) {
+        se += sv[0][w];
+        nll += sv[1][w];
     }
+    S.max = mx;
     S.sum = se;
     S.nll = nll;
-    S.loss = se > 0.0 ? A.T * (dkey_inv(S.maxkey) + log(se)) + A.lambda * nll * L.inv_n_acc
-                      : A.lambda * nll * L.inv_n_acc;
+    S.loss = se > 0.0 ? A.T * (mx + log(se)) + A.lambda * nll * L.inv_n_acc : A.lambda * nll * L.inv_n_acc;
 }
 
 // ---------------------------------------------------------------------------
 // Mixture densities of the rows and their gradients, as products on the FP64
-// matrix cores, one wave per chunk (at most 32 rows of one point, two tiles
-// of 16 rows).  log q_net = LSE_j(-K ln qf_j) - ln S - log|L0|/2 over the S
+// matrix cores, one wave per chunk (tiles of 16 rows of one point).  log q_net = LSE_j(-K ln qf_j) - ln S - log|L0|/2 over the S
 // shifts; c_s = dL/d log q_net(x_s) = -w_s rho_s [kinds 0, 1] - lambda/n_acc
 // [kinds 0, 2] with w_s = softmax_s(r_s/T), rho_s = (1 - eps) q_net/q_mix.
 //   Forward: Y = X B (rows x 64, column 2j + q holds y_jq) by 16x16x4 FP64
@@ -404,92 +429,159 @@ __device__ __forceinline__ unsigned chunk_row(const LearnArgs &A, unsigned c0, u
     return A.order[c0 + (i < (int)nc ? i : 0)];
 }
 
-// y products of 16 rows (this lane's A-operand row: rowA) into acc[t] (column
-// tile t), and the row's Q = x^T A x and t = sum k^2 x_k^2 (lanes l % 16 = i).
-template <int K>
-__device__ __forceinline__ void mix_products(const LearnArgs &A, const LearnParam &Q, unsigned rowA, int lane,
-                                             d4_t (&acc)[4], double &Qr, double &tr)
+// y products of NT tiles of 16 rows (this lane's A-operand rows: rowA) into
+// acc[r][t] (row tile r, column tile t), and the rows' Q = x^T A x and
+// t = sum k^2 x_k^2 (lanes l % 16 = i).
+template <int K, int NT>
+__device__ __forceinline__ void mix_products(const LearnArgs &A, const LearnParam &Q, const unsigned (&rowA)[NT],
+                                             int lane, d4_t (&acc)[NT][4], double (&Qr)[NT], double (&tr)[NT])
 {
     const int g = lane >> 4, i16 = lane & 15;
+    const double *x[NT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = d4_t{0.0, 0.0, 0.0, 0.0};
-    double qa = 0.0, ta = 0.0;
-    const double *x = A.X + (size_t)rowA * 2 * K;
+    for (int r = 0; r < NT; ++r) {
 #pragma unroll
-    for (int s = 0; s < K / 2; ++s) {  // k-steps of 4 coordinates
-        const int m = 4 * s + g, k = m % K;
-        const double xv = x[m];
-        qa += Q.a[k] * xv * xv;
-        ta += (double)((k + 1) * (k + 1)) * xv * xv;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = mma_f64(xv, Q.B[m][16 * t + i16], acc[t]);
+        for (int t = 0; t < 4; ++t) acc[r][t] = d4_t{0.0, 0.0, 0.0, 0.0};
+        Qr[r] = tr[r] = 0.0;
+        x[r] = A.X + (size_t)rowA[r] * 2 * K;
     }
-    qa += __shfl_xor(qa, 16, 64);
-    qa += __shfl_xor(qa, 32, 64);
-    ta += __shfl_xor(ta, 16, 64);
-    ta += __shfl_xor(ta, 32, 64);
-    Qr = qa;
-    tr = ta;
+#pragma unroll 4
+    for (int s = 0; s < K / 2; ++s) {  // k-steps of 4 coordinates, the loads of four at a time
+        const int m = 4 * s + g, k = m % K;
+        double b[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) b[t] = Q.B[m][16 * t + i16];
+#pragma unroll
+        for (int r = 0; r < NT; ++r) {
+            const double xv = x[r][m];
+            Qr[r] += Q.a[k] * xv * xv;
+            tr[r] += (double)((k + 1) * (k + 1)) * xv * xv;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[r][t] = mma_f64(xv, b[t], acc[r][t]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NT; ++r) {
+        Qr[r] += __shfl_xor(Qr[r], 16, 64);
+        Qr[r] += __shfl_xor(Qr[r], 32, 64);
+        tr[r] += __shfl_xor(tr[r], 16, 64);
+        tr[r] += __shfl_xor(tr[r], 32, 64);
+    }
+}
+
+// The (y0, y1) of two of this lane's four shifts of a row: lanes l and l ^ 1 hold
+// q = 0 and 1 of the shifts 8t + (l % 16)/2; the even lane takes t = 0, 1, the odd
+// t = 2, 3 (u = 0, 1).
+__device__ __forceinline__ void own_shifts(const d4_t (&acc)[4], int v, int q, double (&y0)[2], double (&y1)[2])
+{
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const double own = q ? acc[u + 2][v] : acc[u][v], got = dpp<kXor1>(q ? acc[u][v] : acc[u + 2][v]);
+        y0[u] = q ? got : own;
+        y1[u] = q ? own : got;
+    }
+}
+
+// Bound by the FP64 logs and exponentials: one of each per row and shift, and
+// five more a row, with four lanes a row in the last (each pair of lanes took
+// every shift twice, sixteen lanes every row, and pairs of lanes merged their
+// sums by exponentials: 76 a lane and tile, now 21).  Two row tiles share each
+// load of B.  65920 rows at K = 32: 83 us, with the chunks' maxima and sums in two
+// kernels more 250; now 39.
+template <int K, int NT>
+__device__ __forceinline__ void fwd_tiles(const LearnArgs &A, const LearnPoint &L, const LearnParam &Q, unsigned c0,
+                                          unsigned nc, int row0, int lane, double &top, double &se, double &nll)
+{
+    const int g = lane >> 4, i16 = lane & 15, q = lane & 1;
+    const double gi00 = Q.gi[0][0], gi01 = Q.gi[0][1], gi11 = Q.gi[1][1];
+    const double cst = -log((double)kMixS) - 0.5 * Q.logdet;
+    d4_t acc[NT][4];
+    double Qa[NT], ta[NT];
+    unsigned rowA[NT];
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) rowA[rt] = chunk_row(A, c0, nc, row0 + rt * kTileRows + i16);
+    mix_products<K, NT>(A, Q, rowA, lane, acc, Qa, ta);
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) {
+        double mxr = 0.0, ser = 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const double Qr = __shfl(Qa[rt], 4 * v + g, 64);  // tile row 4v + g
+            double y0[2], y1[2], lj[2];
+            own_shifts(acc[rt], v, q, y0, y1);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const double qf = Qr - (gi00 * y0[u] * y0[u] + 2.0 * gi01 * y0[u] * y1[u] + gi11 * y1[u] * y1[u]);
+                lj[u] = -K * log(qf);
+            }
+            const double mx = max16(fmax(lj[0], lj[1]));
+            const double sm = sum16(exp(lj[0] - mx) + exp(lj[1] - mx));
+            const bool mine = (i16 & 3) == v;
+            mxr = mine ? mx : mxr;
+            ser = mine ? sm : ser;
+        }
+        const int ri = 4 * (i16 & 3) + g, rr = row0 + rt * kTileRows + ri;  // this lane's row
+        const double tr = __shfl(ta[rt], ri, 64);
+        const double lnet = mxr + log(ser) + cst;
+        const double lg = L.lng - K * log1p(L.gc * tr);
+        const double a1 = A.log_eps + lg, b1 = A.log_1m_eps + lnet;
+        const double hi = fmax(a1, b1);
+        const double lm = hi + log(exp(a1 - hi) + exp(b1 - hi));
+        if (i16 < 4 && rr < (int)nc) {
+            const unsigned row = A.order[c0 + rr];
+            const uint8_t kd = A.kind[row];
+            A.lnet[row] = lnet;
+            A.lmix[row] = lm;
+            if (kd != 2) {  // kind 2: likelihood term only
+                const double r = (A.lf[row] - lm) / A.T;
+                if (r > top) {
+                    se = se * exp(top - r) + 1.0;  // top = -inf: no term yet
+                    top = r;
+                } else {
+                    se += exp(r - top);
+                }
+            }
+            if (kd != 1) nll -= lnet;
+        }
+    }
 }
 
 template <int K>
-__global__ void __launch_bounds__(256) k_mix_fwd_mm(LearnArgs A)
+__global__ void __launch_bounds__(256, kStepWaves) k_mix_fwd_mm(LearnArgs A)
 {
-    const int lane = threadIdx.x & 63, g = lane >> 4, i16 = lane & 15;
+    const int lane = threadIdx.x & 63;
     const unsigned c = __builtin_amdgcn_readfirstlane((blockIdx.x * 256 + threadIdx.x) >> 6);
     if (c >= A.n_chunks) return;
     const int p = A.chunk_point[c];
     const LearnPoint &L = A.pts[p];
     const LearnParam &Q = A.par[p];
     const unsigned c0 = A.chunk_start[c], nc = A.chunk_start[c + 1] - c0;
-    const double gi00 = Q.gi[0][0], gi01 = Q.gi[0][1], gi11 = Q.gi[1][1];
-    const double cst = -log((double)kMixS) - 0.5 * Q.logdet;
-    for (int rt = 0; rt * 16 < (int)nc; ++rt) {
-        d4_t acc[4];
-        double Qa, ta;
-        mix_products<K>(A, Q, chunk_row(A, c0, nc, rt * 16 + i16), lane, acc, Qa, ta);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int ri = 4 * v + g;  // the tile row of this lane's results
-            const double Qr = __shfl(Qa, ri, 64), tr = __shfl(ta, ri, 64);
-            double lj[4], mx = -INFINITY;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {  // shift j = 8t + i16/2; lanes l, l^1 hold q = 0, 1
-                const double y = acc[t][v], yo = __shfl_xor(y, 1, 64);
-                const double y0 = (lane & 1) ? yo : y, y1 = (lane & 1) ? y : yo;
-                const double qf = Qr - (gi00 * y0 * y0 + 2.0 * gi01 * y0 * y1 + gi11 * y1 * y1);
-                lj[t] = -K * log(qf);
-                mx = fmax(mx, lj[t]);
-            }
-            double se = 0.0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) se += exp(lj[t] - mx);
-#pragma unroll
-            for (int o = 2; o <= 8; o <<= 1) {  // the other shifts of the row (lane bits 1..3)
-                const double m2 = __shfl_xor(mx, o, 64), s2 = __shfl_xor(se, o, 64);
-                const double mm = fmax(mx, m2);
-                se = se * exp(mx - mm) + s2 * exp(m2 - mm);
-                mx = mm;
-            }
-            const double lnet = mx + log(se) + cst;
-            const double lg = L.lng - K * log1p(L.gc * tr);
-            const double a1 = A.log_eps + lg, b1 = A.log_1m_eps + lnet;
-            const double hi = fmax(a1, b1);
-            const double lm = hi + log(exp(a1 - hi) + exp(b1 - hi));
-            const int rr = rt * 16 + ri;
-            if (i16 == 0 && rr < (int)nc) {
-                const unsigned row = A.order[c0 + rr];
-                A.lnet[row] = lnet;
-                A.lmix[row] = lm;
-            }
-        }
+    double top = -INFINITY, se = 0.0, nll = 0.0;  // of this lane's rows: largest r/T, sum of exp(r/T - top)
+    int row0 = 0;
+    for (; row0 + kTileRows < (int)nc; row0 += 2 * kTileRows) fwd_tiles<K, 2>(A, L, Q, c0, nc, row0, lane, top, se, nll);
+    if (row0 < (int)nc) fwd_tiles<K, 1>(A, L, Q, c0, nc, row0, lane, top, se, nll);
+    const double mx = wmax(top);
+    se = wsum(se > 0.0 ? se * exp(top - mx) : 0.0);
+    nll = wsum(nll);
+    if (lane == 0) {
+        double *o = A.part + (size_t)c * A.pt_len;
+        o[0] = se;
+        o[1] = nll;
+        o[2] = mx;
     }
 }
 
+// Two waves per SIMD where the products' sums, a shift's log and exponential in
+// one lane of a pair, and mode-by-mode sums at the end fit 256 registers: 65920
+// rows at K = 32, 119 us with one wave, every shift twice and chunks of two tiles
+// that came to 2.02 rounds; now 62.
 template <int K>
-__global__ void __launch_bounds__(256) k_mix_bwd_mm(LearnArgs A)
+__global__ void __launch_bounds__(256, kStepWaves) k_mix_bwd_mm(LearnArgs A)
 {
     constexpr int MT = 2 * K / 16;  // 16-coordinate tiles of M
+    __shared__ double s_rot[2 * kMixS];
+    if (threadIdx.x < 2 * kMixS) s_rot[threadIdx.x] = threadIdx.x < kMixS ? c_cs[threadIdx.x] : c_sn[threadIdx.x - kMixS];
+    __syncthreads();
     const int lane = threadIdx.x & 63, g = lane >> 4, i16 = lane & 15, q = lane & 1;
     const unsigned c = __builtin_amdgcn_readfirstlane((blockIdx.x * 256 + threadIdx.x) >> 6);
     if (c >= A.n_chunks) return;
@@ -497,7 +589,7 @@ __global__ void __launch_bounds__(256) k_mix_bwd_mm(LearnArgs A)
     const LearnPoint &L = A.pts[p];
     const LearnParam &Q = A.par[p];
     const LearnStats &St = A.st[p];
-    const double mxL = dkey_inv(St.maxkey), inv_sum = 1.0 / St.sum;
+    const double mxL = St.max, inv_sum = 1.0 / St.sum;
     const unsigned c0 = A.chunk_start[c], nc = A.chunk_start[c + 1] - c0;
     const double gi00 = Q.gi[0][0], gi01 = Q.gi[0][1], gi11 = Q.gi[1][1];
     const double lse0 = log((double)kMixS) + 0.5 * Q.logdet;
@@ -521,34 +613,32 @@ __global__ void __launch_bounds__(256) k_mix_bwd_mm(LearnArgs A)
         const double cf = valid ? -ws * rho - (kd != 1 ? A.lambda * L.inv_n_acc : 0.0) : 0.0;
         const double lse = lnet + lse0;
         if (g == 0) cs_acc += cf;
-        d4_t acc[4];
-        double Qa, ta;
-        mix_products<K>(A, Q, rowA, lane, acc, Qa, ta);
+        d4_t acc[1][4];
+        double Qa[1], ta[1];
+        mix_products<K, 1>(A, Q, {rowA}, lane, acc, Qa, ta);
         double Cv[4][4], Fv[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int ri = 4 * v + g;
-            const double Qr = __shfl(Qa, ri, 64), cfr = __shfl(cf, ri, 64), lser = __shfl(lse, ri, 64);
-            double fsum = 0.0;
+            const double Qr = __shfl(Qa[0], ri, 64), cfr = __shfl(cf, ri, 64), lser = __shfl(lse, ri, 64);
+            double y0[2], y1[2], fsum = 0.0;
+            own_shifts(acc[0], v, q, y0, y1);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const double y = acc[t][v], yo = __shfl_xor(y, 1, 64);
-                const double y0 = q ? yo : y, y1 = q ? y : yo;
-                const double qf = Qr - (gi00 * y0 * y0 + 2.0 * gi01 * y0 * y1 + gi11 * y1 * y1);
-                const double g0 = gi00 * y0 + gi01 * y1, g1 = gi01 * y0 + gi11 * y1;
+            for (int u = 0; u < 2; ++u) {
+                const double qf = Qr - (gi00 * y0[u] * y0[u] + 2.0 * gi01 * y0[u] * y1[u] + gi11 * y1[u] * y1[u]);
+                const double g0 = gi00 * y0[u] + gi01 * y1[u], g1 = gi01 * y0[u] + gi11 * y1[u];
                 const double pi = exp(-K * log(qf) - lser);
                 const double f = cfr * pi * K / qf;
-                Cv[v][t] = f * (q ? g1 : g0);
-                if (!q) {  // each (row, shift) once
-                    S00 += f * g0 * g0;
-                    S01 += f * g0 * g1;
-                    S11 += f * g1 * g1;
-                    fsum += f;
-                }
+                // this lane's q of the shift, and of its partner's
+                const double own = f * (q ? g1 : g0), got = dpp<kXor1>(f * (q ? g0 : g1));
+                Cv[v][u] = q ? got : own;
+                Cv[v][u + 2] = q ? own : got;
+                S00 += f * g0 * g0;
+                S01 += f * g0 * g1;
+                S11 += f * g1 * g1;
+                fsum += f;
             }
-#pragma unroll
-            for (int o = 1; o <= 8; o <<= 1) fsum += __shfl_xor(fsum, o, 64);
-            Fv[v] = fsum;  // sum_j f of tile row 4v + g
+            Fv[v] = sum16(fsum);  // sum_j f of tile row 4v + g
         }
         // M += X^T C over the tile's rows: k-step s covers rows 4s .. 4s + 3
 #pragma unroll
@@ -563,37 +653,10 @@ __global__ void __launch_bounds__(256) k_mix_bwd_mm(LearnArgs A)
             }
         }
     }
-    // P_mq = sum_j (R_j^T M_(j,q))_m for m = 16 mt + 4v + g
-    double P[MT][4];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int m = 16 * mt + 4 * v + g, k1 = m % K + 1;
-            // cos coordinate (m < K; a compile-time fact: 4v + g < 16), and the partner
-            // coordinate m -+ K: another tile (K >= 16) or another v (K = 8)
-            constexpr bool big = K >= 16;
-            const bool cosc = big ? mt < K / 16 : v < 2;
-            const int mtp = big ? (cosc ? mt + K / 16 : mt - K / 16) : mt;
-            const int vp = big ? v : (cosc ? v + 2 : v - 2);
-            double acc = 0.0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int j = 8 * t + (i16 >> 1), mi = (k1 * j) & (kMixS - 1);
-                const double Mv = macc[mt][t][v], Mp = macc[mtp][t][vp];
-                acc += cosc ? c_cs[mi] * Mv - c_sn[mi] * Mp : c_cs[mi] * Mv + c_sn[mi] * Mp;
-            }
-#pragma unroll
-            for (int o = 2; o <= 8; o <<= 1) acc += __shfl_xor(acc, o, 64);
-            P[mt][v] = acc;  // lanes with lane & 1 = q
-        }
-#pragma unroll
-    for (int o = 1; o <= 32; o <<= 1) {
-        S00 += __shfl_xor(S00, o, 64);
-        S01 += __shfl_xor(S01, o, 64);
-        S11 += __shfl_xor(S11, o, 64);
-        cs_acc += __shfl_xor(cs_acc, o, 64);
-    }
+    S00 = wsum(S00);
+    S01 = wsum(S01);
+    S11 = wsum(S11);
+    cs_acc = wsum(cs_acc);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         Epart[mt] += __shfl_xor(Epart[mt], 16, 64);
@@ -601,44 +664,59 @@ __global__ void __launch_bounds__(256) k_mix_bwd_mm(LearnArgs A)
     }
     double *o = A.part + (size_t)c * A.pt_len;
     if (lane == 0) o[2] = cs_acc;
+    // per mode k: P_mq = sum_j (R_j^T M_(j,q))_m of its two coordinates m = k (cos) and
+    // k + K, in another tile (K >= 16) or another v (K = 8); lanes with lane & 1 = q
+    constexpr int CT = K >= 16 ? K / 16 : 1, CV = K >= 16 ? 4 : 2;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < CT; ++mt)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int m = 16 * mt + 4 * v + g, k = m % K;
-            const double ak = Q.a[k];
-            const double Pq = P[mt][v], Po = __shfl_xor(Pq, 1, 64);
-            const double P0 = q ? Po : Pq, P1 = q ? Pq : Po;
-            const double V0 = Q.V[m][0], V1 = Q.V[m][1];
-            // dL/dV_mq
-            if ((i16 >> 1) == 0) o[3 + K + 2 * m + q] = 2.0 * ak * (Pq - (q ? V0 * S01 + V1 * S11 : V0 * S00 + V1 * S01));
-            // this coordinate's share of dL/dlog d_k, summed with its partner's in the cos lane
-            const double Em = __shfl(Epart[mt], 4 * v + g, 64);
-            const double term = Em - 2.0 * (V0 * P0 + V1 * P1) + V0 * V0 * S00 + 2.0 * V0 * V1 * S01 + V1 * V1 * S11;
-            constexpr bool big = K >= 16;
-            const bool cosc = big ? mt < K / 16 : v < 2;
-            const int mtp = big ? (cosc ? mt + K / 16 : mt - K / 16) : mt;
-            const int vp = big ? v : (cosc ? v + 2 : v - 2);
-            const int mp = cosc ? m + K : m - K;
-            const double Ppq = P[mtp][vp], Ppo = __shfl_xor(Ppq, 1, 64);
-            const double Pp0 = q ? Ppo : Ppq, Pp1 = q ? Ppq : Ppo;
-            const double W0 = Q.V[mp][0], W1 = Q.V[mp][1];
-            const double Ep = __shfl(Epart[mtp], (16 * mtp + 4 * vp + g) % 16, 64);
-            const double termp = Ep - 2.0 * (W0 * Pp0 + W1 * Pp1) + W0 * W0 * S00 + 2.0 * W0 * W1 * S01 + W1 * W1 * S11;
-            if (cosc && i16 == 0) o[3 + k] = ak * (term + termp);
+        for (int v = 0; v < CV; ++v) {
+            const int mtp = K >= 16 ? mt + CT : mt, vp = K >= 16 ? v : v + 2;
+            const int m = 16 * mt + 4 * v + g;
+            double Pc = 0.0, Ps = 0.0;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int j = 8 * t + (i16 >> 1), mi = ((m + 1) * j) & (kMixS - 1);
+                const double cs = s_rot[mi], sn = s_rot[kMixS + mi];
+                const double Mc = macc[mt][t][v], Ms = macc[mtp][t][vp];
+                Pc += cs * Mc - sn * Ms;
+                Ps += cs * Ms + sn * Mc;
+            }
+            const double ak = Q.a[m];
+            double term = 0.0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int mm = h ? m + K : m;
+                const double Pq = sum16<2>(h ? Ps : Pc), Po = dpp<kXor1>(Pq);
+                const double P0 = q ? Po : Pq, P1 = q ? Pq : Po;
+                const double V0 = Q.V[mm][0], V1 = Q.V[mm][1];
+                // dL/dV_mq, and the coordinate's share of dL/dlog d_k
+                if ((i16 >> 1) == 0) o[3 + K + 2 * mm + q] = 2.0 * ak * (Pq - (q ? V0 * S01 + V1 * S11 : V0 * S00 + V1 * S01));
+                const double Em = h ? __shfl(Epart[mtp], 4 * vp + g, 64) : __shfl(Epart[mt], 4 * v + g, 64);
+                term += Em - 2.0 * (V0 * P0 + V1 * P1) + V0 * V0 * S00 + 2.0 * V0 * V1 * S01 + V1 * V1 * S11;
+            }
+            if (i16 == 0) o[3 + m] = ak * term;
+            __builtin_amdgcn_sched_barrier(0);  // mode by mode: the registers are the products'
         }
 }
 
-// Per point: dL/dtheta = chunk sums (in order) - (1/2) csum d log|L0|/dtheta; dL/do.
+// Per point (one workgroup): dL/dtheta = chunk sums - (1/2) csum d log|L0|/dtheta,
+// dL/do, and back through the layers: dh2 = (W3 do) (1 - h2^2),
+// dh1 = (W2 dh2) (1 - h1^2).  Wave w takes every 16th chunk from w, a lane a
+// coordinate; the waves' sums are added in order.
 template <int K>
-__global__ void __launch_bounds__(64) k_param_grad(const LearnArgs A, int n_out, double v_scale, double *dout,
-                                                   double *gmix)
+__global__ void __launch_bounds__(kMlpBlock) k_param_grad(const LearnArgs A, const double *W, int H, double v_scale,
+                                                          const double *h1, const double *h2, double *dout,
+                                                          double *gmix, double *dh1, double *dh2)
 {
-    const int p = blockIdx.x, m = threadIdx.x;
+    constexpr int n_out = 5 * K, NW = kMlpBlock / kWave;
+    __shared__ double part[NW][1 + n_out], so[n_out], s1[kMaxHidden], s2[kMaxHidden];
+    const int p = blockIdx.x, tid = threadIdx.x, m = tid & 63, wv = tid >> 6;
     const LearnParam &Q = A.par[p];
     const LearnPoint &L = A.pts[p];
     double cs = 0.0, gd = 0.0, g0 = 0.0, g1 = 0.0;
-    for (unsigned c = L.chunk0; c < L.chunk1; ++c) {
+#pragma unroll 4
+    for (unsigned c = L.chunk0 + wv; c < L.chunk1; c += NW) {
         const double *o = A.part + (size_t)c * A.pt_len;
         cs += o[2];
         if (m < K) gd += o[3 + m];
@@ -647,19 +725,35 @@ __global__ void __launch_bounds__(64) k_param_grad(const LearnArgs A, int n_out,
             g1 += o[3 + K + 2 * m + 1];
         }
     }
-    double *d = dout + (size_t)p * n_out;
-    double *g = gmix + (size_t)p * 5 * K;
-    if (m < K) {
-        const double v = gd - 0.5 * cs * Q.dld_logd[m];
-        d[m] = v;
-        g[m] = v;
-    }
+    if (m == 0) part[wv][0] = cs;
+    if (m < K) part[wv][1 + m] = gd;
     if (m < 2 * K) {
-        const double v0 = g0 - 0.5 * cs * Q.dld_V[m][0], v1 = g1 - 0.5 * cs * Q.dld_V[m][1];
-        g[K + 2 * m] = v0;
-        g[K + 2 * m + 1] = v1;
-        d[K + 2 * m] = v_scale * v0;
-        d[K + 2 * m + 1] = v_scale * v1;
+        part[wv][1 + K + 2 * m] = g0;
+        part[wv][1 + K + 2 * m + 1] = g1;
+    }
+    __syncthreads();
+    if (tid < n_out) {
+        double v = 0.0;
+        cs = 0.0;
+        for (int w = 0; w < NW; ++w) {
+            v += part[w][1 + tid];
+            cs += part[w][0];
+        }
+        const int e = tid - K;
+        v -= 0.5 * cs * (tid < K ? Q.dld_logd[tid] : Q.dld_V[e >> 1][e & 1]);
+        gmix[(size_t)p * n_out + tid] = v;
+        so[tid] = tid < K ? v : v_scale * v;
+        dout[(size_t)p * n_out + tid] = so[tid];
+    }
+    __syncthreads();
+    const MlpView w(W, H, n_out);
+    mlp_rows_back(w.W3, H, n_out, so, h2 + (size_t)p * H, s2);
+    __syncthreads();
+    mlp_rows_back(w.W2, H, H, s2, h1 + (size_t)p * H, s1);
+    __syncthreads();
+    if (tid < H) {
+        dh2[(size_t)p * H + tid] = s2[tid];
+        dh1[(size_t)p * H + tid] = s1[tid];
     }
 }
 
@@ -705,7 +799,7 @@ struct tkdv_learner {
     int n_points = 0;
     std::vector<LearnPoint> hpts;
     std::vector<uint64_t> n_acc;
-    Buf W, gW, m1, m2, z, h1, h2, out, dh1, dh2, dout, gmix, par, pts, st;
+    Buf W, gW, m1, m2, z, h1, h2, dh1, dh2, dout, gmix, par, pts, st;
     Buf X, row_point, kind, lf, lnet, lmix;
     Buf order, chunk_start, chunk_point, part;  // rows grouped by point, chunks, chunk partials
     Buf shift_src;                              // base rows and phases of tkdv_learner_add_shifted_rows
@@ -754,20 +848,22 @@ tkdv_status make_learn_point(const tkdv_learner *L, const tkdv_point &pt, const 
 }
 
 template <int K>
-hipError_t launch_prep(tkdv_learner *L, const double *out, const LearnPoint *pts, LearnParam *par, int np,
-                       hipStream_t st)
+hipError_t launch_net(tkdv_learner *L, int np, const double *z, const LearnPoint *pts, double *h1, double *h2,
+                      LearnParam *par, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_mix_prep<K>, dim3(np), dim3(64), 0, st, out, L->n_out, pts, par, L->cfg.v_amp,
-                       L->cfg.v_scale);
+    hipLaunchKernelGGL(k_mlp_fwd<K>, dim3(np), dim3(kMlpBlock), 0, st, L->W.as<double>(), L->H, z, pts, h1, h2, par,
+                       L->cfg.v_amp, L->cfg.v_scale);
     return hipGetLastError();
 }
 
-hipError_t prep(tkdv_learner *L, const double *out, const LearnPoint *pts, LearnParam *par, int np, hipStream_t st)
+// The network and the mixture's parameters of np points.
+hipError_t net(tkdv_learner *L, int np, const double *z, const LearnPoint *pts, double *h1, double *h2,
+               LearnParam *par, hipStream_t st)
 {
     switch (L->K) {
-    case 8: return launch_prep<8>(L, out, pts, par, np, st);
-    case 16: return launch_prep<16>(L, out, pts, par, np, st);
-    default: return launch_prep<32>(L, out, pts, par, np, st);
+    case 8: return launch_net<8>(L, np, z, pts, h1, h2, par, st);
+    case 16: return launch_net<16>(L, np, z, pts, h1, h2, par, st);
+    default: return launch_net<32>(L, np, z, pts, h1, h2, par, st);
     }
 }
 
@@ -822,28 +918,22 @@ hipError_t rows_pass(tkdv_learner *L, const LearnArgs &A, hipStream_t st, bool b
 template <int K>
 hipError_t launch_pgrad(tkdv_learner *L, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_param_grad<K>, dim3(L->n_points), dim3(64), 0, st, args(L), L->n_out, L->cfg.v_scale,
-                       L->dout.as<double>(), L->gmix.as<double>());
+    hipLaunchKernelGGL(k_param_grad<K>, dim3(L->n_points), dim3(kMlpBlock), 0, st, args(L), L->W.as<double>(), L->H,
+                       L->cfg.v_scale, L->h1.as<double>(), L->h2.as<double>(), L->dout.as<double>(),
+                       L->gmix.as<double>(), L->dh1.as<double>(), L->dh2.as<double>());
     return hipGetLastError();
 }
 
-// Loss and gradients at the current weights (gW holds dL/dweights after it).
-tkdv_status evaluate(tkdv_learner *L, hipStream_t st)
+// Loss and gradients at the current weights (gW holds dL/dweights after it),
+// and the update of ad.
+tkdv_status evaluate(tkdv_learner *L, const Adam &ad, hipStream_t st)
 {
     const int np = L->n_points, H = L->H, no = L->n_out;
-    hipLaunchKernelGGL(k_mlp_fwd, dim3(np), dim3(kMaxHidden), 0, st, L->W.as<double>(), H, no, L->z.as<double>(),
-                       L->h1.as<double>(), L->h2.as<double>(), L->out.as<double>());
-    LTRY(hipGetLastError());
-    LTRY(prep(L, L->out.as<double>(), L->pts.as<LearnPoint>(), L->par.as<LearnParam>(), np, st));
-    LTRY(launch_fill_u32(L->st.p, sizeof(LearnStats) * np / 4, 0u, st));
+    LTRY(net(L, np, L->z.as<double>(), L->pts.as<LearnPoint>(), L->h1.as<double>(), L->h2.as<double>(),
+             L->par.as<LearnParam>(), st));
     LearnArgs A = args(L);
     LTRY(rows_pass(L, A, st, false));
-    const unsigned long long g = std::min<unsigned long long>((L->n_rows + 255) / 256 + 1, 4096);
-    hipLaunchKernelGGL(k_loss_max, dim3((unsigned)g), dim3(256), 0, st, A);
-    LTRY(hipGetLastError());
-    hipLaunchKernelGGL(k_loss_chunk, dim3((A.n_chunks + 3) / 4), dim3(256), 0, st, A);
-    LTRY(hipGetLastError());
-    hipLaunchKernelGGL(k_loss_final, dim3((np + 63) / 64), dim3(64), 0, st, A, np);
+    hipLaunchKernelGGL(k_loss_final, dim3(np), dim3(256), 0, st, A);
     LTRY(hipGetLastError());
     LTRY(rows_pass(L, A, st, true));
     switch (L->K) {
@@ -851,14 +941,10 @@ tkdv_status evaluate(tkdv_learner *L, hipStream_t st)
     case 16: LTRY(launch_pgrad<16>(L, st)); break;
     default: LTRY(launch_pgrad<32>(L, st)); break;
     }
-    hipLaunchKernelGGL(k_mlp_bwd_hidden, dim3(np), dim3(kMaxHidden), 0, st, L->W.as<double>(), H, no,
-                       L->h1.as<double>(), L->h2.as<double>(), L->dout.as<double>(), L->dh1.as<double>(),
-                       L->dh2.as<double>());
-    LTRY(hipGetLastError());
     const unsigned long long gw = std::min<unsigned long long>((L->nW + 255) / 256, 2048);
-    hipLaunchKernelGGL(k_mlp_bwd_weights, dim3((unsigned)gw), dim3(256), 0, st, H, no, np, L->z.as<double>(),
+    hipLaunchKernelGGL(k_weights, dim3((unsigned)gw), dim3(256), 0, st, H, no, np, L->z.as<double>(),
                        L->h1.as<double>(), L->h2.as<double>(), L->dh1.as<double>(), L->dh2.as<double>(),
-                       L->dout.as<double>(), L->gW.as<double>());
+                       L->dout.as<double>(), L->gW.as<double>(), ad);
     LTRY(hipGetLastError());
     return TKDV_OK;
 }
@@ -905,7 +991,7 @@ tkdv_status grow_rows(tkdv_learner *L, unsigned long long need, hipStream_t st)
     return TKDV_OK;
 }
 
-// Rows grouped by point in insertion order, cut into chunks of at most kChunk
+// Rows grouped by point in insertion order, cut into chunks (kTileRows)
 // rows of one point; uploads the index order, the chunk table and the
 // points' chunk ranges.
 tkdv_status build_chunks(tkdv_learner *L, hipStream_t st)
@@ -915,10 +1001,18 @@ tkdv_status build_chunks(tkdv_learner *L, hipStream_t st)
     for (uint32_t r = 0; r < (uint32_t)L->h_row_point.size(); ++r) by[L->h_row_point[r]].push_back(r);
     std::vector<uint32_t> order, cstart;
     std::vector<int> cpoint;
+    unsigned long long tiles = 0;
+    for (int p = 0; p < np; ++p) tiles += (by[p].size() + kTileRows - 1) / kTileRows;
+    const unsigned long long waves = 4ull * kStepWaves * L->n_cu;
     for (int p = 0; p < np; ++p) {
         L->hpts[p].chunk0 = (uint32_t)cpoint.size();
-        for (size_t q = 0; q < by[p].size(); q += kChunk) {
-            cstart.push_back((uint32_t)(order.size() + q));
+        // an even share of the waves, the point's tiles dealt out evenly: with chunks of two
+        // tiles 2064 of them took a third round for the last sixteen
+        const unsigned long long tp = (by[p].size() + kTileRows - 1) / kTileRows;
+        unsigned long long nc = tiles <= waves ? tp : std::max<unsigned long long>(waves * tp / tiles, 1);
+        if (nc > tp) nc = tp;
+        for (unsigned long long q = 0; q < nc; ++q) {
+            cstart.push_back((uint32_t)(order.size() + tp * q / nc * kTileRows));
             cpoint.push_back(p);
         }
         order.insert(order.end(), by[p].begin(), by[p].end());
@@ -1060,7 +1154,7 @@ tkdv_status tkdv_learner_destroy(tkdv_learner *L)
 {
     if (!L) return TKDV_OK;
     (void)hipSetDevice(L->device);
-    Buf *bs[] = {&L->W, &L->gW, &L->m1, &L->m2, &L->z, &L->h1, &L->h2, &L->out, &L->dh1, &L->dh2, &L->dout,
+    Buf *bs[] = {&L->W, &L->gW, &L->m1, &L->m2, &L->z, &L->h1, &L->h2, &L->dh1, &L->dh2, &L->dout,
                  &L->gmix, &L->par, &L->pts, &L->st, &L->X, &L->row_point, &L->kind, &L->lf, &L->lnet, &L->lmix,
                  &L->order, &L->chunk_start, &L->chunk_point, &L->part, &L->shift_src};
     for (Buf *b : bs) b->release();
@@ -1089,7 +1183,6 @@ tkdv_status tkdv_learner_set_points(tkdv_learner *L, int32_t n_points, const tkd
     LTRY(L->h2.ensure(np * H * 8));
     LTRY(L->dh1.ensure(np * H * 8));
     LTRY(L->dh2.ensure(np * H * 8));
-    LTRY(L->out.ensure(np * no * 8));
     LTRY(L->dout.ensure(np * no * 8));
     LTRY(L->gmix.ensure(np * 5 * L->K * 8));
     LTRY(L->par.ensure(np * sizeof(LearnParam)));
@@ -1226,15 +1319,12 @@ tkdv_status tkdv_learner_train(tkdv_learner *L, int32_t n_steps, double *h_loss,
     hipStream_t st = (hipStream_t)stream;
     const tkdv_learner_cfg &c = L->cfg;
     for (int it = 0; it < n_steps; ++it) {
-        tkdv_status s = evaluate(L, st);
+        const double step = (double)(L->step + 1);
+        const Adam ad{L->W.as<double>(), L->m1.as<double>(), L->m2.as<double>(), c.lr, c.beta1, c.beta2, c.adam_eps,
+                      1.0 - std::pow(c.beta1, step), 1.0 - std::pow(c.beta2, step)};
+        tkdv_status s = evaluate(L, ad, st);
         if (s != TKDV_OK) return s;
         ++L->step;
-        const double c1 = 1.0 - std::pow(c.beta1, (double)L->step), c2 = 1.0 - std::pow(c.beta2, (double)L->step);
-        const unsigned long long g = std::min<unsigned long long>((L->nW + 255) / 256, 2048);
-        hipLaunchKernelGGL(k_adam, dim3((unsigned)g), dim3(256), 0, st, L->W.as<double>(), L->gW.as<double>(),
-                           L->m1.as<double>(), L->m2.as<double>(), (long long)L->nW, c.lr, c.beta1, c.beta2,
-                           c.adam_eps, c1, c2);
-        LTRY(hipGetLastError());
     }
     if (n_steps > 0) return read_loss(L, h_loss, st);
     LTRY(hipStreamSynchronize(st));
@@ -1248,7 +1338,7 @@ tkdv_status tkdv_learner_gradients(tkdv_learner *L, double *h_loss, double *h_gr
     if (L->n_points < 1 || L->n_rows == 0) return record_error(TKDV_E_ARG, "no training rows");
     LTRY(hipSetDevice(L->device));
     hipStream_t st = (hipStream_t)stream;
-    tkdv_status s = evaluate(L, st);
+    tkdv_status s = evaluate(L, Adam{}, st);
     if (s != TKDV_OK) return s;
     if (h_grad_mix)
         LTRY(hipMemcpyAsync(h_grad_mix, L->gmix.p, (size_t)L->n_points * 5 * L->K * 8, hipMemcpyDeviceToHost, st));
@@ -1265,12 +1355,11 @@ tkdv_status tkdv_learner_mixture(tkdv_learner *L, const tkdv_point *pt, const tk
     LearnPoint lp;
     tkdv_status s = make_learn_point(L, *pt, *sigma_plan, lp);
     if (s != TKDV_OK) return s;
-    const int H = L->H, no = L->n_out, K = L->K;
-    Buf z, h1, h2, o, pts, par;
+    const int H = L->H, K = L->K;
+    Buf z, h1, h2, pts, par;
     LTRY(z.ensure(3 * 8));
     LTRY(h1.ensure(H * 8));
     LTRY(h2.ensure(H * 8));
-    LTRY(o.ensure(no * 8));
     LTRY(pts.ensure(sizeof(LearnPoint)));
     LTRY(par.ensure(sizeof(LearnParam)));
     tkdv_status rs = TKDV_OK;
@@ -1282,16 +1371,14 @@ tkdv_status tkdv_learner_mixture(tkdv_learner *L, const tkdv_point *pt, const tk
             rs = record_error(TKDV_E_DEVICE, hipGetErrorString(e));
             break;
         }
-        hipLaunchKernelGGL(k_mlp_fwd, dim3(1), dim3(kMaxHidden), 0, nullptr, L->W.as<double>(), H, no,
-                           z.as<double>(), h1.as<double>(), h2.as<double>(), o.as<double>());
-        if ((e = hipGetLastError()) != hipSuccess ||
-            (e = prep(L, o.as<double>(), pts.as<LearnPoint>(), par.as<LearnParam>(), 1, nullptr)) != hipSuccess ||
+        if ((e = net(L, 1, z.as<double>(), pts.as<LearnPoint>(), h1.as<double>(), h2.as<double>(),
+                     par.as<LearnParam>(), nullptr)) != hipSuccess ||
             (e = hipMemcpy(&hp, par.p, sizeof(hp), hipMemcpyDeviceToHost)) != hipSuccess) {
             rs = record_error(TKDV_E_DEVICE, hipGetErrorString(e));
             break;
         }
     } while (false);
-    Buf *bs[] = {&z, &h1, &h2, &o, &pts, &par};
+    Buf *bs[] = {&z, &h1, &h2, &pts, &par};
     for (Buf *b : bs) b->release();
     if (rs != TKDV_OK) return rs;
     std::memset(out, 0, sizeof(*out));
