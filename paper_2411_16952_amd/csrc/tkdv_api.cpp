@@ -88,7 +88,7 @@ struct tkdv_ctx {
     hipEvent_t join[2] = {};
     DevBuf sweep, active;
     DevBuf plan_pts, plan_val, plan_x, plan_ev, plan_mix, plan_user;  // tkdv_plan_batch, _mixture_batch
-    DevBuf ext_keys, ext_jmax, ext_misc, ext_list;  // tkdv_extremes
+    DevBuf ext_keys, ext_jmax, ext_misc;  // tkdv_extremes
     DevBuf sir_pt, sir_w, sir_tile, sir_chunk, sir_part;  // tkdv_sir
     void *h_poll = nullptr;  // pinned: active count, FP64 list count
     std::string arch;
@@ -1253,7 +1253,7 @@ tkdv_status tkdv_destroy(tkdv_ctx *ctx)
                       &ctx->seg, &ctx->seg_cnt, &ctx->seg_base, &ctx->seg_stats, &ctx->hist, &ctx->results, &ctx->plist,
                       &ctx->mix, &ctx->mix_tab, &ctx->sweep, &ctx->active, &ctx->plan_pts, &ctx->plan_val,
                       &ctx->plan_x, &ctx->plan_ev, &ctx->plan_mix, &ctx->plan_user, &ctx->ext_keys, &ctx->ext_jmax, &ctx->ext_misc,
-                      &ctx->ext_list, &ctx->sir_pt, &ctx->sir_w, &ctx->sir_tile, &ctx->sir_chunk, &ctx->sir_part};
+                      &ctx->sir_pt, &ctx->sir_w, &ctx->sir_tile, &ctx->sir_chunk, &ctx->sir_part};
     for (DevBuf *b : bufs)
         if (b->p) (void)hipFree(b->p);
     for (DevBuf *b : {&ctx->qstat[0], &ctx->qstat[1]})
@@ -1531,13 +1531,17 @@ tkdv_status tkdv_extremes(tkdv_ctx *ctx, int32_t K, double E0, const float *d_xh
     hipStream_t st = (hipStream_t)stream;
     const int ki = kindex(K);
     const unsigned long long cap_eq = 1ull << 16;
+    const size_t k = (size_t)std::min<uint64_t>((uint64_t)top_k, n), first_eq = 64;
     HIP_TRY(ctx, ensure(ctx->ext_keys, n * sizeof(uint32_t)));
     if (!d_jmax) HIP_TRY(ctx, ensure(ctx->ext_jmax, n * sizeof(int32_t)));
-    // misc: n_exceed, histogram[256], counts[2], then the gathered keys and grid indices
-    HIP_TRY(ctx, ensure(ctx->ext_misc, (1 + 256 + 2) * sizeof(unsigned long long) + (size_t)top_k * 8));
-    HIP_TRY(ctx, ensure(ctx->ext_list, ((size_t)top_k + cap_eq) * sizeof(unsigned long long)));
-    unsigned long long *misc = (unsigned long long *)ctx->ext_misc.p;
-    HIP_TRY(ctx, hipMemsetAsync(misc, 0, (1 + 256 + 2) * sizeof(unsigned long long), st));
+    // the selection's state, then the rows above the k-th key and those equal to it;
+    // its result, the former and the first of the latter are one copy
+    const size_t head = offsetof(ExtSelect, out), back = sizeof(ExtSelect) - head + (k + first_eq) * sizeof(ExtRow);
+    HIP_TRY(ctx, ensure(ctx->ext_misc, sizeof(ExtSelect) + (k + cap_eq) * sizeof(ExtRow)));
+    HIP_TRY(ctx, ensure_host(ctx->h_misc, ctx->h_misc_bytes, back));
+    ExtSelect *sel = (ExtSelect *)ctx->ext_misc.p;
+    ExtRow *above = (ExtRow *)(sel + 1), *equal = above + k;
+    HIP_TRY(ctx, launch_ext_begin(sel, k, st));
     ExtArgs ea{};
     ea.xhat = d_xhat;
     ea.n = n;
@@ -1548,73 +1552,40 @@ tkdv_status tkdv_extremes(tkdv_ctx *ctx, int32_t K, double E0, const float *d_xh
     ea.keys = (uint32_t *)ctx->ext_keys.p;
     ea.umax = d_umax;
     ea.jmax = d_jmax ? d_jmax : (int *)ctx->ext_jmax.p;
-    ea.n_exceed = misc;
+    ea.n_exceed = &sel->out.n_exceed;
+    ea.hist = sel->hist[0];
     HIP_TRY(ctx, launch_grid_max(K, ea, ctx->n_cu, st));
-    unsigned long long n_exc = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(&n_exc, misc, sizeof(n_exc), hipMemcpyDeviceToHost, st));
+    if (k > 0) HIP_TRY(ctx, launch_ext_select(ea.keys, ea.jmax, n, sel, above, k, equal, cap_eq, ctx->n_cu, st));
+    char *h = (char *)ctx->h_misc;
+    HIP_TRY(ctx, hipMemcpyAsync(h, (char *)sel + head, k > 0 ? back : sizeof(ExtSelect) - head, hipMemcpyDeviceToHost, st));
     HIP_TRY(ctx, hipStreamSynchronize(st));
-    *h_n_exceed = n_exc;
-    const int k = (int)std::min<uint64_t>((uint64_t)top_k, n);
+    ExtSelect::Out out;
+    std::memcpy(&out, h, sizeof(out));
+    *h_n_exceed = out.n_exceed;
     if (k == 0) return TKDV_OK;
-    // radix select of the k-th largest key, 8 bits per pass from the top
-    uint32_t prefix = 0;
-    unsigned long long need = (unsigned long long)k;  // still to take at or below the prefix
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        HIP_TRY(ctx, hipMemsetAsync(misc + 1, 0, 256 * sizeof(unsigned long long), st));
-        HIP_TRY(ctx, launch_key_hist(ea.keys, n, prefix, shift, misc + 1, ctx->n_cu, st));
-        unsigned long long hist[256];
-        HIP_TRY(ctx, hipMemcpyAsync(hist, misc + 1, sizeof(hist), hipMemcpyDeviceToHost, st));
-        HIP_TRY(ctx, hipStreamSynchronize(st));
-        int b = 255;
-        for (; b > 0; --b) {
-            if (hist[b] >= need) break;
-            need -= hist[b];
-        }
-        prefix = (prefix << 8) | (uint32_t)b;
-    }
-    const uint32_t kth = prefix;  // rows with a larger key: k - need; with this key: >= need
-    unsigned long long *above = (unsigned long long *)ctx->ext_list.p;
-    unsigned long long *equal = above + top_k;
-    HIP_TRY(ctx, launch_key_collect(ea.keys, n, kth, above, (unsigned long long)top_k, equal, cap_eq, misc + 257,
-                                    ctx->n_cu, st));
-    unsigned long long counts[2];
-    HIP_TRY(ctx, hipMemcpyAsync(counts, misc + 257, sizeof(counts), hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipStreamSynchronize(st));
-    if (counts[0] != (unsigned long long)k - need || counts[1] < need)
+    if (out.above != k - out.need || out.equal < out.need)
         return set_err(ctx, TKDV_E_DEVICE, "tkdv_extremes: inconsistent selection counts");
-    if (counts[1] > cap_eq) return set_err(ctx, TKDV_E_UNSUPPORTED, "tkdv_extremes: more than 65536 tied maxima");
-    std::vector<unsigned long long> ra(counts[0]), re(counts[1]);
-    if (!ra.empty())
-        HIP_TRY(ctx, hipMemcpyAsync(ra.data(), above, ra.size() * 8, hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipMemcpyAsync(re.data(), equal, re.size() * 8, hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipStreamSynchronize(st));
-    std::sort(re.begin(), re.end());
-    re.resize(need);
-    ra.insert(ra.end(), re.begin(), re.end());  // the k rows
-    // the selected rows' keys and grid indices, gathered on the device
-    std::vector<uint32_t> keys(ra.size());
-    std::vector<int32_t> jm(ra.size());
-    uint32_t *g_keys = (uint32_t *)(misc + 259);
-    int *g_jm = (int *)(g_keys + top_k);
-    HIP_TRY(ctx, hipMemcpyAsync(above, ra.data(), ra.size() * 8, hipMemcpyHostToDevice, st));
-    HIP_TRY(ctx, launch_ext_gather(above, (int)ra.size(), ea.keys, ea.jmax, g_keys, g_jm, st));
-    HIP_TRY(ctx, hipMemcpyAsync(keys.data(), g_keys, keys.size() * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipMemcpyAsync(jm.data(), g_jm, jm.size() * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipStreamSynchronize(st));
-    std::vector<size_t> order(ra.size());
-    for (size_t i = 0; i < order.size(); ++i) order[i] = i;
-    std::sort(order.begin(), order.end(), [&](size_t x, size_t y) {
-        return keys[x] != keys[y] ? keys[x] > keys[y] : ra[x] < ra[y];
-    });
-    for (int i = 0; i < k; ++i) {
-        const size_t o = order[i];
-        const uint32_t kk = keys[o];
-        const uint32_t bits = (kk & 0x80000000u) ? (kk & 0x7FFFFFFFu) : ~kk;
+    if (out.equal > cap_eq) return set_err(ctx, TKDV_E_UNSUPPORTED, "tkdv_extremes: more than 65536 tied maxima");
+    const ExtRow *rows = (const ExtRow *)(h + (sizeof(ExtSelect) - head));
+    std::vector<ExtRow> top(rows, rows + out.above), tied(out.equal);
+    if (out.equal <= first_eq) {
+        std::copy(rows + k, rows + k + out.equal, tied.begin());
+    } else {
+        HIP_TRY(ctx, hipMemcpyAsync(tied.data(), equal, out.equal * sizeof(ExtRow), hipMemcpyDeviceToHost, st));
+        HIP_TRY(ctx, hipStreamSynchronize(st));
+    }
+    // larger maxima first, lower rows first among equal ones
+    auto before = [](const ExtRow &x, const ExtRow &y) { return x.key != y.key ? x.key > y.key : x.row < y.row; };
+    std::sort(tied.begin(), tied.end(), before);
+    top.insert(top.end(), tied.begin(), tied.begin() + (std::ptrdiff_t)out.need);
+    std::sort(top.begin(), top.end(), before);
+    for (size_t i = 0; i < k; ++i) {
+        const uint32_t bits = (top[i].key & 0x80000000u) ? (top[i].key & 0x7FFFFFFFu) : ~top[i].key;
         float f;
         std::memcpy(&f, &bits, 4);
-        h_rows[i] = ra[o];
+        h_rows[i] = top[i].row;
         h_umax[i] = f;
-        h_jmax[i] = jm[o];
+        h_jmax[i] = top[i].j;
     }
     return TKDV_OK;
 }
