@@ -50,13 +50,16 @@ __host__ __device__ constexpr int decide_lds_bytes()
 // ---------------------------------------------------------------------------
 // B threads per workgroup sharing one copy of the tables; G tile pairs of the
 // half-period synthesis with their accumulators live together (a tile variant
-// the sweep's autotuner chooses among; G divides the K/16 tile pairs).
+// the sweep's autotuner chooses among; G divides the K/16 tile pairs).  At K = 16
+// two registers more than the 128 of four waves per SIMD would leave three.
 template <int K, int PREC, int PROP, int B = decide_block(K), int G = 1>
-__global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, int n_plist)
+__global__ void __launch_bounds__(B, K <= 16 ? 4 : 1) k_decide(KernelArgs a, const int *plist, int n_plist)
 {
     static_assert(K < 16 || (K / 16) % G == 0, "G must divide the tile pairs");
     if (a.d_active && *a.d_active == 0ull) return;  // a sweep window without unfinished points
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ DeferList deferred;
+    deferred.begin();
     constexpr int tab = decide_tab_bytes<K, PREC>();
     if constexpr (!decide_half_period<K>()) {
         const uint4 *s0 = reinterpret_cast<const uint4 *>(a.phi_hi);
@@ -149,9 +152,10 @@ __global__ void __launch_bounds__(B) k_decide(KernelArgs a, const int *plist, in
         }
         // one coalesced store of the claim's accept words
         if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
-        push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
+        deferred.push(a, C, p, P.i0 + base * kTile, my_def, lane);
         count_accepted(P, C, tally, my_word, len, lane);
     }
+    deferred.flush(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -187,6 +191,8 @@ template <int K, int PREC>
 __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const int *plist, int n_plist)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ DeferList deferred;
+    deferred.begin();
     constexpr bool EO = mix_half_period<K>();
     constexpr int tab = mix_tab_bytes<K, PREC>();
     constexpr int phi_bytes = (PREC == PREC_BF16X3 ? 2 : 1) * tab;
@@ -342,11 +348,12 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
                 }
             }
             if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
-            push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
+            deferred.push(a, C, p, P.i0 + base * kTile, my_def, lane);
             count_accepted(P, C, tally, my_word, len, lane);
         }
         tally.report(C, lane);
     }
+    deferred.flush(a);
 }
 
 // ---------------------------------------------------------------------------

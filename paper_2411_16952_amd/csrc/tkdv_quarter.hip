@@ -31,6 +31,8 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
 {
     if (a.d_active && *a.d_active == 0ull) return;  // a sweep window without unfinished points
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ DeferList deferred;
+    deferred.begin();
     constexpr int B = BL, CPL = K / 4;
     {
         const uint4 *s0 = reinterpret_cast<const uint4 *>(a.phi_hi);
@@ -152,9 +154,10 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
             }
         }
         if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
-        push_deferred(a, C, p, P.i0 + base * kTile, my_def, lane);
+        deferred.push(a, C, p, P.i0 + base * kTile, my_def, lane);
         count_accepted(P, C, tally, my_word, len, lane);
     }
+    deferred.flush(a);
 }
 
 // ---------------------------------------------------------------------------
