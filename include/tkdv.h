@@ -334,7 +334,7 @@ tkdv_status tkdv_sample(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_proposal propo
  * same kernels, outputs and statistics, with every work buffer of the call
  * (accept bitmap, FP64 re-decision list, counters, segment arrays) taken from
  * a fixed array in device memory that the library holds per GPU from its
- * first tkdv_create on that GPU until the process ends (18 MiB); the context
+ * first tkdv_create on that GPU until the process ends (19 MiB); the context
  * has built every K's synthesis tables at creation.  The call allocates
  * nothing, on the device or in pinned host memory.  Limits: plan must not be
  * NULL; proposal UNIFORM or SIGMA; at most 2^26 proposals (n, or

@@ -1004,18 +1004,32 @@ struct GridSums {
     }
 };
 
-// The segments of a call from the tiles decided (one workgroup of B threads):
-// their size and each point's first one.
+// First segment of point p (p = n_points: their number), and words of its segments.
+__device__ __forceinline__ unsigned long long seg_first(const KernelArgs &a, int p)
+{
+    return a.seg->at[p] & ((1ull << kSegShiftBit) - 1);
+}
+__device__ __forceinline__ unsigned long long seg_words(const KernelArgs &a, int p)
+{
+    return 1ull << (a.seg->at[p] >> kSegShiftBit);
+}
+
+// The segments of a call from the tiles decided (one workgroup of B threads).
 template <int B>
 __device__ void plan_segments(const KernelArgs &a)
 {
     __shared__ unsigned long long buf[B], acc[B];
-    __shared__ unsigned long long words_s;
     const int tid = threadIdx.x;
+    // accepted proposals that the output takes, as far as counted (count_accepted)
+    auto accepted_of = [&](int p) {
+        unsigned long long v = 0;
+        for (int s = 0; s < kShards; ++s) v += load_relaxed(&a.cnt[p].shard[s].accepted);
+        return v < a.pts[p].target ? v : a.pts[p].target;
+    };
     unsigned long long sum = 0, accepted = 0;
     for (int p = tid; p < a.n_points; p += B) {
         sum += tiles_taken(a.pts[p], a.cnt[p].next_tile);
-        for (int s = 0; s < kShards; ++s) accepted += load_relaxed(&a.cnt[p].shard[s].accepted);
+        accepted += accepted_of(p);
     }
     buf[tid] = sum;
     acc[tid] = accepted;
@@ -1027,17 +1041,22 @@ __device__ void plan_segments(const KernelArgs &a)
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        words_s = seg_words_for(buf[0], acc[0]);
-        a.seg->words = words_s;
-    }
-    __syncthreads();
-    const unsigned long long w = words_s;
-    const int sh = __ffsll((long long)w) - 1;
+    const int sh_most = seg_shift_for(buf[0]);
+    // accepted per segment: halved by the rounding to a power of two, and no more than
+    // seg_extra segments for all that were accepted
+    unsigned long long per = 2 * acc[0] / seg_extra(buf[0]) + 1;
+    if (per < (unsigned long long)kSegAccepts) per = kSegAccepts;
     unsigned long long run = 0;
     for (int p0 = 0; p0 < a.n_points; p0 += B) {
         const int p = p0 + tid;
-        const unsigned long long v = p < a.n_points ? (tiles_taken(a.pts[p], a.cnt[p].next_tile) + w - 1) >> sh : 0ull;
+        unsigned long long v = 0;
+        int sh = sh_most;
+        if (p < a.n_points) {
+            const unsigned long long w = tiles_taken(a.pts[p], a.cnt[p].next_tile);
+            const double dense = (double)accepted_of(p) / (double)per;  // segments by what was accepted
+            while (sh > 3 && (double)(1 << sh) * dense > (double)w) --sh;
+            v = (w + (1ull << sh) - 1) >> sh;
+        }
         __syncthreads();
         buf[tid] = v;
         __syncthreads();
@@ -1047,19 +1066,18 @@ __device__ void plan_segments(const KernelArgs &a)
             buf[tid] += add;
             __syncthreads();
         }
-        if (p < a.n_points) a.seg->off[p] = run + buf[tid] - v;
+        if (p < a.n_points) a.seg->at[p] = (run + buf[tid] - v) | ((unsigned long long)sh << kSegShiftBit);
         run += buf[B - 1];
     }
-    if (tid == 0) a.seg->off[a.n_points] = run;
+    if (tid == 0) a.seg->at[a.n_points] = run;
 }
 
-// The point of segment gs: the last one whose first segment is at or before it.
 __device__ __forceinline__ int point_of_segment(const KernelArgs &a, unsigned long long gs)
 {
     int lo = 0, hi = a.n_points - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (a.seg->off[mid] <= gs) lo = mid; else hi = mid - 1;
+        if (seg_first(a, mid) <= gs) lo = mid; else hi = mid - 1;
     }
     return lo;
 }

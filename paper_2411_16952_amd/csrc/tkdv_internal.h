@@ -46,33 +46,38 @@ constexpr uint64_t static_share(uint64_t n, uint64_t at_least, int n_points)
     if (at_least >= n) return n <= cap ? n : 0;
     return at_least < cap ? at_least : cap;
 }
-// The accept words of a call are cut into segments of 8 to 2048 words (a power
-// of two), one wave each in the ordered output: about kSegments of them, so that
-// small calls fill the chip too; more, of no fewer than kSegWordsMid words, where
-// each still has kSegAccepts accepted proposals, so that waves of points of unlike
-// acceptance end together.  Fixed segments of 2048 words, a workgroup each, left a
-// million near-linear samples at K = 16 to 16 workgroups (1.6 ms of ordered
-// output, now 0.1 ms); 6.5e7 accepted of four points at K = 64 and 128 took
-// 28.7 ms in 7300 segments and take 25.0 in 58600, while 1e9 proposals with 5e5
-// accepted would pay 0.25 ms for as many.
-constexpr int kSegWordsMin = 8, kSegWordsMid = 128, kSegWordsMax = 2048;
-constexpr int kSegments = 8192, kSegmentsMax = 65536, kSegAccepts = 1024;
-constexpr unsigned long long seg_words_for(unsigned long long words, unsigned long long accepted)
+// The accept words of a call are cut into segments of 8 to 2048 words (a power of
+// two for each point), one wave each in the ordered output: kSegments of them at
+// most where 2048 words allow it, so that small calls fill the chip too, and
+// smaller ones for points that accept more, down to kSegAccepts accepted each, so
+// that waves end together: as many more as seg_extra.  Fixed segments of 2048
+// words, a workgroup each, left a million near-linear samples at K = 16 to 16
+// workgroups (1.6 ms of ordered output, now 0.1 ms).  In segments of one size for
+// all points, 6.5e7 accepted of four points at K = 64 and 128 took 28.7 ms in 7300
+// and 25.0 in 58600 (1e9 proposals with 5e5 accepted would pay 0.25 ms for as
+// many); and in a sweep of 24 points to targets of 1e4 to 3e5, whose dense points
+// are few words beside the sparse ones', single waves took most of 27.6 ms, now 12.2.
+constexpr int kSegWordsMin = 8, kSegWordsMax = 2048;
+constexpr int kSegments = 8192, kSegExtraMin = 4096, kSegExtraMax = 65536, kSegAccepts = 512;
+constexpr unsigned long long seg_extra(unsigned long long words)
 {
-    unsigned long long most = accepted / kSegAccepts;
-    if (most < (unsigned long long)kSegments) most = kSegments;
-    if (most > (unsigned long long)kSegmentsMax) most = kSegmentsMax;
-    unsigned long long s = kSegWordsMin;
-    while (s < (unsigned long long)kSegWordsMax && words > s * (s < (unsigned long long)kSegWordsMid ? kSegments : most)) s *= 2;
-    return s;
+    const unsigned long long e = words / 128;
+    return e < (unsigned long long)kSegExtraMin ? (unsigned long long)kSegExtraMin
+                                                : (e > (unsigned long long)kSegExtraMax ? (unsigned long long)kSegExtraMax : e);
+}
+// log2 of the words of a segment of a point that accepts little, for a call of `words` accept words
+constexpr int seg_shift_for(unsigned long long words)
+{
+    int sh = 3;
+    while ((1 << sh) < kSegWordsMax && words > ((unsigned long long)kSegments << sh)) ++sh;
+    return sh;
 }
 // most segments of a call of n_points points with at most `words` accept words
 constexpr unsigned long long max_segments(unsigned long long words, int n_points)
 {
-    const unsigned long long mid = words / kSegWordsMid, by_size = words / kSegWordsMax;
-    unsigned long long n = mid < (unsigned long long)kSegmentsMax ? mid : (unsigned long long)kSegmentsMax;
-    if (n < (unsigned long long)kSegments) n = kSegments;
-    return (by_size > n ? by_size : n) + (unsigned long long)n_points;
+    const unsigned long long by_size = words / kSegWordsMax;
+    return (by_size > (unsigned long long)kSegments ? by_size : (unsigned long long)kSegments) + seg_extra(words) +
+           (unsigned long long)n_points;
 }
 constexpr int kNBins = TKDV_NBINS;
 constexpr int kMixBlock = 1024;    // threads per workgroup of the mixture sampling kernel
@@ -226,11 +231,11 @@ struct SweepState {
     PointResult total;            // statistics of the accepted samples so far
 };
 
-// The segments of the tiles decided so far (plan_segments): their size, and
-// per point the first one (off[n_points]: their number).
+// The segments of the tiles decided so far (plan_segments): each point's first
+// one, and from bit kSegShiftBit on log2 of its segments' words; then their number.
+constexpr int kSegShiftBit = 48;
 struct SegPlan {
-    unsigned long long words;
-    unsigned long long off[1];
+    unsigned long long at[1];
 };
 constexpr size_t seg_plan_bytes(int n_points) { return sizeof(SegPlan) + sizeof(unsigned long long) * (size_t)n_points; }
 

@@ -657,14 +657,14 @@ __global__ void __launch_bounds__(kBlock) k_fixup_mix(KernelArgs a, int plan)
 __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a)
 {
     const int lane = threadIdx.x & 63;
-    const unsigned long long total = a.seg->off[a.n_points], S = a.seg->words;
+    const unsigned long long total = seg_first(a, a.n_points);
     const unsigned long long waves = (unsigned long long)gridDim.x * (kBlock / kWave);
     for (unsigned long long gs = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6));
          gs < total; gs += waves) {
         const int p = point_of_segment(a, gs);
         const DevPoint &P = a.pts[p];
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long w0 = (gs - a.seg->off[p]) * S, w1 = w0 + S < nw ? w0 + S : nw;
+        const unsigned long long S = seg_words(a, p), w0 = (gs - seg_first(a, p)) * S, w1 = w0 + S < nw ? w0 + S : nw;
         unsigned int c = 0;
 #pragma unroll 4
         for (unsigned long long w = w0 + lane; w < w1; w += kWave) c += __popc(a.bitmap[P.bm_off + w]);
@@ -679,7 +679,7 @@ __global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a)
 {
     __shared__ unsigned long long wsum[16];
     const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const unsigned long long s0 = a.seg->off[p], n = a.seg->off[p + 1] - s0;
+    const unsigned long long s0 = seg_first(a, p), n = seg_first(a, p + 1) - s0;
     const unsigned long long per = (n + 1023) / 1024, b = per * tid < n ? per * tid : n, e = b + per < n ? b + per : n;
     unsigned long long own = 0;
 #pragma unroll 8
@@ -735,7 +735,7 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int tab = materialize_tab_bytes<K>();
-    const unsigned long long total = a.seg->off[a.n_points], S = a.seg->words;
+    const unsigned long long total = seg_first(a, a.n_points);
     if ((unsigned long long)blockIdx.x * (kBlock / kWave) >= total) return;
     {
         const uint4 *s0 = reinterpret_cast<const uint4 *>(a.phi_hi);
@@ -758,7 +758,7 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
         if (P.K != K || P.proposal != PROP || in_seg == 0u || first >= limit) continue;
         hist.enter(a, p, lane);
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long w_first = (gs - a.seg->off[p]) * S;
+        const unsigned long long S = seg_words(a, p), w_first = (gs - seg_first(a, p)) * S;
         unsigned long long rank = first;
         GridSums sums;
         unsigned int n_max4 = 0;
@@ -921,7 +921,7 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
     if (a.d_active && *a.d_active == 0ull) return;
     const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const DevPoint &P = a.pts[p];
-    const unsigned long long s0 = a.seg->off[p], s1 = a.seg->off[p + 1];
+    const unsigned long long s0 = seg_first(a, p), s1 = seg_first(a, p + 1);
     double S[4] = {0.0, 0.0, 0.0, 0.0};
     unsigned long long E[4] = {0, 0, 0, 0}, pi = ~0ull;  // above 2 sigma, 4 sigma, samples above 4 sigma, samples
     unsigned int pk = 0u;

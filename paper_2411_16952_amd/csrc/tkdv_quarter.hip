@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
     constexpr int GW = MatQ<K>::GROUP;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ unsigned int wave_hist[W][kNBins];
-    const unsigned long long total = a.seg->off[a.n_points], S = a.seg->words;
+    const unsigned long long total = seg_first(a, a.n_points);
     if ((unsigned long long)blockIdx.x * W >= total) return;
     {
         const uint4 *s0 = reinterpret_cast<const uint4 *>(a.phi_hi);
@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
         if (P.K != K || P.proposal != PROP || in_seg == 0u || first >= limit) continue;
         hist.enter(a, p, lane);
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long w_first = (gs - a.seg->off[p]) * S;
+        const unsigned long long S = seg_words(a, p), w_first = (gs - seg_first(a, p)) * S;
         unsigned long long rank = first;
         GridSums sums;
         unsigned int n_max4 = 0;

@@ -10,9 +10,9 @@ namespace tkdv {
 // accepted-count mode), and the size of its FP64 re-decision list.
 constexpr unsigned long long kScratchMaxProposals = 1ull << 26;
 constexpr unsigned long long kScratchDeferCap = 1ull << 20;
-// accept bitmap 8 MiB + re-decision list 8 MiB + 2 MiB for the counters,
+// accept bitmap 8 MiB + re-decision list 8 MiB + 3 MiB for the counters,
 // segment arrays and point records
-constexpr size_t kScratchBytes = (kScratchMaxProposals / 32) * 4 + kScratchDeferCap * 8 + (2u << 20);
+constexpr size_t kScratchBytes = (kScratchMaxProposals / 32) * 4 + kScratchDeferCap * 8 + (3u << 20);
 
 // Looks up the scratch array's address on `device` (made current for the
 // call) once and keeps it; later calls return at once.
