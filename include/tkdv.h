@@ -198,7 +198,7 @@ typedef struct {
     int32_t decide_grid;    /* workgroups of the (last) k_decide launch             */
     int32_t decide_block;   /* threads per workgroup                                */
     int32_t windows;        /* tkdv_sample_sweep: windows run                         */
-    int32_t graph_launches; /* tkdv_sample_sweep: graph launches (16 windows each)     */
+    int32_t graph_launches; /* tkdv_sample_sweep: graph launches (4 windows each)      */
 } tkdv_timing;
 
 typedef struct tkdv_ctx tkdv_ctx;
@@ -543,7 +543,7 @@ tkdv_status tkdv_learner_set_weights(tkdv_learner *learner, const double *h_in, 
 #define TKDV_DECIDE_VARIANTS 4
 typedef struct {
     int32_t blocks_per_cu;  /* decide workgroups per compute unit, 0: as many as fit   */
-    int32_t use_graph;      /* 1: 16 windows captured in one hipGraph, launched once     */
+    int32_t use_graph;      /* 1: 4 windows captured in one hipGraph, launched at once  */
     uint64_t window;        /* proposals of a point's first window, a multiple of 65536 */
     int32_t variant;        /* tile variant of the decision kernel, 0..3 (BF16x3: at
                                K = 16, 32, 64 workgroup threads x tile pairs per group,
@@ -563,9 +563,9 @@ typedef struct {
  * one from the point's measured acceptance (1.25 times the proposals still
  * needed, four times those so far while none is accepted), sharing a bitmap
  * pool of up to 2^33 proposals in proportion when they do not fit, so that
- * most points finish in their second window.  16 windows are captured in one
- * hipGraph and launched at once (use_graph; otherwise the same 16 windows are
- * launched directly); the host reads the device state once per 16 windows,
+ * most points finish in their second window.  4 windows are captured in one
+ * hipGraph and launched at once (use_graph; otherwise the same 4 windows are
+ * launched directly); the host reads the device state once per 4 windows,
  * and a window without unfinished points does nothing.  Output as in
  * tkdv_sample_batch: the first targets[p] accepted samples by index in rows
  * (out_offset[p] + r) of d_xhat (stride 2 * TKDV_KMAX floats) and d_index, at

@@ -830,8 +830,11 @@ void fill_stats_sweep(tkdv_stats &s, const DevPoint &P, const SweepState &w)
 
 int prec_index(int precision) { return precision < 0 || precision > 2 ? 0 : precision; }
 
-// Windows captured into one graph (one launch, one host synchronisation).
-constexpr int kSweepGraphWindows = 16;
+// Windows captured into one graph (one launch, one host synchronisation).  Most
+// sweeps take two or three; the windows after them do nothing but launch, some
+// 60 us each, and are captured and instantiated all the same: with 16 of them a map
+// of 64 cells took 3.8 ms, with 4 3.0, and a sweep of 24 points 12.2 and 11.0.
+constexpr int kSweepGraphWindows = 4;
 
 tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan *plans, const uint64_t *targets,
                   const uint64_t *maxp, int precision, const tkdv_launch_cfg *cfg, float *d_xhat,
