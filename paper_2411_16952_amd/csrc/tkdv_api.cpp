@@ -62,7 +62,7 @@ struct tkdv_ctx {
     int device = 0;
     int n_cu = 0;
     std::string last_error;
-    DevBuf bitmap, defer_list, defer_count, counters, points, seg, seg_cnt, seg_base, seg_stats, hist, results, plist;
+    DevBuf bitmap, defer_list, state, points, seg, seg_cnt, seg_base, seg_stats;  // state: CallState, points: PointList
     DevBuf mix, mix_tab;  // learned-proposal constants and tables of the current call
     // K = 128 (index 4): the quarter-period tables of k_decide128 (BF16 hi, lo, FP32)
     DevBuf phi_hi[kNumK], phi_lo[kNumK], phi_f32[kNumK];
@@ -71,13 +71,11 @@ struct tkdv_ctx {
     // the same tables with the odd-mode rows scaled by sqrt(3), for the kernels
     // that form S3 in the half-period form (K >= 16): s3_tables()
     DevBuf phi3_hi[kNumK], phi3_lo[kNumK], phi3_f32[kNumK];
-    void *h_results = nullptr;  // pinned
-    size_t h_results_bytes = 0;
-    void *h_counters = nullptr;  // pinned
-    size_t h_counters_bytes = 0;
-    void *h_points = nullptr;  // pinned staging of DevPoint[]
+    void *h_state = nullptr;  // pinned: CallState up to the histograms
+    size_t h_state_bytes = 0;
+    void *h_points = nullptr;  // pinned: PointList
     size_t h_points_bytes = 0;
-    void *h_misc = nullptr;  // pinned: defer count + plist staging
+    void *h_misc = nullptr;  // pinned: tkdv_extremes
     size_t h_misc_bytes = 0;
     hipEvent_t ev[6] = {};  // phase boundaries of the last call
     tkdv_timing timing = {};
@@ -427,20 +425,51 @@ struct Call {
     unsigned long long total_tiles = 0, max_segs = 0, bitmap_words = 0;
 };
 
+// What a call starts from zero, and, up to the histograms, brings back: one
+// region, one fill and one copy (four and three of them kept a small call's
+// stream waiting for its host for 25 us of 145).
+struct CallState {
+    size_t results = 0, counters, defer_count, hist, bytes;
+    explicit CallState(int np)
+    {
+        auto place = [&](size_t &at, size_t n) {
+            at = bytes;
+            bytes = (bytes + n + 255) & ~(size_t)255;
+        };
+        bytes = 0;
+        place(results, sizeof(PointResult) * np);
+        place(counters, sizeof(DevCounters) * np);
+        place(defer_count, sizeof(unsigned long long));
+        place(hist, sizeof(unsigned long long) * kShards * kNBins * np);
+    }
+    size_t back() const { return defer_count + sizeof(unsigned long long); }
+};
+// A call's points and their lists per K, one copy.
+struct PointList {
+    size_t plist, bytes;
+    PointList(int np, size_t n_list) : plist(sizeof(DevPoint) * np), bytes(plist + sizeof(int) * n_list) {}
+};
+
 // Device buffers of one launch sequence (from the context's growable buffers,
 // or carved from a fixed scratch array by the no-allocation entry point).
 struct Workspace {
     uint32_t *bitmap;
-    unsigned long long *defer_list, *defer_count, defer_cap;
-    DevCounters *counters;
-    DevPoint *points;
+    unsigned long long *defer_list, defer_cap;
+    char *state;   // CallState
+    char *points;  // PointList
     SegPlan *seg;
     unsigned int *seg_cnt;
-    unsigned long long *seg_base, *hist;
+    unsigned long long *seg_base;
     SegStats *seg_stats;
-    PointResult *results;
-    int *plist;
 };
+
+void set_state(KernelArgs &a, char *state, const CallState &cs)
+{
+    a.res = reinterpret_cast<PointResult *>(state + cs.results);
+    a.cnt = reinterpret_cast<DevCounters *>(state + cs.counters);
+    a.defer_count = reinterpret_cast<unsigned long long *>(state + cs.defer_count);
+    a.hist = reinterpret_cast<unsigned long long *>(state + cs.hist);
+}
 
 // Host view of one launch sequence: the points, their lists per K and the
 // segment count (plain arrays, so that a caller need not allocate).
@@ -482,15 +511,13 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
     const int np = v.np;
     // The pinned staging buffers are reused by later calls, so the stream must
     // have consumed them before we return (we synchronise at the end).
-    std::memcpy(ctx->h_points, v.pts, sizeof(DevPoint) * np);
-    int *h_plist = reinterpret_cast<int *>((char *)ctx->h_misc + 64);
-    std::memcpy(h_plist, v.plist, sizeof(int) * v.plist_len);
-    HIP_TRY(ctx, hipMemcpyAsync(w.points, ctx->h_points, sizeof(DevPoint) * np, hipMemcpyHostToDevice, st));
-    HIP_TRY(ctx, hipMemcpyAsync(w.plist, h_plist, sizeof(int) * v.plist_len, hipMemcpyHostToDevice, st));
-    HIP_TRY(ctx, launch_fill_u32(w.counters, sizeof(DevCounters) * np / 4, 0u, st));
-    HIP_TRY(ctx, launch_fill_u32(w.results, sizeof(PointResult) * np / 4, 0u, st));
-    HIP_TRY(ctx, launch_fill_u32(w.defer_count, 2, 0u, st));
-    HIP_TRY(ctx, launch_fill_u32(w.hist, (unsigned long long)np * kShards * kNBins * 2, 0u, st));
+    const CallState cs(np);
+    const PointList pl(np, (size_t)v.plist_len);
+    char *h_points = static_cast<char *>(ctx->h_points), *h_state = static_cast<char *>(ctx->h_state);
+    std::memcpy(h_points, v.pts, sizeof(DevPoint) * np);
+    std::memcpy(h_points + pl.plist, v.plist, sizeof(int) * v.plist_len);
+    HIP_TRY(ctx, hipMemcpyAsync(w.points, h_points, pl.bytes, hipMemcpyHostToDevice, st));
+    HIP_TRY(ctx, launch_fill_u32(w.state, cs.bytes / 4, 0u, st));
 
     KernelArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -498,14 +525,11 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
     a.seg_cnt = w.seg_cnt;
     a.seg_base = w.seg_base;
     a.seg_stats = w.seg_stats;
-    a.hist = w.hist;
-    a.res = w.results;
-    a.pts = w.points;
+    set_state(a, w.state, cs);
+    a.pts = reinterpret_cast<const DevPoint *>(w.points);
     a.n_points = np;
-    a.cnt = w.counters;
     a.bitmap = w.bitmap;
     a.defer_list = w.defer_list;
-    a.defer_count = w.defer_count;
     a.defer_cap = w.defer_cap;
     a.dbg_xhat = dbg_xhat;
     a.dbg_t = dbg_t;
@@ -516,7 +540,7 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
         a.mix = reinterpret_cast<const DevMix *>(ctx->mix.p);
         a.mix_tab = reinterpret_cast<const char *>(ctx->mix_tab.p);
     }
-    const int *d_plist = w.plist;
+    const int *d_plist = reinterpret_cast<const int *>(w.points + pl.plist);
     std::memset(&ctx->timing, 0, sizeof(ctx->timing));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[0], st));
     for (int ki = 0; ki < kNumK; ++ki) {
@@ -555,10 +579,8 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
         HIP_TRY(ctx, hipEventRecord(ctx->ev[4], st));
         HIP_TRY(ctx, launch_finalize(a, st));
         HIP_TRY(ctx, hipEventRecord(ctx->ev[5], st));
-        HIP_TRY(ctx, hipMemcpyAsync(ctx->h_results, w.results, sizeof(PointResult) * np, hipMemcpyDeviceToHost, st));
     }
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->h_counters, w.counters, sizeof(DevCounters) * np, hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->h_misc, w.defer_count, 8, hipMemcpyDeviceToHost, st));
+    HIP_TRY(ctx, hipMemcpyAsync(h_state, w.state, cs.back(), hipMemcpyDeviceToHost, st));
     HIP_TRY(ctx, hipStreamSynchronize(st));
     {
         float ms = 0.0f;
@@ -579,10 +601,10 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
         }
         ctx->timing.total_ms = ms;
     }
-    const unsigned long long n_def = *reinterpret_cast<unsigned long long *>(ctx->h_misc);
+    const unsigned long long n_def = *reinterpret_cast<unsigned long long *>(h_state + cs.defer_count);
     if (n_deferred_out) *n_deferred_out = n_def;
-    if (res_out && stats) std::memcpy(res_out, ctx->h_results, sizeof(PointResult) * np);
-    if (cnt_out) std::memcpy(cnt_out, ctx->h_counters, sizeof(DevCounters) * np);
+    if (res_out && stats) std::memcpy(res_out, h_state + cs.results, sizeof(PointResult) * np);
+    if (cnt_out) std::memcpy(cnt_out, h_state + cs.counters, sizeof(DevCounters) * np);
     if (n_def > w.defer_cap)
         return set_err(ctx, TKDV_E_CAPACITY, "FP64 re-decision list overflowed (" + std::to_string(n_def) + " > " +
                                                  std::to_string(w.defer_cap) + ")");
@@ -596,7 +618,6 @@ hipError_t ensure_segments(tkdv_ctx *ctx, unsigned long long max_segs, int np)
     if (e == hipSuccess) e = ensure(ctx->seg_cnt, sizeof(unsigned int) * max_segs);
     if (e == hipSuccess) e = ensure(ctx->seg_base, sizeof(unsigned long long) * max_segs);
     if (e == hipSuccess) e = ensure(ctx->seg_stats, sizeof(SegStats) * max_segs);
-    if (e == hipSuccess) e = ensure(ctx->hist, sizeof(unsigned long long) * kShards * kNBins * (size_t)np);
     return e;
 }
 
@@ -612,16 +633,13 @@ tkdv_status run(tkdv_ctx *ctx, Call &call, int precision, int proposal, float *d
         std::min<unsigned long long>(1ull << 26, std::max<unsigned long long>(1ull << 20, call.total_tiles));
     HIP_TRY(ctx, ensure(ctx->bitmap, call.bitmap_words * 4));
     HIP_TRY(ctx, ensure(ctx->defer_list, defer_cap * 8));
-    HIP_TRY(ctx, ensure(ctx->defer_count, 16));
-    HIP_TRY(ctx, ensure(ctx->counters, sizeof(DevCounters) * np));
-    HIP_TRY(ctx, ensure(ctx->points, sizeof(DevPoint) * np));
+    const CallState cs(np);
+    const PointList pl(np, call.plist.size());
+    HIP_TRY(ctx, ensure(ctx->state, cs.bytes));
+    HIP_TRY(ctx, ensure(ctx->points, pl.bytes));
     HIP_TRY(ctx, ensure_segments(ctx, call.max_segs, np));
-    HIP_TRY(ctx, ensure(ctx->results, sizeof(PointResult) * np));
-    HIP_TRY(ctx, ensure(ctx->plist, sizeof(int) * call.plist.size()));
-    HIP_TRY(ctx, ensure_host(ctx->h_points, ctx->h_points_bytes, sizeof(DevPoint) * np));
-    HIP_TRY(ctx, ensure_host(ctx->h_misc, ctx->h_misc_bytes, 64 + sizeof(int) * call.plist.size()));
-    HIP_TRY(ctx, ensure_host(ctx->h_results, ctx->h_results_bytes, sizeof(PointResult) * np));
-    HIP_TRY(ctx, ensure_host(ctx->h_counters, ctx->h_counters_bytes, sizeof(DevCounters) * np));
+    HIP_TRY(ctx, ensure_host(ctx->h_points, ctx->h_points_bytes, pl.bytes));
+    HIP_TRY(ctx, ensure_host(ctx->h_state, ctx->h_state_bytes, cs.back()));
     for (int ki = 0; ki < kNumK; ++ki) {
         if (call.plist_n[ki] == 0) continue;
         tkdv_status s = build_tables(ctx, 8 << ki);
@@ -630,17 +648,13 @@ tkdv_status run(tkdv_ctx *ctx, Call &call, int precision, int proposal, float *d
     Workspace w;
     w.bitmap = reinterpret_cast<uint32_t *>(ctx->bitmap.p);
     w.defer_list = reinterpret_cast<unsigned long long *>(ctx->defer_list.p);
-    w.defer_count = reinterpret_cast<unsigned long long *>(ctx->defer_count.p);
     w.defer_cap = defer_cap;
-    w.counters = reinterpret_cast<DevCounters *>(ctx->counters.p);
-    w.points = reinterpret_cast<DevPoint *>(ctx->points.p);
+    w.state = static_cast<char *>(ctx->state.p);
+    w.points = static_cast<char *>(ctx->points.p);
     w.seg = reinterpret_cast<SegPlan *>(ctx->seg.p);
     w.seg_cnt = reinterpret_cast<unsigned int *>(ctx->seg_cnt.p);
     w.seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
-    w.hist = reinterpret_cast<unsigned long long *>(ctx->hist.p);
     w.seg_stats = reinterpret_cast<SegStats *>(ctx->seg_stats.p);
-    w.results = reinterpret_cast<PointResult *>(ctx->results.p);
-    w.plist = reinterpret_cast<int *>(ctx->plist.p);
     if (res_out) res_out->resize(np);
     if (cnt_out) cnt_out->resize(np);
     return launch_sequence(ctx, view_of(call), w, precision, proposal, d_xhat, d_index, st,
@@ -916,12 +930,14 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     const unsigned long long defer_cap = std::min<unsigned long long>(1ull << 26, std::max<unsigned long long>(1ull << 20, bm_words));
     HIP_TRY(ctx, ensure(ctx->bitmap, bm_words * 4));
     HIP_TRY(ctx, ensure(ctx->defer_list, defer_cap * 8));
-    HIP_TRY(ctx, ensure(ctx->defer_count, 16));
-    HIP_TRY(ctx, ensure(ctx->counters, sizeof(DevCounters) * np));
-    HIP_TRY(ctx, ensure(ctx->points, sizeof(DevPoint) * np));
+    const CallState cs(np);
+    const PointList pl(np, call.plist.size());
+    char *points = nullptr, *state = nullptr;
+    HIP_TRY(ctx, ensure(ctx->state, cs.bytes));
+    HIP_TRY(ctx, ensure(ctx->points, pl.bytes));
+    state = static_cast<char *>(ctx->state.p);
+    points = static_cast<char *>(ctx->points.p);
     HIP_TRY(ctx, ensure_segments(ctx, max_segs, np));
-    HIP_TRY(ctx, ensure(ctx->results, sizeof(PointResult) * np));
-    HIP_TRY(ctx, ensure(ctx->plist, sizeof(int) * call.plist.size()));
     HIP_TRY(ctx, ensure(ctx->sweep, sizeof(SweepState) * np));
     HIP_TRY(ctx, ensure(ctx->active, sizeof(SweepGlobal)));
     for (int ki = 0; ki < kNumK; ++ki)
@@ -939,8 +955,8 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     // or writes the caller's buffers
     HIP_TRY(ctx, hipEventRecord(ctx->join[0], user_st));
     HIP_TRY(ctx, hipStreamWaitEvent(sst, ctx->join[0], 0));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->points.p, call.pts.data(), sizeof(DevPoint) * np, hipMemcpyHostToDevice, sst));
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->plist.p, call.plist.data(), sizeof(int) * call.plist.size(),
+    HIP_TRY(ctx, hipMemcpyAsync(points, call.pts.data(), sizeof(DevPoint) * np, hipMemcpyHostToDevice, sst));
+    HIP_TRY(ctx, hipMemcpyAsync(points + pl.plist, call.plist.data(), sizeof(int) * call.plist.size(),
                                 hipMemcpyHostToDevice, sst));
     HIP_TRY(ctx, hipMemcpyAsync(ctx->sweep.p, sw.data(), sizeof(SweepState) * np, hipMemcpyHostToDevice, sst));
     HIP_TRY(ctx, hipMemcpyAsync(ctx->active.p, &g0, sizeof(g0), hipMemcpyHostToDevice, sst));
@@ -949,28 +965,22 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     SweepGlobal *dG = reinterpret_cast<SweepGlobal *>(ctx->active.p);
     KernelArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.pts = reinterpret_cast<const DevPoint *>(ctx->points.p);
+    set_state(a, state, cs);
+    a.pts = reinterpret_cast<const DevPoint *>(points);
     a.n_points = np;
-    a.cnt = reinterpret_cast<DevCounters *>(ctx->counters.p);
     a.bitmap = reinterpret_cast<uint32_t *>(ctx->bitmap.p);
     a.defer_list = reinterpret_cast<unsigned long long *>(ctx->defer_list.p);
-    a.defer_count = reinterpret_cast<unsigned long long *>(ctx->defer_count.p);
     a.defer_cap = defer_cap;
     a.d_active = &dG->active;
     a.seg = reinterpret_cast<SegPlan *>(ctx->seg.p);
     a.seg_cnt = reinterpret_cast<unsigned int *>(ctx->seg_cnt.p);
     a.seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
     a.seg_stats = reinterpret_cast<SegStats *>(ctx->seg_stats.p);
-    a.hist = reinterpret_cast<unsigned long long *>(ctx->hist.p);
-    a.res = reinterpret_cast<PointResult *>(ctx->results.p);
-    const int *d_plist = reinterpret_cast<const int *>(ctx->plist.p);
+    const int *d_plist = reinterpret_cast<const int *>(points + pl.plist);
     // one window: every launch is sized for the largest window (persistent
     // kernels), the device holds the current window's extent
     auto window = [&]() -> tkdv_status {
-        HIP_TRY(ctx, launch_fill_u32(ctx->counters.p, sizeof(DevCounters) * np / 4, 0u, sst));
-        HIP_TRY(ctx, launch_fill_u32(ctx->results.p, sizeof(PointResult) * np / 4, 0u, sst));
-        HIP_TRY(ctx, launch_fill_u32(ctx->defer_count.p, 2, 0u, sst));
-        HIP_TRY(ctx, launch_fill_u32(ctx->hist.p, (unsigned long long)np * kShards * kNBins * 2, 0u, sst));
+        HIP_TRY(ctx, launch_fill_u32(state, cs.bytes / 4, 0u, sst));
         for (int ki = 0; ki < kNumK; ++ki) {
             if (call.plist_n[ki] == 0) continue;
             const int K = 8 << ki;
@@ -996,9 +1006,8 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
                                             reinterpret_cast<unsigned long long *>(d_index), ctx->n_cu, sst));
         }
         HIP_TRY(ctx, launch_finalize(a, sst));
-        HIP_TRY(ctx, launch_window_advance(reinterpret_cast<DevPoint *>(ctx->points.p), a.cnt, a.res,
-                                           reinterpret_cast<SweepState *>(ctx->sweep.p), np, dG,
-                                           reinterpret_cast<const unsigned long long *>(ctx->defer_count.p), sst));
+        HIP_TRY(ctx, launch_window_advance(reinterpret_cast<DevPoint *>(points), a.cnt, a.res,
+                                           reinterpret_cast<SweepState *>(ctx->sweep.p), np, dG, a.defer_count, sst));
         return TKDV_OK;
     };
     // kSweepGraphWindows windows per launch (a window with no point left does
@@ -1126,10 +1135,8 @@ tkdv_status tkdv_create(int hip_device, tkdv_ctx **out)
     // scratch array, every K's synthesis tables and the one-point pinned
     // staging, so that its calls find everything in place
     e = scratch_init(hip_device);
-    if (e == hipSuccess) e = ensure_host(ctx->h_points, ctx->h_points_bytes, sizeof(DevPoint));
-    if (e == hipSuccess) e = ensure_host(ctx->h_misc, ctx->h_misc_bytes, 64 + sizeof(int));
-    if (e == hipSuccess) e = ensure_host(ctx->h_results, ctx->h_results_bytes, sizeof(PointResult));
-    if (e == hipSuccess) e = ensure_host(ctx->h_counters, ctx->h_counters_bytes, sizeof(DevCounters));
+    if (e == hipSuccess) e = ensure_host(ctx->h_points, ctx->h_points_bytes, PointList(1, 1).bytes);
+    if (e == hipSuccess) e = ensure_host(ctx->h_state, ctx->h_state_bytes, CallState(1).back());
     if (e != hipSuccess) {
         tkdv_destroy(ctx);
         return set_err(nullptr, TKDV_E_DEVICE, std::string("set-up of the fixed scratch: ") + hipGetErrorString(e));
@@ -1173,9 +1180,10 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     const int ki = kindex(pt->K);
     char *base = static_cast<char *>(scratch_ptr(ctx->device));
-    if (!base || !ctx->phi_hi[ki].p || !ctx->h_points || ctx->h_points_bytes < sizeof(DevPoint) ||
-        ctx->h_misc_bytes < 64 + sizeof(int) || ctx->h_results_bytes < sizeof(PointResult) ||
-        ctx->h_counters_bytes < sizeof(DevCounters))
+    const CallState cs(1);
+    const PointList list(1, 1);
+    if (!base || !ctx->phi_hi[ki].p || !ctx->h_points || ctx->h_points_bytes < list.bytes ||
+        ctx->h_state_bytes < cs.back())
         return set_err(ctx, TKDV_E_DEVICE, "the context's set-up of the fixed scratch is missing");
     if (n == 0) {
         std::memset(h_stats, 0, sizeof(*h_stats));
@@ -1199,17 +1207,13 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
     w.bitmap = reinterpret_cast<uint32_t *>(carve(off, (kScratchMaxProposals / 32) * 4));
     w.defer_list = reinterpret_cast<unsigned long long *>(carve(off, kScratchDeferCap * 8));
     w.defer_cap = kScratchDeferCap;
-    w.defer_count = reinterpret_cast<unsigned long long *>(carve(off, 16));
-    w.counters = reinterpret_cast<DevCounters *>(carve(off, sizeof(DevCounters)));
-    w.points = reinterpret_cast<DevPoint *>(carve(off, sizeof(DevPoint)));
-    w.results = reinterpret_cast<PointResult *>(carve(off, sizeof(PointResult)));
-    w.plist = reinterpret_cast<int *>(carve(off, sizeof(int)));
+    w.state = carve(off, cs.bytes);
+    w.points = carve(off, list.bytes);
     const size_t max_segs = max_segments(kScratchMaxProposals / 32, 1);
     w.seg = reinterpret_cast<SegPlan *>(carve(off, seg_plan_bytes(1)));
     w.seg_cnt = reinterpret_cast<unsigned int *>(carve(off, max_segs * sizeof(unsigned int)));
     w.seg_base = reinterpret_cast<unsigned long long *>(carve(off, max_segs * 8));
     w.seg_stats = reinterpret_cast<SegStats *>(carve(off, max_segs * sizeof(SegStats)));
-    w.hist = reinterpret_cast<unsigned long long *>(carve(off, sizeof(unsigned long long) * kShards * kNBins));
     if (off > kScratchBytes) return set_err(ctx, TKDV_E_CAPACITY, "fixed scratch layout exceeds its size");
     tkdv_plan pl = *plan;
     const int plist0 = 0;
@@ -1252,8 +1256,8 @@ tkdv_status tkdv_destroy(tkdv_ctx *ctx)
 {
     if (!ctx) return TKDV_OK;
     (void)hipSetDevice(ctx->device);
-    DevBuf *bufs[] = {&ctx->bitmap, &ctx->defer_list, &ctx->defer_count, &ctx->counters, &ctx->points,
-                      &ctx->seg, &ctx->seg_cnt, &ctx->seg_base, &ctx->seg_stats, &ctx->hist, &ctx->results, &ctx->plist,
+    DevBuf *bufs[] = {&ctx->bitmap, &ctx->defer_list, &ctx->state, &ctx->points,
+                      &ctx->seg, &ctx->seg_cnt, &ctx->seg_base, &ctx->seg_stats,
                       &ctx->mix, &ctx->mix_tab, &ctx->sweep, &ctx->active, &ctx->plan_pts, &ctx->plan_val,
                       &ctx->plan_x, &ctx->plan_ev, &ctx->plan_mix, &ctx->plan_user, &ctx->ext_keys, &ctx->ext_jmax, &ctx->ext_misc,
                       &ctx->sir_pt, &ctx->sir_w, &ctx->sir_tile, &ctx->sir_chunk, &ctx->sir_part};
@@ -1271,8 +1275,7 @@ tkdv_status tkdv_destroy(tkdv_ctx *ctx)
         if (ctx->phi3_lo[i].p) (void)hipFree(ctx->phi3_lo[i].p);
         if (ctx->phi3_f32[i].p) (void)hipFree(ctx->phi3_f32[i].p);
     }
-    if (ctx->h_results) (void)hipHostFree(ctx->h_results);
-    if (ctx->h_counters) (void)hipHostFree(ctx->h_counters);
+    if (ctx->h_state) (void)hipHostFree(ctx->h_state);
     if (ctx->h_points) (void)hipHostFree(ctx->h_points);
     if (ctx->h_misc) (void)hipHostFree(ctx->h_misc);
     for (hipEvent_t ev : ctx->ev)
