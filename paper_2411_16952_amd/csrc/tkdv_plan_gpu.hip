@@ -90,7 +90,13 @@ __device__ double mix_log_q(const PlanMix &M, int K, int lane, double x0, double
 
 // phi at the unit vector x (lane l holds coordinates l + 64 c, c < C) and its
 // tangent gradient g.  Sums over a lane's coordinates run in the order c = 0,
-// 1, ..., so C = 4 gives K <= 64 the bits of C = 2 (the extra terms are zeros).
+// 1, ..., so C = 2 and 4 give K <= 32 the bits of C = 1, and C = 4 gives K <= 64
+// those of C = 2 (the extra terms are zeros).  Bound by LDS: each term gathers a
+// cosine, and with one wave per SIMD a load that is waited for shows in full.
+// Two grid rows and two coordinates go together, the amplitudes and the squares
+// come in pairs, and four terms' loads are issued ahead; the sums run term by
+// term as before.  64 points at K = 32, 16 starts each: 1.65 ms, now 1.05;
+// at K = 64 7.5 and 4.1, at K = 128 35 and 28.
 template <int C>
 __device__ double plan_eval(const PlanPoint &P, const PlanMix *mix, double *xs, double *us, const double *ct,
                             int lane, const double (&x)[C], double (&g)[C])
@@ -103,7 +109,7 @@ __device__ double plan_eval(const PlanPoint &P, const PlanMix *mix, double *xs, 
         const int m = lane + 64 * c;
         v[c] = m < n2;
         kk[c] = m % K + 1;
-        if (v[c]) xs[m] = x[c];
+        if (v[c]) xs[m < K ? 2 * m : 2 * (m - K) + 1] = x[c];  // (cos, sin) of each mode
     }
     wave_sync_lds();
     double tl = v[0] ? (double)kk[0] * kk[0] * x[0] * x[0] : 0.0;
@@ -111,40 +117,74 @@ __device__ double plan_eval(const PlanPoint &P, const PlanMix *mix, double *xs, 
     for (int c = 1; c < C; ++c) tl += v[c] ? (double)kk[c] * kk[c] * x[c] * x[c] : 0.0;
     const double t = wsum(tl);
     double s3 = 0.0;
+    const double2 *xp = reinterpret_cast<const double2 *>(xs);
 #pragma unroll
-    for (int r = 0; r < 2 * C; ++r) {  // grid points lane + 64 r (N <= 128 C)
-        const int j = lane + 64 * r;
-        if (j < N) {
-            double u = 0.0;
-            int ic = 0;
-            for (int k = 1; k <= K; ++k) {
-                ic += j;
-                if (ic >= N) ic -= N;
-                int is = ic - q;
+    for (int r0 = 0; r0 < 2 * C; r0 += 2) {  // grid points lane + 64 r (N <= 128 C), two rows r at a time
+        if (64 * r0 >= N) break;
+        double u[2] = {0.0, 0.0};
+        int jr[2], ic[2] = {0, 0};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = lane + 64 * (r0 + h);
+            jr[h] = j < N ? j : 0;
+        }
+#pragma unroll 4
+        for (int k = 1; k <= K; ++k) {
+            const double2 xk = xp[k - 1];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                ic[h] += jr[h];
+                if (ic[h] >= N) ic[h] -= N;
+                int is = ic[h] - q;
                 if (is < 0) is += N;
-                const double term = xs[k - 1] * ct[ic] + xs[K + k - 1] * ct[is];
-                u += (k & 1) ? -term : term;
+                const double term = xk.x * ct[ic[h]] + xk.y * ct[is];
+                u[h] += (k & 1) ? -term : term;
             }
-            us[j] = u * u;
-            s3 += u * u * u;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = lane + 64 * (r0 + h);
+            if (j < N) {
+                us[j] = u[h] * u[h];
+                s3 += u[h] * u[h] * u[h];
+            }
         }
     }
     const double S3 = wsum(s3);
     wave_sync_lds();
-    auto dh = [&](int m) {
-        const int k = m % K + 1;
-        const int off = m >= K ? q : 0;
-        double acc = 0.0;
-        int ic = 0;
-        for (int j = 0; j < N; ++j) {
-            int idx = ic - off;
-            if (idx < 0) idx += N;
-            acc += us[j] * ct[idx];
-            ic += k;
-            if (ic >= N) ic -= N;
+    double dhv[C];  // d S3/d x_m up to the factor, per coordinate
+    const double2 *up = reinterpret_cast<const double2 *>(us);
+    constexpr int CP = C < 2 ? 1 : 2;
+#pragma unroll
+    for (int c0 = 0; c0 < C; c0 += CP) {
+        double acc[CP];
+        int ic[CP];
+#pragma unroll
+        for (int h = 0; h < CP; ++h) {
+            acc[h] = 0.0;
+            ic[h] = 0;
         }
-        return (k & 1) ? -acc : acc;
-    };
+        if (64 * c0 < n2) {
+#pragma unroll 2
+            for (int j = 0; j < N; j += 2) {
+                const double2 uj = up[j / 2];
+#pragma unroll
+                for (int h = 0; h < CP; ++h) {
+                    const int off = lane + 64 * (c0 + h) >= K ? q : 0;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        int idx = ic[h] - off;
+                        if (idx < 0) idx += N;
+                        acc[h] += (e ? uj.y : uj.x) * ct[idx];
+                        ic[h] += kk[c0 + h];
+                        if (ic[h] >= N) ic[h] -= N;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < CP; ++h) dhv[c0 + h] = (kk[c0 + h] & 1) ? -acc[h] : acc[h];
+    }
     double val = P.dt0 * t + P.cH * (kPiP / (3.0 * N)) * P.amp3 * S3;
     double dt = P.dt0;
     if (P.sigma) {
@@ -154,10 +194,9 @@ __device__ double plan_eval(const PlanPoint &P, const PlanMix *mix, double *xs, 
     const double cg = P.cH * kPiP * P.amp3 / N;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        const double d = v[c] ? dh(lane + 64 * c) : 0.0;
-        g[c] = v[c] ? dt * 2.0 * kk[c] * kk[c] * x[c] + cg * d : 0.0;
+        g[c] = v[c] ? dt * 2.0 * kk[c] * kk[c] * x[c] + cg * dhv[c] : 0.0;
     }
-    if constexpr (C == 2) {
+    if constexpr (C <= 2) {
         if (mix) {  // phi = log f - log q_mix (K <= 32: coordinate `lane` only)
             double dq;
             val -= mix_log_q(*mix, K, lane, x[0], t, dq);
@@ -187,8 +226,8 @@ __device__ __forceinline__ double dotl(const double (&a)[C], const double (&b)[C
 template <int C>
 __global__ void __launch_bounds__(64 * kPlanWaves) k_plan_search(PlanArgs a)
 {
-    __shared__ double xs_all[kPlanWaves][64 * C];
-    __shared__ double us_all[kPlanWaves][128 * C];
+    __shared__ __attribute__((aligned(16))) double xs_all[kPlanWaves][64 * C];
+    __shared__ __attribute__((aligned(16))) double us_all[kPlanWaves][128 * C];
     __shared__ double ct_all[kPlanWaves][128 * C];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -349,7 +388,8 @@ hipError_t launch_plan_search(const PlanArgs &a, int max_K, hipStream_t st)
     if (a.n_items <= 0) return hipSuccess;
     if (max_K > kPlanStride / 2) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)((a.n_items + kPlanWaves - 1) / kPlanWaves);
-    if (max_K <= 64) hipLaunchKernelGGL(k_plan_search<2>, dim3(grid), dim3(64 * kPlanWaves), 0, st, a);
+    if (max_K <= 32) hipLaunchKernelGGL(k_plan_search<1>, dim3(grid), dim3(64 * kPlanWaves), 0, st, a);
+    else if (max_K <= 64) hipLaunchKernelGGL(k_plan_search<2>, dim3(grid), dim3(64 * kPlanWaves), 0, st, a);
     else hipLaunchKernelGGL(k_plan_search<4>, dim3(grid), dim3(64 * kPlanWaves), 0, st, a);
     return hipGetLastError();
 }
