@@ -1629,11 +1629,11 @@ tkdv_status tkdv_sir(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_proposal proposal
     d.n = n;
     d.n_tiles = (n + kTile - 1) / kTile;
     const unsigned long long n_tiles = d.n_tiles, n_chunks = (n_tiles + kSirChunk - 1) / kSirChunk;
-    const int waves = sir_waves(K, ctx->n_cu);
+    const int grid = sir_grid(K, ctx->n_cu, n_tiles), waves = grid * (sir_block(K) / kWave);
     HIP_TRY(ctx, ensure(ctx->sir_pt, sizeof(DevPoint)));
     if (!d_weight) HIP_TRY(ctx, ensure(ctx->sir_w, n * sizeof(float)));
     HIP_TRY(ctx, ensure(ctx->sir_tile, 2 * n_tiles * sizeof(double)));
-    HIP_TRY(ctx, ensure(ctx->sir_chunk, (2 * n_chunks + 1) * sizeof(double)));
+    HIP_TRY(ctx, ensure(ctx->sir_chunk, (2 * n_chunks + 1 + kSirPart) * sizeof(double)));
     HIP_TRY(ctx, ensure(ctx->sir_part, (size_t)waves * kSirPart * sizeof(double)));
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(ctx, hipMemcpyAsync(ctx->sir_pt.p, &d, sizeof(d), hipMemcpyHostToDevice, st));
@@ -1648,7 +1648,9 @@ tkdv_status tkdv_sir(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_proposal proposal
     a.tile_off = a.tile_sum + n_tiles;
     a.chunk_sum = (double *)ctx->sir_chunk.p;
     a.chunk_off = a.chunk_sum + n_chunks;
+    a.sums = a.chunk_off + n_chunks + 1;
     a.n_chunks = n_chunks;
+    a.waves = waves;
     a.wave_part = (double *)ctx->sir_part.p;
     a.m = m;
     a.u0 = u0;
@@ -1658,36 +1660,22 @@ tkdv_status tkdv_sir(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_proposal proposal
     HIP_TRY(ctx, launch_sir_weights(K, precision, proposal, a, ctx->n_cu, st));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[1], st));
     HIP_TRY(ctx, launch_sir_scan(a, st));
-    double W = 0.0;
-    std::vector<double> part((size_t)waves * kSirPart);
-    HIP_TRY(ctx, hipMemcpyAsync(&W, a.chunk_off + n_chunks, sizeof(double), hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipMemcpyAsync(part.data(), a.wave_part, part.size() * sizeof(double), hipMemcpyDeviceToHost, st));
-    HIP_TRY(ctx, hipStreamSynchronize(st));
-    if (m > 0) {
-        if (!(W > 0.0)) return set_err(ctx, TKDV_E_UNSUPPORTED, "all weights are zero: nothing to resample");
-        a.W = W;
-        a.scale = (double)m / W;
-        HIP_TRY(ctx, launch_sir_resample(K, proposal, a, ctx->n_cu, st));
-    }
+    if (m > 0) HIP_TRY(ctx, launch_sir_resample(K, proposal, a, ctx->n_cu, st));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[2], st));
+    double back[1 + kSirPart];  // W and the sums over the waves
+    HIP_TRY(ctx, hipMemcpyAsync(back, a.chunk_off + n_chunks, sizeof(back), hipMemcpyDeviceToHost, st));
     HIP_TRY(ctx, hipStreamSynchronize(st));
+    const double W = back[0];
+    if (m > 0 && !(W > 0.0)) return set_err(ctx, TKDV_E_UNSUPPORTED, "all weights are zero: nothing to resample");
     {
         float ms = 0.0f;
         ctx->timing = tkdv_timing{};
         if (hipEventElapsedTime(&ms, ctx->ev[0], ctx->ev[1]) == hipSuccess) ctx->timing.decide_ms = ms;
         if (hipEventElapsedTime(&ms, ctx->ev[0], ctx->ev[2]) == hipSuccess) ctx->timing.total_ms = ms;
-        ctx->timing.decide_grid = K == 128 ? ctx->n_cu : 4 * ctx->n_cu;
+        ctx->timing.decide_grid = grid;
         ctx->timing.decide_block = sir_block(K);
     }
-    // per-wave partials in wave order
-    double W2 = 0.0, mx = 0.0, M[4] = {0.0, 0.0, 0.0, 0.0}, over = 0.0;
-    for (int w = 0; w < waves; ++w) {
-        const double *o = &part[(size_t)w * kSirPart];
-        W2 += o[0];
-        mx = std::max(mx, o[1]);
-        for (int c = 0; c < 4; ++c) M[c] += o[2 + c];
-        over += o[6];
-    }
+    const double W2 = back[1], mx = back[2], *M = back + 3, over = back[7];
     std::memset(h_stats, 0, sizeof(*h_stats));
     h_stats->n = n;
     h_stats->m = m;

@@ -1120,6 +1120,13 @@ struct WaveHist {
 };
 static_assert(kNBins == kWave, "one bin per lane");
 
+__device__ __forceinline__ unsigned long long read_lane_u64(unsigned long long v, int l)
+{
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, l);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), l);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
 __device__ __forceinline__ double wave_sum_f64(double v)
 {
 #pragma unroll

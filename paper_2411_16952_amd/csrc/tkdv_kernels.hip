@@ -495,13 +495,6 @@ __device__ __forceinline__ double half_max_f64(double v)
     for (int o = 16; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
     return v;
 }
-__device__ __forceinline__ unsigned long long read_lane_u64(unsigned long long v, int l)
-{
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, l);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), l);
-    return ((unsigned long long)hi << 32) | lo;
-}
-
 template <int K>
 __global__ void __launch_bounds__(kBlock) k_fixup_mix(KernelArgs a, int plan)
 {

@@ -31,6 +31,10 @@ __device__ __forceinline__ double sum64(double v)
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
+__device__ __forceinline__ double lane_f64(double v, int lane)
+{
+    return __longlong_as_double((long long)read_lane_u64((unsigned long long)__double_as_longlong(v), lane));
+}
 __device__ __forceinline__ double max64(double v)
 {
 #pragma unroll
@@ -179,7 +183,7 @@ __device__ __forceinline__ void grid_power_sums(const float (&x)[K], const char 
 }
 
 template <int K, int PREC, int PROP>
-__global__ void __launch_bounds__(kBlock) k_sir_weights(SirArgs a)
+__global__ void __launch_bounds__(kBlock, K <= 32 ? 4 : 1) k_sir_weights(SirArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int tab = sir_tab_bytes<K, PREC>();
@@ -200,34 +204,49 @@ __global__ void __launch_bounds__(kBlock) k_sir_weights(SirArgs a)
     const unsigned long long gwave = (unsigned long long)blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
     const unsigned long long nwaves = (unsigned long long)gridDim.x * (kBlock / kWave);
     double w2 = 0.0, mx = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0, m4 = 0.0, over = 0.0;
-    for (unsigned long long tile = gwave; tile < a.n_tiles; tile += nwaves) {
-        const unsigned long long local = tile * kTile + pl;
-        const bool valid = local < a.n;
-        const uint64_t i = P.i0 + local;
-        float x[K], r2, tk;
-        gen_x_part<K, PROP, true>(P, i, half, x, r2, tk);
-        const float inv = __builtin_amdgcn_rsqf(sum32(r2)), t = sum32(tk) * (inv * inv);
-        float s1, s2, s3, s4;
+    const PairCarry<6> carry{reinterpret_cast<float *>(lds + (PREC == PREC_BF16X3 ? 2 : 1) * tab) +
+                             (threadIdx.x >> 6) * (PairCarry<6>::BYTES / 4)};
+    int c = 0;
+#pragma unroll 1
+    for (unsigned long long tile = gwave; c == 1 || tile < a.n_tiles; tile += nwaves) {
+        float x[K], r2, tk, s1, s2, s3, s4;
+        gen_x_part<K, PROP, true>(P, P.i0 + tile * kTile + pl, half, x, r2, tk);
+        carry.put(0, c, lane, r2);
+        carry.put(1, c, lane, tk);
         grid_power_sums<K, PREC>(x, lds, lds + tab, lane, s1, s2, s3, s4);
-        const float i2 = inv * inv;
-        s1 = (s1 + xor32(s1)) * inv;
-        s2 = (s2 + xor32(s2)) * i2;
-        s3 = (s3 + xor32(s3)) * (i2 * inv);
-        s4 = (s4 + xor32(s4)) * (i2 * i2);
+        carry.put(2, c, lane, s1);
+        carry.put(3, c, lane, s2);
+        carry.put(4, c, lane, s3);
+        carry.put(5, c, lane, s4);
+        c ^= 1;
+        if (c == 1) continue;
+        // settle this tile and the one before it at once, a proposal per lane (k_decide;
+        // the tile after the last one of an odd number is drawn and dropped)
+        wave_lds_sync();
+        const float inv = __builtin_amdgcn_rsqf(carry.sum(0, half, pl)), i2 = inv * inv;
+        const float t = carry.sum(1, half, pl) * (inv * inv);
+        s1 = carry.sum(2, half, pl) * inv;
+        s2 = carry.sum(3, half, pl) * i2;
+        s3 = carry.sum(4, half, pl) * (i2 * inv);
+        s4 = carry.sum(5, half, pl) * (i2 * i2);
+        wave_lds_sync();
+        const unsigned long long at = half ? tile : tile - nwaves, local = at * kTile + pl;
+        const bool valid = local < a.n;
         const float la = log_a_f32<PROP>(P, t, s3);
         const float w = __builtin_amdgcn_exp2f(la * 1.4426950408889634f);
-        const bool mine = valid && half == 0;
-        if (mine) a.w[local] = w;
-        const double wd = mine ? (double)w : 0.0;
-        const double ts = sum64(wd);
-        if (lane == 0) a.tile_sum[tile] = ts;
+        if (valid) a.w[local] = w;
+        const double wd = valid ? (double)w : 0.0;
+        double ts = wd;  // over the tile's 32 proposals
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) ts += __shfl_xor(ts, o, 64);
+        if (pl == 0 && at < a.n_tiles) a.tile_sum[at] = ts;
         w2 += wd * wd;
         mx = fmax(mx, wd);
         m1 += wd * (double)s1;
         m2 += wd * (double)s2;
         m3 += wd * (double)s3;
         m4 += wd * (double)s4;
-        over += (mine && la > P.tau) ? 1.0 : 0.0;  // above 1 beyond the fast path's error
+        over += (valid && la > P.tau) ? 1.0 : 0.0;  // above 1 beyond the fast path's error
     }
     w2 = sum64(w2);
     mx = max64(mx);
@@ -414,16 +433,51 @@ __global__ void __launch_bounds__(256) k_sir_scan_chunks(SirArgs a)
 }
 
 // Level 2: the chunk sums in one sequential pass (one FP64 add per kSirChunk
-// tiles); chunk_off[n_chunks] is the grand total.
-__global__ void __launch_bounds__(64) k_sir_scan_top(SirArgs a)
+// tiles; a thread that also fetched them took 103 us for 763, now the workgroup
+// brings them to LDS); chunk_off[n_chunks] is the grand total.  Beside it a second
+// workgroup adds up the waves' partials (the host took them one by one).
+constexpr int kSirTop = 1024;
+__global__ void __launch_bounds__(kSirTop) k_sir_scan_top(SirArgs a)
 {
-    if (threadIdx.x != 0) return;
-    double run = 0.0;
-    for (unsigned long long c = 0; c < a.n_chunks; ++c) {
-        a.chunk_off[c] = run;
-        run += a.chunk_sum[c];
+    __shared__ double s[kSirTop];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 1) {
+        // thread t: column t % kSirPart of every (kSirTop / kSirPart)-th row; then a fixed tree
+        const int col = tid % kSirPart;
+        const bool top = col == 1;  // max w
+        double v = 0.0;
+        for (int w = tid / kSirPart; w < a.waves; w += kSirTop / kSirPart) {
+            const double o = a.wave_part[(size_t)w * kSirPart + col];
+            v = top ? fmax(v, o) : v + o;
+        }
+        s[tid] = v;
+        __syncthreads();
+        for (int o = kSirTop / 2; o >= kSirPart; o >>= 1) {
+            if (tid < o) s[tid] = top ? fmax(s[tid], s[tid + o]) : s[tid] + s[tid + o];
+            __syncthreads();
+        }
+        if (tid < kSirPart) a.sums[tid] = s[tid];
+        return;
     }
-    a.chunk_off[a.n_chunks] = run;
+    double run = 0.0;  // thread 0's
+    for (unsigned long long c0 = 0; c0 < a.n_chunks; c0 += kSirTop) {
+        const unsigned long long c = c0 + tid;
+        s[tid] = c < a.n_chunks ? a.chunk_sum[c] : 0.0;
+        __syncthreads();
+        if (tid == 0) {
+            const int n = a.n_chunks - c0 < kSirTop ? (int)(a.n_chunks - c0) : kSirTop;
+#pragma unroll 8
+            for (int k = 0; k < n; ++k) {
+                const double v = s[k];
+                s[k] = run;
+                run += v;
+            }
+        }
+        __syncthreads();
+        if (c < a.n_chunks) a.chunk_off[c] = s[tid];
+        __syncthreads();
+    }
+    if (tid == 0) a.chunk_off[a.n_chunks] = run;
 }
 
 __global__ void __launch_bounds__(256) k_sir_scan_add(SirArgs a)
@@ -433,14 +487,18 @@ __global__ void __launch_bounds__(256) k_sir_scan_add(SirArgs a)
         a.tile_off[t] += a.chunk_off[t / kSirChunk];
 }
 
-__device__ __forceinline__ unsigned long long draw_of(double c, const SirArgs &a, unsigned long long lo,
+__device__ __forceinline__ unsigned long long draw_of(double c, double scale, const SirArgs &a, unsigned long long lo,
                                                       unsigned long long hi)
 {
-    const double v = ceil(c * a.scale - a.u0);
+    const double v = ceil(c * scale - a.u0);
     unsigned long long r = v <= 0.0 ? 0ull : (v >= (double)a.m ? a.m : (unsigned long long)v);
     return r < lo ? lo : (r > hi ? hi : r);
 }
 
+// A wave looks at G tiles at a time, a lane each, and then goes through those that
+// have draws: G is what there are tiles per wave, up to 64, so that a short range
+// of many draws still fills the chip.  1e5 draws of 1e8 proposals, a tile in
+// thirty: a tile at a time 720 us, now 210.
 // QROWS (K = 128): the rows of x^ from the quarter-period draw (gen_x128, the
 // sampler's rows), proposal 16 h + l % 16 of the tile in lanes l, h = 0, 1.
 template <int K, int PROP, bool QROWS>
@@ -450,12 +508,32 @@ __global__ void __launch_bounds__(kBlock) k_sir_resample(SirArgs a)
     const int lane = threadIdx.x & 63, half = lane >> 5, pl = lane & 31;
     const unsigned long long gwave = (unsigned long long)blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
     const unsigned long long nwaves = (unsigned long long)gridDim.x * (kBlock / kWave);
-    for (unsigned long long tile = gwave; tile < a.n_tiles; tile += nwaves) {
-        const double off = a.tile_off[tile];
-        const bool last_tile = tile + 1 == a.n_tiles;
-        const unsigned long long A0 = draw_of(off, a, 0ull, a.m);
-        const unsigned long long A1 = last_tile ? a.m : draw_of(a.tile_off[tile + 1], a, 0ull, a.m);
-        if (__builtin_amdgcn_readfirstlane((int)(A1 <= A0))) continue;  // no draw in this tile
+    const double W = a.chunk_off[a.n_chunks], scale = (double)a.m / W;
+    if (!(W > 0.0)) return;  // nothing to resample: the host says so
+    int G = 1;
+    while (G < kWave && (unsigned long long)(2 * G) * nwaves <= a.n_tiles) G *= 2;
+    unsigned long long hits = 0, t0 = gwave * G, mA0 = 0, mA1 = 0;  // tiles of the group with draws; this lane's draws
+    double moff = 0.0;
+    bool fresh = true;
+    for (;;) {
+        if (hits == 0) {  // the next group
+            if (!fresh) t0 += nwaves * G;
+            fresh = false;
+            if (t0 >= a.n_tiles) break;
+            const unsigned long long t = t0 + lane;
+            const bool mine = lane < G && t < a.n_tiles;
+            moff = mine ? a.tile_off[t] : 0.0;
+            const double next = mine && t + 1 < a.n_tiles ? a.tile_off[t + 1] : 0.0;
+            mA0 = mine ? draw_of(moff, scale, a, 0ull, a.m) : 0ull;
+            mA1 = !mine ? 0ull : (t + 1 == a.n_tiles ? a.m : draw_of(next, scale, a, 0ull, a.m));
+            hits = __ballot(mA1 > mA0);
+            continue;
+        }
+        const int b = __ffsll((long long)hits) - 1;
+        hits &= hits - 1;
+        const unsigned long long tile = t0 + b;
+        const double off = lane_f64(moff, b);
+        const unsigned long long A0 = read_lane_u64(mA0, b), A1 = read_lane_u64(mA1, b);
         const unsigned long long local = tile * kTile + pl;
         const bool valid = local < a.n;
         const double w = (half == 0 && valid) ? (double)a.w[local] : 0.0;
@@ -463,15 +541,15 @@ __global__ void __launch_bounds__(kBlock) k_sir_resample(SirArgs a)
         double run = 0.0, excl = 0.0, incl = 0.0;
 #pragma unroll
         for (int q = 0; q < kTile; ++q) {
-            const double v = __shfl(w, q, 64);
+            const double v = lane_f64(w, q);
             if (pl == q) excl = run;
             run += v;
             if (pl == q) incl = run;
         }
         const unsigned long long n_in = a.n - tile * kTile;  // valid proposals of the tile (>= 1)
         const int last = (int)(n_in < (unsigned long long)kTile ? n_in - 1 : kTile - 1);
-        unsigned long long r0 = pl == 0 ? A0 : draw_of(off + excl, a, A0, A1);
-        unsigned long long r1 = pl == last ? A1 : draw_of(off + incl, a, A0, A1);
+        unsigned long long r0 = pl == 0 ? A0 : draw_of(off + excl, scale, a, A0, A1);
+        unsigned long long r1 = pl == last ? A1 : draw_of(off + incl, scale, a, A0, A1);
         if (half != 0 || !valid || r1 < r0) r1 = r0;
         // the sin-block lanes take the draws of their proposal
         const unsigned long long q0 = __shfl(r0, pl, 64), q1 = __shfl(r1, pl, 64);
@@ -515,9 +593,16 @@ __global__ void __launch_bounds__(kBlock) k_sir_resample(SirArgs a)
 }  // namespace
 
 int sir_block(int K) { return K == 128 ? Quarter<128>::BLOCK : kBlock; }
-int sir_waves(int K, int n_cu)
+// K <= 64: four workgroups a CU, and up to kSirRounds times as many where each wave
+// then still has four tiles: waves of a SIMD advance at different speeds, and
+// workgroups that follow even them out (1e8 proposals at K = 32: 6.8 ms in one
+// round, 5.95 in four).  Two tiles settled at once take 0.2 ms off that.
+constexpr int kSirRounds = 4;
+int sir_grid(int K, int n_cu, unsigned long long n_tiles)
 {
-    return K == 128 ? n_cu * (Quarter<128>::BLOCK / kWave) : 4 * n_cu * (kBlock / kWave);
+    if (K == 128) return n_cu;  // the tables fill LDS
+    const unsigned long long want = n_tiles / (4 * (kBlock / kWave)), least = 4ull * n_cu;
+    return (int)(want < least ? least : (want < kSirRounds * least ? want : kSirRounds * least));
 }
 
 template <int PREC, int PROP>
@@ -528,8 +613,7 @@ hipError_t launch_sir_weights_q128(const SirArgs &a, int n_cu, hipStream_t st)
     auto kern = k_sir_weights_q<K, PREC, PROP>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    // one workgroup per CU (the tables fill LDS): sir_waves(128, n_cu) waves
-    hipLaunchKernelGGL(kern, dim3(n_cu), dim3(Quarter<K>::BLOCK), lds, st, a);
+    hipLaunchKernelGGL(kern, dim3(sir_grid(K, n_cu, a.n_tiles)), dim3(Quarter<K>::BLOCK), lds, st, a);
     return hipGetLastError();
 }
 
@@ -544,11 +628,11 @@ hipError_t launch_sir_weights(int K, int prec, int proposal, const SirArgs &a, i
                                           : launch_sir_weights_q128<PREC_BF16X3, PROP_UNIFORM>(a, n_cu, st);
         return hipErrorInvalidValue;
     }
-    const int grid = 4 * n_cu;  // sir_waves(K, n_cu) waves
+    const int grid = sir_grid(K, n_cu, a.n_tiles);
 #define TKDV_SIRW(KK, PR, PP)                                                                            \
     if (K == KK && prec == PR && proposal == PP) {                                                       \
         constexpr int tab = sir_tab_bytes<KK, PR>();                                                     \
-        constexpr int lds = PR == PREC_BF16X3 ? 2 * tab : tab;                                           \
+        constexpr int lds = (PR == PREC_BF16X3 ? 2 * tab : tab) + kBlock / kWave * PairCarry<6>::BYTES;  \
         auto kern = k_sir_weights<KK, PR, PP>;                                                           \
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
         if (e != hipSuccess) return e;                                                                   \
@@ -569,7 +653,7 @@ hipError_t launch_sir_scan(const SirArgs &a, hipStream_t st)
     hipLaunchKernelGGL(k_sir_scan_chunks, dim3((unsigned)a.n_chunks), dim3(256), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sir_scan_top, dim3(1), dim3(64), 0, st, a);
+    hipLaunchKernelGGL(k_sir_scan_top, dim3(2), dim3(kSirTop), 0, st, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     unsigned long long g = (a.n_tiles + 255) / 256;
