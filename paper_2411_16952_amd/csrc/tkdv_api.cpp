@@ -540,6 +540,9 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
         a.mix = reinterpret_cast<const DevMix *>(ctx->mix.p);
         a.mix_tab = reinterpret_cast<const char *>(ctx->mix_tab.p);
     }
+    a.dealt = 1;
+    for (int q = 0; q < np; ++q)
+        if (v.pts[q].static_tiles < v.pts[q].n_tiles) a.dealt = 0;
     const int *d_plist = reinterpret_cast<const int *>(w.points + pl.plist);
     std::memset(&ctx->timing, 0, sizeof(ctx->timing));
     HIP_TRY(ctx, hipEventRecord(ctx->ev[0], st));

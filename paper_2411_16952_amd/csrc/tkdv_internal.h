@@ -40,6 +40,18 @@ constexpr uint64_t kAlwaysTiles = 1ull << 16;
 // and larger ones claimed.  at_least: tiles wanted in any case (accepted-count
 // mode, where the rest of the range may not be needed).
 constexpr uint64_t kMaxStatic = 1ull << 20;
+// A launch whose tiles are all dealt out takes up to kDealtRounds rounds of
+// workgroups, of waves with kDealtTiles tiles each at least: the next workgroup
+// starts where one ends, which evens out the waves' different speeds (K = 32, 3e7
+// proposals: 1.59 -> 1.47 ms; K = 64: 3.40 -> 3.14; K = 8: 517 -> 479 us; 1e6 and
+// fewer are one round).  Larger ranges dealt out in 16 or 64 rounds are no faster
+// than claimed at K = 32 and slower at K = 64 and 128 (6e7 each: 41.0 -> 45.1 ms).
+constexpr int kDealtRounds = 4, kDealtTiles = 16;
+constexpr unsigned long long dealt_rounds(unsigned long long tiles, unsigned long long waves)
+{
+    const unsigned long long r = tiles / (waves * kDealtTiles);
+    return r < 1 ? 1 : (r > kDealtRounds ? kDealtRounds : r);
+}
 constexpr uint64_t static_share(uint64_t n, uint64_t at_least, int n_points)
 {
     const uint64_t cap = kMaxStatic / (uint64_t)n_points;
@@ -256,6 +268,7 @@ struct KernelArgs {
     const DevPoint *pts;
     int n_points;
     int blocks_per_cu;     // decide-kernel workgroups per compute unit (0: as many as fit)
+    int dealt;             // every tile of the launch is dealt out (static_share): rounds of workgroups
     DevCounters *cnt;
     uint32_t *bitmap;
     unsigned long long *defer_list;

@@ -1144,6 +1144,7 @@ static hipError_t launch_decide_t(const KernelArgs &a, const int *plist, int n_p
     // at least two tiles per wave (the shortest claim)
     unsigned long long want = (total_tiles + 2ull * (B / kWave) - 1) / (2ull * (B / kWave));
     unsigned long long grid = (unsigned long long)per_cu * n_cu;
+    if (a.dealt) grid *= dealt_rounds(total_tiles, grid * (B / kWave));
     if (want < grid) grid = want;
     if (grid < 1) grid = 1;
     if (grid_out) *grid_out = (int)grid;

@@ -515,6 +515,7 @@ hipError_t launch_decide128_t(const KernelArgs &a, const int *plist, int n_plist
     const unsigned long long per_block = 2ull * (B / kWave);  // at least two accept words per wave
     unsigned long long want = (total_tiles + per_block - 1) / per_block;
     unsigned long long grid = (unsigned long long)per_cu * n_cu;
+    if (a.dealt) grid *= dealt_rounds(total_tiles, grid * (B / kWave));
     if (want < grid) grid = want;
     if (grid < 1) grid = 1;
     if (grid_out) *grid_out = (int)grid;
