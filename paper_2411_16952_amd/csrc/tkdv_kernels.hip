@@ -1,17 +1,19 @@
 // gfx950 kernels of the TKdV rejection sampler.
 //
 // Pipeline of one sampling call (all on one stream, no host round trip):
-//   k_decide       persistent: per wave, tiles of 32 proposals claimed from a
-//                  per-point queue; Philox -> Box-Muller -> scale -> project
-//                  -> t, matrix-core synthesis -> sum u^3 -> log a -> decision.
+//   k_decide       per wave, tiles of 32 proposals dealt out evenly or claimed
+//                  from a per-point queue; Philox -> Box-Muller -> scale ->
+//                  project -> t, matrix-core synthesis -> sum u^3 -> log a ->
+//                  decision, two tiles at once.
 //                  Writes one accept-bit word per tile; proposals within the
 //                  decision window go to the FP64 list.
 //   k_fixup        FP64 re-decision of the listed proposals (H3 by the double
-//                  sum of Sec. IV.A), OR-ed into the accept bitmap.
-//   k_seg_count    accepted count per 65536-proposal segment.
+//                  sum of Sec. IV.A), OR-ed into the accept bitmap; lays out
+//                  the segments of the ordered output.
+//   k_seg_count    accepted count per segment.
 //   k_seg_scan     exclusive scan of the segment counts, per point.
-//   k_materialize  LDS-staged stream compaction of the accepted bits in
-//                  proposal order; regenerates each accepted x^ (same
+//   k_materialize  a wave per segment: the accepted bits in proposal order,
+//                  queued in LDS; regenerates each accepted x^ (same
 //                  arithmetic as k_decide), writes it at its rank, and
 //                  accumulates FP64 moments, 2-sigma exceedances and the u(0)
 //                  histogram from an FP32 matrix-core synthesis.
