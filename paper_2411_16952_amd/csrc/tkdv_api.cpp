@@ -62,7 +62,7 @@ struct tkdv_ctx {
     int device = 0;
     int n_cu = 0;
     std::string last_error;
-    DevBuf bitmap, defer_list, state, points, seg, seg_cnt, seg_base, seg_stats;  // state: CallState, points: PointList
+    DevBuf bitmap, defer_list, state, points, seg, seg_cnt, seg_base, runs, run_stats;  // state: CallState, points: PointList
     DevBuf mix, mix_tab;  // learned-proposal constants and tables of the current call
     // K = 128 (index 4): the quarter-period tables of k_decide128 (BF16 hi, lo, FP32)
     DevBuf phi_hi[kNumK], phi_lo[kNumK], phi_f32[kNumK];
@@ -422,7 +422,7 @@ struct Call {
     std::vector<DevPoint> pts;
     std::vector<int> plist_off, plist_n;  // per K index
     std::vector<int> plist;               // concatenated point lists
-    unsigned long long total_tiles = 0, max_segs = 0, bitmap_words = 0;
+    unsigned long long total_tiles = 0, max_segs = 0, max_runs = 0, bitmap_words = 0;
 };
 
 // What a call starts from zero, and, up to the histograms, brings back: one
@@ -457,10 +457,10 @@ struct Workspace {
     unsigned long long *defer_list, defer_cap;
     char *state;   // CallState
     char *points;  // PointList
-    SegPlan *seg;
+    Cuts *seg, *runs;
     unsigned int *seg_cnt;
     unsigned long long *seg_base;
-    SegStats *seg_stats;
+    RunStats *run_stats;
 };
 
 void set_state(KernelArgs &a, char *state, const CallState &cs)
@@ -479,7 +479,7 @@ struct CallView {
     const int *plist;
     int plist_len;
     int plist_off[kNumK], plist_n[kNumK];
-    unsigned long long max_segs;
+    unsigned long long max_segs, max_runs;
 };
 
 CallView view_of(const Call &call)
@@ -494,6 +494,7 @@ CallView view_of(const Call &call)
         v.plist_n[ki] = call.plist_n[ki];
     }
     v.max_segs = call.max_segs;
+    v.max_runs = call.max_runs;
     return v;
 }
 
@@ -524,7 +525,8 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
     a.seg = w.seg;
     a.seg_cnt = w.seg_cnt;
     a.seg_base = w.seg_base;
-    a.seg_stats = w.seg_stats;
+    a.runs = w.runs;
+    a.run_stats = w.run_stats;
     set_state(a, w.state, cs);
     a.pts = reinterpret_cast<const DevPoint *>(w.points);
     a.n_points = np;
@@ -577,7 +579,7 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
         for (int ki = 0; ki < kNumK; ++ki) {
             if (v.plist_n[ki] == 0) continue;
             a.phi_hi = ki >= 3 ? ctx->qstat[ki - 3].p : ctx->phi_f32[ki].p;
-            HIP_TRY(ctx, launch_materialize(8 << ki, proposal, a, v.max_segs, d_xhat, d_index, ctx->n_cu, st));
+            HIP_TRY(ctx, launch_materialize(8 << ki, proposal, a, v.max_runs, d_xhat, d_index, ctx->n_cu, st));
         }
         HIP_TRY(ctx, hipEventRecord(ctx->ev[4], st));
         HIP_TRY(ctx, launch_finalize(a, st));
@@ -614,13 +616,15 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
     return TKDV_OK;
 }
 
-// The ordered output's buffers for at most max_segs segments and np points.
-hipError_t ensure_segments(tkdv_ctx *ctx, unsigned long long max_segs, int np)
+// The ordered output's buffers for at most max_segs segments, max_runs runs of
+// ranks and np points.
+hipError_t ensure_output(tkdv_ctx *ctx, unsigned long long max_segs, unsigned long long max_runs, int np)
 {
-    hipError_t e = ensure(ctx->seg, seg_plan_bytes(np));
+    hipError_t e = ensure(ctx->seg, cuts_bytes(np));
+    if (e == hipSuccess) e = ensure(ctx->runs, cuts_bytes(np));
     if (e == hipSuccess) e = ensure(ctx->seg_cnt, sizeof(unsigned int) * max_segs);
     if (e == hipSuccess) e = ensure(ctx->seg_base, sizeof(unsigned long long) * max_segs);
-    if (e == hipSuccess) e = ensure(ctx->seg_stats, sizeof(SegStats) * max_segs);
+    if (e == hipSuccess) e = ensure(ctx->run_stats, sizeof(RunStats) * max_runs);
     return e;
 }
 
@@ -640,7 +644,7 @@ tkdv_status run(tkdv_ctx *ctx, Call &call, int precision, int proposal, float *d
     const PointList pl(np, call.plist.size());
     HIP_TRY(ctx, ensure(ctx->state, cs.bytes));
     HIP_TRY(ctx, ensure(ctx->points, pl.bytes));
-    HIP_TRY(ctx, ensure_segments(ctx, call.max_segs, np));
+    HIP_TRY(ctx, ensure_output(ctx, call.max_segs, call.max_runs, np));
     HIP_TRY(ctx, ensure_host(ctx->h_points, ctx->h_points_bytes, pl.bytes));
     HIP_TRY(ctx, ensure_host(ctx->h_state, ctx->h_state_bytes, cs.back()));
     for (int ki = 0; ki < kNumK; ++ki) {
@@ -654,10 +658,11 @@ tkdv_status run(tkdv_ctx *ctx, Call &call, int precision, int proposal, float *d
     w.defer_cap = defer_cap;
     w.state = static_cast<char *>(ctx->state.p);
     w.points = static_cast<char *>(ctx->points.p);
-    w.seg = reinterpret_cast<SegPlan *>(ctx->seg.p);
+    w.seg = reinterpret_cast<Cuts *>(ctx->seg.p);
+    w.runs = reinterpret_cast<Cuts *>(ctx->runs.p);
     w.seg_cnt = reinterpret_cast<unsigned int *>(ctx->seg_cnt.p);
     w.seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
-    w.seg_stats = reinterpret_cast<SegStats *>(ctx->seg_stats.p);
+    w.run_stats = reinterpret_cast<RunStats *>(ctx->run_stats.p);
     if (res_out) res_out->resize(np);
     if (cnt_out) cnt_out->resize(np);
     return launch_sequence(ctx, view_of(call), w, precision, proposal, d_xhat, d_index, st,
@@ -740,7 +745,7 @@ tkdv_status prepare(tkdv_ctx *ctx, Call &call, int n_points, const tkdv_point *p
     call.plist_n.assign(kNumK, 0);
     call.plist_off.assign(kNumK, 0);
     std::vector<std::vector<int>> by_k(kNumK);
-    unsigned long long bm = 0, tiles = 0;
+    unsigned long long bm = 0, tiles = 0, runs = 0;
     for (int p = 0; p < n_points; ++p) {
         tkdv_status s = check_point(ctx, pts[p]);
         if (s != TKDV_OK) return s;
@@ -772,6 +777,7 @@ tkdv_status prepare(tkdv_ctx *ctx, Call &call, int n_points, const tkdv_point *p
         d.capacity = capacity ? capacity[p] : 0;
         d.row_stride = row_stride;
         bm += d.n_tiles;
+        runs += max_runs(d.K, std::min(d.target, d.n));
         tiles += d.n_tiles;
         by_k[kindex(pts[p].K)].push_back(p);
     }
@@ -783,6 +789,7 @@ tkdv_status prepare(tkdv_ctx *ctx, Call &call, int n_points, const tkdv_point *p
     }
     call.bitmap_words = bm;
     call.max_segs = max_segments(bm, n_points);
+    call.max_runs = runs;
     call.total_tiles = tiles;
     return TKDV_OK;
 }
@@ -923,6 +930,8 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
                                                                               (1ull << 33) / kTile, sum_maxp / kTile));
     const unsigned long long bm_words = pool_words + (unsigned long long)np * 2048;
     const unsigned long long max_segs = max_segments(bm_words, np);
+    unsigned long long n_runs = 0;  // most of a window
+    for (int p = 0; p < np; ++p) n_runs += max_runs(pts[p].K, std::min(targets[p], maxp[p]));
     call.plist.clear();
     for (int ki = 0; ki < kNumK; ++ki) {
         call.plist_off[ki] = (int)call.plist.size();
@@ -940,7 +949,7 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     HIP_TRY(ctx, ensure(ctx->points, pl.bytes));
     state = static_cast<char *>(ctx->state.p);
     points = static_cast<char *>(ctx->points.p);
-    HIP_TRY(ctx, ensure_segments(ctx, max_segs, np));
+    HIP_TRY(ctx, ensure_output(ctx, max_segs, n_runs, np));
     HIP_TRY(ctx, ensure(ctx->sweep, sizeof(SweepState) * np));
     HIP_TRY(ctx, ensure(ctx->active, sizeof(SweepGlobal)));
     for (int ki = 0; ki < kNumK; ++ki)
@@ -975,10 +984,11 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     a.defer_list = reinterpret_cast<unsigned long long *>(ctx->defer_list.p);
     a.defer_cap = defer_cap;
     a.d_active = &dG->active;
-    a.seg = reinterpret_cast<SegPlan *>(ctx->seg.p);
+    a.seg = reinterpret_cast<Cuts *>(ctx->seg.p);
+    a.runs = reinterpret_cast<Cuts *>(ctx->runs.p);
     a.seg_cnt = reinterpret_cast<unsigned int *>(ctx->seg_cnt.p);
     a.seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
-    a.seg_stats = reinterpret_cast<SegStats *>(ctx->seg_stats.p);
+    a.run_stats = reinterpret_cast<RunStats *>(ctx->run_stats.p);
     const int *d_plist = reinterpret_cast<const int *>(points + pl.plist);
     // one window: every launch is sized for the largest window (persistent
     // kernels), the device holds the current window's extent
@@ -1005,7 +1015,7 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
         for (int ki = 0; ki < kNumK; ++ki) {
             if (call.plist_n[ki] == 0) continue;
             a.phi_hi = ki >= 3 ? ctx->qstat[ki - 3].p : ctx->phi_f32[ki].p;
-            HIP_TRY(ctx, launch_materialize(8 << ki, TKDV_PROP_SIGMA, a, max_segs, d_xhat,
+            HIP_TRY(ctx, launch_materialize(8 << ki, TKDV_PROP_SIGMA, a, n_runs, d_xhat,
                                             reinterpret_cast<unsigned long long *>(d_index), ctx->n_cu, sst));
         }
         HIP_TRY(ctx, launch_finalize(a, sst));
@@ -1213,10 +1223,11 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
     w.state = carve(off, cs.bytes);
     w.points = carve(off, list.bytes);
     const size_t max_segs = max_segments(kScratchMaxProposals / 32, 1);
-    w.seg = reinterpret_cast<SegPlan *>(carve(off, seg_plan_bytes(1)));
+    w.seg = reinterpret_cast<Cuts *>(carve(off, cuts_bytes(1)));
+    w.runs = reinterpret_cast<Cuts *>(carve(off, cuts_bytes(1)));
     w.seg_cnt = reinterpret_cast<unsigned int *>(carve(off, max_segs * sizeof(unsigned int)));
     w.seg_base = reinterpret_cast<unsigned long long *>(carve(off, max_segs * 8));
-    w.seg_stats = reinterpret_cast<SegStats *>(carve(off, max_segs * sizeof(SegStats)));
+    w.run_stats = reinterpret_cast<RunStats *>(carve(off, max_runs(pt->K, kScratchMaxProposals) * sizeof(RunStats)));
     if (off > kScratchBytes) return set_err(ctx, TKDV_E_CAPACITY, "fixed scratch layout exceeds its size");
     tkdv_plan pl = *plan;
     const int plist0 = 0;
@@ -1241,6 +1252,7 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
         for (int q = 0; q < kNumK; ++q) v.plist_off[q] = v.plist_n[q] = 0;
         v.plist_n[ki] = 1;
         v.max_segs = max_segments(n_tiles, 1);
+        v.max_runs = max_runs(pt->K, std::min(d.target, d.n));
         PointResult res;
         DevCounters cnt;
         s = launch_sequence(ctx, v, w, precision, proposal, d_xhat, reinterpret_cast<unsigned long long *>(d_index),
@@ -1260,7 +1272,7 @@ tkdv_status tkdv_destroy(tkdv_ctx *ctx)
     if (!ctx) return TKDV_OK;
     (void)hipSetDevice(ctx->device);
     DevBuf *bufs[] = {&ctx->bitmap, &ctx->defer_list, &ctx->state, &ctx->points,
-                      &ctx->seg, &ctx->seg_cnt, &ctx->seg_base, &ctx->seg_stats,
+                      &ctx->seg, &ctx->seg_cnt, &ctx->seg_base, &ctx->runs, &ctx->run_stats,
                       &ctx->mix, &ctx->mix_tab, &ctx->sweep, &ctx->active, &ctx->plan_pts, &ctx->plan_val,
                       &ctx->plan_x, &ctx->plan_ev, &ctx->plan_mix, &ctx->plan_user, &ctx->ext_keys, &ctx->ext_jmax, &ctx->ext_misc,
                       &ctx->sir_pt, &ctx->sir_w, &ctx->sir_tile, &ctx->sir_chunk, &ctx->sir_part};

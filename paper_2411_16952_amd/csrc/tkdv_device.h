@@ -862,17 +862,13 @@ __device__ __forceinline__ unsigned int wave_sum_u32(unsigned int v)
 }
 
 // What a wave has seen of a point since it last reported: violations of the
-// bound, the largest log a and, in long ranges, the accepted proposals.
-// Reported when the wave leaves the point.
+// bound and the largest log a.  Reported when the wave leaves the point.
 struct PointTally {
     unsigned int n_viol = 0;
-    unsigned int n_acc = 0;  // accepted, in proposal-count mode (wave-uniform)
     float max_la = -INFINITY;
     __device__ __forceinline__ void report(DevCounters *C, int lane)
     {
         CounterShard &S = C->shard[blockIdx.x % kShards];
-        if (n_acc) add_lane0(&S.accepted, n_acc, lane);
-        n_acc = 0;
         if (__ballot(n_viol != 0u) != 0ull) {
             unsigned int v = n_viol;
 #pragma unroll
@@ -892,21 +888,12 @@ struct PointTally {
     }
 };
 
-// The finished tiles and their definite accepts (lane c: the word of tile c):
-// at once in accepted-count mode, where claims depend on them; otherwise with
-// the wave's other tallies, for the size of the segments (kTallyTiles).
-constexpr unsigned long long kTallyTiles = 1ull << 16;
-__device__ __forceinline__ void count_accepted(const DevPoint &P, DevCounters *C, PointTally &tally, uint32_t word,
-                                               int len, int lane)
+// The finished tiles and their definite accepts (lane c: the word of tile c), on
+// which claims depend in accepted-count mode.
+__device__ __forceinline__ void count_accepted(const DevPoint &P, DevCounters *C, uint32_t word, int len, int lane)
 {
-    // a small range has the same segments whatever it accepted, and an atomic
-    // of every wave would show in its time
-    if (P.target == ~0ull && P.n_tiles < kTallyTiles) return;
+    if (P.target == ~0ull) return;
     const unsigned int v = __builtin_amdgcn_readfirstlane(wave_sum_u32(__popc(word)));
-    if (P.target == ~0ull) {
-        tally.n_acc += v;
-        return;
-    }
     CounterShard &S = C->shard[blockIdx.x % kShards];
     add_lane0(&S.accepted, v, lane);
     add_lane0(&S.finished, (unsigned long long)len, lane);
@@ -1017,59 +1004,36 @@ struct GridSums {
     }
 };
 
-// First segment of point p (p = n_points: their number), and words of its segments.
-__device__ __forceinline__ unsigned long long seg_first(const KernelArgs &a, int p)
+// First piece of point p (p = n_points: their number), and log2 of its pieces' length.
+__device__ __forceinline__ unsigned long long cut_first(const Cuts *c, int p)
 {
-    return a.seg->at[p] & ((1ull << kSegShiftBit) - 1);
+    return c->at[p] & ((1ull << kCutShiftBit) - 1);
 }
-__device__ __forceinline__ unsigned long long seg_words(const KernelArgs &a, int p)
+__device__ __forceinline__ int cut_shift(const Cuts *c, int p) { return (int)(c->at[p] >> kCutShiftBit); }
+
+// The point of piece i.
+__device__ __forceinline__ int point_of_cut(const Cuts *c, int n_points, unsigned long long i)
 {
-    return 1ull << (a.seg->at[p] >> kSegShiftBit);
+    int lo = 0, hi = n_points - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (cut_first(c, mid) <= i) lo = mid; else hi = mid - 1;
+    }
+    return lo;
 }
 
-// The segments of a call from the tiles decided (one workgroup of B threads).
-template <int B>
-__device__ void plan_segments(const KernelArgs &a)
+// Fills c from every point's number of pieces and their log2 length, piece(p, sh)
+// (one workgroup of B threads).
+template <int B, class Piece>
+__device__ void place_cuts(Cuts *c, int n_points, Piece piece)
 {
-    __shared__ unsigned long long buf[B], acc[B];
+    __shared__ unsigned long long buf[B];
     const int tid = threadIdx.x;
-    // accepted proposals that the output takes, as far as counted (count_accepted)
-    auto accepted_of = [&](int p) {
-        unsigned long long v = 0;
-        for (int s = 0; s < kShards; ++s) v += load_relaxed(&a.cnt[p].shard[s].accepted);
-        return v < a.pts[p].target ? v : a.pts[p].target;
-    };
-    unsigned long long sum = 0, accepted = 0;
-    for (int p = tid; p < a.n_points; p += B) {
-        sum += tiles_taken(a.pts[p], a.cnt[p].next_tile);
-        accepted += accepted_of(p);
-    }
-    buf[tid] = sum;
-    acc[tid] = accepted;
-    __syncthreads();
-    for (int o = B / 2; o > 0; o >>= 1) {
-        if (tid < o) {
-            buf[tid] += buf[tid + o];
-            acc[tid] += acc[tid + o];
-        }
-        __syncthreads();
-    }
-    const int sh_most = seg_shift_for(buf[0]);
-    // accepted per segment: halved by the rounding to a power of two, and no more than
-    // seg_extra segments for all that were accepted
-    unsigned long long per = 2 * acc[0] / seg_extra(buf[0]) + 1;
-    if (per < (unsigned long long)kSegAccepts) per = kSegAccepts;
     unsigned long long run = 0;
-    for (int p0 = 0; p0 < a.n_points; p0 += B) {
+    for (int p0 = 0; p0 < n_points; p0 += B) {
         const int p = p0 + tid;
-        unsigned long long v = 0;
-        int sh = sh_most;
-        if (p < a.n_points) {
-            const unsigned long long w = tiles_taken(a.pts[p], a.cnt[p].next_tile);
-            const double dense = (double)accepted_of(p) / (double)per;  // segments by what was accepted
-            while (sh > 3 && (double)(1 << sh) * dense > (double)w) --sh;
-            v = (w + (1ull << sh) - 1) >> sh;
-        }
+        int sh = 0;
+        const unsigned long long v = p < n_points ? piece(p, sh) : 0ull;
         __syncthreads();
         buf[tid] = v;
         __syncthreads();
@@ -1079,21 +1043,187 @@ __device__ void plan_segments(const KernelArgs &a)
             buf[tid] += add;
             __syncthreads();
         }
-        if (p < a.n_points) a.seg->at[p] = (run + buf[tid] - v) | ((unsigned long long)sh << kSegShiftBit);
+        if (p < n_points) c->at[p] = (run + buf[tid] - v) | ((unsigned long long)sh << kCutShiftBit);
         run += buf[B - 1];
     }
-    if (tid == 0) a.seg->at[a.n_points] = run;
+    if (tid == 0) c->at[n_points] = run;
 }
 
-__device__ __forceinline__ int point_of_segment(const KernelArgs &a, unsigned long long gs)
+// The segments of a call from the tiles decided (one workgroup of B threads).
+template <int B>
+__device__ void plan_segments(const KernelArgs &a)
 {
-    int lo = 0, hi = a.n_points - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (seg_first(a, mid) <= gs) lo = mid; else hi = mid - 1;
+    __shared__ unsigned long long words[B];
+    const int tid = threadIdx.x;
+    unsigned long long sum = 0;
+    for (int p = tid; p < a.n_points; p += B) sum += tiles_taken(a.pts[p], a.cnt[p].next_tile);
+    words[tid] = sum;
+    __syncthreads();
+    for (int o = B / 2; o > 0; o >>= 1) {
+        if (tid < o) words[tid] += words[tid + o];
+        __syncthreads();
     }
-    return lo;
+    const int shift = seg_shift_for(words[0]);
+    place_cuts<B>(a.seg, a.n_points, [&](int p, int &sh) {
+        sh = shift;
+        return (tiles_taken(a.pts[p], a.cnt[p].next_tile) + (1ull << shift) - 1) >> shift;
+    });
 }
+
+// Samples of point p that its output takes.
+__device__ __forceinline__ unsigned long long samples_of(const KernelArgs &a, int p)
+{
+    const unsigned long long n = a.res[p].n_accepted, t = a.pts[p].target;
+    return n < t ? n : t;
+}
+
+__device__ __forceinline__ unsigned long long read_lane_u64(unsigned long long v, int l)
+{
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, l);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), l);
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// Inclusive prefix sum over the wave's lanes (all of them active), in registers.
+__device__ __forceinline__ int wave_prefix_i32(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8: within 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // lane 15 of a row to the next: rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // lane 31 to rows 2 and 3
+    return v;
+}
+
+// The accepted proposals of ranks [first, end) of a point, in order, for one wave:
+// from the segment on that holds the first of them it reads the accept words GW at
+// a time (one per lane) and queues the offsets of their accepted proposals in LDS;
+// the part of a tile of TILE that a group leaves waits in registers.
+template <int GW, int TILE>
+struct RankReader {
+    static_assert(GW <= kWave && kWave % TILE == 0, "a word per lane, and a waiting proposal");
+    static constexpr int N = GW * 32;  // most offsets of a group
+    static constexpr int kAhead = GW / 4;  // groups loaded together (twice as many: no faster)
+    uint16_t *list;                    // N of LDS, this wave's
+    const uint32_t *words;
+    const unsigned long long *seg_base;
+    unsigned long long s0, n_segs;     // the point's segments, of 2^shift words
+    int shift;
+    unsigned long long n_words, at = 0;  // the point's accept words; the first of the group
+    unsigned long long rank, end;      // rank of the first proposal not done yet
+    unsigned long long held = 0;       // the proposal that waits at place lane % TILE
+    int n_held = 0, fresh = 0;         // how many wait; the group's that are wanted
+    int skip;                          // accepted ones still to pass before the first
+
+    __device__ __forceinline__ RankReader(const KernelArgs &a, int p, uint16_t *lds, unsigned long long first_,
+                                          unsigned long long end_, int lane)
+        : list(lds), rank(bcast_lane0(first_)), end(bcast_lane0(end_))
+    {
+        const DevPoint &P = a.pts[p];
+        words = a.bitmap + P.bm_off;
+        n_words = bcast_lane0(tiles_taken(P, a.cnt[p].next_tile));
+        seg_base = a.seg_base;
+        s0 = bcast_lane0(cut_first(a.seg, p));
+        n_segs = bcast_lane0(cut_first(a.seg, p + 1)) - s0;
+        shift = __builtin_amdgcn_readfirstlane(cut_shift(a.seg, p));
+        skip = (int)(rank - seek(rank, 0ull, lane));
+    }
+    // To the segment that holds rank r, the last that begins there or before, if that is
+    // ahead: it is looked for in 64 segments together, from `from` on; the rank it
+    // begins at.
+    __device__ __forceinline__ unsigned long long seek(unsigned long long r, unsigned long long from, int lane)
+    {
+        unsigned long long lo = from, n = n_segs - from, before = 0;
+        while (n > 1) {
+            const unsigned long long step = (n + kWave - 1) / kWave, i = step * lane;
+            const unsigned long long base = i < n ? seg_base[s0 + lo + i] : ~0ull;
+            const int c = __popcll(__ballot(base <= r)) - 1;  // the one at lo begins there or before
+            before = read_lane_u64(base, c);
+            lo += step * c;
+            n = n - step * c < step ? n - step * c : step;
+        }
+        at = at > lo << shift ? at : lo << shift;
+        return before;
+    }
+    // Past the segments from this one on that hold none before rank r.
+    __device__ __forceinline__ void skip_empty(unsigned long long r, int lane)
+    {
+        const unsigned long long cur = at >> shift, i = cur + lane;
+        const unsigned long long base = i < n_segs ? seg_base[s0 + i] : ~0ull;
+        const int c = __popcll(__ballot(base <= r)) - 1;
+        if (c == kWave - 1) seek(r, cur + c, lane);
+        else if (c > 0) at = (cur + c) << shift;
+    }
+    // Queues the next proposals: how many, a multiple of TILE or all that are left, or
+    // 0 when all are done.  Where few are accepted the loads are what a group takes,
+    // hence kAhead groups' together (4096 samples among 3e6 words at K = 32: 0.4 ms
+    // more, one at a time), and where hardly any the segments' counts lead past the
+    // words that hold none.
+    __device__ __forceinline__ int next(int lane)
+    {
+        while (rank < end && at < n_words) {
+            uint32_t ahead[kAhead], some = 0u;  // some: the groups that hold any
+#pragma unroll
+            for (int h = 0; h < kAhead; ++h) {
+                const unsigned long long w = at + h * GW + lane;
+                ahead[h] = lane < GW && w < n_words ? words[w] : 0u;
+            }
+#pragma unroll
+            for (int h = 0; h < kAhead; ++h) some |= __ballot(ahead[h] != 0u) != 0ull ? 1u << h : 0u;
+            const unsigned long long at0 = at;
+            const bool none = some == 0u;
+            for (; some; some &= some - 1) {
+                const int h0 = __ffs(some) - 1;
+                at = at0 + h0 * GW;
+                uint32_t word = ahead[0];
+#pragma unroll
+                for (int h = 1; h < kAhead; ++h) word = h0 == h ? ahead[h] : word;
+                const int cntw = __popc(word);
+                const int incl = wave_prefix_i32(cntw);
+                const int total = __builtin_amdgcn_readlane(incl, 63);
+                if (total <= skip) {
+                    skip -= total;
+                    continue;
+                }
+                int pos = incl - cntw - skip;
+                const unsigned long long want = end - rank - n_held;
+                const bool last = (unsigned long long)(total - skip) >= want;
+                fresh = last ? (int)want : total - skip;
+                skip = 0;
+                for (uint32_t m = word; m; m &= m - 1, ++pos)
+                    if (pos >= 0) list[pos] = (uint16_t)(lane * 32 + __ffs(m) - 1);
+                wave_lds_sync();
+                if (last) return n_held + fresh;
+                if (n_held + fresh >= TILE) return (n_held + fresh) & ~(TILE - 1);
+                keep(0, lane);
+            }
+            at = at0 + kAhead * GW;
+            if (none && at >> shift != at0 >> shift && at < n_words) skip_empty(rank + n_held, lane);
+        }
+        return 0;
+    }
+    // The e-th of them (e = lane modulo TILE), from the point's first proposal.
+    __device__ __forceinline__ unsigned long long local(int e) const
+    {
+        return e < n_held ? held : at * kTile + list[e - n_held];
+    }
+    // n of them are done (what next gave).
+    __device__ __forceinline__ void done(int n, int lane)
+    {
+        rank += n;
+        keep(n, lane);
+        at += GW;
+    }
+    // All but the first n wait, fewer than TILE.
+    __device__ __forceinline__ void keep(int n, int lane)
+    {
+        const int left = n_held + fresh - n, q = lane % TILE;
+        if (n == 0 ? q >= n_held && q < left : q < left) held = at * kTile + list[n + q - n_held];
+        n_held = left;
+        wave_lds_sync();
+    }
+};
 
 // Per-wave u(0) histogram in LDS, kept while the wave stays with one point and
 // added to the point's global one (a shard per workgroup) when it leaves.
@@ -1120,12 +1250,6 @@ struct WaveHist {
 };
 static_assert(kNBins == kWave, "one bin per lane");
 
-__device__ __forceinline__ unsigned long long read_lane_u64(unsigned long long v, int l)
-{
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, l);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), l);
-    return ((unsigned long long)hi << 32) | lo;
-}
 
 __device__ __forceinline__ double wave_sum_f64(double v)
 {

@@ -58,28 +58,12 @@ constexpr uint64_t static_share(uint64_t n, uint64_t at_least, int n_points)
     if (at_least >= n) return n <= cap ? n : 0;
     return at_least < cap ? at_least : cap;
 }
-// The accept words of a call are cut into segments of 8 to 2048 words (a power of
-// two for each point), one wave each in the ordered output: kSegments of them at
-// most where 2048 words allow it, so that small calls fill the chip too, and
-// smaller ones for points that accept more, down to kSegAccepts accepted each, so
-// that waves end together: as many more as seg_extra.  Fixed segments of 2048
-// words, a workgroup each, left a million near-linear samples at K = 16 to 16
-// workgroups (1.6 ms of ordered output, now 0.1 ms).  In segments of one size for
-// all points, 6.5e7 accepted of four points at K = 64 and 128 took 28.7 ms in 7300
-// and 25.0 in 58600 (1e9 proposals with 5e5 accepted would pay 0.25 ms for as
-// many); and in a sweep of 24 points to targets of 1e4 to 3e5, whose dense points
-// are few words beside the sparse ones', single waves took most of 27.6 ms, now 12.2.
-// (8192 segments of sparse points kept 2e7 proposals at K = 16 8 us longer in the
-// ordered output and 3 in the final sums than 4096 do.)
-constexpr int kSegWordsMin = 8, kSegWordsMax = 2048;
-constexpr int kSegments = 4096, kSegExtraMin = 8192, kSegExtraMax = 65536, kSegAccepts = 256;
-constexpr unsigned long long seg_extra(unsigned long long words)
-{
-    const unsigned long long e = words / 128;
-    return e < (unsigned long long)kSegExtraMin ? (unsigned long long)kSegExtraMin
-                                                : (e > (unsigned long long)kSegExtraMax ? (unsigned long long)kSegExtraMax : e);
-}
-// log2 of the words of a segment of a point that accepts little, for a call of `words` accept words
+// The ordered output finds the accepted sample of a rank through the accept counts
+// of segments of 8 to 2048 words (a power of two, the same for all points of a
+// call): about kSegments of them, as many as waves to count them, unless they would
+// be longer than 2048 words.
+constexpr int kSegWordsMax = 2048, kSegments = 4096;
+// log2 of a segment's words for a call of `words` accept words
 constexpr int seg_shift_for(unsigned long long words)
 {
     int sh = 3;
@@ -90,8 +74,45 @@ constexpr int seg_shift_for(unsigned long long words)
 constexpr unsigned long long max_segments(unsigned long long words, int n_points)
 {
     const unsigned long long by_size = words / kSegWordsMax;
-    return (by_size > (unsigned long long)kSegments ? by_size : (unsigned long long)kSegments) + seg_extra(words) +
+    return (by_size > (unsigned long long)kSegments ? by_size : (unsigned long long)kSegments) +
            (unsigned long long)n_points;
+}
+// The accepted samples that a point's output takes are cut into runs of R = 2^j
+// successive ranks, one wave each, whose statistics are summed in the order of the
+// runs.  R follows from the number of samples (and K) alone, so that the moments are
+// a function of the samples: not of the tiles decided past a target, whose number
+// depends on timing, nor of the call's other points.  Runs shorter than a tile of the
+// ordered output (32 proposals, 16 at K = 64 and 128) leave lanes idle, but a wave
+// reads the accept words between its samples one group after the other (some 800 samples
+// of 1e9 proposals at K = 16: 91 us in runs of 16, 50 in runs of 8); they are for few
+// samples, of which many points still fit the chip.  From there on short runs share
+// out one point's samples better (3e4 at K = 64: 31 us in runs of 32, 51 in runs of
+// 64), long ones take less to find their first sample (24 points of 1e5 at K = 16: 199
+// us in runs of 64, 173 in runs of 128) and give the final sums, which one workgroup a
+// point reads, fewer records.
+constexpr unsigned long long run_most(int K, int j)  // most samples that are cut into runs of 2^j
+{
+    constexpr unsigned long long few[7] = {64, 128, 256, 8192, 16384, 32768, 65536};
+    return j < 3 || (j < 7 && K < 64) ? few[j] : 32ull << (2 * j);
+}
+constexpr int run_shift(int K, unsigned long long samples)
+{
+    int j = 0;
+    while (j < 28 && samples > run_most(K, j)) ++j;
+    return j;
+}
+constexpr unsigned long long runs_of(int K, unsigned long long samples)
+{
+    const int j = run_shift(K, samples);
+    return (samples >> j) + ((samples & ((1ull << j) - 1)) != 0);
+}
+// most runs of a point with at most `samples` samples: those of the most samples
+// with the next shorter runs, if these are more
+constexpr unsigned long long max_runs(int K, unsigned long long samples)
+{
+    const int j = run_shift(K, samples);
+    const unsigned long long own = runs_of(K, samples), shorter = j > 0 ? run_most(K, j - 1) >> (j - 1) : 0ull;
+    return own > shorter ? own : shorter;
 }
 constexpr int kNBins = TKDV_NBINS;
 constexpr int kMixBlock = 1024;    // threads per workgroup of the mixture sampling kernel
@@ -205,23 +226,21 @@ constexpr CounterShard shard_totals(const DevCounters &c)
     return t;
 }
 
-// Per-segment partial statistics (FP64 sums in a fixed order).
-struct SegStats {
+// Statistics of a run of ranks (FP64 sums in the order of the ranks).
+struct RunStats {
     double S1, S2, S3, S4;
-    unsigned long long n_exceed;
-    unsigned long long n_samples;
-    unsigned long long n_exceed4;   // grid values above 4 sigma
-    unsigned long long n_max4;      // samples whose largest grid value is above 4 sigma
     unsigned long long peak_index;  // proposal index of the sample with the largest grid value
     unsigned int peak_key;          // float_key of that value of u~ (0: no sample)
-    unsigned int pad;
+    unsigned int n_exceed;          // grid values above 2 sigma
+    unsigned int n_exceed4;         // grid values above 4 sigma
+    unsigned int n_max4;            // samples whose largest grid value is above 4 sigma
 };
 
 // Per-point result of the finalisation kernel.
 struct PointResult {
     double S1, S2, S3, S4;
     unsigned long long n_exceed;
-    unsigned long long n_exceed4, n_max4, peak_index;  // as in SegStats
+    unsigned long long n_exceed4, n_max4, peak_index;  // as in RunStats
     unsigned int peak_key, pad;
     unsigned long long n_samples;      // accepted samples covered by the statistics
     unsigned long long n_accepted;     // all accepted in the processed range
@@ -245,13 +264,13 @@ struct SweepState {
     PointResult total;            // statistics of the accepted samples so far
 };
 
-// The segments of the tiles decided so far (plan_segments): each point's first
-// one, and from bit kSegShiftBit on log2 of its segments' words; then their number.
-constexpr int kSegShiftBit = 48;
-struct SegPlan {
+// Cuts of every point's words or ranks into pieces: the first piece of each point
+// and, from bit kCutShiftBit on, log2 of its pieces' length; then their number.
+constexpr int kCutShiftBit = 48;
+struct Cuts {
     unsigned long long at[1];
 };
-constexpr size_t seg_plan_bytes(int n_points) { return sizeof(SegPlan) + sizeof(unsigned long long) * (size_t)n_points; }
+constexpr size_t cuts_bytes(int n_points) { return sizeof(Cuts) + sizeof(unsigned long long) * (size_t)n_points; }
 
 // Shared state of a sweep on the device.
 struct SweepGlobal {
@@ -282,12 +301,14 @@ struct KernelArgs {
     float *dbg_xhat, *dbg_t, *dbg_s3, *dbg_log_a, *dbg_log_u;
     // sweeps: the number of unfinished points (NULL elsewhere)
     const unsigned long long *d_active;
-    // ordered output: the segments, their accept counts and exclusive prefix,
-    // their statistics, and the u(0) histograms [point][kShards][kNBins]
-    SegPlan *seg;
+    // ordered output: the segments of the accept words, their accept counts and
+    // exclusive prefix, the runs of ranks, their statistics, and the u(0) histograms
+    // [point][kShards][kNBins]
+    Cuts *seg;
     unsigned int *seg_cnt;
     unsigned long long *seg_base;
-    SegStats *seg_stats;
+    Cuts *runs;
+    RunStats *run_stats;
     unsigned long long *hist;
     PointResult *res;
 };

@@ -22,9 +22,11 @@ int decide_variant_max_blocks_per_cu(int K, int prec, int variant);
 // the launch also lays out the segments of the ordered output
 hipError_t launch_fixup(int K, const KernelArgs &a, bool plan, int n_cu, hipStream_t st);
 hipError_t launch_fixup_mix(int K, const KernelArgs &a, bool plan, int n_cu, hipStream_t st);
-// accept counts of the segments and their prefix, n_segs_max segments at most
+// accept counts of the segments and their prefix, n_segs_max segments at most, and
+// the runs of ranks
 hipError_t launch_segments(const KernelArgs &a, unsigned long long n_segs_max, int n_cu, hipStream_t st);
-hipError_t launch_materialize(int K, int prop, const KernelArgs &a, unsigned long long n_segs_max, float *out_xhat,
+// the accepted samples of the points with this K, n_runs_max runs of ranks at most in all
+hipError_t launch_materialize(int K, int prop, const KernelArgs &a, unsigned long long n_runs_max, float *out_xhat,
                               unsigned long long *out_index, int n_cu, hipStream_t st);
 hipError_t launch_finalize(const KernelArgs &a, hipStream_t st);
 // the standalone synthesis (tkdv_synth.hip); ev_start (optional) is recorded
@@ -57,7 +59,7 @@ int decide_n_variants(int K, int prec);
 size_t quarter_table_bytes(int K, int prec);
 // The ordered output and statistics at K = 64 and 128 (quarter-period form on
 // the statistics grid; a.phi_hi: the table of upload_quarter_stats).
-hipError_t launch_materialize_quarter(int K, int prop, const KernelArgs &a, unsigned long long n_segs_max,
+hipError_t launch_materialize_quarter(int K, int prop, const KernelArgs &a, unsigned long long n_runs_max,
                                       float *out_xhat, unsigned long long *out_index, int n_cu, hipStream_t st);
 hipError_t launch_window_advance(DevPoint *pts, const DevCounters *cnt, const PointResult *res, SweepState *sw,
                                  int n_points, SweepGlobal *G, const unsigned long long *defer_count, hipStream_t st);

@@ -11,8 +11,9 @@
 //                  sum of Sec. IV.A), OR-ed into the accept bitmap; lays out
 //                  the segments of the ordered output.
 //   k_seg_count    accepted count per segment.
-//   k_seg_scan     exclusive scan of the segment counts, per point.
-//   k_materialize  a wave per segment: the accepted bits in proposal order,
+//   k_seg_scan     exclusive scan of the segment counts, per point; the runs of
+//                  ranks (k_plan_runs for several points).
+//   k_materialize  a wave per run of ranks: the accepted proposals in order,
 //                  queued in LDS; regenerates each accepted x^ (same
 //                  arithmetic as k_decide), writes it at its rank, and
 //                  accumulates FP64 moments, 2-sigma exceedances and the u(0)
@@ -155,7 +156,7 @@ __global__ void __launch_bounds__(B, K <= 16 ? 4 : 1) k_decide(KernelArgs a, con
         // one coalesced store of the claim's accept words
         if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
         deferred.push(a, C, p, P.i0 + base * kTile, my_def, lane);
-        count_accepted(P, C, tally, my_word, len, lane);
+        count_accepted(P, C, my_word, len, lane);
     }
     deferred.flush(a);
 }
@@ -351,7 +352,7 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
             }
             if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
             deferred.push(a, C, p, P.i0 + base * kTile, my_def, lane);
-            count_accepted(P, C, tally, my_word, len, lane);
+            count_accepted(P, C, my_word, len, lane);
         }
         tally.report(C, lane);
     }
@@ -652,14 +653,15 @@ __global__ void __launch_bounds__(kBlock) k_fixup_mix(KernelArgs a, int plan)
 __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a)
 {
     const int lane = threadIdx.x & 63;
-    const unsigned long long total = seg_first(a, a.n_points);
+    const unsigned long long total = cut_first(a.seg, a.n_points);
     const unsigned long long waves = (unsigned long long)gridDim.x * (kBlock / kWave);
     for (unsigned long long gs = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6));
          gs < total; gs += waves) {
-        const int p = point_of_segment(a, gs);
+        const int p = point_of_cut(a.seg, a.n_points, gs);
         const DevPoint &P = a.pts[p];
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long S = seg_words(a, p), w0 = (gs - seg_first(a, p)) * S, w1 = w0 + S < nw ? w0 + S : nw;
+        const unsigned long long S = 1ull << cut_shift(a.seg, p), w0 = (gs - cut_first(a.seg, p)) * S;
+        const unsigned long long w1 = w0 + S < nw ? w0 + S : nw;
         unsigned int c = 0;
 #pragma unroll 4
         for (unsigned long long w = w0 + lane; w < w1; w += kWave) c += __popc(a.bitmap[P.bm_off + w]);
@@ -669,12 +671,13 @@ __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a)
 }
 
 // One workgroup per point: exclusive prefix of its segments' counts (each
-// thread a contiguous run of them), and the point's totals.
+// thread a contiguous run of them), the point's totals and, for a point alone, its
+// runs of ranks.
 __global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a)
 {
     __shared__ unsigned long long wsum[16];
     const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const unsigned long long s0 = seg_first(a, p), n = seg_first(a, p + 1) - s0;
+    const unsigned long long s0 = cut_first(a.seg, p), n = cut_first(a.seg, p + 1) - s0;
     const unsigned long long per = (n + 1023) / 1024, b = per * tid < n ? per * tid : n, e = b + per < n ? b + per : n;
     unsigned long long own = 0;
 #pragma unroll 8
@@ -703,15 +706,29 @@ __global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a)
         const unsigned long long done = tiles_taken(P, a.cnt[p].next_tile) * kTile;
         a.res[p].n_accepted = all;
         a.res[p].n_processed = done < P.n ? done : P.n;
+        if (a.n_points == 1) {
+            const unsigned long long m = all < P.target ? all : P.target;
+            a.runs->at[0] = (unsigned long long)run_shift(P.K, m) << kCutShiftBit;
+            a.runs->at[1] = runs_of(P.K, m);
+        }
     }
 }
 
+// The runs of ranks of several points.
+__global__ void __launch_bounds__(1024) k_plan_runs(KernelArgs a)
+{
+    place_cuts<1024>(a.runs, a.n_points, [&](int p, int &sh) {
+        const unsigned long long m = samples_of(a, p);
+        sh = run_shift(a.pts[p].K, m);
+        return runs_of(a.pts[p].K, m);
+    });
+}
+
 // ---------------------------------------------------------------------------
-// k_materialize: one wave per segment; no work past the accepted-sample target
-// (dense segments beyond it cost a map of 500 samples per cell 26 ms of 37).
+// k_materialize: one wave per run of ranks; no work past the accepted-sample
+// target (dense words beyond it cost a map of 500 samples per cell 26 ms of 37).
 // ---------------------------------------------------------------------------
-constexpr int kGroupWords = kWave;                         // one word per lane per group
-constexpr int kQueue = kGroupWords * 32 + kTile;           // one group's offsets + a partial chunk
+using Ranks = RankReader<kWave, kTile>;
 
 template <int K>
 __host__ __device__ constexpr int materialize_tab_bytes()
@@ -722,7 +739,7 @@ __host__ __device__ constexpr int materialize_tab_bytes()
 template <int K>
 __host__ __device__ constexpr int materialize_lds_bytes()
 {
-    return materialize_tab_bytes<K>() + (kBlock / kWave) * (kQueue * 2 + kNBins * 4);
+    return materialize_tab_bytes<K>() + (kBlock / kWave) * (Ranks::N * 2 + kNBins * 4);
 }
 
 template <int K, int PROP>
@@ -730,7 +747,7 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int tab = materialize_tab_bytes<K>();
-    const unsigned long long total = seg_first(a, a.n_points);
+    const unsigned long long total = cut_first(a.runs, a.n_points);
     if ((unsigned long long)blockIdx.x * (kBlock / kWave) >= total) return;
     {
         const uint4 *s0 = reinterpret_cast<const uint4 *>(a.phi_hi);
@@ -739,63 +756,28 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
     }
     const int lane = threadIdx.x & 63, half = lane >> 5, pl = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint16_t *mylist = reinterpret_cast<uint16_t *>(lds + tab) + wv * kQueue;
+    uint16_t *mylist = reinterpret_cast<uint16_t *>(lds + tab) + wv * Ranks::N;
     WaveHist hist;
-    hist.bins = reinterpret_cast<unsigned int *>(lds + tab + (kBlock / kWave) * kQueue * 2) + wv * kNBins;
+    hist.bins = reinterpret_cast<unsigned int *>(lds + tab + (kBlock / kWave) * Ranks::N * 2) + wv * kNBins;
     __syncthreads();
     const unsigned long long waves = (unsigned long long)gridDim.x * (kBlock / kWave);
-    for (unsigned long long gs = (unsigned long long)blockIdx.x * (kBlock / kWave) + wv; gs < total; gs += waves) {
-        const int p = __builtin_amdgcn_readfirstlane(point_of_segment(a, gs));
+    for (unsigned long long run = (unsigned long long)blockIdx.x * (kBlock / kWave) + wv; run < total; run += waves) {
+        const int p = __builtin_amdgcn_readfirstlane(point_of_cut(a.runs, a.n_points, run));
         const DevPoint &P = a.pts[p];
-        const unsigned long long limit = P.target;  // ranks >= target are not part of the result
-        const unsigned long long first = bcast_lane0(a.seg_base[gs]);
-        const unsigned int in_seg = __builtin_amdgcn_readfirstlane(a.seg_cnt[gs]);
-        if (P.K != K || P.proposal != PROP || in_seg == 0u || first >= limit) continue;
+        if (P.K != K || P.proposal != PROP) continue;
         hist.enter(a, p, lane);
-        const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long S = seg_words(a, p), w_first = (gs - seg_first(a, p)) * S;
-        unsigned long long rank = first;
+        const int sh = cut_shift(a.runs, p);
+        const unsigned long long first = (run - cut_first(a.runs, p)) << sh, n = samples_of(a, p);
+        Ranks ranks(a, p, mylist, first, n - first < (1ull << sh) ? n : first + (1ull << sh), lane);
         GridSums sums;
         unsigned int n_max4 = 0;
         unsigned long long peak_idx = ~0ull;
         unsigned int peak_key = 0u;
-        // accepted offsets (proposals from the segment's first word) queue up in
-        // index order; full chunks are regenerated, the last group flushes
-        int queued = 0;
-        const int groups = (int)((S + kGroupWords - 1) / kGroupWords);
-        for (int g = 0; g < groups && rank < limit; ++g) {
-            const unsigned wi = (unsigned)(g * kGroupWords + lane);
-            const unsigned long long w = w_first + wi;
-            const uint32_t word = wi < S && w < nw ? a.bitmap[P.bm_off + w] : 0u;
-            const int cntw = __popc(word);
-            // inclusive prefix over lanes
-            int incl = cntw;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int up = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += up;
-            }
-            const int total_g = __builtin_amdgcn_readlane(incl, 63);
-            int pos = queued + incl - cntw;
-            uint32_t m = word;
-            while (m) {
-                const int bit = __ffs(m) - 1;
-                m &= m - 1;
-                mylist[pos++] = (uint16_t)(wi * 32 + bit);
-            }
-            queued += total_g;
-            const int upto = g + 1 == groups ? queued : queued & ~(kTile - 1);
-            if (upto == 0) continue;
-            // the list is written and read by lanes of this wave only
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            for (int c0 = 0; c0 < upto && rank + c0 < limit; c0 += kTile) {
-                const bool in_chunk = c0 + pl < upto;
-                const int off = in_chunk ? (int)mylist[c0 + pl] : 0;
-                const unsigned long long local = w_first * kTile + (unsigned long long)off;
-                const uint64_t i = P.i0 + local;
-                const unsigned long long r = rank + c0 + pl;
-                const bool valid = in_chunk && r < limit;
+        while (const int upto = ranks.next(lane)) {
+            for (int c0 = 0; c0 < upto; c0 += kTile) {
+                const bool valid = c0 + pl < upto;
+                const uint64_t i = P.i0 + (valid ? ranks.local(c0 + pl) : 0ull);
+                const unsigned long long r = ranks.rank + c0 + pl;
                 float x[K];
                 float t;
                 if constexpr (PROP == PROP_MIXTURE) {
@@ -814,7 +796,7 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
                     }
                     if (out_index && half == 0) out_index[P.out_off + r] = i;
                 }
-                if (valid && half == 0 && r + 1 == limit) a.cnt[p].last_index = i;
+                if (valid && half == 0 && r + 1 == P.target) a.cnt[p].last_index = i;
                 // statistics on the grid: u = sqrt(2 E0/pi) u~, u~ from FP32 products
                 // (K >= 16: the half-period form, u~ = E + O and E - O on the two halves)
                 const float4 *ftab = reinterpret_cast<const float4 *>(lds);
@@ -879,53 +861,39 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
                     atomicAdd(&hist.bins[bin], 1u);
                 }
             }
-            rank += upto;
-            // the partial chunk left moves to the front of the queue
-            const int left = queued - upto;
-            const uint16_t keep = lane < left ? mylist[upto + lane] : (uint16_t)0;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            if (lane < left) mylist[lane] = keep;
-            queued = left;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            ranks.done(upto, lane);
         }
         const double amp2 = P.amp * P.amp;
         const double S1 = P.amp * wave_sum_f64(sums.S1), S2 = amp2 * wave_sum_f64(sums.S2);
         const double S3 = amp2 * P.amp * wave_sum_f64(sums.S3), S4 = amp2 * amp2 * wave_sum_f64(sums.S4);
         n_max4 = wave_sum_u32(n_max4);
         wave_peak(peak_key, peak_idx);
-        if (lane == 0) {
-            const unsigned long long left = limit - first;
-            const unsigned long long ns = in_seg < left ? in_seg : left;
-            a.seg_stats[gs] = SegStats{S1, S2, S3, S4, sums.n_ex, ns, sums.n_ex4, n_max4, peak_idx, peak_key, 0u};
-        }
+        if (lane == 0)
+            a.run_stats[run] = RunStats{S1, S2, S3, S4, peak_idx, peak_key, sums.n_ex, sums.n_ex4, n_max4};
     }
     hist.flush(a, lane);
 }
 
-// Per point (one workgroup): segment partials summed in a fixed order --
-// each thread takes every 1024th segment in order, then a fixed pairwise tree
-// over the threads -- so the result does not depend on scheduling.
+// Per point (one workgroup): the runs' partials summed in a fixed order -- each
+// thread takes every 1024th run in order, then a fixed pairwise tree over the
+// threads -- so that the result depends on the accepted samples alone.
 constexpr int kFinBlock = 1024;
 __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
 {
     __shared__ double sS[4][kFinBlock / kWave];
-    __shared__ unsigned long long sE[4][kFinBlock / kWave], sPI[kFinBlock / kWave];
+    __shared__ unsigned long long sE[3][kFinBlock / kWave], sPI[kFinBlock / kWave];
     __shared__ unsigned int sPK[kFinBlock / kWave];
     if (a.d_active && *a.d_active == 0ull) return;
     const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const DevPoint &P = a.pts[p];
-    const unsigned long long s0 = seg_first(a, p), s1 = seg_first(a, p + 1);
+    const unsigned long long r0 = cut_first(a.runs, p), r1 = cut_first(a.runs, p + 1), n = samples_of(a, p);
     double S[4] = {0.0, 0.0, 0.0, 0.0};
-    unsigned long long E[4] = {0, 0, 0, 0}, pi = ~0ull;  // above 2 sigma, 4 sigma, samples above 4 sigma, samples
+    unsigned long long E[3] = {0, 0, 0}, pi = ~0ull;  // above 2 sigma, 4 sigma, samples above 4 sigma
     unsigned int pk = 0u;
     // the next record's loads are issued beside this one's sums
 #pragma unroll 2
-    for (unsigned long long gs = s0 + tid; gs < s1; gs += kFinBlock) {
-        const bool in = a.seg_cnt[gs] != 0u && a.seg_base[gs] < P.target;
-        SegStats st = a.seg_stats[gs];  // not written where !in
-        if (!in) st = SegStats{0.0, 0.0, 0.0, 0.0, 0ull, 0ull, 0ull, 0ull, ~0ull, 0u, 0u};
+    for (unsigned long long r = r0 + tid; r < r1; r += kFinBlock) {
+        const RunStats st = a.run_stats[r];
         S[0] += st.S1;
         S[1] += st.S2;
         S[2] += st.S3;
@@ -933,21 +901,18 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
         E[0] += st.n_exceed;
         E[1] += st.n_exceed4;
         E[2] += st.n_max4;
-        E[3] += st.n_samples;
         peak_merge(pk, pi, st.peak_key, st.peak_index);
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        S[q] = wave_sum_f64(S[q]);
+    for (int q = 0; q < 4; ++q) S[q] = wave_sum_f64(S[q]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) E[q] += __shfl_xor(E[q], o, 64);
-    }
     wave_peak(pk, pi);
     if (lane == 0) {
-        for (int q = 0; q < 4; ++q) {
-            sS[q][wv] = S[q];
-            sE[q][wv] = E[q];
-        }
+        for (int q = 0; q < 4; ++q) sS[q][wv] = S[q];
+        for (int q = 0; q < 3; ++q) sE[q][wv] = E[q];
         sPK[wv] = pk;
         sPI[wv] = pi;
     }
@@ -963,8 +928,9 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
     // unrolled into 138 spilled registers)
     const bool mine = lane < kFinBlock / kWave;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        S[q] = wave_sum_f64(mine ? sS[q][lane] : 0.0);
+    for (int q = 0; q < 4; ++q) S[q] = wave_sum_f64(mine ? sS[q][lane] : 0.0);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
         E[q] = mine ? sE[q][lane] : 0ull;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) E[q] += __shfl_xor(E[q], o, 64);
@@ -982,8 +948,8 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
         R.n_max4 = E[2];
         R.peak_key = pk;
         R.peak_index = pi;
-        R.n_samples = E[3];
-        R.n_written = E[3] < P.capacity ? E[3] : P.capacity;
+        R.n_samples = n;
+        R.n_written = n < P.capacity ? n : P.capacity;
     }
 }
 
@@ -1371,29 +1337,33 @@ hipError_t launch_segments(const KernelArgs &a, unsigned long long n_segs_max, i
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_seg_scan, dim3(a.n_points), dim3(1024), 0, st, a);
+    e = hipGetLastError();
+    if (e != hipSuccess || a.n_points == 1) return e;
+    hipLaunchKernelGGL(k_plan_runs, dim3(1), dim3(1024), 0, st, a);
     return hipGetLastError();
 }
 
 template <int K, int PROP>
-static hipError_t launch_materialize_t(const KernelArgs &a, unsigned long long n_segs_max, float *out_xhat,
+static hipError_t launch_materialize_t(const KernelArgs &a, unsigned long long n_runs_max, float *out_xhat,
                                        unsigned long long *out_index, int n_cu, hipStream_t st)
 {
     constexpr int lds = materialize_lds_bytes<K>();
     auto kern = k_materialize<K, PROP>;
     hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    unsigned long long g = (n_segs_max + kBlock / kWave - 1) / (kBlock / kWave);
+    unsigned long long g = (n_runs_max + kBlock / kWave - 1) / (kBlock / kWave);
     if (g > 8ull * n_cu) g = 8ull * n_cu;
+    if (g < 1) g = 1;
     hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(kBlock), lds, st, a, out_xhat, out_index);
     return hipGetLastError();
 }
 
-hipError_t launch_materialize(int K, int prop, const KernelArgs &a, unsigned long long n_segs_max, float *out_xhat,
+hipError_t launch_materialize(int K, int prop, const KernelArgs &a, unsigned long long n_runs_max, float *out_xhat,
                               unsigned long long *out_index, int n_cu, hipStream_t st)
 {
-    if (K == 64 || K == 128) return launch_materialize_quarter(K, prop, a, n_segs_max, out_xhat, out_index, n_cu, st);
+    if (K == 64 || K == 128) return launch_materialize_quarter(K, prop, a, n_runs_max, out_xhat, out_index, n_cu, st);
 #define TKDV_DISPATCH_M(KK, PP) \
-    if (K == KK && prop == PP) return launch_materialize_t<KK, PP>(a, n_segs_max, out_xhat, out_index, n_cu, st);
+    if (K == KK && prop == PP) return launch_materialize_t<KK, PP>(a, n_runs_max, out_xhat, out_index, n_cu, st);
     TKDV_DISPATCH_M(8, PROP_UNIFORM)
     TKDV_DISPATCH_M(8, PROP_SIGMA)
     TKDV_DISPATCH_M(16, PROP_UNIFORM)

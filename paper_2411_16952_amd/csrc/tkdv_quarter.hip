@@ -155,36 +155,34 @@ __global__ void __launch_bounds__(BL) k_decide128(KernelArgs a, const int *plist
         }
         if (lane < len) a.bitmap[P.bm_off + base + lane] = my_word;
         deferred.push(a, C, p, P.i0 + base * kTile, my_def, lane);
-        count_accepted(P, C, tally, my_word, len, lane);
+        count_accepted(P, C, my_word, len, lane);
     }
     deferred.flush(a);
 }
 
 // ---------------------------------------------------------------------------
 // k_materialize_q: the ordered output and the statistics at K = 64 and 128.
-// A wave takes one segment at a time, its accept words in groups of 32;
-// accepted proposals in chunks of 16 (the decision kernel's layout),
-// regenerated with the decision kernel's arithmetic and written at their
-// rank, up to the accepted-sample target.  The grid values come from the
+// A wave takes one run of ranks at a time (RankReader), its accepted proposals
+// in chunks of 16 (the decision kernel's layout), regenerated with the decision
+// kernel's arithmetic and written at their rank.  The grid values come from the
 // quarter-period form on the statistics grid xi_j = -pi + 2 pi j/N itself:
 // representatives xi_rho = 2 pi rho/N, rho < K (FP32 16x16x4 products, table
 // in LDS, entries unscaled), each giving u at xi, -xi, pi - xi and xi - pi
 // from Ce, Co, Se, So; rho = 0 has only the two points 0 and pi, and the
 // points +-pi/2 (rho = K) come from direct sums: cos(k pi/2) and sin(k pi/2)
-// are 0 or +-1.  Each wave queues its accepted offsets in LDS, in index order,
-// and regenerates full chunks only (the last group flushes the rest): at an
-// acceptance of 1e-3 a group of 32 words holds one accepted proposal.
+// are 0 or +-1.  Full chunks only are regenerated (but for a run's last): at an
+// acceptance of 1e-3 a group of 32 accept words holds one accepted proposal.
 // Bound by the draw (VALU) and the FP32 products (matrix cores), which waves of
 // a SIMD overlap: four points of 6e7 proposals at K = 64 and 128, 6.5e7
 // accepted, 31.6 ms with ten FP64 operations and two counters a grid value,
-// three waves per SIMD at K = 64 and long segments; now 25.0.
+// three waves per SIMD at K = 64 and long segments of accept words; now 24.0.
 // ---------------------------------------------------------------------------
 template <int K>
 struct MatQ {
     static constexpr int W = 8;                      // waves per workgroup
     static constexpr int GROUP = 32;                 // words per group (lanes 0..31)
-    static constexpr int QUEUE = GROUP * 32 + 16;    // one group's offsets + a partial chunk
-    static constexpr int LIST_BYTES = W * QUEUE * 2;
+    using Ranks = RankReader<GROUP, kTile16>;
+    static constexpr int LIST_BYTES = W * Ranks::N * 2;
     static constexpr int LDS = Quarter<K>::F32_BYTES + LIST_BYTES;
 };
 
@@ -193,10 +191,9 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                                                                       unsigned long long *out_index)
 {
     constexpr int W = MatQ<K>::W, B = W * kWave, CPL = K / 4, QG = Quarter<K>::QG;
-    constexpr int GW = MatQ<K>::GROUP;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ unsigned int wave_hist[W][kNBins];
-    const unsigned long long total = seg_first(a, a.n_points);
+    const unsigned long long total = cut_first(a.runs, a.n_points);
     if ((unsigned long long)blockIdx.x * W >= total) return;
     {
         const uint4 *s0 = reinterpret_cast<const uint4 *>(a.phi_hi);
@@ -206,60 +203,28 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
     const float4 *tab = reinterpret_cast<const float4 *>(lds);
     const int lane = threadIdx.x & 63, g = lane >> 4, pl = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint16_t *mylist = reinterpret_cast<uint16_t *>(lds + Quarter<K>::F32_BYTES) + wv * MatQ<K>::QUEUE;
+    uint16_t *mylist = reinterpret_cast<uint16_t *>(lds + Quarter<K>::F32_BYTES) + wv * MatQ<K>::Ranks::N;
     WaveHist hist;
     hist.bins = wave_hist[wv];
     __syncthreads();
     const unsigned long long waves = (unsigned long long)gridDim.x * W;
-    for (unsigned long long gs = (unsigned long long)blockIdx.x * W + wv; gs < total; gs += waves) {
-        const int p = __builtin_amdgcn_readfirstlane(point_of_segment(a, gs));
+    for (unsigned long long run = (unsigned long long)blockIdx.x * W + wv; run < total; run += waves) {
+        const int p = __builtin_amdgcn_readfirstlane(point_of_cut(a.runs, a.n_points, run));
         const DevPoint &P = a.pts[p];
-        const unsigned long long limit = P.target;  // ranks >= target are not part of the result
-        const unsigned long long first = bcast_lane0(a.seg_base[gs]);
-        const unsigned int in_seg = __builtin_amdgcn_readfirstlane(a.seg_cnt[gs]);
-        if (P.K != K || P.proposal != PROP || in_seg == 0u || first >= limit) continue;
+        if (P.K != K || P.proposal != PROP) continue;
         hist.enter(a, p, lane);
-        const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
-        const unsigned long long S = seg_words(a, p), w_first = (gs - seg_first(a, p)) * S;
-        unsigned long long rank = first;
+        const int sh = cut_shift(a.runs, p);
+        const unsigned long long first = (run - cut_first(a.runs, p)) << sh, n = samples_of(a, p);
+        typename MatQ<K>::Ranks ranks(a, p, mylist, first, n - first < (1ull << sh) ? n : first + (1ull << sh), lane);
         GridSums sums;
         unsigned int n_max4 = 0;
         unsigned long long peak_idx = ~0ull;
         unsigned int peak_key = 0u;
-        int queued = 0;  // offsets (proposals from the segment's first word) waiting in mylist
-        const int groups = (int)((S + GW - 1) / GW);
-        for (int grp = 0; grp < groups && rank < limit; ++grp) {
-            const unsigned wi = (unsigned)(grp * GW + lane);
-            const unsigned long long w = w_first + wi;
-            const uint32_t word = (lane < GW && wi < S && w < nw) ? a.bitmap[P.bm_off + w] : 0u;
-            const int cntw = __popc(word);
-            int incl = cntw;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int up = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += up;
-            }
-            const int total_g = __builtin_amdgcn_readlane(incl, 63);
-            int pos = queued + incl - cntw;
-            uint32_t m = word;
-            while (m) {
-                const int bit = __ffs(m) - 1;
-                m &= m - 1;
-                mylist[pos++] = (uint16_t)(wi * 32 + bit);
-            }
-            queued += total_g;
-            const int upto = grp + 1 == groups ? queued : queued & ~(kTile16 - 1);
-            if (upto == 0) continue;
-            // the list is written and read by lanes of this wave only
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            for (int c0 = 0; c0 < upto && rank + c0 < limit; c0 += kTile16) {
-                const bool in_chunk = c0 + pl < upto;
-                const int off = in_chunk ? (int)mylist[c0 + pl] : 0;
-                const unsigned long long local = w_first * kTile + (unsigned long long)off;
-                const uint64_t i = P.i0 + local;
-                const unsigned long long r = rank + c0 + pl;
-                const bool valid = in_chunk && r < limit;
+        while (const int upto = ranks.next(lane)) {
+            for (int c0 = 0; c0 < upto; c0 += kTile16) {
+                const bool valid = c0 + pl < upto;
+                const uint64_t i = P.i0 + (valid ? ranks.local(c0 + pl) : 0ull);
+                const unsigned long long r = ranks.rank + c0 + pl;
                 float c[CPL], s[CPL], t;
                 gen_x128<K, PROP, true>(P, i, g, c, s, t);
                 if (valid && r < P.capacity) {
@@ -273,7 +238,7 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                     }
                     if (out_index && g == 0) out_index[P.out_off + r] = i;
                 }
-                if (valid && g == 0 && r + 1 == limit) a.cnt[p].last_index = i;
+                if (valid && g == 0 && r + 1 == P.target) a.cnt[p].last_index = i;
                 if (__any(!valid)) {  // no sample, no contribution: u~ = 0
 #pragma unroll
                     for (int j = 0; j < CPL; ++j) {
@@ -346,27 +311,15 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
                     atomicAdd(&hist.bins[bin], 1u);
                 }
             }
-            rank += upto;
-            // the partial chunk left moves to the front of the queue
-            const int left = queued - upto;
-            const uint16_t keep = lane < left ? mylist[upto + lane] : (uint16_t)0;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            if (lane < left) mylist[lane] = keep;
-            queued = left;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
+            ranks.done(upto, lane);
         }
         const double amp2 = P.amp * P.amp;
         const double S1 = P.amp * wave_sum_f64(sums.S1), S2 = amp2 * wave_sum_f64(sums.S2);
         const double S3 = amp2 * P.amp * wave_sum_f64(sums.S3), S4 = amp2 * amp2 * wave_sum_f64(sums.S4);
         n_max4 = wave_sum_u32(n_max4);
         wave_peak(peak_key, peak_idx);
-        if (lane == 0) {
-            const unsigned long long left = limit - first;
-            const unsigned long long ns = in_seg < left ? in_seg : left;
-            a.seg_stats[gs] = SegStats{S1, S2, S3, S4, sums.n_ex, ns, sums.n_ex4, n_max4, peak_idx, peak_key, 0u};
-        }
+        if (lane == 0)
+            a.run_stats[run] = RunStats{S1, S2, S3, S4, peak_idx, peak_key, sums.n_ex, sums.n_ex4, n_max4};
     }
     hist.flush(a, lane);
 }
@@ -475,7 +428,7 @@ hipError_t launch_synth_q_t(const float *xhat, unsigned long long n, float *s3, 
 }
 
 template <int K, int PROP>
-hipError_t launch_materialize_q_t(const KernelArgs &a, unsigned long long n_segs_max, float *out_xhat,
+hipError_t launch_materialize_q_t(const KernelArgs &a, unsigned long long n_runs_max, float *out_xhat,
                                   unsigned long long *out_index, int n_cu, hipStream_t st)
 {
     constexpr int lds = MatQ<K>::LDS, B = MatQ<K>::W * kWave;
@@ -490,7 +443,7 @@ hipError_t launch_materialize_q_t(const KernelArgs &a, unsigned long long n_segs
     // round a wave's segments of a dense and of a sparse point add up or not by
     // chance (26.0 ms; 25.0 in four or eight)
     unsigned long long g = 8ull * per_cu * n_cu;
-    const unsigned long long want = (n_segs_max + MatQ<K>::W - 1) / MatQ<K>::W;
+    const unsigned long long want = (n_runs_max + MatQ<K>::W - 1) / MatQ<K>::W;
     if (want < g) g = want;
     if (g < 1) g = 1;
     hipLaunchKernelGGL(kern, dim3((unsigned)g), dim3(B), lds, st, a, out_xhat, out_index);
@@ -615,11 +568,11 @@ int decide_quarter64_max_blocks_per_cu(int prec)
                              : blocks_per_cu128_t<64, PREC_BF16X3, PROP_SIGMA>();
 }
 
-hipError_t launch_materialize_quarter(int K, int prop, const KernelArgs &a, unsigned long long n_segs_max,
+hipError_t launch_materialize_quarter(int K, int prop, const KernelArgs &a, unsigned long long n_runs_max,
                                       float *out_xhat, unsigned long long *out_index, int n_cu, hipStream_t st)
 {
 #define TKDV_DISPATCH_MQ(KK, PP) \
-    if (K == KK && prop == PP) return launch_materialize_q_t<KK, PP>(a, n_segs_max, out_xhat, out_index, n_cu, st);
+    if (K == KK && prop == PP) return launch_materialize_q_t<KK, PP>(a, n_runs_max, out_xhat, out_index, n_cu, st);
     TKDV_DISPATCH_MQ(64, PROP_SIGMA)
     TKDV_DISPATCH_MQ(64, PROP_UNIFORM)
     TKDV_DISPATCH_MQ(128, PROP_SIGMA)

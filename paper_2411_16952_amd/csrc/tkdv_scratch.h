@@ -11,7 +11,7 @@ namespace tkdv {
 constexpr unsigned long long kScratchMaxProposals = 1ull << 26;
 constexpr unsigned long long kScratchDeferCap = 1ull << 20;
 // accept bitmap 8 MiB + re-decision list 8 MiB + 3 MiB for the counters,
-// segment arrays and point records
+// segment arrays, statistics of the runs and point records
 constexpr size_t kScratchBytes = (kScratchMaxProposals / 32) * 4 + kScratchDeferCap * 8 + (3u << 20);
 
 // Looks up the scratch array's address on `device` (made current for the
