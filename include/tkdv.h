@@ -74,7 +74,8 @@ typedef enum {
  * definition of M as a supremum); M comes from a numerical search, which
  * bounds the supremum only from below.  Every sampling call counts proposals
  * with log a = log f/(M g) > 0 (n_M_violations; decisions inside the FP64
- * window by their FP64 value) and then acts by the context's policy:
+ * window by their FP64 value, for the paper's proposals where it is above 0 by
+ * more than its rounding) and then acts by the context's policy:
  *   TKDV_MV_RAISE (default): raise log M above the largest log a seen (its
  *     FP32 value, plus half the decision window that bounds that value's
  *     error, plus log 1.02), discard the point's output and run it again from
@@ -163,7 +164,7 @@ typedef struct {
     uint64_t n_accepted;      /* accepted among them                                         */
     uint64_t n_written;       /* samples stored (<= capacity)                                */
     uint64_t n_fp64_fixups;   /* proposals re-decided in FP64                                */
-    uint64_t n_M_violations;  /* proposals with log a > 0                                    */
+    uint64_t n_M_violations;  /* proposals with log a > 0 (by more than its FP64 rounding)   */
     uint64_t n_exceed_2sigma; /* grid values with u > 2 sqrt(E0/pi) over accepted samples    */
     uint64_t n_grid_values;   /* accepted samples x N                                        */
     double max_log_a;         /* largest log f/(M g) seen (FP32 fast path)                   */

@@ -373,6 +373,7 @@ __global__ void __launch_bounds__(kMixBlock) k_decide_mix(KernelArgs a, const in
 // kernel took 0.6 ms for 83 thousand proposals at K = 16, 2.0 ms for 700 at
 // K = 128; split over lanes 0.03 ms and 0.02 ms.
 // ---------------------------------------------------------------------------
+constexpr double kRoundLogA = 0x1p-48;  // 32 roundings of each term: five operations a term, a log1p, log M's own
 template <int K>
 __global__ void __launch_bounds__(kBlock) k_fixup(KernelArgs a, int plan)
 {
@@ -456,15 +457,22 @@ __global__ void __launch_bounds__(kBlock) k_fixup(KernelArgs a, int plan)
         const double pi = 3.14159265358979323846;
         const double s = sqrt(P.E0 / (2.0 * pi));
         const double H3 = 2.0 * pi * (s * s * s) * group_sum(tri);
-        double lr = -(P.beta_p / (P.E0 * (double)K * K) * (P.E0 * t - P.c32 * H3));
-        if (P.proposal == PROP_SIGMA) lr += K * log1p(P.alpha_star * P.beta_p * t / ((double)K * K * K));
+        const double bh = P.beta_p / (P.E0 * (double)K * K);
+        double lr = -(bh * (P.E0 * t - P.c32 * H3)), lg = 0.0;
+        if (P.proposal == PROP_SIGMA) {
+            lg = K * log1p(P.alpha_star * P.beta_p * t / ((double)K * K * K));
+            lr += lg;
+        }
         const double la = lr - P.log_M64, lu = log(((double)w_acc + 0.5) * 0x1p-32);
+        // the rounding of la's terms where it is near 0: with an exact M (C3/C2 = 0) f/(M g)
+        // comes as near to 1 as that, and there t's own error does not count (its maximum)
+        const double eps = kRoundLogA * (bh * (P.E0 * t + fabs(P.c32 * H3)) + lg + fabs(P.log_M64));
         if (mine && l == 0) {
             if (lu < la) {
                 const uint64_t local = i - P.i0;
                 atomicOr(&a.bitmap[P.bm_off + local / 32], 1u << (local % 32));
             }
-            if (la > 0.0) {  // f/(M g) > 1 (eq. M_sup broken): counted here for window proposals
+            if (la > eps) {  // f/(M g) > 1 (eq. M_sup broken): counted here for window proposals
                 atomicAdd(&a.cnt[p].shard[0].violations, 1ull);
                 atomicMax(&a.cnt[p].shard[0].max_log_a_key, float_key((float)la));
             }
