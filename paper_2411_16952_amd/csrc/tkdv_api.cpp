@@ -62,7 +62,7 @@ struct tkdv_ctx {
     int device = 0;
     int n_cu = 0;
     std::string last_error;
-    DevBuf bitmap, defer_list, state, points, seg, seg_cnt, seg_base, runs, run_stats;  // state: CallState, points: PointList
+    DevBuf bitmap, defer_list, state, points, seg, seg_cnt, seg_base, ranks, runs, run_stats;  // state: CallState, points: PointList
     DevBuf mix, mix_tab;  // learned-proposal constants and tables of the current call
     // K = 128 (index 4): the quarter-period tables of k_decide128 (BF16 hi, lo, FP32)
     DevBuf phi_hi[kNumK], phi_lo[kNumK], phi_f32[kNumK];
@@ -460,6 +460,7 @@ struct Workspace {
     Cuts *seg, *runs;
     unsigned int *seg_cnt;
     unsigned long long *seg_base;
+    PointRanks *ranks;
     RunStats *run_stats;
 };
 
@@ -525,6 +526,7 @@ tkdv_status launch_sequence(tkdv_ctx *ctx, const CallView &v, const Workspace &w
     a.seg = w.seg;
     a.seg_cnt = w.seg_cnt;
     a.seg_base = w.seg_base;
+    a.ranks = w.ranks;
     a.runs = w.runs;
     a.run_stats = w.run_stats;
     set_state(a, w.state, cs);
@@ -623,7 +625,8 @@ hipError_t ensure_output(tkdv_ctx *ctx, unsigned long long max_segs, unsigned lo
     hipError_t e = ensure(ctx->seg, cuts_bytes(np));
     if (e == hipSuccess) e = ensure(ctx->runs, cuts_bytes(np));
     if (e == hipSuccess) e = ensure(ctx->seg_cnt, sizeof(unsigned int) * max_segs);
-    if (e == hipSuccess) e = ensure(ctx->seg_base, sizeof(unsigned long long) * max_segs);
+    if (e == hipSuccess) e = ensure(ctx->seg_base, sizeof(unsigned long long) * (max_segs + 1));
+    if (e == hipSuccess) e = ensure(ctx->ranks, sizeof(PointRanks) * (size_t)np);
     if (e == hipSuccess) e = ensure(ctx->run_stats, sizeof(RunStats) * max_runs);
     return e;
 }
@@ -660,6 +663,7 @@ tkdv_status run(tkdv_ctx *ctx, Call &call, int precision, int proposal, float *d
     w.points = static_cast<char *>(ctx->points.p);
     w.seg = reinterpret_cast<Cuts *>(ctx->seg.p);
     w.runs = reinterpret_cast<Cuts *>(ctx->runs.p);
+    w.ranks = reinterpret_cast<PointRanks *>(ctx->ranks.p);
     w.seg_cnt = reinterpret_cast<unsigned int *>(ctx->seg_cnt.p);
     w.seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
     w.run_stats = reinterpret_cast<RunStats *>(ctx->run_stats.p);
@@ -986,6 +990,7 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
     a.d_active = &dG->active;
     a.seg = reinterpret_cast<Cuts *>(ctx->seg.p);
     a.runs = reinterpret_cast<Cuts *>(ctx->runs.p);
+    a.ranks = reinterpret_cast<PointRanks *>(ctx->ranks.p);
     a.seg_cnt = reinterpret_cast<unsigned int *>(ctx->seg_cnt.p);
     a.seg_base = reinterpret_cast<unsigned long long *>(ctx->seg_base.p);
     a.run_stats = reinterpret_cast<RunStats *>(ctx->run_stats.p);
@@ -1226,7 +1231,8 @@ tkdv_status tkdv_sample_noalloc(tkdv_ctx *ctx, const tkdv_point *pt, tkdv_propos
     w.seg = reinterpret_cast<Cuts *>(carve(off, cuts_bytes(1)));
     w.runs = reinterpret_cast<Cuts *>(carve(off, cuts_bytes(1)));
     w.seg_cnt = reinterpret_cast<unsigned int *>(carve(off, max_segs * sizeof(unsigned int)));
-    w.seg_base = reinterpret_cast<unsigned long long *>(carve(off, max_segs * 8));
+    w.seg_base = reinterpret_cast<unsigned long long *>(carve(off, (max_segs + 1) * 8));
+    w.ranks = reinterpret_cast<PointRanks *>(carve(off, sizeof(PointRanks)));
     w.run_stats = reinterpret_cast<RunStats *>(carve(off, max_runs(pt->K, kScratchMaxProposals) * sizeof(RunStats)));
     if (off > kScratchBytes) return set_err(ctx, TKDV_E_CAPACITY, "fixed scratch layout exceeds its size");
     tkdv_plan pl = *plan;
@@ -1272,7 +1278,7 @@ tkdv_status tkdv_destroy(tkdv_ctx *ctx)
     if (!ctx) return TKDV_OK;
     (void)hipSetDevice(ctx->device);
     DevBuf *bufs[] = {&ctx->bitmap, &ctx->defer_list, &ctx->state, &ctx->points,
-                      &ctx->seg, &ctx->seg_cnt, &ctx->seg_base, &ctx->runs, &ctx->run_stats,
+                      &ctx->seg, &ctx->seg_cnt, &ctx->seg_base, &ctx->ranks, &ctx->runs, &ctx->run_stats,
                       &ctx->mix, &ctx->mix_tab, &ctx->sweep, &ctx->active, &ctx->plan_pts, &ctx->plan_val,
                       &ctx->plan_x, &ctx->plan_ev, &ctx->plan_mix, &ctx->plan_user, &ctx->ext_keys, &ctx->ext_jmax, &ctx->ext_misc,
                       &ctx->sir_pt, &ctx->sir_w, &ctx->sir_tile, &ctx->sir_chunk, &ctx->sir_part};

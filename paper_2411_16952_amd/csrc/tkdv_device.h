@@ -1011,15 +1011,42 @@ __device__ __forceinline__ unsigned long long cut_first(const Cuts *c, int p)
 }
 __device__ __forceinline__ int cut_shift(const Cuts *c, int p) { return (int)(c->at[p] >> kCutShiftBit); }
 
-// The point of piece i.
-__device__ __forceinline__ int point_of_cut(const Cuts *c, int n_points, unsigned long long i)
+// The point of piece i, by a wave: 64 points looked at together.
+__device__ __forceinline__ int point_of_cut(const Cuts *c, int n_points, unsigned long long i, int lane)
 {
-    int lo = 0, hi = n_points - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (cut_first(c, mid) <= i) lo = mid; else hi = mid - 1;
+    int lo = 0, n = n_points;
+    while (n > 1) {
+        const int step = (n + kWave - 1) / kWave;
+        const unsigned long long first = step * lane < n ? cut_first(c, lo + step * lane) : ~0ull;
+        const int q = __popcll(__ballot(first <= i)) - 1;  // the one at lo begins there or before
+        lo += step * q;
+        n = n - step * q < step ? n - step * q : step;
     }
     return lo;
+}
+
+// Exclusive prefix of v over a workgroup of B threads, and the sum of all.
+template <int B>
+__device__ __forceinline__ unsigned long long block_prefix(unsigned long long v, unsigned long long (&wsum)[B / kWave],
+                                                           unsigned long long &all)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    unsigned long long incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
+    }
+    __syncthreads();  // wsum of the last call has been read
+    if (lane == 63) wsum[wv] = incl;
+    __syncthreads();
+    unsigned long long before = 0;
+    all = 0;
+    for (int w = 0; w < B / kWave; ++w) {
+        before += w < wv ? wsum[w] : 0ull;
+        all += wsum[w];
+    }
+    return before + incl - v;
 }
 
 // Fills c from every point's number of pieces and their log2 length, piece(p, sh)
@@ -1027,24 +1054,17 @@ __device__ __forceinline__ int point_of_cut(const Cuts *c, int n_points, unsigne
 template <int B, class Piece>
 __device__ void place_cuts(Cuts *c, int n_points, Piece piece)
 {
-    __shared__ unsigned long long buf[B];
+    __shared__ unsigned long long wsum[B / kWave];
     const int tid = threadIdx.x;
     unsigned long long run = 0;
     for (int p0 = 0; p0 < n_points; p0 += B) {
         const int p = p0 + tid;
         int sh = 0;
         const unsigned long long v = p < n_points ? piece(p, sh) : 0ull;
-        __syncthreads();
-        buf[tid] = v;
-        __syncthreads();
-        for (int o = 1; o < B; o <<= 1) {  // inclusive scan
-            const unsigned long long add = tid >= o ? buf[tid - o] : 0ull;
-            __syncthreads();
-            buf[tid] += add;
-            __syncthreads();
-        }
-        if (p < n_points) c->at[p] = (run + buf[tid] - v) | ((unsigned long long)sh << kCutShiftBit);
-        run += buf[B - 1];
+        unsigned long long all;
+        const unsigned long long before = run + block_prefix<B>(v, wsum, all);
+        if (p < n_points) c->at[p] = before | ((unsigned long long)sh << kCutShiftBit);
+        run += all;
     }
     if (tid == 0) c->at[n_points] = run;
 }
@@ -1068,13 +1088,6 @@ __device__ void plan_segments(const KernelArgs &a)
         sh = shift;
         return (tiles_taken(a.pts[p], a.cnt[p].next_tile) + (1ull << shift) - 1) >> shift;
     });
-}
-
-// Samples of point p that its output takes.
-__device__ __forceinline__ unsigned long long samples_of(const KernelArgs &a, int p)
-{
-    const unsigned long long n = a.res[p].n_accepted, t = a.pts[p].target;
-    return n < t ? n : t;
 }
 
 __device__ __forceinline__ unsigned long long read_lane_u64(unsigned long long v, int l)
@@ -1107,26 +1120,21 @@ struct RankReader {
     static constexpr int kAhead = GW / 4;  // groups loaded together (twice as many: no faster)
     uint16_t *list;                    // N of LDS, this wave's
     const uint32_t *words;
-    const unsigned long long *seg_base;
-    unsigned long long s0, n_segs;     // the point's segments, of 2^shift words
+    const unsigned long long *seg_base;  // of the point's first segment
+    unsigned long long base0, n_segs;    // accepted before it (all points'); the segments, of 2^shift words
     int shift;
     unsigned long long n_words, at = 0;  // the point's accept words; the first of the group
-    unsigned long long rank, end;      // rank of the first proposal not done yet
-    unsigned long long held = 0;       // the proposal that waits at place lane % TILE
-    int n_held = 0, fresh = 0;         // how many wait; the group's that are wanted
-    int skip;                          // accepted ones still to pass before the first
+    unsigned long long rank, end;        // rank of the first proposal not done yet
+    unsigned long long held = 0;         // the proposal that waits at place lane % TILE
+    int n_held = 0, fresh = 0;           // how many wait; the group's that are wanted
+    int skip;                            // accepted ones still to pass before the first
 
-    __device__ __forceinline__ RankReader(const KernelArgs &a, int p, uint16_t *lds, unsigned long long first_,
-                                          unsigned long long end_, int lane)
-        : list(lds), rank(bcast_lane0(first_)), end(bcast_lane0(end_))
+    __device__ __forceinline__ RankReader(const KernelArgs &a, const PointRanks &R, unsigned long long bm_off, uint16_t *lds,
+                                          unsigned long long first_, unsigned long long end_, int lane)
+        : list(lds), words(a.bitmap + bm_off), seg_base(a.seg_base + bcast_lane0(R.seg_first)), base0(bcast_lane0(R.base)),
+          n_segs(bcast_lane0(R.n_segs)), shift(__builtin_amdgcn_readfirstlane(R.seg_shift)), n_words(bcast_lane0(R.n_words)),
+          rank(bcast_lane0(first_)), end(bcast_lane0(end_))
     {
-        const DevPoint &P = a.pts[p];
-        words = a.bitmap + P.bm_off;
-        n_words = bcast_lane0(tiles_taken(P, a.cnt[p].next_tile));
-        seg_base = a.seg_base;
-        s0 = bcast_lane0(cut_first(a.seg, p));
-        n_segs = bcast_lane0(cut_first(a.seg, p + 1)) - s0;
-        shift = __builtin_amdgcn_readfirstlane(cut_shift(a.seg, p));
         skip = (int)(rank - seek(rank, 0ull, lane));
     }
     // To the segment that holds rank r, the last that begins there or before, if that is
@@ -1137,7 +1145,7 @@ struct RankReader {
         unsigned long long lo = from, n = n_segs - from, before = 0;
         while (n > 1) {
             const unsigned long long step = (n + kWave - 1) / kWave, i = step * lane;
-            const unsigned long long base = i < n ? seg_base[s0 + lo + i] : ~0ull;
+            const unsigned long long base = i < n ? seg_base[lo + i] - base0 : ~0ull;
             const int c = __popcll(__ballot(base <= r)) - 1;  // the one at lo begins there or before
             before = read_lane_u64(base, c);
             lo += step * c;
@@ -1150,7 +1158,7 @@ struct RankReader {
     __device__ __forceinline__ void skip_empty(unsigned long long r, int lane)
     {
         const unsigned long long cur = at >> shift, i = cur + lane;
-        const unsigned long long base = i < n_segs ? seg_base[s0 + i] : ~0ull;
+        const unsigned long long base = i < n_segs ? seg_base[i] - base0 : ~0ull;
         const int c = __popcll(__ballot(base <= r)) - 1;
         if (c == kWave - 1) seek(r, cur + c, lane);
         else if (c > 0) at = (cur + c) << shift;

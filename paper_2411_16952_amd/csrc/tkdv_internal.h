@@ -92,12 +92,15 @@ constexpr unsigned long long max_segments(unsigned long long words, int n_points
 // point reads, fewer records.
 constexpr unsigned long long run_most(int K, int j)  // most samples that are cut into runs of 2^j
 {
-    constexpr unsigned long long few[7] = {64, 128, 256, 8192, 16384, 32768, 65536};
-    return j < 3 || (j < 7 && K < 64) ? few[j] : 32ull << (2 * j);
+    constexpr unsigned long long few[2][9] = {
+        {64, 128, 256, 2048, 8192, 32768, 65536, 1 << 19, 1 << 21},   // K <= 32
+        {64, 128, 256, 2048, 8192, 65536, 1 << 19, 1 << 20, 1 << 21}};  // K >= 64: workgroups of 8 waves, dear tiles
+    return j < 9 ? few[K >= 64][j] : 32ull << (2 * j);
 }
 constexpr int run_shift(int K, unsigned long long samples)
 {
     int j = 0;
+#pragma unroll 1
     while (j < 28 && samples > run_most(K, j)) ++j;
     return j;
 }
@@ -226,6 +229,15 @@ constexpr CounterShard shard_totals(const DevCounters &c)
     return t;
 }
 
+// Where a point's accepted samples are (k_seg_scan).
+struct PointRanks {
+    unsigned long long samples;            // those that its output takes
+    unsigned long long seg_first, n_segs;  // its segments, of 2^seg_shift words
+    unsigned long long base;               // accepted before them (all points')
+    unsigned long long n_words;            // its accept words
+    int seg_shift, pad;
+};
+
 // Statistics of a run of ranks (FP64 sums in the order of the ranks).
 struct RunStats {
     double S1, S2, S3, S4;
@@ -302,11 +314,12 @@ struct KernelArgs {
     // sweeps: the number of unfinished points (NULL elsewhere)
     const unsigned long long *d_active;
     // ordered output: the segments of the accept words, their accept counts and
-    // exclusive prefix, the runs of ranks, their statistics, and the u(0) histograms
-    // [point][kShards][kNBins]
+    // exclusive prefix (over all points, and the sum), where each point's samples are,
+    // the runs of ranks, their statistics, and the u(0) histograms [point][kShards][kNBins]
     Cuts *seg;
     unsigned int *seg_cnt;
     unsigned long long *seg_base;
+    PointRanks *ranks;
     Cuts *runs;
     RunStats *run_stats;
     unsigned long long *hist;

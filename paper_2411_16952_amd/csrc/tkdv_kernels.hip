@@ -11,8 +11,7 @@
 //                  sum of Sec. IV.A), OR-ed into the accept bitmap; lays out
 //                  the segments of the ordered output.
 //   k_seg_count    accepted count per segment.
-//   k_seg_scan     exclusive scan of the segment counts, per point; the runs of
-//                  ranks (k_plan_runs for several points).
+//   k_seg_scan     exclusive scan of the segment counts; the runs of ranks.
 //   k_materialize  a wave per run of ranks: the accepted proposals in order,
 //                  queued in LDS; regenerates each accepted x^ (same
 //                  arithmetic as k_decide), writes it at its rank, and
@@ -665,7 +664,7 @@ __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a)
     const unsigned long long waves = (unsigned long long)gridDim.x * (kBlock / kWave);
     for (unsigned long long gs = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6));
          gs < total; gs += waves) {
-        const int p = point_of_cut(a.seg, a.n_points, gs);
+        const int p = __builtin_amdgcn_readfirstlane(point_of_cut(a.seg, a.n_points, gs, lane));
         const DevPoint &P = a.pts[p];
         const unsigned long long nw = tiles_taken(P, a.cnt[p].next_tile);
         const unsigned long long S = 1ull << cut_shift(a.seg, p), w0 = (gs - cut_first(a.seg, p)) * S;
@@ -678,57 +677,52 @@ __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a)
     }
 }
 
-// One workgroup per point: exclusive prefix of its segments' counts (each
-// thread a contiguous run of them), the point's totals and, for a point alone, its
-// runs of ranks.
+// One workgroup: exclusive prefix of the segments' counts (each thread a contiguous
+// run of them), the points' totals and their runs of ranks.
 __global__ void __launch_bounds__(1024) k_seg_scan(KernelArgs a)
 {
     __shared__ unsigned long long wsum[16];
-    const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const unsigned long long s0 = cut_first(a.seg, p), n = cut_first(a.seg, p + 1) - s0;
+    const int tid = threadIdx.x, seg_shift = cut_shift(a.seg, 0);
+    const unsigned long long n = cut_first(a.seg, a.n_points);
+    // of the first point, beside the scan's loads: all there is for a point alone
+    const int K0 = a.pts[0].K;
+    const unsigned long long words0 = tiles_taken(a.pts[0], a.cnt[0].next_tile), last0 = a.pts[0].n, target0 = a.pts[0].target;
     const unsigned long long per = (n + 1023) / 1024, b = per * tid < n ? per * tid : n, e = b + per < n ? b + per : n;
     unsigned long long own = 0;
 #pragma unroll 8
-    for (unsigned long long s = b; s < e; ++s) own += a.seg_cnt[s0 + s];
-    unsigned long long incl = own;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned long long up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
-    }
-    if (lane == 63) wsum[tid >> 6] = incl;
-    __syncthreads();
-    unsigned long long before = 0, all = 0;
-    for (int w = 0; w < 16; ++w) {
-        if (w < (tid >> 6)) before += wsum[w];
-        all += wsum[w];
-    }
-    unsigned long long run = before + incl - own;
+    for (unsigned long long s = b; s < e; ++s) own += a.seg_cnt[s];
+    unsigned long long all;
+    unsigned long long run = block_prefix<1024>(own, wsum, all);
 #pragma unroll 8
     for (unsigned long long s = b; s < e; ++s) {
-        a.seg_base[s0 + s] = run;
-        run += a.seg_cnt[s0 + s];
+        a.seg_base[s] = run;
+        run += a.seg_cnt[s];
     }
-    if (tid == 0) {
-        const DevPoint &P = a.pts[p];
-        const unsigned long long done = tiles_taken(P, a.cnt[p].next_tile) * kTile;
-        a.res[p].n_accepted = all;
-        a.res[p].n_processed = done < P.n ? done : P.n;
-        if (a.n_points == 1) {
-            const unsigned long long m = all < P.target ? all : P.target;
-            a.runs->at[0] = (unsigned long long)run_shift(P.K, m) << kCutShiftBit;
-            a.runs->at[1] = runs_of(P.K, m);
-        }
+    if (tid == 0) a.seg_base[n] = all;
+    // point p of the segments [s0, s1), the accepted before each: its runs
+    auto point = [&](int p, unsigned long long words, unsigned long long last, unsigned long long target, int K,
+                     unsigned long long s0, unsigned long long s1, unsigned long long base, unsigned long long upto,
+                     int &sh) {
+        const unsigned long long done = words * kTile, accepted = upto - base;
+        const unsigned long long samples = accepted < target ? accepted : target;
+        a.ranks[p] = PointRanks{samples, s0, s1 - s0, base, words, seg_shift, 0};
+        a.res[p].n_accepted = accepted;
+        a.res[p].n_processed = done < last ? done : last;
+        sh = run_shift(K, samples);
+        return runs_of(K, samples);
+    };
+    if (a.n_points == 1) {
+        if (tid != 0) return;
+        int sh;
+        a.runs->at[1] = point(0, words0, last0, target0, K0, 0ull, n, 0ull, all, sh);
+        a.runs->at[0] = (unsigned long long)sh << kCutShiftBit;
+        return;
     }
-}
-
-// The runs of ranks of several points.
-__global__ void __launch_bounds__(1024) k_plan_runs(KernelArgs a)
-{
+    __syncthreads();  // the points read what other threads wrote
     place_cuts<1024>(a.runs, a.n_points, [&](int p, int &sh) {
-        const unsigned long long m = samples_of(a, p);
-        sh = run_shift(a.pts[p].K, m);
-        return runs_of(a.pts[p].K, m);
+        const unsigned long long s0 = cut_first(a.seg, p), s1 = cut_first(a.seg, p + 1);
+        const DevPoint &P = a.pts[p];
+        return point(p, tiles_taken(P, a.cnt[p].next_tile), P.n, P.target, P.K, s0, s1, a.seg_base[s0], a.seg_base[s1], sh);
     });
 }
 
@@ -770,13 +764,14 @@ __global__ void __launch_bounds__(kBlock) k_materialize(KernelArgs a, float *out
     __syncthreads();
     const unsigned long long waves = (unsigned long long)gridDim.x * (kBlock / kWave);
     for (unsigned long long run = (unsigned long long)blockIdx.x * (kBlock / kWave) + wv; run < total; run += waves) {
-        const int p = __builtin_amdgcn_readfirstlane(point_of_cut(a.runs, a.n_points, run));
+        const int p = __builtin_amdgcn_readfirstlane(point_of_cut(a.runs, a.n_points, run, lane));
         const DevPoint &P = a.pts[p];
         if (P.K != K || P.proposal != PROP) continue;
         hist.enter(a, p, lane);
+        const PointRanks &R = a.ranks[p];
         const int sh = cut_shift(a.runs, p);
-        const unsigned long long first = (run - cut_first(a.runs, p)) << sh, n = samples_of(a, p);
-        Ranks ranks(a, p, mylist, first, n - first < (1ull << sh) ? n : first + (1ull << sh), lane);
+        const unsigned long long first = (run - cut_first(a.runs, p)) << sh, n = R.samples;
+        Ranks ranks(a, R, P.bm_off, mylist, first, n - first < (1ull << sh) ? n : first + (1ull << sh), lane);
         GridSums sums;
         unsigned int n_max4 = 0;
         unsigned long long peak_idx = ~0ull;
@@ -894,7 +889,7 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
     if (a.d_active && *a.d_active == 0ull) return;
     const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const DevPoint &P = a.pts[p];
-    const unsigned long long r0 = cut_first(a.runs, p), r1 = cut_first(a.runs, p + 1), n = samples_of(a, p);
+    const unsigned long long r0 = cut_first(a.runs, p), r1 = cut_first(a.runs, p + 1), n = a.ranks[p].samples;
     double S[4] = {0.0, 0.0, 0.0, 0.0};
     unsigned long long E[3] = {0, 0, 0}, pi = ~0ull;  // above 2 sigma, 4 sigma, samples above 4 sigma
     unsigned int pk = 0u;
@@ -1344,10 +1339,7 @@ hipError_t launch_segments(const KernelArgs &a, unsigned long long n_segs_max, i
     hipLaunchKernelGGL(k_seg_count, dim3((unsigned)g), dim3(kBlock), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_seg_scan, dim3(a.n_points), dim3(1024), 0, st, a);
-    e = hipGetLastError();
-    if (e != hipSuccess || a.n_points == 1) return e;
-    hipLaunchKernelGGL(k_plan_runs, dim3(1), dim3(1024), 0, st, a);
+    hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, st, a);
     return hipGetLastError();
 }
 

@@ -209,13 +209,15 @@ __global__ void __launch_bounds__(MatQ<K>::W * kWave) k_materialize_q(KernelArgs
     __syncthreads();
     const unsigned long long waves = (unsigned long long)gridDim.x * W;
     for (unsigned long long run = (unsigned long long)blockIdx.x * W + wv; run < total; run += waves) {
-        const int p = __builtin_amdgcn_readfirstlane(point_of_cut(a.runs, a.n_points, run));
+        const int p = __builtin_amdgcn_readfirstlane(point_of_cut(a.runs, a.n_points, run, lane));
         const DevPoint &P = a.pts[p];
         if (P.K != K || P.proposal != PROP) continue;
         hist.enter(a, p, lane);
+        const PointRanks &R = a.ranks[p];
         const int sh = cut_shift(a.runs, p);
-        const unsigned long long first = (run - cut_first(a.runs, p)) << sh, n = samples_of(a, p);
-        typename MatQ<K>::Ranks ranks(a, p, mylist, first, n - first < (1ull << sh) ? n : first + (1ull << sh), lane);
+        const unsigned long long first = (run - cut_first(a.runs, p)) << sh, n = R.samples;
+        typename MatQ<K>::Ranks ranks(a, R, P.bm_off, mylist, first, n - first < (1ull << sh) ? n : first + (1ull << sh),
+                                      lane);
         GridSums sums;
         unsigned int n_max4 = 0;
         unsigned long long peak_idx = ~0ull;

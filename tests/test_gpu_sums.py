@@ -5,8 +5,8 @@ alone or beside others, an accepted-count call (which decides some tiles past it
 target, how many depends on timing) or the proposal-count call that ends at its
 last sample, any launch.  And their values against 64 bits, from the rows that
 the call wrote, where the ordered output's runs of ranks begin, end and change
-length (R = 1, 2, 4, 8, ... ranks a run up to 64, 128, 256, 8192, ... samples; for
-K >= 64 from R = 8 and otherwise from R = 128 on up to 32 R^2).
+length (R = 1, 2, 4, 8, 16 ranks a run up to 64, 128, 256, 2048, 8192 samples and
+so on, to 2^21 samples for R = 256).
 
 A row's coordinates are FP32 and a grid value is an FP32 product of 2K terms:
 within tol = 2e-6 sqrt(K) amp of its 64-bit value.  So a sum of p-th powers is

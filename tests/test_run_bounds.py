@@ -27,8 +27,8 @@ int main()
         for (u64 n : at) {
             const u64 R = 1ull << run_shift(K, n), r = runs_of(K, n);
             if (r * R < n || (n && (r - 1) * R >= n)) return printf("runs of %llu\n", n), 1;
-            if (r > 1024 && r > 32 * R) return printf("short runs of %llu\n", n), 1;
-            if (R >= 128 && r <= 2 * R) return printf("long runs of %llu\n", n), 1;
+            if (r > (32 * R > 8192 ? 32 * R : 8192)) return printf("short runs of %llu\n", n), 1;
+            if (R >= 128 && r <= 512) return printf("long runs of %llu\n", n), 1;
             most = std::max(most, r);
             if (max_runs(K, n) < most) return printf("max_runs(%llu) = %llu < %llu\n", n, max_runs(K, n), most), 1;
             if (max_runs(K, n) > most + most / 8) return printf("max_runs(%llu) far above %llu\n", n, most), 1;
