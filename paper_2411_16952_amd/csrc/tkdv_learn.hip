@@ -537,7 +537,7 @@ __device__ __forceinline__ void fwd_tiles(const LearnArgs &A, const LearnPoint &
                 if (r > top) {
                     se = se * exp(top - r) + 1.0;  // top = -inf: no term yet
                     top = r;
-                } else {
+                } else if (r != -INFINITY) {  // no density of the target, no term
                     se += exp(r - top);
                 }
             }
