@@ -29,7 +29,10 @@
  * z_2m+1 = r sin 2pi U2, r = sqrt(-2 ln U1), U = (w + 1/2) 2^-32) and word 2K
  * gives the acceptance uniform.  Results are a deterministic function of
  * (point, proposal, plan, seed, point_id, n, precision): independent of the
- * launch configuration and of the stream's other work.
+ * launch configuration, of a call's other points and of the stream's other work
+ * (but for the last bits of a sweep's moments, see tkdv_sample_sweep, and, in
+ * accepted-count mode, what is counted over all proposals decided:
+ * n_fp64_fixups, n_M_violations and max_log_a).
  *
  * Exactness.  The fast path evaluates log a = log f/(M g) in FP32 with the
  * spectral-to-grid synthesis on the matrix cores; every proposal whose
@@ -570,8 +573,10 @@ typedef struct {
  * and a window without unfinished points does nothing.  Output as in
  * tkdv_sample_batch: the first targets[p] accepted samples by index in rows
  * (out_offset[p] + r) of d_xhat (stride 2 * TKDV_KMAX floats) and d_index, at
- * most capacity[p] rows; stats cover the same samples; n_proposed counts the
- * proposals up to the last of them (or max_proposals[p]).  cfg NULL: the
+ * most capacity[p] rows; stats cover the same samples (S1..S4 summed window by
+ * window: their last bits follow the windows, i.e. cfg and, where the pool is
+ * shared out, the other points); n_proposed counts the proposals up to the last
+ * of them (or max_proposals[p]).  cfg NULL: the
  * context's configuration of each K (tkdv_set_launch_cfg / tkdv_autotune), by
  * default all workgroups that fit, first windows of 2^26 proposals, variant 0,
  * adaptive; otherwise cfg for every K.  Plans must be Sigma plans (or NULL:

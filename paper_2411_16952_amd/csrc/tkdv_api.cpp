@@ -473,7 +473,7 @@ void set_state(KernelArgs &a, char *state, const CallState &cs)
 }
 
 // Host view of one launch sequence: the points, their lists per K and the
-// segment count (plain arrays, so that a caller need not allocate).
+// most segments and runs (plain arrays, so that a caller need not allocate).
 struct CallView {
     const DevPoint *pts;
     int np;
@@ -861,7 +861,11 @@ int prec_index(int precision) { return precision < 0 || precision > 2 ? 0 : prec
 // Windows captured into one graph (one launch, one host synchronisation).  Most
 // sweeps take two or three; the windows after them do nothing but launch, some
 // 60 us each, and are captured and instantiated all the same: with 16 of them a map
-// of 64 cells took 3.8 ms, with 4 3.0, and a sweep of 24 points 12.2 and 11.0.
+// of 64 cells took 3.8 ms, with 4 3.0, and a sweep of 24 points 12.2 and 11.0.  A
+// look at the state costs some 13 us: sweeps in fixed windows of 65536 proposals
+// (one point, K = 16) take 0.66 ms with 4 and 1.01 with 16 for 5 windows, 2.93 and
+// 3.10 for 41, 6.75 and 6.70 for 101, 25.6 and 24.3 for 400; of 2^20 proposals 0.94
+// and 1.24, 4.99 and 5.08, 11.8 and 11.9, 46.5 and 45.4.
 constexpr int kSweepGraphWindows = 4;
 
 tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan *plans, const uint64_t *targets,
@@ -927,8 +931,8 @@ tkdv_status sweep(tkdv_ctx *ctx, int np, const tkdv_point *pts, const tkdv_plan 
         by_k[ki].push_back(p);
     }
     // the window's accept bitmap: the first windows, or (adaptive) a pool of up
-    // to 2^33 proposals shared by the points' later windows, plus one segment
-    // per point of rounding
+    // to 2^33 proposals shared by the points' later windows, plus 65536
+    // proposals per point of rounding
     unsigned long long pool_words = first_words;
     if (adaptive) pool_words = std::max<unsigned long long>(first_words, std::min<unsigned long long>(
                                                                               (1ull << 33) / kTile, sum_maxp / kTile));

@@ -744,7 +744,7 @@ __device__ __forceinline__ void static_range(const DevPoint &P, int p, unsigned 
 // from their even shares together and read all eight wait for each other at those
 // lines (K = 16, a million near-linear samples, 178 us, now 147).  (Claims of a fixed
 // 64 tiles by every wave gave a near-linear point of a million samples eight
-// times the proposals it needed: K = 16, 1.0 ms of decisions, now 0.18 ms.)
+// times the proposals it needed: K = 16, 1.0 ms of decisions.)
 // Every lane issues the atomic (lane 0 adds, the others add 0) and lane 0's
 // old value is taken, so no lane-divergent region sits next to the loop
 // back-edge (the compiler may otherwise thread lanes 1-63 past lane 0's region

@@ -17,7 +17,7 @@
 //                  arithmetic as k_decide), writes it at its rank, and
 //                  accumulates FP64 moments, 2-sigma exceedances and the u(0)
 //                  histogram from an FP32 matrix-core synthesis.
-//   k_finalize     per point, segment partials summed in a fixed order.
+//   k_finalize     per point, the runs' partials summed in a fixed order.
 //   (mixture)      k_decide_mix and k_fixup_mix take the places of k_decide
 //                  and k_fixup for the learned proposal.
 #include <hip/hip_runtime.h>
@@ -655,7 +655,7 @@ __global__ void __launch_bounds__(kBlock) k_fixup_mix(KernelArgs a, int plan)
 }
 
 // ---------------------------------------------------------------------------
-// Segments: accept counts (a wave per segment) and their prefix per point.
+// Segments: accept counts (a wave per segment) and their prefix.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(kBlock) k_seg_count(KernelArgs a)
 {
@@ -964,11 +964,11 @@ __global__ void __launch_bounds__(kFinBlock) k_finalize(KernelArgs a)
 //   (a done point gets no tiles);
 //   then, in point order: the next window of every active point -- its first
 //   index, size, remaining target and capacity, output offset, and its place
-//   in the window's accept bitmap and segments.  Adaptive windows take the
-//   proposals the point still needs at its measured acceptance, times 1.25
-//   (four times the proposals so far while it has accepted none), shared out
-//   of the bitmap pool in proportion when they do not fit; otherwise every
-//   window has the first window's size.
+//   in the window's accept bitmap.  Adaptive windows take the proposals the
+//   point still needs at its measured acceptance, times 1.25 (four times the
+//   proposals so far while it has accepted none), shared out of the bitmap pool
+//   in proportion when they do not fit; otherwise every window has the first
+//   window's size.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(1024) k_window_advance(DevPoint *pts, const DevCounters *cnt,
                                                          const PointResult *res, SweepState *sw, int n_points,

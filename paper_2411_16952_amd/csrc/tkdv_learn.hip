@@ -991,8 +991,8 @@ tkdv_status grow_rows(tkdv_learner *L, unsigned long long need, hipStream_t st)
     return TKDV_OK;
 }
 
-// Rows grouped by point in insertion order, cut into chunks (kTileRows)
-// rows of one point; uploads the index order, the chunk table and the
+// Rows grouped by point in insertion order, cut into chunks of whole tiles
+// (kTileRows rows) of one point; uploads the index order, the chunk table and the
 // points' chunk ranges.
 tkdv_status build_chunks(tkdv_learner *L, hipStream_t st)
 {

@@ -16,8 +16,8 @@ namespace {
 constexpr int kCarry128 = 3 * kWave * 4;
 
 // ---------------------------------------------------------------------------
-// k_decide128: persistent; claims of up to 64 accept words (2048 proposals, 128
-// tiles of 16) from per-point queues, as the other decision kernels.
+// k_decide128: per wave, up to 64 accept words at a time (2048 proposals, 128 tiles
+// of 16), dealt out or claimed from per-point queues as in the other decision kernels.
 // ---------------------------------------------------------------------------
 // DBG: the verification entry's instantiation (per-proposal outputs written,
 // workgroups of Quarter<K>::BLOCK); the sampling calls run the one without,
@@ -442,7 +442,7 @@ hipError_t launch_materialize_q_t(const KernelArgs &a, unsigned long long n_runs
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
     // several rounds of workgroups, so that they even out among the CUs: with one
-    // round a wave's segments of a dense and of a sparse point add up or not by
+    // round a wave's parts of a dense and of a sparse point add up or not by
     // chance (26.0 ms; 25.0 in four or eight)
     unsigned long long g = 8ull * per_cu * n_cu;
     const unsigned long long want = (n_runs_max + MatQ<K>::W - 1) / MatQ<K>::W;
