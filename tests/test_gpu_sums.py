@@ -60,6 +60,26 @@ def test_a_point_beside_others(T, ctx, K, beta, c, n):
         _equal(out[0], one)
 
 
+@pytest.mark.parametrize("n_points", [65, 1500])
+def test_many_points(T, ctx, n_points):
+    """More points than lanes, and than threads of the kernel that lays out the runs; some accept nothing."""
+    rng = np.random.default_rng(n_points)
+    pts = [T.make_point(int(rng.choice([8, 16, 32, 64])), 1.0, 40.0, float(rng.choice([0.5, 20.0, 60.0])), seed=3, point_id=i)
+           for i in range(n_points)]
+    plans = ctx.plan_batch(pts, T.SIGMA, n_starts=4)[0]
+    n = [int(v) for v in rng.integers(1, 3000, n_points)]
+    out, xh, ix = ctx.sample_batch(pts, n, plans=plans, capacity=n)
+    off = np.concatenate([[0], np.cumsum(n)]).astype(int)
+    assert any(o["n_accepted"] == 0 for o in out) and any(o["n_accepted"] > 500 for o in out)
+    for q in sorted(set(rng.integers(0, n_points, 40).tolist() + [0, 63, 64, n_points - 1])):
+        one = ctx.sample(pts[q], n[q], plan=plans[q], capacity=n[q])
+        w = one["n_written"]
+        assert out[q]["n_accepted"] == one["n_accepted"] == w and out[q]["n_proposed"] == n[q]
+        assert all(out[q][k] == one[k] for k in SUMS + ("n_exceed_2sigma", "peak_u", "peak_index")), q
+        assert np.array_equal(ix[off[q]:off[q] + w].cpu().numpy(), one["index"].cpu().numpy())
+        assert np.array_equal(xh[off[q]:off[q] + w, : 2 * pts[q].K].cpu().numpy(), one["xhat"].cpu().numpy())
+
+
 @pytest.mark.parametrize("K,c,targets", [(8, 20.0, (1, 2_900)), (16, 0.0, (33, 65_536, 1_000_000)),
                                          (32, 75.0, (500, 30_000)), (64, 1.0, (8_193, 200_000)), (128, 1.0, (17, 60_000))])
 def test_accepted_count_calls(T, ctx, K, c, targets):
