@@ -1110,29 +1110,33 @@ __device__ __forceinline__ int wave_prefix_i32(int v)
 }
 
 // The accepted proposals of ranks [first, end) of a point, in order, for one wave:
-// from the segment on that holds the first of them it reads the accept words GW at
-// a time (one per lane) and queues the offsets of their accepted proposals in LDS;
-// the part of a tile of TILE that a group leaves waits in registers.
+// from the segment on that holds the first of them it reads the accept words in
+// groups of GW (one per lane), kAhead groups at a time, and queues the offsets of
+// their accepted proposals in LDS; the part of a tile of TILE that is left waits in
+// registers.
 template <int GW, int TILE>
 struct RankReader {
     static_assert(GW <= kWave && kWave % TILE == 0, "a word per lane, and a waiting proposal");
-    static constexpr int N = GW * 32;  // most offsets of a group
-    static constexpr int kAhead = GW / 4;  // groups loaded together (twice as many: no faster)
+    // groups loaded together: where few are accepted the loads are what a group takes (4096
+    // samples among 3e6 words at K = 32: 0.4 ms more, one at a time); twice as many are no faster
+    static constexpr int kAhead = GW / 4;
+    static constexpr int N = GW * 32;  // offsets queued at a time: any group's
+    static_assert(kAhead * N <= 1 << 16, "offsets of 16 bits");
     uint16_t *list;                    // N of LDS, this wave's
     const uint32_t *words;
-    const unsigned long long *seg_base;  // of the point's first segment
-    unsigned long long base0, n_segs;    // accepted before it (all points'); the segments, of 2^shift words
-    int shift;
-    unsigned long long n_words, at = 0;  // the point's accept words; the first of the group
+    const PointRanks &R;
+    const unsigned long long *seg_base;  // KernelArgs
+    int shift;                           // log2 of a segment's words
+    unsigned long long n_words, at = 0, after = 0;  // the point's accept words; the first of those queued, and after them
     unsigned long long rank, end;        // rank of the first proposal not done yet
     unsigned long long held = 0;         // the proposal that waits at place lane % TILE
-    int n_held = 0, fresh = 0;           // how many wait; the group's that are wanted
+    int n_held = 0, fresh = 0;           // how many wait; how many are queued
     int skip;                            // accepted ones still to pass before the first
 
-    __device__ __forceinline__ RankReader(const KernelArgs &a, const PointRanks &R, unsigned long long bm_off, uint16_t *lds,
+    __device__ __forceinline__ RankReader(const KernelArgs &a, const PointRanks &R_, unsigned long long bm_off, uint16_t *lds,
                                           unsigned long long first_, unsigned long long end_, int lane)
-        : list(lds), words(a.bitmap + bm_off), seg_base(a.seg_base + bcast_lane0(R.seg_first)), base0(bcast_lane0(R.base)),
-          n_segs(bcast_lane0(R.n_segs)), shift(__builtin_amdgcn_readfirstlane(R.seg_shift)), n_words(bcast_lane0(R.n_words)),
+        : list(lds), words(a.bitmap + bm_off), R(R_), seg_base(a.seg_base),
+          shift(__builtin_amdgcn_readfirstlane(R_.seg_shift)), n_words(bcast_lane0(R_.n_words)),
           rank(bcast_lane0(first_)), end(bcast_lane0(end_))
     {
         skip = (int)(rank - seek(rank, 0ull, lane));
@@ -1142,10 +1146,11 @@ struct RankReader {
     // begins at.
     __device__ __forceinline__ unsigned long long seek(unsigned long long r, unsigned long long from, int lane)
     {
-        unsigned long long lo = from, n = n_segs - from, before = 0;
+        const unsigned long long *base0 = seg_base + bcast_lane0(R.seg_first), before0 = bcast_lane0(R.base);
+        unsigned long long lo = from, n = bcast_lane0(R.n_segs) - from, before = 0;
         while (n > 1) {
             const unsigned long long step = (n + kWave - 1) / kWave, i = step * lane;
-            const unsigned long long base = i < n ? seg_base[lo + i] - base0 : ~0ull;
+            const unsigned long long base = i < n ? base0[lo + i] - before0 : ~0ull;
             const int c = __popcll(__ballot(base <= r)) - 1;  // the one at lo begins there or before
             before = read_lane_u64(base, c);
             lo += step * c;
@@ -1154,20 +1159,19 @@ struct RankReader {
         at = at > lo << shift ? at : lo << shift;
         return before;
     }
-    // Past the segments from this one on that hold none before rank r.
-    __device__ __forceinline__ void skip_empty(unsigned long long r, int lane)
+    // From word `from` on nothing was found before `at`: if that is another segment, past
+    // those that hold none before rank r.
+    __device__ __forceinline__ void skip_empty(unsigned long long r, unsigned long long from, int lane)
     {
+        if (at >> shift == from >> shift || at >= n_words) return;
         const unsigned long long cur = at >> shift, i = cur + lane;
-        const unsigned long long base = i < n_segs ? seg_base[i] - base0 : ~0ull;
+        const unsigned long long base = i < R.n_segs ? seg_base[R.seg_first + i] - R.base : ~0ull;
         const int c = __popcll(__ballot(base <= r)) - 1;
         if (c == kWave - 1) seek(r, cur + c, lane);
         else if (c > 0) at = (cur + c) << shift;
     }
-    // Queues the next proposals: how many, a multiple of TILE or all that are left, or
-    // 0 when all are done.  Where few are accepted the loads are what a group takes,
-    // hence kAhead groups' together (4096 samples among 3e6 words at K = 32: 0.4 ms
-    // more, one at a time), and where hardly any the segments' counts lead past the
-    // words that hold none.
+    // Queues the next proposals: how many, with those that wait, a multiple of TILE or
+    // all that are left, or 0 when all are done.
     __device__ __forceinline__ int next(int lane)
     {
         while (rank < end && at < n_words) {
@@ -1179,11 +1183,13 @@ struct RankReader {
             }
 #pragma unroll
             for (int h = 0; h < kAhead; ++h) some |= __ballot(ahead[h] != 0u) != 0ull ? 1u << h : 0u;
-            const unsigned long long at0 = at;
             const bool none = some == 0u;
+            const unsigned long long want = end - rank - n_held;
+            bool last = false;
+            fresh = 0;
+            after = at + kAhead * GW;
             for (; some; some &= some - 1) {
                 const int h0 = __ffs(some) - 1;
-                at = at0 + h0 * GW;
                 uint32_t word = ahead[0];
 #pragma unroll
                 for (int h = 1; h < kAhead; ++h) word = h0 == h ? ahead[h] : word;
@@ -1194,20 +1200,28 @@ struct RankReader {
                     skip -= total;
                     continue;
                 }
-                int pos = incl - cntw - skip;
-                const unsigned long long want = end - rank - n_held;
-                const bool last = (unsigned long long)(total - skip) >= want;
-                fresh = last ? (int)want : total - skip;
-                skip = 0;
+                if (fresh + total - skip > N) {  // no room: the next time
+                    after = at + h0 * GW;
+                    break;
+                }
+                int pos = fresh + incl - cntw - skip;
                 for (uint32_t m = word; m; m &= m - 1, ++pos)
-                    if (pos >= 0) list[pos] = (uint16_t)(lane * 32 + __ffs(m) - 1);
-                wave_lds_sync();
-                if (last) return n_held + fresh;
-                if (n_held + fresh >= TILE) return (n_held + fresh) & ~(TILE - 1);
-                keep(0, lane);
+                    if (pos >= fresh) list[pos] = (uint16_t)((h0 * GW + lane) * 32 + __ffs(m) - 1);
+                fresh += total - skip;
+                skip = 0;
+                last = (unsigned long long)fresh >= want;
+                if (last) break;
             }
-            at = at0 + kAhead * GW;
-            if (none && at >> shift != at0 >> shift && at < n_words) skip_empty(rank + n_held, lane);
+            wave_lds_sync();
+            if (last) {
+                fresh = (int)want;
+                return n_held + fresh;
+            }
+            if (n_held + fresh >= TILE) return (n_held + fresh) & ~(TILE - 1);
+            keep(0, lane);
+            const unsigned long long from = at;
+            at = after;
+            if (none) skip_empty(rank + n_held, from, lane);
         }
         return 0;
     }
@@ -1221,7 +1235,7 @@ struct RankReader {
     {
         rank += n;
         keep(n, lane);
-        at += GW;
+        at = after;
     }
     // All but the first n wait, fewer than TILE.
     __device__ __forceinline__ void keep(int n, int lane)

@@ -93,7 +93,7 @@ constexpr unsigned long long max_segments(unsigned long long words, int n_points
 constexpr unsigned long long run_most(int K, int j)  // most samples that are cut into runs of 2^j
 {
     constexpr unsigned long long few[2][9] = {
-        {64, 128, 256, 2048, 8192, 32768, 65536, 1 << 19, 1 << 21},   // K <= 32
+        {64, 128, 256, 4096, 8192, 32768, 65536, 1 << 19, 1 << 21},   // K <= 32
         {64, 128, 256, 2048, 8192, 65536, 1 << 19, 1 << 20, 1 << 21}};  // K >= 64: workgroups of 8 waves, dear tiles
     return j < 9 ? few[K >= 64][j] : 32ull << (2 * j);
 }

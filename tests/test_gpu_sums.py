@@ -5,8 +5,8 @@ alone or beside others, an accepted-count call (which decides some tiles past it
 target, how many depends on timing) or the proposal-count call that ends at its
 last sample, any launch.  And their values against 64 bits, from the rows that
 the call wrote, where the ordered output's runs of ranks begin, end and change
-length (R = 1, 2, 4, 8, 16 ranks a run up to 64, 128, 256, 2048, 8192 samples and
-so on, to 2^21 samples for R = 256).
+length (R = 1, 2, 4, 8, 16 ranks a run up to 64, 128, 256, 2048 or 4096, 8192
+samples and so on, to 2^21 samples for R = 256).
 
 A row's coordinates are FP32 and a grid value is an FP32 product of 2K terms:
 within tol = 2e-6 sqrt(K) amp of its 64-bit value.  So a sum of p-th powers is
@@ -128,7 +128,7 @@ def test_mixture_accepted_count(T, ctx):
         _equal(r, whole)
 
 
-EDGES = (1, 64, 65, 127, 129, 256, 257, 2_048, 2_049, 8_191, 8_192, 8_193, 16_384, 16_385, 32_769, 65_536, 65_537,
+EDGES = (1, 64, 65, 127, 129, 256, 257, 2_048, 2_049, 4_096, 4_097, 8_191, 8_192, 8_193, 16_384, 16_385, 32_769, 65_536, 65_537,
          131_072, 131_073)
 
 
